@@ -77,10 +77,11 @@ int32_t check_common(const char* fn, int32_t B, int32_t d, int32_t h, int32_t dt
 struct HistoryPlan {
   float *Qt, *Ks, *Vs;        // Q[T] = LC Wq; K[S] = E Wk; V[S] = E Wv
   float *Qs, *Kt, *Vt;        // only for O[S]: Q[S] = E Wq; K[T] = LC Wk; V[T] = LC Wv
-  size_t bytes;
+  void* scratch;              // states of the key chunks, where the attention is cut into any; last, and optional:
+  size_t needed, bytes;       // a workspace of `needed` bytes does without it
 };
 
-HistoryPlan plan_history(void* ws, int64_t B, int64_t N, int64_t d, int64_t m, bool per_user_links, bool want_os) {
+HistoryPlan plan_history(void* ws, int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, bool per_user_links, bool want_os) {
   Arena a(ws);
   HistoryPlan p{};
   const int64_t link_rows = (per_user_links ? B : 1) * m;
@@ -92,6 +93,9 @@ HistoryPlan plan_history(void* ws, int64_t B, int64_t N, int64_t d, int64_t m, b
     p.Kt = a.take<float>(link_rows * d);
     p.Vt = a.take<float>(link_rows * d);
   }
+  p.needed = a.used;
+  p.scratch = a.take<char>(std::max(lime::generic_attention_scratch(B, m, N, d, h),
+                                    want_os ? lime::generic_attention_scratch(B, N, m, d, h) : size_t{0}));
   p.bytes = a.used;
   return p;
 }
@@ -117,7 +121,7 @@ XorLayersPlan plan_xor_layers(void* ws, int64_t B, int64_t N, int64_t d, int64_t
   const size_t es = dtype == LIME_BF16 ? 2 : 4;
   // (sized for whichever kernels the XORA step picks: with misaligned caller tensors the first layer runs on the
   // general kernels and the later ones, whose inputs live in this workspace, on the matrix cores)
-  p.hist_bytes = plan_history(nullptr, B, N, d, m, true, true).bytes;
+  p.hist_bytes = plan_history(nullptr, B, N, d, h, m, true, true).bytes;
   if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m))
     p.hist_bytes = std::max(p.hist_bytes, lime::links_over_history_workspace(B, N, d, h, m, true) +
                                               lime::queries_over_links_workspace(B, d, m, true));
@@ -142,6 +146,17 @@ size_t xor_layers_workspace(int64_t B, int64_t N, int64_t d, int64_t h, int64_t 
   if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m))
     need = std::max(need, plan_xor_layers(nullptr, B, N, d, h, m, dtype, true).bytes);
   return need;
+}
+
+// The m links over the history on the general kernels (the projections of `p` done).
+lime::GenericAttention history_attention(const HistoryPlan& p, const int32_t* lens, int64_t link_stride, void* LP, int32_t B, int32_t N,
+                                         int32_t d, int32_t h, int32_t m, float scale, int phi, int32_t dtype) {
+  lime::GenericAttention t{};
+  t.Q = p.Qt, t.K = p.Ks, t.V = p.Vs;
+  t.q_user_stride = link_stride, t.k_user_stride = t.v_user_stride = static_cast<int64_t>(N) * d;
+  t.O = LP, t.q_lens = nullptr, t.k_lens = lens, t.scratch = p.scratch;
+  t.B = B, t.q_rows = m, t.n_keys = N, t.d = d, t.h = h, t.scale = scale, t.phi = phi, t.dtype = dtype;
+  return t;
 }
 
 // O[S] of XORA on the candidate-side kernel: every history row attends over the m links, SiLU / m.
@@ -198,36 +213,30 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     q.packed = true;
     LIME_HIP(lime::links_over_history(q, workspace, s));
   } else {
-    p = plan_history(nullptr, B, N, d, m, per_user, want_os && !os_on_mfma);
-    const size_t os_bytes = os_on_mfma ? lime::queries_over_links_workspace(B, d, m, per_user) : 0;
-    if (!workspace || ws_bytes < p.bytes + os_bytes)
-      return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.bytes + os_bytes,
-                  workspace ? ws_bytes : 0);
-    p = plan_history(workspace, B, N, d, m, per_user, want_os && !os_on_mfma);
-    LIME_HIP(lime::generic_project(LC, Wq, p.Qt, link_rows, d, dtype, s));
-    LIME_HIP(lime::generic_project(E, Wk, p.Ks, hist_rows, d, dtype, s));
-    LIME_HIP(lime::generic_project(E, Wv, p.Vs, hist_rows, d, dtype, s));
-    lime::GenericAttention t{};
-    t.Q = p.Qt, t.K = p.Ks, t.V = p.Vs;
-    t.q_user_stride = link_stride, t.k_user_stride = t.v_user_stride = static_cast<int64_t>(N) * d;
-    t.O = LP, t.q_lens = nullptr, t.k_lens = lens;
-    t.B = B, t.q_rows = m, t.n_keys = N, t.d = d, t.h = h, t.scale = scale, t.phi = phi, t.dtype = dtype;
-    LIME_HIP(lime::generic_attention(t, s));
+    p = plan_history(nullptr, B, N, d, h, m, per_user, want_os);
+    if (!workspace || ws_bytes < p.needed)
+      return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.needed, workspace ? ws_bytes : 0);
+    const bool chunked = ws_bytes >= p.bytes;
+    p = plan_history(workspace, B, N, d, h, m, per_user, want_os);
+    if (!chunked) p.scratch = nullptr;
+    const lime::Projection jobs[6] = {{LC, Wq, p.Qt, link_rows}, {E, Wk, p.Ks, hist_rows, lens, N}, {E, Wv, p.Vs, hist_rows, lens, N},
+                                      {E, Wq, p.Qs, hist_rows, lens, N}, {LC, Wk, p.Kt, link_rows}, {LC, Wv, p.Vt, link_rows}};
+    LIME_HIP(lime::generic_project(jobs, want_os ? 6 : 3, d, dtype, s));
+    LIME_HIP(lime::generic_attention(history_attention(p, lens, link_stride, LP, B, N, d, h, m, scale, phi, dtype), s));
+    if (want_os) {
+      lime::GenericAttention o{};
+      o.Q = p.Qs, o.K = p.Kt, o.V = p.Vt;
+      o.q_user_stride = static_cast<int64_t>(N) * d, o.k_user_stride = o.v_user_stride = link_stride;
+      o.O = OS, o.q_lens = lens, o.k_lens = nullptr, o.scratch = p.scratch;
+      o.B = B, o.q_rows = N, o.n_keys = m, o.d = d, o.h = h, o.scale = scale, o.phi = lime::kPhiSilu, o.dtype = dtype;
+      LIME_HIP(lime::generic_attention(o, s));
+    }
+    return LIME_OK;
   }
   if (os_on_mfma) {
     lime::QueriesOverLinks q = os_query(E, lens, LC, link_stride, Wq, Wk, Wv, OS, B, N, d, h, m, scale);
     q.packed = true;
     LIME_HIP(lime::queries_over_links(q, static_cast<char*>(workspace) + p.bytes, s));
-  } else if (want_os) {
-    LIME_HIP(lime::generic_project(E, Wq, p.Qs, hist_rows, d, dtype, s));
-    LIME_HIP(lime::generic_project(LC, Wk, p.Kt, link_rows, d, dtype, s));
-    LIME_HIP(lime::generic_project(LC, Wv, p.Vt, link_rows, d, dtype, s));
-    lime::GenericAttention o{};
-    o.Q = p.Qs, o.K = p.Kt, o.V = p.Vt;
-    o.q_user_stride = static_cast<int64_t>(N) * d, o.k_user_stride = o.v_user_stride = link_stride;
-    o.O = OS, o.q_lens = lens, o.k_lens = nullptr;
-    o.B = B, o.q_rows = N, o.n_keys = m, o.d = d, o.h = h, o.scale = scale, o.phi = lime::kPhiSilu, o.dtype = dtype;
-    LIME_HIP(lime::generic_attention(o, s));
   }
   return LIME_OK;
 }
@@ -235,17 +244,40 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
 // ----------------------------------------------------------------------------- candidate side (Eq. 4) and baseline (Eq. 1)
 struct QueryPlan {
   float *Qt, *Kt, *Vt;
-  size_t bytes;
+  void* scratch;         // as in HistoryPlan
+  size_t needed, bytes;
 };
 
-QueryPlan plan_queries(void* ws, int64_t q_rows_total, int64_t k_rows_total, int64_t v_rows_total, int64_t d) {
+QueryPlan plan_queries(void* ws, int64_t q_rows_total, int64_t k_rows_total, int64_t v_rows_total, int64_t d, size_t scratch = 0) {
   Arena a(ws);
   QueryPlan p{};
   p.Qt = a.take<float>(q_rows_total * d);
   p.Kt = a.take<float>(k_rows_total * d);
   p.Vt = a.take<float>(v_rows_total * d);
+  p.needed = a.used;
+  p.scratch = a.take<char>(scratch);
   p.bytes = a.used;
   return p;
+}
+
+// Eq. 4's workspace on the general kernels: raw links as keys, link states as values.
+QueryPlan plan_candidates(void* ws, int64_t B, int64_t C, int64_t d, int64_t h, int64_t m) {
+  return plan_queries(ws, B * C, m, B * m, d, lime::generic_attention_scratch(B, C, m, d, h));
+}
+// Eq. 1's
+QueryPlan plan_target(void* ws, int64_t B, int64_t C, int64_t N, int64_t d, int64_t h) {
+  return plan_queries(ws, B * C, B * N, B * N, d, lime::generic_attention_scratch(B, C, N, d, h));
+}
+
+// The candidates over the m links on the general kernels (the projections of `p` done).
+lime::GenericAttention candidate_attention(const QueryPlan& p, void* O, int32_t B, int32_t C, int32_t d, int32_t h, int32_t m, float scale,
+                                           int32_t dtype) {
+  lime::GenericAttention a{};
+  a.Q = p.Qt, a.K = p.Kt, a.V = p.Vt;
+  a.q_user_stride = static_cast<int64_t>(C) * d, a.k_user_stride = 0, a.v_user_stride = static_cast<int64_t>(m) * d;
+  a.O = O, a.q_lens = nullptr, a.k_lens = nullptr, a.scratch = p.scratch;
+  a.B = B, a.q_rows = C, a.n_keys = m, a.d = d, a.h = h, a.scale = scale, a.phi = lime::kPhiSoftmax, a.dtype = dtype;
+  return a;
 }
 
 }  // namespace
@@ -289,19 +321,15 @@ int32_t lime_score_candidates(const void* T, const void* L, const void* LP, cons
     LIME_HIP(lime::queries_over_links(q, workspace, s));
     return LIME_OK;
   }
-  QueryPlan p = plan_queries(nullptr, q_rows, m, v_rows, d);
-  if (!workspace || ws_bytes < p.bytes)
-    return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.bytes, workspace ? ws_bytes : 0);
-  p = plan_queries(workspace, q_rows, m, v_rows, d);
-  LIME_HIP(lime::generic_project(T, Wq, p.Qt, q_rows, d, dtype, s));
-  LIME_HIP(lime::generic_project(L, Wk, p.Kt, m, d, dtype, s));
-  LIME_HIP(lime::generic_project(LP, Wv, p.Vt, v_rows, d, dtype, s));
-  lime::GenericAttention a{};
-  a.Q = p.Qt, a.K = p.Kt, a.V = p.Vt;
-  a.q_user_stride = static_cast<int64_t>(C) * d, a.k_user_stride = 0, a.v_user_stride = static_cast<int64_t>(m) * d;
-  a.O = O, a.q_lens = nullptr, a.k_lens = nullptr;
-  a.B = B, a.q_rows = C, a.n_keys = m, a.d = d, a.h = h, a.scale = scale, a.phi = lime::kPhiSoftmax, a.dtype = dtype;
-  LIME_HIP(lime::generic_attention(a, s));
+  QueryPlan p = plan_candidates(nullptr, B, C, d, h, m);
+  if (!workspace || ws_bytes < p.needed)
+    return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.needed, workspace ? ws_bytes : 0);
+  const bool chunked = ws_bytes >= p.bytes;
+  p = plan_candidates(workspace, B, C, d, h, m);
+  if (!chunked) p.scratch = nullptr;
+  const lime::Projection jobs[3] = {{T, Wq, p.Qt, q_rows}, {L, Wk, p.Kt, m}, {LP, Wv, p.Vt, v_rows}};
+  LIME_HIP(lime::generic_project(jobs, 3, d, dtype, s));
+  LIME_HIP(lime::generic_attention(candidate_attention(p, O, B, C, d, h, m, scale, dtype), s));
   return LIME_OK;
 }
 
@@ -323,17 +351,18 @@ int32_t mha_target_attention(const void* T, const void* E, const int32_t* lens, 
     LIME_HIP(lime::target_attention(q, workspace, s));
     return LIME_OK;
   }
-  QueryPlan p = plan_queries(nullptr, q_rows, k_rows, k_rows, d);
-  if (!workspace || ws_bytes < p.bytes)
-    return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.bytes, workspace ? ws_bytes : 0);
-  p = plan_queries(workspace, q_rows, k_rows, k_rows, d);
-  LIME_HIP(lime::generic_project(T, Wq, p.Qt, q_rows, d, dtype, s));
-  LIME_HIP(lime::generic_project(E, Wk, p.Kt, k_rows, d, dtype, s));
-  LIME_HIP(lime::generic_project(E, Wv, p.Vt, k_rows, d, dtype, s));
+  QueryPlan p = plan_target(nullptr, B, C, N, d, h);
+  if (!workspace || ws_bytes < p.needed)
+    return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.needed, workspace ? ws_bytes : 0);
+  const bool chunked = ws_bytes >= p.bytes;
+  p = plan_target(workspace, B, C, N, d, h);
+  if (!chunked) p.scratch = nullptr;
+  const lime::Projection jobs[3] = {{T, Wq, p.Qt, q_rows}, {E, Wk, p.Kt, k_rows, lens, N}, {E, Wv, p.Vt, k_rows, lens, N}};
+  LIME_HIP(lime::generic_project(jobs, 3, d, dtype, s));
   lime::GenericAttention a{};
   a.Q = p.Qt, a.K = p.Kt, a.V = p.Vt;
   a.q_user_stride = static_cast<int64_t>(C) * d, a.k_user_stride = a.v_user_stride = static_cast<int64_t>(N) * d;
-  a.O = O, a.q_lens = nullptr, a.k_lens = lens;
+  a.O = O, a.q_lens = nullptr, a.k_lens = lens, a.scratch = p.scratch;
   a.B = B, a.q_rows = C, a.n_keys = N, a.d = d, a.h = h, a.scale = scale, a.phi = lime::kPhiSoftmax, a.dtype = dtype;
   LIME_HIP(lime::generic_attention(a, s));
   return LIME_OK;
@@ -364,8 +393,8 @@ int32_t lime_build_qk_cache(const void* T, const void* L, const void* Wq, const 
   if (!workspace || ws_bytes < p.bytes)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.bytes, workspace ? ws_bytes : 0);
   p = plan_queries(workspace, q_rows, m, 0, d);
-  LIME_HIP(lime::generic_project(T, Wq, p.Qt, q_rows, d, dtype, s));
-  LIME_HIP(lime::generic_project(L, Wk, p.Kt, m, d, dtype, s));
+  const lime::Projection jobs[2] = {{T, Wq, p.Qt, q_rows}, {L, Wk, p.Kt, m}};
+  LIME_HIP(lime::generic_project(jobs, 2, d, dtype, s));
   LIME_HIP(lime::generic_qk_weights(p.Qt, p.Kt, W, q_rows, d, h, m, scale, dtype, s));
   return LIME_OK;
 }
@@ -395,7 +424,8 @@ int32_t cached_impl(const char* fn, const void* W, const int32_t* ids, int32_t n
   if (!workspace || ws_bytes < p.bytes)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, p.bytes, workspace ? ws_bytes : 0);
   p = plan_queries(workspace, 0, 0, v_rows, d);
-  LIME_HIP(lime::generic_project(LP, Wv, p.Vt, v_rows, d, dtype, s));
+  const lime::Projection job{LP, Wv, p.Vt, v_rows};
+  LIME_HIP(lime::generic_project(&job, 1, d, dtype, s));
   LIME_HIP(lime::generic_cached_sum(W, ids, n_items, p.Vt, O, B, C, d, h, m, dtype, s));
   return LIME_OK;
 }
@@ -539,8 +569,12 @@ RequestPlan plan_request(bool on_mfma, bool any_path, bool per_user, int32_t B, 
     p.total = p.hist_bytes + lime::queries_over_links_workspace(B, d, m, false);
   } else {
     // the two stages in turn: each picks its kernels by itself, so each part is sized for either choice
-    p.hist_bytes = plan_history(nullptr, B, N, d, m, per_user, false).bytes;
-    size_t cand = plan_queries(nullptr, static_cast<int64_t>(B) * C, m, static_cast<int64_t>(B) * m, d).bytes;
+    // (without the states of key chunks, which an attention does without, where the room is fixed and they do not fit)
+    const HistoryPlan hp = plan_history(nullptr, B, N, d, h, m, per_user, false);
+    const QueryPlan cp = plan_candidates(nullptr, B, C, d, h, m);
+    const bool chunked = hp.bytes + cp.bytes <= kStaticScratchBytes;
+    p.hist_bytes = chunked ? hp.bytes : hp.needed;
+    size_t cand = chunked ? cp.bytes : cp.needed;
     if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m)) {
       p.hist_bytes = std::max(p.hist_bytes, lime::links_over_history_workspace(B, N, d, h, m, per_user));
       cand = std::max(cand, lime::queries_over_links_workspace(B, d, m, false));
@@ -579,8 +613,29 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   const int phi = xor_attention ? lime::kPhiSilu : lime::kPhiSoftmax;
   const bool per_user = lc_user_stride != 0;
   void* cand_ws = static_cast<char*>(workspace) + p.hist_bytes;
+  if (!p.on_mfma && norms != nullptr) return fail(LIME_UNSUPPORTED, "%s: normalised operands need the matrix-core path", fn);
+  if (!p.on_mfma && (dtype != LIME_BF16 || !lime::links_over_history_supported(d, h, m))) {
+    // Both stages on the general kernels: everything but the projection of the link states does not depend on the
+    // history stage's result and is projected by one launch, so that the request is four launches (with the history cut
+    // into chunks five).
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    HistoryPlan hp = plan_history(workspace, B, N, d, h, m, per_user, false);
+    QueryPlan cp = plan_candidates(cand_ws, B, C, d, h, m);
+    if (p.hist_bytes < hp.bytes) hp.scratch = nullptr;
+    if (p.total - p.hist_bytes < cp.bytes) cp.scratch = nullptr;
+    const int64_t link_rows = (per_user ? B : 1) * static_cast<int64_t>(m), hist_rows = static_cast<int64_t>(B) * N;
+    const lime::Projection first[5] = {{LC, Wq_hist, hp.Qt, link_rows}, {E, Wk_hist, hp.Ks, hist_rows, lens, N},
+                                       {E, Wv_hist, hp.Vs, hist_rows, lens, N}, {T, Wq_cand, cp.Qt, static_cast<int64_t>(B) * C},
+                                       {L, Wk_cand, cp.Kt, m}};
+    const lime::Projection values{LP, Wv_cand, cp.Vt, static_cast<int64_t>(B) * m};
+    LIME_HIP(lime::generic_project(first, 5, d, dtype, s));
+    LIME_HIP(lime::generic_attention(history_attention(hp, lens, per_user ? static_cast<int64_t>(m) * d : 0, LP, B, N, d, h, m, scale_hist,
+                                                       phi, dtype), s));
+    LIME_HIP(lime::generic_project(&values, 1, d, dtype, s));
+    LIME_HIP(lime::generic_attention(candidate_attention(cp, O, B, C, d, h, m, scale_cand, dtype), s));
+    return LIME_OK;
+  }
   if (!p.on_mfma) {  // the two stages as they are (general kernels, or the matrix-core ones where each applies)
-    if (norms != nullptr) return fail(LIME_UNSUPPORTED, "%s: normalised operands need the matrix-core path", fn);
     if (int32_t st = history_impl(fn, phi, E, lens, LC, lc_user_stride, Wq_hist, Wk_hist, Wv_hist, LP, nullptr, B, N, d, h, m,
                                   scale_hist, dtype, workspace, p.hist_bytes, stream))
       return st;
@@ -1021,7 +1076,7 @@ size_t lime_workspace_bytes(int32_t op, int32_t B, int32_t N, int32_t C, int32_t
       // sized for per-user links, the larger of the two link layouts
     {
       const bool os = op == LIME_OP_XOR_HISTORY && (flags & 1);
-      size_t need = plan_history(nullptr, B, N, d, m, true, os).bytes;
+      size_t need = plan_history(nullptr, B, N, d, h, m, true, os).bytes;
       if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m))
         need = std::max(need, lime::links_over_history_workspace(B, N, d, h, m, true) +
                                   (os ? lime::queries_over_links_workspace(B, d, m, true) : size_t{0}));
@@ -1042,12 +1097,12 @@ size_t lime_workspace_bytes(int32_t op, int32_t B, int32_t N, int32_t C, int32_t
       return xor_layers_workspace(B, N, d, h, m, dtype);
     case LIME_OP_SCORE_CANDIDATES:
       if (C <= 0 || m <= 0) return 0;
-      return std::max(plan_queries(nullptr, static_cast<int64_t>(B) * C, m, static_cast<int64_t>(B) * m, d).bytes,
+      return std::max(plan_candidates(nullptr, B, C, d, h, m).bytes,
                       dtype == LIME_BF16 && lime::queries_over_links_supported(d, h, m)
                           ? lime::queries_over_links_workspace(B, d, m, false) : size_t{0});
     case LIME_OP_MHA_TARGET:
       if (C <= 0 || N <= 0) return 0;
-      return std::max(plan_queries(nullptr, static_cast<int64_t>(B) * C, static_cast<int64_t>(B) * N, static_cast<int64_t>(B) * N, d).bytes,
+      return std::max(plan_target(nullptr, B, C, N, d, h).bytes,
                       dtype == LIME_BF16 && lime::target_attention_supported(d, h)
                           ? lime::target_attention_workspace(B, C, N, d) : size_t{0});
     case LIME_OP_BUILD_QK_CACHE:

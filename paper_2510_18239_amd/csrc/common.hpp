@@ -56,7 +56,16 @@ inline void launch_timed(int kernel_id, void (*kernel)(KA...), dim3 grid, dim3 b
 
 // ----------------------------------------------------------------------------- general kernels (generic.hip)
 // Y[rows][d] (fp32) = X[rows][d] * W[d][d]; W == nullptr copies X (identity projection).
-hipError_t generic_project(const void* X, const void* W, float* Y, int64_t rows, int d, int dtype, hipStream_t s);
+struct Projection {
+  const void* X;
+  const void* W;
+  float* Y;
+  int64_t rows;
+  const int32_t* lens = nullptr;  // nullable; row r belongs to user r / rows_per_user, and the rows of a user at or past
+  int rows_per_user = 0;          // its length may be left out (nothing reads them)
+};
+constexpr int kMaxProjections = 8;  // products one launch takes
+hipError_t generic_project(const Projection* jobs, int n, int d, int dtype, hipStream_t s);
 
 struct GenericAttention {
   const float* Q;      // [.][q_rows][d], user b at Q + b * q_user_stride
@@ -70,7 +79,9 @@ struct GenericAttention {
   float scale;
   int phi;    // kPhiSoftmax: softmax over valid keys; kPhiSilu: SiLU(logit) / (number of valid keys)
   int dtype;  // of O
+  void* scratch;  // generic_attention_scratch bytes; nullptr = the keys are not cut into chunks
 };
+size_t generic_attention_scratch(int64_t B, int64_t q_rows, int64_t n_keys, int64_t d, int64_t h);
 hipError_t generic_attention(const GenericAttention& a, hipStream_t s);
 
 // QK cache (Section 3.3): W[rows][h][m] = softmax over m of scale * <Q[row]_head, K[i]_head> (Q, K projected, fp32);

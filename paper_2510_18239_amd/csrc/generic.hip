@@ -1,202 +1,471 @@
-// General kernels: fp32 arithmetic on the vector ALUs, any shape with d/h <= 256.
-// They serve the fp32 storage type and every bf16 shape the matrix-core kernels do
+// General kernels: fp32 arithmetic, any shape with d/h <= 256.
+// They serve the fp32 storage type and every bf16 shape the bf16 matrix-core kernels do
 // not cover.  Each step is the plain definition (Eq. 1): a projection X~ = X W and an
 // attention (phi(scale * Q~ K~^T) restricted to the valid keys) V~.
+//
+// Both run on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums, twice the rate of
+// the vector ALUs' unpacked multiply-add), whose fragments are one float per lane:
+//   A (32 x 2): lane (n, g) = A[row n][k = g];  B (2 x 32): lane (n, g) = B[k = g][col n];
+//   D (32 x 32): lane (n, g), register 4j + r = D[row 8j + 4g + r][col n]          (lane = 32 g + n)
+// A sum does not care about the order of its terms, so the two k of an instruction need not be neighbours: with
+// k = 8j + i and 8j + 4 + i, i = 0..3, a lane's operands of four instructions are four consecutive floats, one 16-byte
+// load; and a D block is, register by register, the B operand of a product that sums over its rows.
+#include <algorithm>
+
 #include "common.hpp"
+#include "mfma.hpp"
 
 namespace lime {
 namespace {
 
-// ----------------------------------------------------------------------------- projection
-constexpr int PT = 64;  // output tile edge
-constexpr int PK = 16;  // k-slice
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+// ----------------------------------------------------------------------------- projections
+// Up to kMaxProjections products Y[rows][d] (fp32) = X[rows][d] W[d][d] in one launch: what a call has to project
+// before its attention is independent, and at a few hundred rows each a launch costs more than the product.
+// A workgroup computes a TM x TN tile (TM TN = 4096, a 32 x 32 block per wave; 128 x 32 for d <= 32), k in steps of 32
+// through two LDS buffers, the next step's loads in flight during the current one's products.  A lane's A operands of
+// four instructions are one 16-byte LDS read (row pitch 36 floats: eight rows cover all banks), its B operands four
+// 4-byte reads of a row of W (pitch TN + 8: the lane halves, four rows apart, fall on different banks).
+// What bounds it: at 16016 x 128 fp32 rows the matrix instruction (64 cycles per 32 x 32 x 2); at a few rows the launch.
+constexpr int kProjK = 32;
+struct ProjectArgs {
+  const void* X[kMaxProjections];
+  const void* W[kMaxProjections];  // nullable = identity: X is copied
+  float* Y[kMaxProjections];
+  const int32_t* lens[kMaxProjections];  // nullable; rows of a user at or past its length need not be computed
+  int64_t rows[kMaxProjections];
+  int rows_per_user[kMaxProjections];
+  int first_tile[kMaxProjections + 1];
+  int n, d;
+};
 
 template <typename T>
-__global__ __launch_bounds__(256) void project_kernel(const T* __restrict__ X, const T* __restrict__ W,
-                                                      float* __restrict__ Y, int64_t rows, int d) {
-  __shared__ float Xs[PK][PT + 1];
-  __shared__ float Ws[PK][PT + 1];
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * PT;
-  const int c0 = blockIdx.y * PT;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < d; k0 += PK) {
-    for (int idx = threadIdx.x; idx < PT * PK; idx += 256) {
-      const int r = idx / PK, k = idx % PK;  // X tile: consecutive threads walk k
-      const int64_t row = r0 + r;
-      Xs[k][r] = (row < rows && k0 + k < d) ? to_float(X[row * d + k0 + k]) : 0.f;
-      const int kk = idx / PT, c = idx % PT;  // W tile: consecutive threads walk c
-      Ws[kk][c] = (k0 + kk < d && c0 + c < d) ? to_float(W[static_cast<int64_t>(k0 + kk) * d + c0 + c]) : 0.f;
+struct Vec8 {  // eight consecutive elements as one or two 16-byte loads
+  float v[8];
+  __device__ __forceinline__ void load(const T* p) {
+    if constexpr (sizeof(T) == 4) {
+      const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+      v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+    } else {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(p);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = static_cast<float>(a[t]);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PK; ++k) {
-      float xv[4], wv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xv[i] = Xs[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wv[j] = Ws[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(xv[i], wv[j], acc[i][j]);
-    }
-    __syncthreads();
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = r0 + ty * 4 + i;
-    if (row >= rows) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = c0 + tx * 4 + j;
-      if (c < d) Y[row * d + c] = acc[i][j];
+};
+
+// VEC: d is a multiple of 8 and every X and W is 16-byte aligned.
+template <typename T, int TN, bool VEC>
+__global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
+  constexpr int TM = 4096 / TN, XP = kProjK + 4, WP = TN + 8;
+  constexpr int XL = TM * kProjK / 8 / 256;  // 8-element pieces of the X tile per thread (1 or 2)
+  constexpr int WL = kProjK * TN / 8;        // 8-element pieces of the W tile (256, or 128: the first half of the threads)
+  __shared__ __attribute__((aligned(16))) float xs[2][TM * XP];
+  __shared__ __attribute__((aligned(16))) float ws[2][kProjK * WP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g = lane >> 5, d = a.d;
+  int job = 0;
+  while (job + 1 < a.n && static_cast<int>(blockIdx.x) >= a.first_tile[job + 1]) ++job;  // uniform
+  const int tile = blockIdx.x - a.first_tile[job], col_tiles = (d + TN - 1) / TN;
+  const int64_t r0 = static_cast<int64_t>(tile / col_tiles) * TM, rows = a.rows[job];
+  const int c0 = (tile % col_tiles) * TN;
+  if (a.lens[job] != nullptr) {  // a tile that holds one user's padding only is skipped: nothing reads it
+    const int64_t b = r0 / a.rows_per_user[job];
+    const int first = static_cast<int>(r0 - b * a.rows_per_user[job]);
+    if (first >= a.lens[job][b] && first + TM <= a.rows_per_user[job]) return;
+  }
+  const T* X = static_cast<const T*>(a.X[job]);
+  const T* W = static_cast<const T*>(a.W[job]);
+  float* Y = a.Y[job];
+  if (W == nullptr) {
+    for (int i = tid; i < TM * TN; i += 256) {
+      const int64_t row = r0 + i / TN;
+      const int c = c0 + i % TN;
+      if (row < rows && c < d) Y[row * d + c] = to_float(X[row * d + c]);
     }
+    return;
+  }
+  Vec8<T> px[XL], pw;
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int l = 0; l < XL; ++l) {
+      const int i = tid + 256 * l;
+      const int64_t row = r0 + i / (kProjK / 8);
+      const int k = k0 + 8 * (i % (kProjK / 8));
+      if constexpr (VEC) {
+        // (rows past the end are read from the last one and not stored; columns past the end count as zeros)
+        if (k < d) px[l].load(X + (row < rows ? row : rows - 1) * d + k);
+        else
+#pragma unroll
+          for (int t = 0; t < 8; ++t) px[l].v[t] = 0.f;
+      } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) px[l].v[t] = (row < rows && k + t < d) ? to_float(X[row * d + k + t]) : 0.f;
+      }
+    }
+    if (WL == 256 || tid < WL) {
+      const int k = k0 + tid / (TN / 8), c = c0 + 8 * (tid % (TN / 8));
+      if constexpr (VEC) {
+        if (k < d && c < d) pw.load(W + static_cast<int64_t>(k) * d + c);
+        else
+#pragma unroll
+          for (int t = 0; t < 8; ++t) pw.v[t] = 0.f;
+      } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) pw.v[t] = (k < d && c + t < d) ? to_float(W[static_cast<int64_t>(k) * d + c + t]) : 0.f;
+      }
+    }
+  };
+  auto park = [&](int buf) {
+#pragma unroll
+    for (int l = 0; l < XL; ++l) {
+      const int i = tid + 256 * l;
+      float* dst = xs[buf] + (i / (kProjK / 8)) * XP + 8 * (i % (kProjK / 8));
+      *reinterpret_cast<float4*>(dst) = make_float4(px[l].v[0], px[l].v[1], px[l].v[2], px[l].v[3]);
+      *reinterpret_cast<float4*>(dst + 4) = make_float4(px[l].v[4], px[l].v[5], px[l].v[6], px[l].v[7]);
+    }
+    if (WL == 256 || tid < WL) {
+      float* dst = ws[buf] + (tid / (TN / 8)) * WP + 8 * (tid % (TN / 8));
+      *reinterpret_cast<float4*>(dst) = make_float4(pw.v[0], pw.v[1], pw.v[2], pw.v[3]);
+      *reinterpret_cast<float4*>(dst + 4) = make_float4(pw.v[4], pw.v[5], pw.v[6], pw.v[7]);
+    }
+  };
+  constexpr int WC = TN / 32;  // waves across the tile's columns
+  const int wr = wave / WC, wc = wave % WC;
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  const int steps = (d + kProjK - 1) / kProjK;
+  fetch(0);
+  for (int s = 0; s < steps; ++s) {
+    park(s & 1);
+    __syncthreads();  // (the other buffer was last read before this barrier's predecessor)
+    if (s + 1 < steps) fetch((s + 1) * kProjK);
+    const float* xrow = xs[s & 1] + (32 * wr + n) * XP + 4 * g;
+    const float* wcol = ws[s & 1] + 4 * g * WP + 32 * wc + n;
+#pragma unroll
+    for (int j = 0; j < kProjK / 8; ++j) {
+      const float4 x = *reinterpret_cast<const float4*>(xrow + 8 * j);
+      const float w0 = wcol[(8 * j) * WP], w1 = wcol[(8 * j + 1) * WP], w2 = wcol[(8 * j + 2) * WP], w3 = wcol[(8 * j + 3) * WP];
+      acc = mfma_f32(x.x, w0, acc), acc = mfma_f32(x.y, w1, acc), acc = mfma_f32(x.z, w2, acc), acc = mfma_f32(x.w, w3, acc);
+    }
+  }
+  const int c = c0 + 32 * wc + n;
+  if (c >= d) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t row = r0 + 32 * wr + 8 * (i >> 2) + 4 * g + (i & 3);
+    if (row < rows) Y[row * d + c] = acc[i];
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void upcast_kernel(const T* __restrict__ X, float* __restrict__ Y, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) Y[i] = to_float(X[i]);
+hipError_t launch_project(const ProjectArgs& a, int tiles, bool vec, hipStream_t s) {
+  if (a.d <= 32) {
+    if (vec) hipLaunchKernelGGL((project_kernel<T, 32, true>), dim3(tiles), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((project_kernel<T, 32, false>), dim3(tiles), dim3(256), 0, s, a);
+  } else {
+    if (vec) hipLaunchKernelGGL((project_kernel<T, 64, true>), dim3(tiles), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((project_kernel<T, 64, false>), dim3(tiles), dim3(256), 0, s, a);
+  }
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------- attention
-constexpr int QT = 16;    // query rows per block
-constexpr int KT = 64;    // keys per step
-constexpr int MAXOUT = 16;  // outputs per thread: QT * (d/h) / 256 <= 16 for d/h <= 256
+// A wave takes 32 query rows of one (user, head) and walks the keys 32 at a time; everything but the operands stays in
+// registers.  S^T = K Q^T (A = key rows, B = query rows, the head's columns summed), so a lane owns a query (column) and
+// 16 of the 32 keys, the other 16 in lane ^ 32: the online softmax is lane-local plus one exchange.  Then
+// O^T += V^T P^T: register i of S^T is the B operand whose two k are the keys that register stands for in the two lane
+// halves, and the A operand is one float of each of those two rows of V: coalesced row reads, no LDS.
+// SPLIT: the four waves of a workgroup share 32 query rows and take every fourth key tile each; their states meet in LDS
+// at the end, added in wave order.  Chosen where the queries alone would leave the compute units idle (the m links
+// over a history); with few workgroups besides, the keys are also cut into chunks of kChunkTiles tiles whose
+// un-normalised states attention_merge_kernel combines in ascending order.  What bounds it: two key tiles per wave are
+// two dependent round trips to the cache, the matrix instruction (64 cycles each, d/h / 2 + 16 per tile at d/h <= 32)
+// from a few thousand tiles up.
+constexpr int kChunkTiles = 32;
 
 struct AttnDev {
   const float *Q, *K, *V;
   int64_t qs, ks, vs;
   void* O;
   const int32_t *q_lens, *k_lens;
-  int q_rows, n_keys, d, dh;
+  int q_rows, n_keys, d, dh, q_tiles, h, chunks;
   float scale;
+  float *part_acc, *part_ml;  // chunks > 1: [B][chunks][q_rows][d], [B][chunks][q_rows][h][2] (running max, running sum)
 };
 
-template <typename OutT, int PHI>
+// DB: 32-column blocks of the head's output (d/h <= 32 DB).  VEC: d/h is a multiple of 4 (16-byte reads of Q and K rows).
+template <typename OutT, int PHI, int DB, bool SPLIT, bool VEC>
 __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
-  extern __shared__ float smem[];
-  float* Qs = smem;                  // [QT][dh], already multiplied by scale
-  float* S = Qs + QT * a.dh;         // [QT][KT] logits, then weights
-  float* row_max = S + QT * KT;      // [QT]
-  float* row_sum = row_max + QT;     // [QT]
-  float* row_alpha = row_sum + QT;   // [QT]
-
-  const int tid = threadIdx.x;
-  const int b = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * QT;
-  const int dh = a.dh, d = a.d;
+  constexpr int KJ = DB * 4;  // groups of eight head columns
+  constexpr bool kPrefetch = DB <= 2;  // the next tile's K and V in flight during the current one (registers permitting)
+  __shared__ float red[SPLIT ? 3 * (DB * 16 + 2) * 64 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, g = lane >> 5;
+  const int b = blockIdx.z, d = a.d, dh = a.dh;
+  const int chunk = SPLIT ? blockIdx.y : 0;
+  const int unit = SPLIT ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * 4 + wave;  // (query tile, head), heads innermost
+  const int head = unit % a.h, q0 = unit / a.h * 32;
+  if (!SPLIT && q0 >= a.q_rows) return;
   const int qlen = a.q_lens ? min(a.q_lens[b], a.q_rows) : a.q_rows;
   const int klen = a.k_lens ? min(a.k_lens[b], a.n_keys) : a.n_keys;
-  const float* Qb = a.Q + b * a.qs + head * dh;
+  const int tile_first = chunk * kChunkTiles + (SPLIT ? wave : 0);
+  const int tiles = (klen + 31) / 32;
+  const int tile_last = SPLIT && a.chunks > 1 ? min(tiles, (chunk + 1) * kChunkTiles) : tiles;
+  if (SPLIT && a.chunks > 1 && chunk > 0 && chunk * kChunkTiles >= tiles) return;  // uniform: no key in this chunk
+  constexpr int kStep = SPLIT ? 4 : 1;
+  const bool dead = q0 >= qlen;  // only rows that are written as zeros
+
+  auto load4 = [&](const float* p, int k) {  // head columns k .. k + 3, zeros past the head's width
+    if constexpr (VEC) return k < dh ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 v;
+    v.x = k < dh ? p[k] : 0.f, v.y = k + 1 < dh ? p[k + 1] : 0.f, v.z = k + 2 < dh ? p[k + 2] : 0.f, v.w = k + 3 < dh ? p[k + 3] : 0.f;
+    return v;
+  };
+  float4 q[KJ];
+  {
+    const float* qrow = a.Q + b * a.qs + static_cast<int64_t>(min(q0 + n, a.q_rows - 1)) * d + head * dh;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      q[j] = load4(qrow, 8 * j + 4 * g);
+      q[j].x *= a.scale, q[j].y *= a.scale, q[j].z *= a.scale, q[j].w *= a.scale;
+    }
+  }
   const float* Kb = a.K + b * a.ks + head * dh;
   const float* Vb = a.V + b * a.vs + head * dh;
-
-  for (int idx = tid; idx < QT * dh; idx += 256) {
-    const int i = idx / dh, t = idx % dh, row = q0 + i;
-    Qs[idx] = row < qlen ? Qb[static_cast<int64_t>(row) * d + t] * a.scale : 0.f;
-  }
-  if (tid < QT) {
-    row_max[tid] = -INFINITY;
-    row_sum[tid] = 0.f;
-  }
-  float acc[MAXOUT];
+  // rows past the last valid key are read from it instead: their weights are zero
+  auto load_k = [&](int k0, float4 (&k)[KJ]) {
+    const float* krow = Kb + static_cast<int64_t>(min(k0 + n, klen - 1)) * d;
 #pragma unroll
-  for (int u = 0; u < MAXOUT; ++u) acc[u] = 0.f;
-  __syncthreads();
-
-  for (int k0 = 0; k0 < klen; k0 += KT) {
-    const int kn = min(KT, klen - k0);
-    // logits of this key block
-    for (int idx = tid; idx < QT * KT; idx += 256) {
-      const int i = idx / KT, j = idx % KT;
-      float s = -INFINITY;
-      if (j < kn) {
-        const float* kr = Kb + static_cast<int64_t>(k0 + j) * d;
-        const float* qr = Qs + i * dh;
-        s = 0.f;
-        for (int t = 0; t < dh; ++t) s = fmaf(qr[t], kr[t], s);
+    for (int j = 0; j < KJ; ++j)
+      if (8 * j < dh) k[j] = load4(krow, 8 * j + 4 * g);
+  };
+  auto load_v = [&](int k0, float (&v)[DB][16]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float* vrow = Vb + static_cast<int64_t>(min(k0 + 8 * (i >> 2) + 4 * g + (i & 3), klen - 1)) * d;
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob)
+        if (32 * ob < dh) v[ob][i] = vrow[min(32 * ob + n, dh - 1)];
+    }
+  };
+  f32x16 acc[DB];
+#pragma unroll
+  for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[ob][i] = 0.f;
+  float run_max = -INFINITY, run_sum = 0.f;
+  float4 kn[kPrefetch ? KJ : 1];
+  float vn[kPrefetch ? DB : 1][16];
+  if constexpr (kPrefetch) {
+    if (!dead && tile_first < tile_last) load_k(tile_first * 32, kn), load_v(tile_first * 32, vn);
+  }
+  for (int t = tile_first; t < tile_last && !dead; t += kStep) {
+    const int k0 = t * 32;
+    float4 k[KJ];
+    float v[DB][16];
+    if constexpr (kPrefetch) {
+#pragma unroll
+      for (int j = 0; j < KJ; ++j) k[j] = kn[j];
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[ob][i] = vn[ob][i];
+      if (t + kStep < tile_last) load_k(k0 + 32 * kStep, kn), load_v(k0 + 32 * kStep, vn);
+    } else {
+      load_k(k0, k);
+    }
+    f32x16 s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      if (8 * j < dh) {  // uniform
+        s = mfma_f32(k[j].x, q[j].x, s), s = mfma_f32(k[j].y, q[j].y, s);
+        s = mfma_f32(k[j].z, q[j].z, s), s = mfma_f32(k[j].w, q[j].w, s);
       }
-      S[idx] = s;
+    }
+    if constexpr (!kPrefetch) load_v(k0, v);
+    // register i of this lane is key k0 + 8 (i / 4) + 4g + i % 4
+    if (k0 + 32 > klen) {  // uniform
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + 8 * (i >> 2) + 4 * g + (i & 3) >= klen) s[i] = PHI == kPhiSoftmax ? -INFINITY : 0.f;  // (SiLU(0) = 0)
+    }
+    if (PHI == kPhiSoftmax) {
+      float tmax = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
+      const float new_max = fmaxf(run_max, pair_max(tmax));  // finite: the tile holds at least one valid key
+      const float alpha = expf(run_max - new_max);           // run_max = -inf on the first tile -> 0
+      float psum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = expf(s[i] - new_max), psum += s[i];  // masked logits are -inf -> 0
+      run_sum = run_sum * alpha + psum;
+      run_max = new_max;
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[ob][i] *= alpha;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = s[i] / (1.f + expf(-s[i]));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (k0 + 8 * j < klen) {  // uniform: eight keys of which at least one is valid
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int ob = 0; ob < DB; ++ob)
+            if (32 * ob < dh) acc[ob] = mfma_f32(v[ob][4 * j + r], s[4 * j + r], acc[ob]);
+      }
+    }
+  }
+  float total = pair_sum(run_sum);
+
+  if constexpr (SPLIT) {
+    // the four waves' states: the common maximum first, then the sums in wave order
+    constexpr int kState = (DB * 16 + 2) * 64;
+    if (wave > 0) {
+      float* mine = red + (wave - 1) * kState + lane;
+      mine[0] = run_max, mine[64] = total;
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine[(2 + ob * 16 + i) * 64] = acc[ob][i];
     }
     __syncthreads();
-    // phi: 16 lanes share one query row
-    {
-      const int i = tid / 16, l = tid % 16;
-      float v[KT / 16];
+    if (wave > 0) return;
+    float mx = run_max, w[4];
+    if (PHI == kPhiSoftmax) {
 #pragma unroll
-      for (int u = 0; u < KT / 16; ++u) v[u] = S[i * KT + l + 16 * u];
+      for (int o = 0; o < 3; ++o) mx = fmaxf(mx, red[o * kState + lane]);
+      w[0] = run_max == -INFINITY ? 0.f : expf(run_max - mx);
+#pragma unroll
+      for (int o = 0; o < 3; ++o) w[o + 1] = red[o * kState + lane] == -INFINITY ? 0.f : expf(red[o * kState + lane] - mx);
+      total *= w[0];
+#pragma unroll
+      for (int o = 0; o < 3; ++o) total = fmaf(w[o + 1], red[o * kState + 64 + lane], total);
+      run_max = mx;
+    } else {
+#pragma unroll
+      for (int o = 0; o < 4; ++o) w[o] = 1.f;
+    }
+#pragma unroll
+    for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[ob][i] *= w[0];
+#pragma unroll
+        for (int o = 0; o < 3; ++o) acc[ob][i] = fmaf(w[o + 1], red[o * kState + (2 + ob * 16 + i) * 64 + lane], acc[ob][i]);
+      }
+  }
+
+  // lane (query n, g) holds head columns 32 ob + 8 j + 4 g + r in register 4 j + r
+  const int row = q0 + n;
+  if (row >= a.q_rows) return;
+  if (SPLIT && a.chunks > 1) {
+    const int64_t slot = (static_cast<int64_t>(b) * a.chunks + chunk) * a.q_rows + row;
+    float* dst = a.part_acc + slot * d + head * dh;
+#pragma unroll
+    for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int t = 32 * ob + 8 * j + 4 * g + r;
+          if (t < dh) dst[t] = acc[ob][4 * j + r];
+        }
+    if (g == 0) {
+      float* ml = a.part_ml + (slot * a.h + head) * 2;
+      ml[0] = run_max, ml[1] = total;
+    }
+    return;
+  }
+  const bool live = row < qlen && klen > 0;
+  const float inv = PHI == kPhiSoftmax ? total : static_cast<float>(klen);
+  OutT* orow = static_cast<OutT*>(a.O) + (static_cast<int64_t>(b) * a.q_rows + row) * d + head * dh;
+#pragma unroll
+  for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int t = 32 * ob + 8 * j + 4 * g + r;
+        if (t < dh) store_as(orow + t, live ? acc[ob][4 * j + r] / inv : 0.f);
+      }
+}
+
+// The chunks' states combined in ascending order, one thread per output element.
+template <typename OutT, int PHI>
+__global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
+  const int b = blockIdx.y;
+  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (idx >= static_cast<int64_t>(a.q_rows) * a.d) return;
+  const int row = static_cast<int>(idx / a.d), col = static_cast<int>(idx % a.d), head = col / a.dh;
+  const int qlen = a.q_lens ? min(a.q_lens[b], a.q_rows) : a.q_rows;
+  const int klen = a.k_lens ? min(a.k_lens[b], a.n_keys) : a.n_keys;
+  const int used = (klen + 32 * kChunkTiles - 1) / (32 * kChunkTiles);
+  float out = 0.f;
+  if (used > 0 && row < qlen) {
+    const int64_t slot0 = static_cast<int64_t>(b) * a.chunks * a.q_rows + row;
+    float mx = -INFINITY, num = 0.f, den = 0.f;
+    if (PHI == kPhiSoftmax)
+      for (int c = 0; c < used; ++c) mx = fmaxf(mx, a.part_ml[((slot0 + static_cast<int64_t>(c) * a.q_rows) * a.h + head) * 2]);
+    for (int c = 0; c < used; ++c) {
+      const int64_t slot = slot0 + static_cast<int64_t>(c) * a.q_rows;
+      const float x = a.part_acc[slot * a.d + col];
       if (PHI == kPhiSoftmax) {
-        float cmax = v[0];
-#pragma unroll
-        for (int u = 1; u < KT / 16; ++u) cmax = fmaxf(cmax, v[u]);
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off, 16));
-        const float old_max = row_max[i];
-        const float new_max = fmaxf(old_max, cmax);  // finite: the block holds at least one valid key
-        float csum = 0.f;
-#pragma unroll
-        for (int u = 0; u < KT / 16; ++u) {
-          v[u] = expf(v[u] - new_max);  // masked logits are -inf -> 0
-          csum += v[u];
-        }
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) csum += __shfl_xor(csum, off, 16);
-        const float alpha = expf(old_max - new_max);  // old_max = -inf on the first block -> 0
-        if (l == 0) {
-          row_max[i] = new_max;
-          row_sum[i] = row_sum[i] * alpha + csum;
-          row_alpha[i] = alpha;
-        }
+        const float w = expf(a.part_ml[(slot * a.h + head) * 2] - mx);
+        num = fmaf(w, x, num), den = fmaf(w, a.part_ml[(slot * a.h + head) * 2 + 1], den);
       } else {
-#pragma unroll
-        for (int u = 0; u < KT / 16; ++u) {
-          const bool valid = l + 16 * u < kn;
-          v[u] = valid ? v[u] / (1.f + expf(-v[u])) : 0.f;
-        }
-        if (l == 0) row_alpha[i] = 1.f;
-      }
-#pragma unroll
-      for (int u = 0; u < KT / 16; ++u) S[i * KT + l + 16 * u] = v[u];
-    }
-    __syncthreads();
-    // weighted sum of the value rows
-#pragma unroll
-    for (int u = 0; u < MAXOUT; ++u) {
-      const int o = tid + u * 256;
-      if (o < QT * dh) {
-        const int i = o / dh, t = o % dh;
-        float x = acc[u] * row_alpha[i];
-        const float* w = S + i * KT;
-        const float* vr = Vb + static_cast<int64_t>(k0) * d + t;
-        for (int j = 0; j < kn; ++j) x = fmaf(w[j], vr[static_cast<int64_t>(j) * d], x);
-        acc[u] = x;
+        num += x;
       }
     }
-    __syncthreads();
+    out = num / (PHI == kPhiSoftmax ? den : static_cast<float>(klen));
   }
+  store_as(static_cast<OutT*>(a.O) + static_cast<int64_t>(b) * a.q_rows * a.d + idx, out);
+}
 
-  OutT* Ob = static_cast<OutT*>(a.O) + (static_cast<int64_t>(b) * a.q_rows) * d + head * dh;
-#pragma unroll
-  for (int u = 0; u < MAXOUT; ++u) {
-    const int o = tid + u * 256;
-    if (o < QT * dh) {
-      const int i = o / dh, t = o % dh, row = q0 + i;
-      if (row >= a.q_rows) continue;
-      float x = 0.f;
-      if (row < qlen && klen > 0) x = PHI == kPhiSoftmax ? acc[u] / row_sum[i] : acc[u] / static_cast<float>(klen);
-      store_as(Ob + static_cast<int64_t>(row) * d + t, x);
-    }
+// (split the keys over a workgroup's waves, chunks) of an attention: rules on what fills the compute units, never on
+// the number of keys a user has, so that a user's result does not depend on the others' lengths.
+struct AttnSplit {
+  bool split;
+  int chunks;
+};
+AttnSplit attention_split(int64_t B, int64_t q_rows, int64_t n_keys, int64_t h) {
+  const int64_t units = B * h * ((q_rows + 31) / 32);  // (user, head, query tile)
+  const int cus = compute_units();
+  if (units >= 4 * static_cast<int64_t>(cus)) return {false, 1};  // a wave per SIMD without splitting
+  if (units >= cus) return {true, 1};                             // a workgroup per compute unit
+  return {true, static_cast<int>((n_keys + 32 * kChunkTiles - 1) / (32 * kChunkTiles))};
+}
+
+template <typename OutT, int PHI, int DB, bool VEC>
+hipError_t launch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
+  const int units = dev.q_tiles * dev.h;
+  if (split)
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, DB, true, VEC>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
+  else
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, DB, false, VEC>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
+  if (dev.chunks > 1) {
+    const int64_t total = static_cast<int64_t>(dev.q_rows) * dev.d;
+    hipLaunchKernelGGL((attention_merge_kernel<OutT, PHI>), dim3(static_cast<unsigned>((total + 255) / 256), B), dim3(256), 0, s, dev);
   }
+  return hipGetLastError();
 }
 
 template <typename OutT, int PHI>
-hipError_t launch_attention(const AttnDev& dev, int B, int h, hipStream_t s) {
-  const size_t smem = (static_cast<size_t>(QT) * dev.dh + QT * KT + 3 * QT) * sizeof(float);
-  dim3 grid((dev.q_rows + QT - 1) / QT, h, B);
-  hipLaunchKernelGGL((attention_kernel<OutT, PHI>), grid, dim3(256), smem, s, dev);
-  return hipGetLastError();
+hipError_t dispatch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
+  // (d is then a multiple of 4 too)
+  const bool vec = dev.dh % 4 == 0 && ((reinterpret_cast<uintptr_t>(dev.Q) | reinterpret_cast<uintptr_t>(dev.K)) & 15u) == 0;
+#define LIME_ATTN_CASE(DB)                                                        \
+  if (dev.dh <= 32 * DB)                                                          \
+    return vec ? launch_attention<OutT, PHI, DB, true>(dev, B, split, s) : launch_attention<OutT, PHI, DB, false>(dev, B, split, s);
+  LIME_ATTN_CASE(1) LIME_ATTN_CASE(2) LIME_ATTN_CASE(4) LIME_ATTN_CASE(8)
+#undef LIME_ATTN_CASE
+  return hipErrorInvalidValue;
 }
 
 // ----------------------------------------------------------------------------- QK cache (Section 3.3)
@@ -288,25 +557,27 @@ hipError_t generic_cached_sum(const void* W, const int32_t* ids, int n_items, co
   return hipGetLastError();
 }
 
-hipError_t generic_project(const void* X, const void* W, float* Y, int64_t rows, int d, int dtype, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if (W == nullptr) {
-    const int64_t n = rows * d;
-    dim3 grid(static_cast<unsigned>((n + 255) / 256));
-    if (dtype == 0)
-      hipLaunchKernelGGL(upcast_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(X), Y, n);
-    else
-      hipLaunchKernelGGL(upcast_kernel<bf16_t>, grid, dim3(256), 0, s, static_cast<const bf16_t*>(X), Y, n);
-    return hipGetLastError();
+hipError_t generic_project(const Projection* jobs, int n, int d, int dtype, hipStream_t s) {
+  if (n > kMaxProjections) return hipErrorInvalidValue;
+  ProjectArgs a{};
+  a.d = d;
+  const int tn = d <= 32 ? 32 : 64, tm = 4096 / tn;
+  bool vec = d % 8 == 0;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const Projection& j = jobs[i];
+    if (j.rows <= 0) continue;
+    const int k = a.n++;
+    a.X[k] = j.X, a.W[k] = j.W, a.Y[k] = j.Y, a.lens[k] = j.lens, a.rows[k] = j.rows;
+    a.rows_per_user[k] = j.rows_per_user > 0 ? j.rows_per_user : 1;
+    a.first_tile[k] = static_cast<int>(tiles);
+    vec = vec && ((reinterpret_cast<uintptr_t>(j.X) | reinterpret_cast<uintptr_t>(j.W)) & 15u) == 0;
+    tiles += (j.rows + tm - 1) / tm * ((d + tn - 1) / tn);
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    a.first_tile[k + 1] = static_cast<int>(tiles);
   }
-  dim3 grid(static_cast<unsigned>((rows + PT - 1) / PT), (d + PT - 1) / PT);
-  if (dtype == 0)
-    hipLaunchKernelGGL(project_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(X),
-                       static_cast<const float*>(W), Y, rows, d);
-  else
-    hipLaunchKernelGGL(project_kernel<bf16_t>, grid, dim3(256), 0, s, static_cast<const bf16_t*>(X),
-                       static_cast<const bf16_t*>(W), Y, rows, d);
-  return hipGetLastError();
+  if (tiles == 0) return hipSuccess;
+  return dtype == 0 ? launch_project<float>(a, static_cast<int>(tiles), vec, s) : launch_project<bf16_t>(a, static_cast<int>(tiles), vec, s);
 }
 
 namespace {
@@ -354,11 +625,13 @@ hipError_t gated_block_typed(const GenericGatedBlock& g, hipStream_t s) {
   const int64_t total = static_cast<int64_t>(g.B) * g.rows * g.d;
   const dim3 grid(static_cast<unsigned>((total + 255) / 256));
   const bool shared = g.x_user_stride == 0;
-  hipError_t e = generic_project(g.X, g.Wu, g.P, shared ? g.rows : static_cast<int64_t>(g.B) * g.rows, g.d, g.dtype, s);
+  const Projection gate{g.X, g.Wu, g.P, shared ? g.rows : static_cast<int64_t>(g.B) * g.rows};
+  hipError_t e = generic_project(&gate, 1, g.d, g.dtype, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(gate_kernel<T>, grid, dim3(256), 0, s, g.P, shared ? int64_t{0} : static_cast<int64_t>(g.rows) * g.d,
                      static_cast<const T*>(g.A), g.lens, static_cast<T*>(g.Z), g.rows, g.d, total);
-  e = generic_project(g.Z, g.Wo, g.P, static_cast<int64_t>(g.B) * g.rows, g.d, g.dtype, s);
+  const Projection out{g.Z, g.Wo, g.P, static_cast<int64_t>(g.B) * g.rows};
+  e = generic_project(&out, 1, g.d, g.dtype, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(residual_kernel<T>, grid, dim3(256), 0, s, g.P, static_cast<const T*>(g.X), g.x_user_stride, g.lens,
                      static_cast<T*>(g.Y), g.sum_in, g.sum_out, static_cast<T*>(g.sum_rounded), g.rows, g.d, total);
@@ -372,15 +645,29 @@ hipError_t generic_gated_block(const GenericGatedBlock& g, hipStream_t s) {
   return g.dtype == 0 ? gated_block_typed<float>(g, s) : gated_block_typed<bf16_t>(g, s);
 }
 
+size_t generic_attention_scratch(int64_t B, int64_t q_rows, int64_t n_keys, int64_t d, int64_t h) {
+  const AttnSplit sp = attention_split(B, q_rows, n_keys, h);
+  if (sp.chunks <= 1) return 0;
+  return align_up(static_cast<size_t>(B) * sp.chunks * q_rows * d * sizeof(float)) +
+         align_up(static_cast<size_t>(B) * sp.chunks * q_rows * h * 2 * sizeof(float));
+}
+
 hipError_t generic_attention(const GenericAttention& a, hipStream_t s) {
   if (a.B <= 0 || a.q_rows <= 0) return hipSuccess;
+  AttnSplit sp = attention_split(a.B, a.q_rows, a.n_keys, a.h);
+  if (a.scratch == nullptr) sp.chunks = 1;
   AttnDev dev{a.Q, a.K, a.V, a.q_user_stride, a.k_user_stride, a.v_user_stride, a.O, a.q_lens, a.k_lens,
-              a.q_rows, a.n_keys, a.d, a.d / a.h, a.scale};
+              a.q_rows, a.n_keys, a.d, a.d / a.h, (a.q_rows + 31) / 32, a.h, sp.chunks, a.scale, nullptr, nullptr};
+  if (sp.chunks > 1) {
+    dev.part_acc = static_cast<float*>(a.scratch);
+    dev.part_ml = reinterpret_cast<float*>(static_cast<char*>(a.scratch) +
+                                           align_up(static_cast<size_t>(a.B) * sp.chunks * a.q_rows * a.d * sizeof(float)));
+  }
   if (a.dtype == 0)
-    return a.phi == kPhiSoftmax ? launch_attention<float, kPhiSoftmax>(dev, a.B, a.h, s)
-                                : launch_attention<float, kPhiSilu>(dev, a.B, a.h, s);
-  return a.phi == kPhiSoftmax ? launch_attention<bf16_t, kPhiSoftmax>(dev, a.B, a.h, s)
-                              : launch_attention<bf16_t, kPhiSilu>(dev, a.B, a.h, s);
+    return a.phi == kPhiSoftmax ? dispatch_attention<float, kPhiSoftmax>(dev, a.B, sp.split, s)
+                                : dispatch_attention<float, kPhiSilu>(dev, a.B, sp.split, s);
+  return a.phi == kPhiSoftmax ? dispatch_attention<bf16_t, kPhiSoftmax>(dev, a.B, sp.split, s)
+                              : dispatch_attention<bf16_t, kPhiSilu>(dev, a.B, sp.split, s);
 }
 
 }  // namespace lime

@@ -625,3 +625,20 @@ def test_random_shapes_all_paths():
               f"lens={None if w.lens is None else w.lens.tolist()}", flush=True)
         for name, (got, ref) in run_all_paths(w, xor_scale=w.softmax_scale if case % 2 else 1.0).items():
             assert_close(got, ref, dtype, f"case {case} {name}")
+
+
+@pytest.mark.parametrize("B,N,C,d,h,m,dtype", [
+    (1, 2500, 70, 36, 1, 9, "fp32"),    # keys cut into chunks (the last one short); a head width that is no multiple of 8
+    (1, 1025, 1, 10, 2, 33, "fp32"),    # one key in the second chunk, one query; heads of width 5 (no 16-byte reads)
+    (40, 40, 900, 64, 8, 31, "bf16"),   # candidates without the split over waves, one key short of a tile
+    (9, 1030, 300, 96, 1, 70, "fp32"),  # three blocks of head columns
+    (3, 31, 129, 32, 4, 16, "bf16"),    # tiles of 128 rows and 32 columns in the projections, one row past a tile
+])
+def test_general_kernels_at_their_edges(B, N, C, d, h, m, dtype):
+    w = _sharp(workload=70 + m, B=B, N=N, C=C, d=d, h=h, m=m, dtype=dtype, len_range=(max(1, N // 3), N), pad_value=np.nan)
+    _check_all(w)
+    g = DeviceWorkload(w)
+    s = w.softmax_scale
+    LP, O = binding.lime_request(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, g.T, g.L, g.Wq, g.Wk, g.Wv, h, s, s)
+    LP2 = binding.lime_link_history(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, h, s)
+    assert torch.equal(LP, LP2) and torch.equal(O, binding.lime_score_candidates(g.T, g.L, LP2, g.Wq, g.Wk, g.Wv, h, s))
