@@ -11,6 +11,7 @@
 // k = 8j + i and 8j + 4 + i, i = 0..3, a lane's operands of four instructions are four consecutive floats, one 16-byte
 // load; and a D block is, register by register, the B operand of a product that sums over its rows.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "mfma.hpp"
@@ -195,11 +196,13 @@ struct AttnDev {
   float *part_acc, *part_ml;  // chunks > 1: [B][chunks][q_rows][d], [B][chunks][q_rows][h][2] (running max, running sum)
 };
 
-// DB: 32-column blocks of the head's output (d/h <= 32 DB).  VEC: d/h is a multiple of 4 (16-byte reads of Q and K rows).
-template <typename OutT, int PHI, int DB, bool SPLIT, bool VEC>
+// KJ: groups of eight head columns (d/h <= 8 KJ; the columns past d/h are zeros in Q and K).  VEC: d/h is a multiple of 4
+// and the rows are 16-byte aligned.  Loads carry no condition: a test per load costs a branch and the copies of a join
+// (12.9 -> 6 us for the 16 links of a one-user request at d/h = 64).
+template <typename OutT, int PHI, int KJ, bool SPLIT, bool VEC>
 __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
-  constexpr int KJ = DB * 4;  // groups of eight head columns
-  constexpr bool kPrefetch = DB <= 2;  // the next tile's K and V in flight during the current one (registers permitting)
+  constexpr int DB = (KJ + 3) / 4;     // 32-column blocks of the head's output
+  constexpr bool kPrefetch = KJ <= 8;  // the next tile's K and V in flight during the current one (registers permitting)
   __shared__ float red[SPLIT ? 3 * (DB * 16 + 2) * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, g = lane >> 5;
   const int b = blockIdx.z, d = a.d, dh = a.dh;
@@ -216,37 +219,51 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   constexpr int kStep = SPLIT ? 4 : 1;
   const bool dead = q0 >= qlen;  // only rows that are written as zeros
 
-  auto load4 = [&](const float* p, int k) {  // head columns k .. k + 3, zeros past the head's width
-    if constexpr (VEC) return k < dh ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 v;
-    v.x = k < dh ? p[k] : 0.f, v.y = k + 1 < dh ? p[k + 1] : 0.f, v.z = k + 2 < dh ? p[k + 2] : 0.f, v.w = k + 3 < dh ? p[k + 3] : 0.f;
-    return v;
-  };
-  float4 q[KJ];
-  {
-    const float* qrow = a.Q + b * a.qs + static_cast<int64_t>(min(q0 + n, a.q_rows - 1)) * d + head * dh;
+  // head columns 8j + 4g .. + 3 of a row, zeros past the head's width (read from its last columns instead)
+  auto load_row = [&](const float* row, float4 (&x)[KJ]) {
 #pragma unroll
     for (int j = 0; j < KJ; ++j) {
-      q[j] = load4(qrow, 8 * j + 4 * g);
-      q[j].x *= a.scale, q[j].y *= a.scale, q[j].z *= a.scale, q[j].w *= a.scale;
+      const int k = 8 * j + 4 * g;
+      if constexpr (VEC) {
+        x[j] = *reinterpret_cast<const float4*>(row + min(k, dh - 4));
+      } else {
+        x[j] = make_float4(row[min(k, dh - 1)], row[min(k + 1, dh - 1)], row[min(k + 2, dh - 1)], row[min(k + 3, dh - 1)]);
+      }
     }
-  }
+  };
+  auto zero_past = [&](float4 (&x)[KJ]) {
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      const int k = 8 * j + 4 * g;
+      if (k >= dh) x[j].x = 0.f;
+      if (k + 1 >= dh) x[j].y = 0.f;
+      if (k + 2 >= dh) x[j].z = 0.f;
+      if (k + 3 >= dh) x[j].w = 0.f;
+    }
+  };
+  float4 q[KJ];
+  load_row(a.Q + b * a.qs + static_cast<int64_t>(min(q0 + n, a.q_rows - 1)) * d + head * dh, q);
   const float* Kb = a.K + b * a.ks + head * dh;
   const float* Vb = a.V + b * a.vs + head * dh;
   // rows past the last valid key are read from it instead: their weights are zero
-  auto load_k = [&](int k0, float4 (&k)[KJ]) {
-    const float* krow = Kb + static_cast<int64_t>(min(k0 + n, klen - 1)) * d;
+  auto load_k = [&](int k0, float4 (&k)[KJ]) { load_row(Kb + static_cast<int64_t>(min(k0 + n, klen - 1)) * d, k); };
+  int vcol[DB];
 #pragma unroll
-    for (int j = 0; j < KJ; ++j)
-      if (8 * j < dh) k[j] = load4(krow, 8 * j + 4 * g);
-  };
+  for (int ob = 0; ob < DB; ++ob) vcol[ob] = min(32 * ob + n, dh - 1);
   auto load_v = [&](int k0, float (&v)[DB][16]) {
+    if (k0 + 32 <= klen) {  // uniform: a scalar row base plus a lane offset that never changes
+      const float* base = Vb + static_cast<int64_t>(k0) * d;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float* vrow = Vb + static_cast<int64_t>(min(k0 + 8 * (i >> 2) + 4 * g + (i & 3), klen - 1)) * d;
+      for (int i = 0; i < 16; ++i)
 #pragma unroll
-      for (int ob = 0; ob < DB; ++ob)
-        if (32 * ob < dh) v[ob][i] = vrow[min(32 * ob + n, dh - 1)];
+        for (int ob = 0; ob < DB; ++ob) v[ob][i] = (base + static_cast<int64_t>(8 * (i >> 2) + (i & 3)) * d)[4 * g * d + vcol[ob]];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float* vrow = Vb + static_cast<int64_t>(min(k0 + 8 * (i >> 2) + 4 * g + (i & 3), klen - 1)) * d;
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) v[ob][i] = vrow[vcol[ob]];
+      }
     }
   };
   f32x16 acc[DB];
@@ -259,7 +276,11 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   float vn[kPrefetch ? DB : 1][16];
   if constexpr (kPrefetch) {
     if (!dead && tile_first < tile_last) load_k(tile_first * 32, kn), load_v(tile_first * 32, vn);
+    __builtin_amdgcn_sched_barrier(0);
   }
+  if (8 * KJ != dh) zero_past(q);  // uniform; a zero in Q leaves whatever K has there out of the sum
+#pragma unroll
+  for (int j = 0; j < KJ; ++j) q[j].x *= a.scale, q[j].y *= a.scale, q[j].z *= a.scale, q[j].w *= a.scale;
   for (int t = tile_first; t < tile_last && !dead; t += kStep) {
     const int k0 = t * 32;
     float4 k[KJ];
@@ -280,10 +301,8 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
     for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < KJ; ++j) {
-      if (8 * j < dh) {  // uniform
-        s = mfma_f32(k[j].x, q[j].x, s), s = mfma_f32(k[j].y, q[j].y, s);
-        s = mfma_f32(k[j].z, q[j].z, s), s = mfma_f32(k[j].w, q[j].w, s);
-      }
+      s = mfma_f32(k[j].x, q[j].x, s), s = mfma_f32(k[j].y, q[j].y, s);
+      s = mfma_f32(k[j].z, q[j].z, s), s = mfma_f32(k[j].w, q[j].w, s);
     }
     if constexpr (!kPrefetch) load_v(k0, v);
     // register i of this lane is key k0 + 8 (i / 4) + 4g + i % 4
@@ -312,15 +331,9 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       for (int i = 0; i < 16; ++i) s[i] = s[i] / (1.f + expf(-s[i]));
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (k0 + 8 * j < klen) {  // uniform: eight keys of which at least one is valid
+    for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int ob = 0; ob < DB; ++ob)
-            if (32 * ob < dh) acc[ob] = mfma_f32(v[ob][4 * j + r], s[4 * j + r], acc[ob]);
-      }
-    }
+      for (int ob = 0; ob < DB; ++ob) acc[ob] = mfma_f32(v[ob][i], s[i], acc[ob]);
   }
   float total = pair_sum(run_sum);
 
@@ -363,6 +376,24 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   }
 
   // lane (query n, g) holds head columns 32 ob + 8 j + 4 g + r in register 4 j + r
+  auto store4 = [&](auto* dst, int t, const f32x16& x, int j, float f) {
+    using D = std::remove_reference_t<decltype(*dst)>;
+    if constexpr (VEC) {
+      if (t >= dh) return;
+      if constexpr (sizeof(D) == 4) {
+        *reinterpret_cast<float4*>(dst + t) = make_float4(x[4 * j] * f, x[4 * j + 1] * f, x[4 * j + 2] * f, x[4 * j + 3] * f);
+      } else {
+        bf16x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = static_cast<__bf16>(x[4 * j + r] * f);
+        *reinterpret_cast<bf16x4*>(dst + t) = v;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (t + r < dh) store_as(dst + t + r, x[4 * j + r] * f);
+    }
+  };
   const int row = q0 + n;
   if (row >= a.q_rows) return;
   if (SPLIT && a.chunks > 1) {
@@ -371,12 +402,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
 #pragma unroll
     for (int ob = 0; ob < DB; ++ob)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = 32 * ob + 8 * j + 4 * g + r;
-          if (t < dh) dst[t] = acc[ob][4 * j + r];
-        }
+      for (int j = 0; j < 4; ++j) store4(dst, 32 * ob + 8 * j + 4 * g, acc[ob], j, 1.f);
     if (g == 0) {
       float* ml = a.part_ml + (slot * a.h + head) * 2;
       ml[0] = run_max, ml[1] = total;
@@ -384,17 +410,17 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
     return;
   }
   const bool live = row < qlen && klen > 0;
-  const float inv = PHI == kPhiSoftmax ? total : static_cast<float>(klen);
+  const float inv = live ? 1.f / (PHI == kPhiSoftmax ? total : static_cast<float>(klen)) : 0.f;
   OutT* orow = static_cast<OutT*>(a.O) + (static_cast<int64_t>(b) * a.q_rows + row) * d + head * dh;
 #pragma unroll
   for (int ob = 0; ob < DB; ++ob)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      if (!live)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = 32 * ob + 8 * j + 4 * g + r;
-        if (t < dh) store_as(orow + t, live ? acc[ob][4 * j + r] / inv : 0.f);
-      }
+        for (int r = 0; r < 4; ++r) acc[ob][4 * j + r] = 0.f;
+      store4(orow, 32 * ob + 8 * j + 4 * g, acc[ob], j, inv);
+    }
 }
 
 // The chunks' states combined in ascending order, one thread per output element.
@@ -442,13 +468,13 @@ AttnSplit attention_split(int64_t B, int64_t q_rows, int64_t n_keys, int64_t h) 
   return {true, static_cast<int>((n_keys + 32 * kChunkTiles - 1) / (32 * kChunkTiles))};
 }
 
-template <typename OutT, int PHI, int DB, bool VEC>
+template <typename OutT, int PHI, int KJ, bool VEC>
 hipError_t launch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
   const int units = dev.q_tiles * dev.h;
   if (split)
-    hipLaunchKernelGGL((attention_kernel<OutT, PHI, DB, true, VEC>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, true, VEC>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
   else
-    hipLaunchKernelGGL((attention_kernel<OutT, PHI, DB, false, VEC>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, false, VEC>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
   if (dev.chunks > 1) {
     const int64_t total = static_cast<int64_t>(dev.q_rows) * dev.d;
     hipLaunchKernelGGL((attention_merge_kernel<OutT, PHI>), dim3(static_cast<unsigned>((total + 255) / 256), B), dim3(256), 0, s, dev);
@@ -458,12 +484,16 @@ hipError_t launch_attention(const AttnDev& dev, int B, bool split, hipStream_t s
 
 template <typename OutT, int PHI>
 hipError_t dispatch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
-  // (d is then a multiple of 4 too)
-  const bool vec = dev.dh % 4 == 0 && ((reinterpret_cast<uintptr_t>(dev.Q) | reinterpret_cast<uintptr_t>(dev.K)) & 15u) == 0;
-#define LIME_ATTN_CASE(DB)                                                        \
-  if (dev.dh <= 32 * DB)                                                          \
-    return vec ? launch_attention<OutT, PHI, DB, true>(dev, B, split, s) : launch_attention<OutT, PHI, DB, false>(dev, B, split, s);
-  LIME_ATTN_CASE(1) LIME_ATTN_CASE(2) LIME_ATTN_CASE(4) LIME_ATTN_CASE(8)
+  const bool vec = dev.dh % 4 == 0 &&
+                   ((reinterpret_cast<uintptr_t>(dev.Q) | reinterpret_cast<uintptr_t>(dev.K) | reinterpret_cast<uintptr_t>(dev.O)) & 15u) == 0;
+#define LIME_ATTN_CASE(KJ, VEC) \
+  if (dev.dh <= 8 * KJ) return launch_attention<OutT, PHI, KJ, VEC>(dev, B, split, s);
+  if (vec) {
+    LIME_ATTN_CASE(1, true) LIME_ATTN_CASE(2, true) LIME_ATTN_CASE(4, true)
+    LIME_ATTN_CASE(8, true) LIME_ATTN_CASE(16, true) LIME_ATTN_CASE(32, true)
+  } else {
+    LIME_ATTN_CASE(4, false) LIME_ATTN_CASE(32, false)
+  }
 #undef LIME_ATTN_CASE
   return hipErrorInvalidValue;
 }
