@@ -1,10 +1,14 @@
-"""ctypes binding of liblime_hip.so: argument marshalling only.
+"""Binding of liblime_hip.so: argument marshalling only.
 
 Every function here has the name and the meaning of the C entry point it calls
 (see include/lime.h); tensors are torch CUDA tensors whose device pointers are
 handed through, work goes onto torch's current stream.  There is no fallback:
 if the library has not been built, or a call returns a non-zero status, an
 exception is raised.
+
+The calls a program makes per request go through the extension _lime_torch
+(csrc/host/torch_calls.cpp: checks, output allocation, workspace, device guard and
+marshalling in native code); the rest, and the C symbols themselves, through ctypes.
 """
 
 from __future__ import annotations
@@ -89,6 +93,7 @@ SIGNATURES.update({
 })
 
 _lib = None
+_native_module = None
 
 
 class LimeError(RuntimeError):
@@ -110,6 +115,21 @@ def lib() -> ctypes.CDLL:
             fn.restype, fn.argtypes = res, args
         _lib = handle
     return _lib
+
+
+def _native():
+    """The extension with the per-request calls; raises if it has not been built."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        try:
+            from . import _lime_torch
+        except ImportError as e:
+            raise RuntimeError("paper_2510_18239_amd/_lime_torch.so is missing or does not load: build it first "
+                               "(python paper_2510_18239_amd/build.py); there is no fallback") from e
+        _lime_torch.set_error_type(LimeError)
+        _native_module = _lime_torch
+    return _native_module
 
 
 def last_error() -> str:
@@ -180,10 +200,6 @@ def _check(*tensors):
     return first
 
 
-_workspaces: dict = {}
-_outgrown: list = []
-
-
 def _stream(stream):
     s = stream if stream is not None else torch.cuda.current_stream()
     return s.cuda_stream
@@ -196,16 +212,8 @@ def get_workspace(nbytes: int, device, stream=None) -> torch.Tensor:
     until the process ends (work already queued on the stream may still use it)."""
     if not isinstance(device, torch.device):
         device = torch.device(device)
-    # (this runs on every call of every wrapper: no device context, one stream query)
-    key = (device.index, stream.cuda_stream if stream is not None else torch.cuda.current_stream(device).cuda_stream)
-    ws = _workspaces.get(key)
-    if ws is None or ws.numel() < nbytes:
-        if ws is not None:
-            _outgrown.append(ws)
-            nbytes = max(nbytes, 2 * ws.numel())
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        _workspaces[key] = ws
-    return ws
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    return _native().workspace(nbytes, index, stream)
 
 
 def _raise(status):
@@ -221,107 +229,30 @@ def _lens_arg(lens, B, device):
     return lens
 
 
-def _history(fn_name, op, E, lens, LC, Wq, Wk, Wv, h, scale, LP, OS, workspace, stream, want_os):
-    first = _check(E, LC, Wq, Wk, Wv, LP, OS)
-    B, N, d = E.shape
-    if LC.dim() == 2:
-        m, stride = LC.shape[0], 0
-    else:
-        if LC.shape[0] != B:
-            raise ValueError("per-user links must be [B, m, d]")
-        m, stride = LC.shape[1], LC.shape[1] * LC.shape[2]
-    lens = _lens_arg(lens, B, E.device)
-    code = _dtype_code(first)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    if want_os and OS is None:
-        OS = torch.empty((B, N, d), dtype=E.dtype, device=E.device)
-    need = workspace_bytes(op, B=B, N=N, d=d, h=h, m=m, dtype=code, flags=1 if want_os else 0)
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    fn = getattr(lib(), fn_name)
-    with torch.cuda.device(E.device):
-        if op == OP_LINK_HISTORY:
-            st = fn(_ptr(E), _ptr(lens), _ptr(LC), stride, _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(LP), B, N, d, h, m,
-                    float(scale), code, _ptr(ws), ws.numel(), _stream(stream))
-        else:
-            st = fn(_ptr(E), _ptr(lens), _ptr(LC), stride, _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(LP), _ptr(OS), B, N, d,
-                    h, m, float(scale), code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return LP, OS
-
-
 def lime_link_history(E, lens, LC, Wq, Wk, Wv, h, scale, LP=None, workspace=None, stream=None):
     """LP[B, m, d] = MHA(LC, E, E) per user, softmax over the valid history rows (Eq. 3)."""
-    return _history("lime_link_history", OP_LINK_HISTORY, E, lens, LC, Wq, Wk, Wv, h, scale, LP, None, workspace,
-                    stream, False)[0]
+    return _native().history(E, lens, LC, Wq, Wk, Wv, h, scale, LP, None, False, False, workspace, stream)[0]
 
 
 def lime_xor_history(E, lens, LC, Wq, Wk, Wv, h, scale=1.0, want_os=False, LP=None, OS=None, workspace=None,
                      stream=None):
     """One XORA layer (Eq. 6-7): returns (O[T] = link states [B, m, d], O[S] [B, N, d] or None)."""
-    return _history("lime_xor_history", OP_XOR_HISTORY, E, lens, LC, Wq, Wk, Wv, h, scale, LP, OS, workspace, stream,
-                    want_os or OS is not None)
+    return _native().history(E, lens, LC, Wq, Wk, Wv, h, scale, LP, OS, want_os or OS is not None, True, workspace, stream)
 
 
 def lime_xor_layers(E, lens, LC, Wq, Wk, Wv, Wu, Wo, h, scale=1.0, LP=None, workspace=None, stream=None):
     """LP[B, m, d] of LIME-XOR with Wu.shape[0] stacked XOR layers (Eq. 8); Wu, Wo [n, d, d] are the gated blocks' weights."""
-    first = _check(E, LC, Wq, Wk, Wv, Wu, Wo, LP)
-    B, N, d = E.shape
-    if LC.dim() == 2:
-        m, stride = LC.shape[0], 0
-    else:
-        if LC.shape[0] != B:
-            raise ValueError("per-user links must be [B, m, d]")
-        m, stride = LC.shape[1], LC.shape[1] * LC.shape[2]
-    if Wu.dim() != 3 or Wu.shape != Wo.shape or tuple(Wu.shape[1:]) != (d, d):
-        raise ValueError("Wu and Wo must both be [n_layers, d, d]")
-    lens = _lens_arg(lens, B, E.device)
-    code = _dtype_code(first)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    need = workspace_bytes(OP_XOR_LAYERS, B=B, N=N, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    with torch.cuda.device(E.device):
-        st = lib().lime_xor_layers(_ptr(E), _ptr(lens), _ptr(LC), stride, _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wu), _ptr(Wo),
-                                   int(Wu.shape[0]), _ptr(LP), B, N, d, h, m, float(scale), code, _ptr(ws), ws.numel(),
-                                   _stream(stream))
-    _raise(st)
-    return LP
+    return _native().xor_layers(E, lens, LC, Wq, Wk, Wv, Wu, Wo, h, scale, LP, workspace, stream)
 
 
 def lime_score_candidates(T, L, LP, Wq, Wk, Wv, h, scale, O=None, workspace=None, stream=None):
     """O[B, C, d] = MHA(T, L, LP) per user, softmax over the m links (Eq. 4); W* may be None (identity)."""
-    first = _check(T, L, LP, Wq, Wk, Wv, O)
-    B, C, d = T.shape
-    m = L.shape[0]
-    code = _dtype_code(first)
-    if O is None:
-        O = torch.empty_like(T)
-    need = workspace_bytes(OP_SCORE_CANDIDATES, B=B, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, T.device, stream)
-    with torch.cuda.device(T.device):
-        st = lib().lime_score_candidates(_ptr(T), _ptr(L), _ptr(LP), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(O), B, C, d,
-                                         h, m, float(scale), code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return O
+    return _native().score_candidates(T, L, LP, Wq, Wk, Wv, h, scale, O, workspace, stream)
 
 
 def mha_target_attention(T, E, lens, Wq, Wk, Wv, h, scale, O=None, workspace=None, stream=None):
     """O[B, C, d] = MHA(T, E, E) per user over the valid history rows (Eq. 1; the baseline)."""
-    first = _check(T, E, Wq, Wk, Wv, O)
-    B, C, d = T.shape
-    N = E.shape[1]
-    lens = _lens_arg(lens, B, E.device)
-    code = _dtype_code(first)
-    if O is None:
-        O = torch.empty_like(T)
-    need = workspace_bytes(OP_MHA_TARGET, B=B, N=N, C=C, d=d, h=h, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, T.device, stream)
-    with torch.cuda.device(T.device):
-        st = lib().mha_target_attention(_ptr(T), _ptr(E), _ptr(lens), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(O), B, C, N,
-                                        d, h, float(scale), code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return O
+    return _native().target_attention(T, E, lens, Wq, Wk, Wv, h, scale, O, workspace, stream)
 
 
 def lime_build_qk_cache(T, L, Wq, Wk, h, scale, W=None, workspace=None, stream=None):
@@ -343,39 +274,13 @@ def lime_build_qk_cache(T, L, Wq, Wk, h, scale, W=None, workspace=None, stream=N
 
 def lime_score_candidates_cached(W, LP, Wv, O=None, workspace=None, stream=None):
     """O[B, C, d] = cached weights W[B, C, h, m] times the projected link states (Section 3.3, online side)."""
-    first = _check(W, LP, Wv, O)
-    B, C, h, m = W.shape
-    d = LP.shape[2]
-    code = _dtype_code(first)
-    if O is None:
-        O = torch.empty((B, C, d), dtype=W.dtype, device=W.device)
-    need = workspace_bytes(OP_SCORE_CACHED, B=B, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, W.device, stream)
-    with torch.cuda.device(W.device):
-        st = lib().lime_score_candidates_cached(_ptr(W), _ptr(LP), _ptr(Wv), _ptr(O), B, C, d, h, m, code, _ptr(ws),
-                                                ws.numel(), _stream(stream))
-    _raise(st)
-    return O
+    return _native().score_cached(W, None, LP, Wv, O, workspace, stream)
 
 
 def lime_score_candidates_gathered(Wtable, ids, LP, Wv, O=None, workspace=None, stream=None):
     """O[B, C, d] from a corpus-wide table of cached weights Wtable[n_items, h, m] and candidate ids [B, C] (int32):
     row ids[b, c] of the table times the projected link states of user b; ids outside the table give zero rows."""
-    first = _check(Wtable, LP, Wv, O)
-    assert ids.dtype == torch.int32 and ids.is_contiguous() and ids.device == Wtable.device, "ids: contiguous int32 on the device"
-    n_items, h, m = Wtable.shape
-    B, C = ids.shape
-    d = LP.shape[2]
-    code = _dtype_code(first)
-    if O is None:
-        O = torch.empty((B, C, d), dtype=Wtable.dtype, device=Wtable.device)
-    need = workspace_bytes(OP_SCORE_CACHED, B=B, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, Wtable.device, stream)
-    with torch.cuda.device(Wtable.device):
-        st = lib().lime_score_candidates_gathered(_ptr(Wtable), _ptr(ids), n_items, _ptr(LP), _ptr(Wv), _ptr(O), B, C, d,
-                                                  h, m, code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return O
+    return _native().score_cached(Wtable, ids, LP, Wv, O, workspace, stream)
 
 
 def lime_prepare(LC, L, Wq_hist, Wk_hist, Wv_hist, Wq_cand, Wk_cand, h, scale_hist, scale_cand, stream=None):
@@ -397,84 +302,24 @@ def lime_prepare(LC, L, Wq_hist, Wk_hist, Wv_hist, Wq_cand, Wk_cand, h, scale_hi
 
 def lime_link_history_prepared(E, lens, prepared, h, m, scale, xor_attention=False, LP=None, workspace=None, stream=None):
     """lime_link_history (or the link states of lime_xor_history) on operands prepared by lime_prepare."""
-    first = _check(E, LP)
-    B, N, d = E.shape
-    code = _dtype_code(first)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    need = workspace_bytes(OP_LINK_HISTORY, B=B, N=N, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    with torch.cuda.device(E.device):
-        st = lib().lime_link_history_prepared(_ptr(E), _ptr(lens), _ptr(prepared), _ptr(LP), B, N, d, h, m, float(scale),
-                                              int(bool(xor_attention)), code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return LP
+    return _native().history_prepared(E, lens, prepared, h, m, scale, xor_attention, LP, workspace, stream)
 
 
 def lime_score_candidates_prepared(T, LP, Wv, prepared, h, scale, O=None, workspace=None, stream=None):
     """lime_score_candidates on operands prepared by lime_prepare (the user's link states LP are projected per call)."""
-    first = _check(T, LP, Wv, O)
-    B, C, d = T.shape
-    m = LP.shape[1]
-    code = _dtype_code(first)
-    if O is None:
-        O = torch.empty_like(T)
-    need = workspace_bytes(OP_SCORE_CANDIDATES, B=B, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, T.device, stream)
-    with torch.cuda.device(T.device):
-        st = lib().lime_score_candidates_prepared(_ptr(T), _ptr(LP), _ptr(Wv), _ptr(prepared), _ptr(O), B, C, d, h, m,
-                                                  float(scale), code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return O
+    return _native().candidates_prepared(T, LP, Wv, prepared, h, scale, O, workspace, stream)
 
 
 def lime_xor_backward(QS, KS, VS, QT, KT, VT, dOT, dOS, lens, h, scale=1.0, workspace=None, stream=None):
     """Gradients of one XORA layer w.r.t. its projected inputs (Appendix H.2): returns (dQS, dKS, dVS, dQT, dKT, dVT)."""
-    first = _check(QS, KS, VS, QT, KT, VT, dOT, dOS)
-    B, N, d = QS.shape
-    m = QT.shape[1]
-    if QT.dim() != 3 or QT.shape[0] != B:
-        raise ValueError("the projected links must be per user: [B, m, d]")
-    code = _dtype_code(first)
-    lens = _lens_arg(lens, B, QS.device)
-    outs = [torch.empty_like(QS) for _ in range(3)] + [torch.empty_like(QT) for _ in range(3)]
-    need = workspace_bytes(OP_XOR_BACKWARD, B=B, N=N, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, QS.device, stream)
-    with torch.cuda.device(QS.device):
-        st = lib().lime_xor_backward(_ptr(QS), _ptr(KS), _ptr(VS), _ptr(QT), _ptr(KT), _ptr(VT), _ptr(dOT), _ptr(dOS),
-                                     _ptr(lens), *[_ptr(o) for o in outs], B, N, m, d, h, float(scale), code, _ptr(ws),
-                                     ws.numel(), _stream(stream))
-    _raise(st)
-    return tuple(outs)
+    return _native().xor_backward(QS, KS, VS, QT, KT, VT, dOT, dOS, lens, h, scale, workspace, stream)
 
 
 def lime_request(E, lens, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, h, scale_hist, scale_cand,
                  xor_attention=False, LP=None, O=None, workspace=None, stream=None):
     """lime_link_history (or the link states of lime_xor_history) followed by lime_score_candidates, as one call; returns (LP, O)."""
-    first = _check(E, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, LP, O)
-    B, N, d = E.shape
-    C = T.shape[1]
-    if LC.dim() == 2:
-        m, stride = LC.shape[0], 0
-    else:
-        if LC.shape[0] != B:
-            raise ValueError("per-user links must be [B, m, d]")
-        m, stride = LC.shape[1], LC.shape[1] * LC.shape[2]
-    code = _dtype_code(first)
-    lens = _lens_arg(lens, B, E.device)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    if O is None:
-        O = torch.empty_like(T)
-    need = workspace_bytes(OP_REQUEST, B=B, N=N, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    with torch.cuda.device(E.device):
-        st = lib().lime_request(_ptr(E), _ptr(lens), _ptr(LC), stride, _ptr(Wq_hist), _ptr(Wk_hist), _ptr(Wv_hist), _ptr(T),
-                                _ptr(L), _ptr(Wq_cand), _ptr(Wk_cand), _ptr(Wv_cand), _ptr(LP), _ptr(O), B, N, C, d, h, m,
-                                float(scale_hist), float(scale_cand), int(bool(xor_attention)), code, _ptr(ws), ws.numel(),
-                                _stream(stream))
-    _raise(st)
-    return LP, O
+    return _native().request(E, lens, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, h, scale_hist, scale_cand,
+                             xor_attention, LP, O, False, workspace, stream)
 
 
 class RequestArgs(ctypes.Structure):
@@ -514,50 +359,14 @@ def lime_request_static(E, lens, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, W
                         xor_attention=False, LP=None, O=None, stream=None):
     """lime_request on the library's own fixed scratch array instead of a workspace; returns (LP, O).  Calls on one
     GPU must not overlap."""
-    first = _check(E, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, LP, O)
-    B, N, d = E.shape
-    C = T.shape[1]
-    if LC.dim() == 2:
-        m, stride = LC.shape[0], 0
-    else:
-        if LC.shape[0] != B:
-            raise ValueError("per-user links must be [B, m, d]")
-        m, stride = LC.shape[1], LC.shape[1] * LC.shape[2]
-    code = _dtype_code(first)
-    lens = _lens_arg(lens, B, E.device)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    if O is None:
-        O = torch.empty_like(T)
-    with torch.cuda.device(E.device):
-        st = lib().lime_request_static(_ptr(E), _ptr(lens), _ptr(LC), stride, _ptr(Wq_hist), _ptr(Wk_hist), _ptr(Wv_hist),
-                                       _ptr(T), _ptr(L), _ptr(Wq_cand), _ptr(Wk_cand), _ptr(Wv_cand), _ptr(LP), _ptr(O), B, N,
-                                       C, d, h, m, float(scale_hist), float(scale_cand), int(bool(xor_attention)), code,
-                                       _stream(stream))
-    _raise(st)
-    return LP, O
+    return _native().request(E, lens, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, h, scale_hist, scale_cand,
+                             xor_attention, LP, O, True, None, stream)
 
 
 def lime_request_prepared(E, lens, T, Wv, prepared, h, m, scale_hist, scale_cand, xor_attention=False, LP=None, O=None,
                           workspace=None, stream=None):
     """lime_link_history_prepared + lime_score_candidates_prepared as one call of three kernels; returns (LP, O)."""
-    first = _check(E, T, Wv, LP, O)
-    B, N, d = E.shape
-    C = T.shape[1]
-    code = _dtype_code(first)
-    lens = _lens_arg(lens, B, E.device)
-    if LP is None:
-        LP = torch.empty((B, m, d), dtype=E.dtype, device=E.device)
-    if O is None:
-        O = torch.empty_like(T)
-    need = workspace_bytes(OP_REQUEST_PREPARED, B=B, N=N, C=C, d=d, h=h, m=m, dtype=code)
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    with torch.cuda.device(E.device):
-        st = lib().lime_request_prepared(_ptr(E), _ptr(lens), _ptr(T), _ptr(Wv), _ptr(prepared), _ptr(LP), _ptr(O), B, N, C,
-                                         d, h, m, float(scale_hist), float(scale_cand), int(bool(xor_attention)), code,
-                                         _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return LP, O
+    return _native().request_prepared(E, lens, T, Wv, prepared, h, m, scale_hist, scale_cand, xor_attention, LP, O, workspace, stream)
 
 
 def lime_layer_norm(X, gamma, beta, eps=1e-5, Y=None, stream=None):
@@ -643,23 +452,4 @@ def scoring_model(L, ctx, hist, cand, ln_hist_q, ln_hist_kv, ln_cand_q, ln_cand_
 def lime_scores(model: ScoringModel, E, lens, EC, T, want_intermediates=False, workspace=None, stream=None):
     """One LIME-MHA request from embeddings to scores (Eq. 2 -> LN -> Eq. 3 -> LN -> Eq. 4 -> interaction network).
     Returns scores [B, C] (fp32), and with want_intermediates also (LC, LP, O)."""
-    first = _check(E, EC, T)
-    B, N, d = E.shape
-    C = T.shape[1]
-    code = _dtype_code(first)
-    lens = _lens_arg(lens, B, E.device)
-    scores = torch.empty((B, C), dtype=torch.float32, device=E.device)
-    LC = LP = O = None
-    if want_intermediates:
-        LC = torch.empty((B, model.m, d), dtype=E.dtype, device=E.device)
-        LP = torch.empty_like(LC)
-        O = torch.empty_like(T)
-    need = int(lib().lime_scores_workspace_bytes(_c.byref(model), B, N, C, code))
-    if need == 0:
-        raise LimeError(1, "lime_scores: the model or the sizes are not valid")
-    ws = workspace if workspace is not None else get_workspace(need, E.device, stream)
-    with torch.cuda.device(E.device):
-        st = lib().lime_scores(_c.byref(model), _ptr(E), _ptr(lens), _ptr(EC), _ptr(T), _ptr(LC), _ptr(LP), _ptr(O), _ptr(scores), B, N,
-                               C, code, _ptr(ws), ws.numel(), _stream(stream))
-    _raise(st)
-    return (scores, LC, LP, O) if want_intermediates else scores
+    return _native().scores(model, E, lens, EC, T, want_intermediates, workspace, stream)

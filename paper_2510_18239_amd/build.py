@@ -1,15 +1,19 @@
-"""Builds the HIP library (gfx950) in-tree: paper_2510_18239_amd/liblime_hip.so."""
+"""Builds the HIP library (gfx950) in-tree, paper_2510_18239_amd/liblime_hip.so, and the extension with the binding's
+per-request calls, paper_2510_18239_amd/_lime_torch.so (host code only)."""
 
 from __future__ import annotations
 
 import concurrent.futures
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblime_hip.so")
 OBJ_DIR = os.path.join(HERE, "_build")
+NATIVE_SRC = os.path.join(CSRC, "host", "torch_calls.cpp")
+NATIVE = os.path.join(HERE, "_lime_torch.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -51,5 +55,24 @@ def build_library(jobs: int = 8, lib: str = LIB, defines: tuple = ()) -> str:
     return lib
 
 
+def build_native() -> str:
+    """Compile and link the binding's extension against torch and the library beside it (built before)."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[x for d in include for x in ("-isystem", d)],
+           NATIVE_SRC, "-o", NATIVE, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10",
+           "-lc10_hip", "-L" + HERE, "-llime_hip", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for {NATIVE_SRC}:\n{r.stdout}\n{r.stderr}")
+    return NATIVE
+
+
 if __name__ == "__main__":
     print(build_library())
+    print(build_native())

@@ -275,3 +275,20 @@ def test_xor_backward_argument_checks():
     assert call(N=0) == 1 and call(m=0) == 1 and call(d=130, h=4) != 0
     assert call(d=512, h=2) == 2 and "64" in binding.last_error()  # d/h = 256: beyond this kernel
     assert binding.workspace_bytes(binding.OP_XOR_BACKWARD, B=2, N=100, d=512, h=2, m=64) == 0
+
+
+def test_per_request_calls_check_their_tensors_before_anything_else():
+    """The extension behind the per-request wrappers: host tensors, a missing tensor and a non-tensor are refused."""
+    import torch
+
+    x = torch.zeros(1, 8, 64)
+    with pytest.raises(ValueError, match="contiguous CUDA"):
+        binding.lime_link_history(x, None, x[0], x[0], x[0], x[0], 2, 1.0)
+    with pytest.raises(ValueError, match="contiguous CUDA"):
+        binding.lime_request(x, None, x[0], x[0], x[0], x[0], x, x[0], None, None, None, 2, 1.0, 1.0)
+    with pytest.raises(ValueError, match="None"):
+        binding.mha_target_attention(x, None, None, x, x, x, 2, 1.0)
+    with pytest.raises(TypeError, match="tensor"):
+        binding.lime_score_candidates(3, x, x, None, None, None, 2, 1.0)
+    with pytest.raises(TypeError):
+        binding.lime_scores(object(), x, None, x, x)
