@@ -78,6 +78,55 @@ __device__ __forceinline__ float group_sum(float x) {
 
 __device__ __forceinline__ float wave_sum(float x) { return pair_sum(group_sum<32>(x)); }
 
+// A 32 x 32 block of a product over 16 NK: one accumulator, k ascending.  Every projection of link rows goes through it,
+// so that an operand has the same bits wherever it is projected.
+template <int NK>
+__device__ __forceinline__ f32x16 project_block(const bf16x8 (&a)[NK], const bf16x8 (&b)[NK]) {
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) acc = mfma32(a[kk], b[kk], acc);
+  return acc;
+}
+
+// Two four-row halves of a chained fragment (rows 4g .. and 8 + 4g ..) as a fragment in natural order (rows 8g ..): the
+// lane halves trade one of theirs.
+__device__ __forceinline__ bf16x8 natural_from_chained(bf16x8 v) {
+  typedef unsigned u32x4_ __attribute__((ext_vector_type(4)));
+  u32x4_ w = __builtin_bit_cast(u32x4_, v);
+  const u32x2 x = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), y = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+  w[0] = x[0], w[1] = y[0], w[2] = x[1], w[3] = y[1];
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+// Layer normalisation of 32 rows held as operand fragments (lane (n, g): columns 16kk + 8g .. + 7 of row n): a lane pair
+// holds a whole row, so its statistics are the lanes' own sums and one exchange.  Mean first, then the centred second
+// moment, in fp32; rounded to bf16 where a normalisation pass of its own would have stored the row.
+template <int D>
+__device__ __forceinline__ void normalise_rows(bf16x8 (&x)[D / 16], const bf16x8 (&gamma)[D / 16], const bf16x8 (&beta)[D / 16], float eps) {
+  float sum = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) sum += static_cast<float>(x[kk][t]);
+  const float mean = pair_sum(sum) * (1.f / D);
+  float q = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const float c = static_cast<float>(x[kk][t]) - mean;
+      q = fmaf(c, c, q);
+    }
+  const float inv = __builtin_amdgcn_rsqf(pair_sum(q) * (1.f / D) + eps);
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      x[kk][t] = static_cast<__bf16>(fmaf((static_cast<float>(x[kk][t]) - mean) * inv, static_cast<float>(gamma[kk][t]), static_cast<float>(beta[kk][t])));
+}
+
 // A 16-byte store that writes through the L2 (agent scope, `sc1`): `base` is uniform over the wave, `offset` the
 // lane's byte offset below `span` bytes.  The XCDs' L2s are not coherent with each other, so whatever a kernel
 // leaves dirty in them is written back when the kernel ends; an output stream that nobody on the chip reads again is

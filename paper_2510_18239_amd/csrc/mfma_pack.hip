@@ -5,8 +5,6 @@
 namespace lime {
 namespace {
 
-constexpr int kPackRows = 4;   // rows of X per block of a projection job
-constexpr int kPackCols = 32;  // columns of W per block
 constexpr int kMaxJobs = kMaxPackProjections, kMaxWeights = kMaxPackWeights;
 
 struct PackArgs {
@@ -24,7 +22,7 @@ struct PackArgs {
   const bf16_t* p_beta[kMaxJobs];
   float p_eps[kMaxJobs];
   int p_norm[kMaxJobs];
-  int p_first_block[kMaxJobs + 1];  // block ranges of the projection jobs, after the weight jobs
+  int p_first_unit[kMaxJobs + 1];   // ranges of the projection jobs' units (a wavefront each), after the weight jobs
   const bf16_t *s_wq, *s_k, *s_wk;  // the score job (at most one), after the projection jobs
   bf16_t* s_img;
   float s_sign;
@@ -90,19 +88,77 @@ __device__ void score_wave(const PackArgs& p, int combo) {
   for (int i = 0; i < 16; ++i) store_as(dst + (8 * (i / 4) + 4 * g + i % 4) * 8, acc[i] * p.s_sign);
 }
 
-// SDH, SM, SNKB: shape of the score job (d/h, m, d/32) this instance can run after its other jobs; 0 = none.
-template <int SDH, int SM, int SNKB>
-__global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
-  extern __shared__ float smem[];
-  const int d = p.d, dh = p.dh, m = p.m, tid = threadIdx.x;
-  int blk = blockIdx.x;
-  if constexpr (SDH != 0) {
-    if (blk >= p.n_weights * p.blocks_per_weight + p.p_first_block[kMaxJobs]) {  // uniform
-      blk -= p.n_weights * p.blocks_per_weight + p.p_first_block[kMaxJobs];
-      score_wave<SDH, SM, SNKB>(p, blk * 4 + tid / 64);
-      return;
+// One wavefront of a projection job: 32 rows x 32 columns of X_u W on the matrix cores (project_block), written as two
+// fragments of the job's image.
+template <int D>
+__device__ __forceinline__ void project_wave(const PackArgs& p, int job, int unit) {
+  constexpr int NK = D / 16, CB = D / 32;
+  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, dh = p.dh, m = p.m;
+  const int lbs = m / 32, lb = unit % lbs, cb = unit / lbs % CB, u = unit / (lbs * CB);
+  const bf16_t* X = p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(32 * lb + n) * D + 8 * g;  // row 32 lb + n
+  const bf16_t* W = p.p_w[job];
+  const int a = 32 * cb / dh, hc = 32 * cb % dh / 32;  // head, and 32-column block of the head
+  const bool keys = p.p_layout[job] == kPackKeys;
+  bf16x8* img = reinterpret_cast<bf16x8*>(p.p_img[job]);
+  bf16x8 lo, hi;  // the block's accumulators, or what they would be
+  if (W == nullptr) {
+    // the identity: the rows as they are (normalised rows always come with a weight)
+    const bf16_t* Xu = p.p_x[job] + u * p.p_stride[job];
+    auto element = [&](int k) { return keys ? Xu[static_cast<int64_t>(32 * lb + n) * D + 32 * cb + k] : Xu[static_cast<int64_t>(32 * lb + k) * D + 32 * cb + n]; };
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      lo[t] = __builtin_bit_cast(__bf16, element(chain_k(g, t)).bits);
+      hi[t] = __builtin_bit_cast(__bf16, element(16 + chain_k(g, t)).bits);
     }
+    if (p.p_sign[job] < 0.f) lo = -lo, hi = -hi;
+  } else {
+    bf16x8 x[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
+    bf16x8 gamma[NK], beta[NK];
+    if (p.p_norm[job]) {  // asked for with everything else
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        gamma[kk] = *reinterpret_cast<const bf16x8*>(p.p_gamma[job] + 16 * kk + 8 * g);
+        beta[kk] = *reinterpret_cast<const bf16x8*>(p.p_beta[job] + 16 * kk + 8 * g);
+      }
+    }
+    bf16x8 w[NK];
+    const bf16_t* wcol = W + static_cast<int64_t>(8 * g) * D + 32 * cb + n;
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) w[kk][t] = __builtin_bit_cast(__bf16, wcol[(16 * kk + t) * D].bits);
+    if (p.p_norm[job]) normalise_rows<D>(x, gamma, beta, p.p_eps[job]);
+    f32x16 acc = keys ? project_block<NK>(w, x) : project_block<NK>(x, w);
+    if (p.p_sign[job] < 0.f) acc = -acc;
+    lo = pack_half(acc, 0), hi = pack_half(acc, 1);
   }
+  if (keys) {
+    // lane (row 32 lb + n, g), registers = the block's columns in chained order: k-steps 2 hc and 2 hc + 1 of the head
+    const int64_t frag = ((static_cast<int64_t>(u) * (D / dh) + a) * (dh / 16) + 2 * hc) * lbs + lb;
+    img[frag * 64 + lane] = lo;
+    img[(frag + lbs) * 64 + lane] = hi;
+  } else {
+    // lane (column 32 cb + n, g), registers = the block's rows in chained order: k-steps 2 lb and 2 lb + 1
+    const int64_t frag = ((static_cast<int64_t>(u) * (D / dh) + a) * (m / 16) + 2 * lb) * (dh / 32) + hc;
+    const int slot = out_rho(n) + 32 * g;
+    const bool natural = p.p_layout[job] == kPackValuesNatural;
+    img[frag * 64 + slot] = natural ? natural_from_chained(lo) : lo;
+    img[(frag + dh / 32) * 64 + slot] = natural ? natural_from_chained(hi) : hi;
+  }
+}
+
+// D: embedding width.  SDH, SM: shape of the score job (d/h, m) this instance can run after its other jobs; 0 = none.
+// A block is four wavefronts: 256 slots of a weight image, or four units of the projection jobs, or four of the score
+// job.  What bounds it is latency (a few KiB per compute unit): every load of a unit is independent of every other.  A
+// projection unit used to be 4 rows x 32 columns in fp32 on the vector ALUs with the sum over k split over a block and
+// combined through LDS; on the matrix cores a wavefront does 32 x 32 without LDS or barriers.
+template <int D, int SDH, int SM>
+__global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
+  constexpr int d = D;
+  const int dh = p.dh, tid = threadIdx.x;
+  int blk = blockIdx.x;
   if (blk < p.n_weights * p.blocks_per_weight) {
     // one thread per (8 consecutive k, column): a 16-byte slot of the weight image
     const int job = blk / p.blocks_per_weight;
@@ -132,120 +188,18 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     return;
   }
   blk -= p.n_weights * p.blocks_per_weight;
-  const int job = blk >= p.p_first_block[2] ? 2 : (blk >= p.p_first_block[1] ? 1 : 0);
-  blk -= p.p_first_block[job];
-  // A block computes kPackRows rows x kPackCols columns of X W: it fetches only its column slice of W
-  // (d x kPackCols), so that no compute unit has to take in the whole matrix.  Thread (cg, kc) owns 8
-  // adjacent columns and every nkc-th k; the partial sums meet in LDS.
-  const int slices = d / kPackCols, groups = m / kPackRows;  // d is a multiple of 32, m of 32
-  const int slice = blk % slices, rg = (blk / slices) % groups, u = blk / (slices * groups);
-  const int row0 = rg * kPackRows, col0 = slice * kPackCols;
-  const bf16_t* X = p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(row0) * d;
-  const bf16_t* W = p.p_w[job];
-
-  float* xs = smem;                          // [kPackRows][d]
-  float* out = xs + kPackRows * d;           // [kPackRows][kPackCols]
-  float* red = out + kPackRows * kPackCols;  // [nkc][kPackRows * kPackCols + 1]: the odd pitch spreads the k-groups over the banks
-  constexpr int CG = kPackCols / 8, nkc = 256 / CG;
-  constexpr int kMaxK = 256 / nkc;  // k-steps per thread at the largest d (256)
-  constexpr int kRedPitch = kPackRows * kPackCols + 1;
-  const int cg = tid % CG, kc = tid / CG;
-  // every load this block needs is issued before the first wait
-  bf16x8 wreg[kMaxK];
-  if (W != nullptr) {
-#pragma unroll
-    for (int it = 0; it < kMaxK; ++it) {
-      const int k = kc + it * nkc;
-      if (k < d) wreg[it] = *reinterpret_cast<const bf16x8*>(W + static_cast<int64_t>(k) * d + col0 + 8 * cg);
+  const int projection_blocks = (p.p_first_unit[kMaxJobs] + 3) / 4;
+  if constexpr (SDH != 0) {
+    if (blk >= projection_blocks) {  // uniform
+      score_wave<SDH, SM, D / 32>(p, (blk - projection_blocks) * 4 + tid / 64);
+      return;
     }
   }
-  // (scale and shift of a normalised job: asked for with everything else, used after the rows have arrived; a lane
-  // takes pairs of neighbouring columns so that they come as 32-bit loads, which nothing touches before their use)
-  constexpr int kNormPairs = 256 / 128;  // column pairs per lane at the largest d
-  uint32_t ln_g[kNormPairs], ln_b[kNormPairs];
-  if (p.p_norm[job]) {
-#pragma unroll
-    for (int i = 0; i < kNormPairs; ++i) {
-      const int k = min(2 * (tid % 64) + 128 * i, d - 2);
-      ln_g[i] = reinterpret_cast<const uint32_t*>(p.p_gamma[job])[k / 2];
-      ln_b[i] = reinterpret_cast<const uint32_t*>(p.p_beta[job])[k / 2];
-    }
-  }
-  for (int i = tid; i < kPackRows * d; i += 256) xs[i] = to_float(X[i]);
-  __syncthreads();
-  if (p.p_norm[job]) {
-    // one wavefront per row (kPackRows of them): mean, centred second moment, then the normalised row rounded to
-    // bf16, as a normalisation pass of its own would have stored it
-    static_assert(kPackRows * 64 == 256, "a wavefront per row");
-    float* xr = xs + (tid / 64) * d;
-    float x[2 * kNormPairs], sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < kNormPairs; ++i) {
-      const int k = 2 * (tid % 64) + 128 * i;
-      x[2 * i] = k < d ? xr[k] : 0.f, x[2 * i + 1] = k < d ? xr[k + 1] : 0.f;
-      sum += x[2 * i] + x[2 * i + 1];
-    }
-    const float mean = wave_sum(sum) / static_cast<float>(d);
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < kNormPairs; ++i) {
-      const int k = 2 * (tid % 64) + 128 * i;
-      x[2 * i] = k < d ? x[2 * i] - mean : 0.f, x[2 * i + 1] = k < d ? x[2 * i + 1] - mean : 0.f;
-      q = fmaf(x[2 * i], x[2 * i], fmaf(x[2 * i + 1], x[2 * i + 1], q));
-    }
-    const float inv = 1.f / sqrtf(wave_sum(q) / static_cast<float>(d) + p.p_eps[job]);
-#pragma unroll
-    for (int i = 0; i < kNormPairs; ++i) {
-      const int k = 2 * (tid % 64) + 128 * i;
-      if (k < d) {
-        xr[k] = static_cast<float>(static_cast<__bf16>(
-            fmaf(x[2 * i] * inv, __uint_as_float(ln_g[i] << 16), __uint_as_float(ln_b[i] << 16))));
-        xr[k + 1] = static_cast<float>(static_cast<__bf16>(
-            fmaf(x[2 * i + 1] * inv, __uint_as_float(ln_g[i] & 0xffff0000u), __uint_as_float(ln_b[i] & 0xffff0000u))));
-      }
-    }
-    __syncthreads();
-  }
-  if (W == nullptr) {
-    for (int i = tid; i < kPackRows * kPackCols; i += 256) out[i] = xs[(i / kPackCols) * d + col0 + i % kPackCols];
-  } else {
-    float acc[kPackRows][8];
-#pragma unroll
-    for (int r = 0; r < kPackRows; ++r)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[r][j] = 0.f;
-#pragma unroll
-    for (int it = 0; it < kMaxK; ++it) {
-      const int k = kc + it * nkc;
-      if (k < d) {
-#pragma unroll
-        for (int r = 0; r < kPackRows; ++r) {
-          const float x = xs[r * d + k];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[r][j] = fmaf(x, static_cast<float>(wreg[it][j]), acc[r][j]);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kPackRows; ++r)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) red[kc * kRedPitch + r * kPackCols + 8 * cg + j] = acc[r][j];
-    __syncthreads();
-    for (int i = tid; i < kPackRows * kPackCols; i += 256) {
-      float sum = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < nkc; ++c) sum += red[c * kRedPitch + i];
-      out[i] = sum;
-    }
-  }
-  __syncthreads();
-  bf16_t* img = p.p_img[job];
-  const bool keys = p.p_layout[job] == kPackKeys;
-  const float sign = p.p_sign[job];
-  for (int i = tid; i < kPackRows * kPackCols; i += 256) {
-    const int row = row0 + i / kPackCols, col = col0 + i % kPackCols;
-    store_as(img + (keys ? keys_slot(u, row, col, d, dh, m) : values_slot(u, row, col, d, dh, m, p.p_layout[job] == kPackValues)), sign * out[i]);
-  }
+  int unit = __builtin_amdgcn_readfirstlane(blk * 4 + tid / 64);
+  if (unit >= p.p_first_unit[kMaxJobs]) return;
+  int job = 0;
+  while (job + 1 < kMaxJobs && unit >= p.p_first_unit[job + 1]) ++job;
+  project_wave<D>(p, job, unit - p.p_first_unit[job]);
 }
 
 }  // namespace
@@ -263,9 +217,9 @@ hipError_t pack_operands(const PackWeight* weights, int n_weights, const PackPro
     p.w_sign[i] = weights[i].sign;
     p.w_pad[i] = weights[i].head_pad;
   }
-  int blocks = 0;
+  int units = 0;
   for (int i = 0; i < kMaxJobs; ++i) {
-    p.p_first_block[i] = blocks;
+    p.p_first_unit[i] = units;
     if (i < n_projections) {
       p.p_x[i] = static_cast<const bf16_t*>(projections[i].X);
       p.p_w[i] = static_cast<const bf16_t*>(projections[i].W);
@@ -277,28 +231,30 @@ hipError_t pack_operands(const PackWeight* weights, int n_weights, const PackPro
       p.p_gamma[i] = static_cast<const bf16_t*>(projections[i].norm.gamma);
       p.p_beta[i] = static_cast<const bf16_t*>(projections[i].norm.beta);
       p.p_eps[i] = projections[i].norm.eps;
-      blocks += projections[i].users * (m / kPackRows) * (d / kPackCols);
+      units += projections[i].users * (m / 32) * (d / 32);
     }
   }
-  p.p_first_block[kMaxJobs] = blocks;
-  for (int i = n_projections; i < kMaxJobs; ++i)
-    if (i > 0) p.p_first_block[i] = 0x7fffffff;
-  constexpr int nkc = 256 / (kPackCols / 8);
-  size_t lds = (static_cast<size_t>(kPackRows) * d + static_cast<size_t>(1 + nkc) * kPackRows * kPackCols + nkc) * sizeof(float);
-  int grid = n_weights * p.blocks_per_weight + blocks;
+  p.p_first_unit[kMaxJobs] = units;
+  int grid = n_weights * p.blocks_per_weight + (units + 3) / 4;
+  const int dh = d / h, nkb = d / 32;
   if (score == nullptr) {
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((pack_kernel<0, 0, 0>), dim3(grid), dim3(256), lds, s, p);
+    switch (d) {  // every d the matrix-core kernels take
+      case 32: hipLaunchKernelGGL((pack_kernel<32, 0, 0>), dim3(grid), dim3(256), 0, s, p); break;
+      case 64: hipLaunchKernelGGL((pack_kernel<64, 0, 0>), dim3(grid), dim3(256), 0, s, p); break;
+      case 128: hipLaunchKernelGGL((pack_kernel<128, 0, 0>), dim3(grid), dim3(256), 0, s, p); break;
+      case 256: hipLaunchKernelGGL((pack_kernel<256, 0, 0>), dim3(grid), dim3(256), 0, s, p); break;
+      default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
   }
   p.s_wq = static_cast<const bf16_t*>(score->Wq), p.s_k = static_cast<const bf16_t*>(score->Ksrc);
   p.s_wk = static_cast<const bf16_t*>(score->Wk), p.s_img = static_cast<bf16_t*>(score->image);
   p.s_sign = score->sign;
-  const int dh = d / h, nkb = d / 32;
   grid += (h * nkb * (m / 32) + 3) / 4;  // four wavefronts per block, one 32 x 32 block of the image each
 #define LIME_SCORE_CASE(DH_, M_, NKB_)                                                              \
   if (dh == DH_ && m == M_ && nkb == NKB_) {                                                        \
-    hipLaunchKernelGGL((pack_kernel<DH_, M_, NKB_>), dim3(grid), dim3(256), lds, s, p);             \
+    hipLaunchKernelGGL((pack_kernel<32 * NKB_, DH_, M_>), dim3(grid), dim3(256), 0, s, p);          \
     return hipGetLastError();                                                                       \
   }
   LIME_SCORE_CASE(64, 64, 8) LIME_SCORE_CASE(64, 64, 4) LIME_SCORE_CASE(64, 64, 2)
