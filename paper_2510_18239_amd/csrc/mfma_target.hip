@@ -17,6 +17,8 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
 // Fragments of one (user, head, tile of 32 items), 64 lanes of 16 bytes each: first the keys, then the values
 //   keys   [K2]    : lane (item n, g), slot t = K~[32 tile + n][a dh + 16 kk + chain_k(g, t)]
 //   values [2][MB] : lane (col c, g),  slot t = V~[32 tile + 16 f + chain_k(g, t)][a dh + 32 ob + c]
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
   constexpr int QB = 2, kBuffers = 4, kStageFrags = 2 * Img::kFrags, kLoads = kStageFrags / 4;
   constexpr float kSlack = 8.f;
   __shared__ bf16x8 kv_lds[kBuffers * kStageFrags * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, g = lane >> 5;
   // Consecutive workgroups go to consecutive XCDs.  A pair's workgroups share its keys and values, so an XCD gets whole
   // pairs: every eighth one (users' lengths differ: neighbours are spread), or a contiguous run of workgroups where the
@@ -196,20 +198,21 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
   }
   const int b = pair / H, head = pair % H;
   const int q0 = (group * 4 + wave) * QB * 32;  // (a wave past the last query works on the last row and stores nothing)
-  const int len = a.lens ? min(a.lens[b], a.N) : a.N;
+  const int len = __builtin_amdgcn_readfirstlane(a.lens ? min(a.lens[b], a.N) : a.N);
   const int tiles = (len + 31) / 32;
 
-  const bf16x8* kv = a.KV + (static_cast<int64_t>(b) * H + head) * ((a.tiles + 1) & ~1) * Img::kFrags * 64 + lane;
+  const bf16x8* kv = a.KV + (static_cast<int64_t>(b) * H + head) * ((a.tiles + 1) & ~1) * Img::kFrags * 64;
   const int last_stage = (tiles - 1) / 2;
   // (a stage past the last is the last one again: the number of outstanding loads is then the same at every wait)
   // (assembly: the compiler would make every later read of LDS wait for the youngest of these loads)
   auto load_stage = [&](int stage, int slot) {
     const bf16x8* src = kv + (static_cast<int64_t>(min(stage, last_stage)) * kStageFrags + wave * kLoads) * 64;
-    const unsigned dst = __builtin_amdgcn_readfirstlane(
-        static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)kv_lds)) + (slot * kStageFrags + wave * kLoads) * 1024);
+    const unsigned dst = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)kv_lds)) +
+                         (slot * kStageFrags + wave * kLoads) * 1024;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst + j * 1024), "v"(src + j * 64) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   : : "s"(__builtin_amdgcn_readfirstlane(dst + j * 1024)), "v"(lane * 16), "s"(src + j * 64) : "memory");
   };
   auto publish = [&] {  // this wave's part of the stage about to be read has arrived; so has everybody's
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(kLoads) : "memory");  // all but the youngest stage
@@ -232,17 +235,26 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
     const bf16_t* row[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) row[qb] = a.T + (static_cast<int64_t>(b) * a.C + min(q0 + 32 * qb + n, a.C - 1)) * D + 8 * g;
+    // all rows are asked for at once, the weights (which every workgroup reads) kAhead k-steps ahead of their use
+    constexpr int kAhead = K1 < 4 ? K1 : 4;
+    bf16x8 x[QB][K1], w[K1][MB];
 #pragma unroll
-    for (int kk = 0; kk < K1; ++kk) {
-      bf16x8 x[QB];
+    for (int kk = 0; kk < K1; ++kk)
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) x[qb] = *reinterpret_cast<const bf16x8*>(row[qb] + 16 * kk);
+      for (int qb = 0; qb < QB; ++qb) x[qb][kk] = *reinterpret_cast<const bf16x8*>(row[qb] + 16 * kk);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16x8 w = wimg[(kk * MB + mb) * 64];
+    for (int kk = 0; kk < K1 + kAhead; ++kk) {
+      if (kk < K1) {
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) q[qb][mb] = mfma32(w, x[qb], q[qb][mb]);
+        for (int mb = 0; mb < MB; ++mb) w[kk][mb] = wimg[(kk * MB + mb) * 64];
       }
+      if (kk >= kAhead) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb) q[qb][mb] = mfma32(w[kk - kAhead][mb], x[qb][kk - kAhead], q[qb][mb]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     const float c = a.scale * kLog2e;
 #pragma unroll
@@ -256,10 +268,10 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
   }
 
   f32x16 acc[QB][MB], base[QB];  // base: minus the value whose exponential has weight one
-  float run_sum[QB];
+  float run_sum[QB][2];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    run_sum[qb] = 0.f;
+    run_sum[qb][0] = run_sum[qb][1] = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       base[qb][i] = 0.f;
@@ -270,15 +282,20 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
 
   if (tiles > 0) {  // uniform
     auto mask_tail = [&](f32x16& s, int t) {  // register 4j + r of this lane is item 32t + 8j + 4g + r
-      const int valid = len - 32 * t - 4 * g;
+      int valid = len - 32 * t - 4 * g;
+      asm volatile("" : "+v"(valid));  // (the comparisons stay in here)
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (8 * (i >> 2) + (i & 3) >= valid) s[i] = -INFINITY;
+      for (int i = 0; i < 16; ++i) {
+        float v = s[i];
+        if (8 * (i >> 2) + (i & 3) >= valid) v = -INFINITY;
+        asm volatile("" : "+v"(v));  // (kept apart from the unmasked maximum, which is one instruction only if nobody shares its halves)
+        s[i] = v;
+      }
     };
     auto move_base = [&](int qb, f32x16& s, float mx) {
       const float by = pair_max(mx);  // the query's other items are in the other lane of the pair
       const float keep = __builtin_amdgcn_exp2f(-by);
-      run_sum[qb] *= keep;
+      run_sum[qb][0] *= keep, run_sum[qb][1] *= keep;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         base[qb][i] -= by;
@@ -287,20 +304,19 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
         for (int ob = 0; ob < MB; ++ob) acc[qb][ob][i] *= keep;
       }
     };
-    auto max_step = [&](const f32x16& s, int j, float mx) { return fmaxf(fmaxf(s[2 * j], s[2 * j + 1]), mx); };  // two of the 16
+    // larger of mx >= 0 and two of the 16 logits, compared as integers: one instruction (a float maximum is two more to
+    // quiet its operands)
+    auto max_step = [&](const f32x16& s, int j, float mx) {
+      return __int_as_float(max(max(__float_as_int(s[2 * j]), __float_as_int(s[2 * j + 1])), __float_as_int(mx)));
+    };
 
-    bf16x8 kf[K2], vf[2][MB], pf[QB][2];
+    bf16x8 kf[K2], vf[2][MB];
+    u32x4 pf[QB][2];  // weights in pairs
     f32x16 s[QB];
     float smax[QB];
     auto read_keys = [&](const bf16x8* tile) {
 #pragma unroll
       for (int kk = 0; kk < K2; ++kk) kf[kk] = tile[kk * 64 + lane];
-    };
-    auto read_values = [&](const bf16x8* tile) {
-#pragma unroll
-      for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int ob = 0; ob < MB; ++ob) vf[f][ob] = tile[(K2 + f * MB + ob) * 64 + lane];
     };
 
     publish();
@@ -314,14 +330,15 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
       mask_tail(s[qb], 0);
       float mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) mx = max_step(s[qb], j, mx);
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[qb][i]);
       move_base(qb, s[qb], mx);  // finite: the tile holds at least one valid item
       smax[qb] = 0.f;
     }
+    read_keys(kv_lds + Img::kFrags * 64);
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) pf[1][f][t] = static_cast<__bf16>(0.f);  // there is no half step before the first
+      for (int t = 0; t < 4; ++t) pf[1][f][t] = 0;  // there is no half step before the first
 #pragma unroll
       for (int ob = 0; ob < MB; ++ob)
 #pragma unroll
@@ -330,7 +347,9 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
 
     // Half step (t, QBI): weights of s[QBI] (tile t), whose registers then take the logits of tile t + 1.
     constexpr int kSlots = K2 + 2 * MB;  // matrix instructions of a half step
-    auto half_step = [&](auto qb_tag, int t) {
+    // After its last use a key or value fragment is read again for the next tile (half a step before its first use there):
+    // the keys of `next_tile` in the second half of a tile, its values in the first.
+    auto half_step = [&](auto qb_tag, int t, const bf16x8* next_tile) {
       constexpr int qb = decltype(qb_tag)::value, other = 1 - qb;
       if (32 * t + 32 > len) {  // uniform: the user's last tile; the maximum has to leave out what is masked
         mask_tail(s[qb], t);
@@ -340,28 +359,42 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
       }
       if (__any(smax[qb] > kSlack)) move_base(qb, s[qb], smax[qb]);
       f32x16 next = base[qb];
-      float mx = 0.f;
+      float mx = 0.f, p0 = 0.f, p1 = 0.f;
+      // a pair of weights, one step after its exponentials were asked for
+      // (pinned where it stands: the compiler would sink all of it to the weights' use, behind the matrix instructions)
+      auto finish = [&](int j) {
+        run_sum[qb][0] += p0;
+        run_sum[qb][1] += p1;
+        bf16x2 pair;
+        pair[0] = static_cast<__bf16>(p0), pair[1] = static_cast<__bf16>(p1);
+        unsigned bits = __builtin_bit_cast(unsigned, pair);
+        asm volatile("" : "+v"(bits), "+v"(run_sum[qb][0]), "+v"(run_sum[qb][1]));
+        pf[qb][j / 4][j % 4] = bits;
+      };
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < kSlots; ++i) {
-        if (i % 2 == 0) {
-          const int kk = i / 2;
-          next = mfma32(kf[kk], qf[qb][kk], next);
-        } else {
-          const int u = i / 2, f = u / MB, ob = u % MB;
-          acc[other][ob] = mfma32(vf[f][ob], pf[other][f], acc[other][ob]);
+        // the product whose fragments this half step replaces comes first, so that they are there when it starts again
+        const int u = i % (kSlots / 2);
+        if ((i < kSlots / 2) == (qb == 1)) next = mfma32(kf[u], qf[qb][u], next);
+        else acc[other][u % MB] = mfma32(vf[u / MB][u % MB], __builtin_bit_cast(bf16x8, pf[other][u / MB]), acc[other][u % MB]);
+        if (i >= 1 && i <= kSlots / 2) {
+          const int r = i - 1;
+          if (qb == 1) kf[r] = next_tile[r * 64 + lane];
+          else vf[r / MB][r % MB] = next_tile[(K2 + r) * 64 + lane];
         }
 #pragma unroll
         for (int j = i * 8 / kSlots; j < (i + 1) * 8 / kSlots; ++j) {
-          const float p0 = __builtin_amdgcn_exp2f(s[qb][2 * j]), p1 = __builtin_amdgcn_exp2f(s[qb][2 * j + 1]);
-          run_sum[qb] += p0;
-          run_sum[qb] += p1;
-          pf[qb][j / 4][2 * (j % 4)] = static_cast<__bf16>(p0);
-          pf[qb][j / 4][2 * (j % 4) + 1] = static_cast<__bf16>(p1);
-          mx = max_step(s[other], j, mx);
+          const float n0 = __builtin_amdgcn_exp2f(s[qb][2 * j]), n1 = __builtin_amdgcn_exp2f(s[qb][2 * j + 1]);
+          if (j > 0) mx = max_step(s[other], j - 1, mx);
+          if (j > 0) finish(j - 1);
+          p0 = n0, p1 = n1;
+          asm volatile("" : "+v"(p0), "+v"(p1), "+v"(mx));
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      mx = max_step(s[other], 7, mx);
+      finish(7);
       smax[other] = mx;
       s[qb] = next;
     };
@@ -371,21 +404,17 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
       const bf16x8* cur = kv_lds + slot * kStageFrags * 64;
       slot = (slot + 1) % kBuffers;
       const bf16x8* nxt = kv_lds + slot * kStageFrags * 64;
-      read_keys(cur + Img::kFrags * 64);
-      half_step(std::integral_constant<int, 0>{}, t);
-      read_values(cur);
-      half_step(std::integral_constant<int, 1>{}, t);
+      half_step(std::integral_constant<int, 0>{}, t, cur);  // reads the values of tile t
       publish();
       load_stage(t / 2 + 3, (slot + 2) % kBuffers);
-      read_keys(nxt);
-      half_step(std::integral_constant<int, 0>{}, t + 1);
-      read_values(cur + Img::kFrags * 64);
-      half_step(std::integral_constant<int, 1>{}, t + 1);
+      half_step(std::integral_constant<int, 1>{}, t, nxt);  // the keys of tile t + 2
+      half_step(std::integral_constant<int, 0>{}, t + 1, cur + Img::kFrags * 64);
+      half_step(std::integral_constant<int, 1>{}, t + 1, nxt + Img::kFrags * 64);
     }
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-      for (int ob = 0; ob < MB; ++ob) acc[1][ob] = mfma32(vf[f][ob], pf[1][f], acc[1][ob]);
+      for (int ob = 0; ob < MB; ++ob) acc[1][ob] = mfma32(vf[f][ob], __builtin_bit_cast(bf16x8, pf[1][f]), acc[1][ob]);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");  // nothing may arrive in LDS after the workgroup has gone
   }
 
@@ -393,7 +422,7 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int q = q0 + 32 * qb + n;
-    const float total = pair_sum(run_sum[qb]);
+    const float total = pair_sum(run_sum[qb][0] + run_sum[qb][1]);
     const float inv = tiles > 0 ? 1.f / total : 0.f;
     if (q >= a.C) continue;
     bf16_t* orow = a.O + (static_cast<int64_t>(b) * a.C + q) * D + head * DH + 4 * g;
