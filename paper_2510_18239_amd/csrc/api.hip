@@ -654,7 +654,7 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   c.k_user_stride = 0, c.v_user_stride = static_cast<int64_t>(m) * d, c.row_lens = nullptr;
   c.B = B, c.rows = C, c.d = d, c.h = h, c.m = m, c.scale = scale_cand, c.phi = lime::kPhiSoftmax;
   if (norms != nullptr)
-    q.q_norm = norms->hist_q, q.values_norm = norms->cand_v, c.x_norm = norms->cand_q, c.k_norm = norms->cand_k;
+    q.q_norm = norms->hist_q, q.values_norm = norms->cand_v, c.x_norm = norms->cand_q, c.k_norm = norms->cand_k, q.walk = phi == lime::kPhiSoftmax;
   lime::PackJobs jobs;
   lime::links_over_history_jobs(q, workspace, jobs);
   lime::queries_over_links_jobs(c, cand_ws, jobs, /*values=*/false);

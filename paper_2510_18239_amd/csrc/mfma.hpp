@@ -137,6 +137,24 @@ __device__ __forceinline__ void store_through(void* base, int span, int offset, 
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, offset, 0, 16 /* sc1 */);
 }
 
+// Asks for 1 KiB to go from memory straight to LDS, 16 bytes per lane: lane i's from base + lane_offset to
+// lds_offset + 16 i (lds_offset and base uniform).  Counted by vmcnt like any load, but unknown to the compiler: whoever
+// reads the data waits for vmcnt and, for other waves' parts, at a barrier (wait_lds_loads, lds_barrier).  Assembly because
+// the compiler makes every read of LDS after its own form of this load wait for the youngest such load.
+__device__ __forceinline__ void load_to_lds(unsigned lds_offset, unsigned lane_offset, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               : : "s"(__builtin_amdgcn_readfirstlane(lds_offset)), "v"(lane_offset), "s"(base) : "memory");
+}
+template <int OUTSTANDING>
+__device__ __forceinline__ void wait_lds_loads() {  // all but the OUTSTANDING youngest loads of this wave have landed
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(OUTSTANDING) : "memory");
+}
+__device__ __forceinline__ unsigned lds_offset_of(const void* p) {
+  return static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+}
+// A workgroup barrier that waits for this wave's LDS accesses but, unlike __syncthreads, for no load from memory.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
+
 // Output-row permutation that makes a lane's 16 accumulator registers 16 consecutive columns:
 // the A-operand row `rho` of an output block carries column out_col(rho); lane-half g then holds
 // columns 16g .. 16g+15 of the 32-wide block in register order.
@@ -342,6 +360,7 @@ struct LinksOverHistory {
   void* values_image;
   RowNorm values_norm;  // applied to the finished link states before that projection (LP itself is stored as it is)
   RowNorm q_norm;       // applied to the link rows LC by the pack step
+  bool walk;            // run on the kernel of mfma_history_walk.hip (softmax only)
 };
 void links_over_history_jobs(const LinksOverHistory& a, void* workspace, PackJobs& jobs);
 bool links_over_history_supported(int d, int h, int m);

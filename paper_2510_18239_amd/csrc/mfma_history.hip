@@ -1,299 +1,348 @@
 // User-side link personalisation on the matrix cores: the m links attend over the N history
 // rows, by softmax (Eq. 3) or by the target-to-source half of XORA, O[T] (Eq. 7, phi = SiLU/n_s).
 //
-// Design: one fused pass over E.  A workgroup is a single wavefront that owns one head of a chunk
-// of one user's history (histories are short next to the chip: many small workgroups keep every
-// compute unit busy and each fetches only its own head's operands).  The wave keeps the head's
-// slices of W_K^T and W_V and the projected link queries Q~_a in fragment form (W_K^T in LDS when
-// d = 256, otherwise in registers) and walks its chunk in tiles of 32 items, requesting the next
-// tile's rows before it computes the current one.  Per tile, with X = the 32 history rows read
-// row-major as stored:
-//   K~^T (d/h x 32) = W_K,a^T . X^T     X is the B operand
-//   V~   (32 x d/h) = X . W_V,a         the same X registers are the A operand
-//   S^T  (32 x m)   = K~ . Q~_a^T       A operand = accumulators of the first product
-//   L^P^T(d/h x m) += V~^T . phi(S)^T   both operands are accumulators (of the 2nd and 3rd product)
-// so the projected keys and values never leave registers.  Each lane owns one link (column of
-// S^T and of L^P^T): the running softmax maximum, the running sum and the rescaling of the
+// Design: one fused pass over E.  A workgroup owns a chunk of one user's history and HG heads, and walks the chunk in
+// steps of TP tiles of 32 items.  A wave owns 32 columns of a head (a head has MB = d/h / 32 such blocks) and one tile of
+// every step; its slices of W_K^T and W_V stay in its registers.  Per tile, with X = the 32 history rows:
+//   K~^T (32 x 32) = W_K^T . X^T      X is the B operand
+//   V~   (32 x 32) = X . W_V          the same X fragments are the A operand
+// The MB waves of a head and tile then trade their blocks of K~ and V~ through LDS and share out the links:
+//   S^T  (32 x links) = K~ . Q~_a^T   A operand = accumulators of the first product
+//   L^P^T(d/h x links) += V~^T . phi(S)^T   both operands are accumulators (of the 2nd and 3rd product)
+// Each lane owns one link (column of S^T and of L^P^T): the running softmax base, the running sum and the rescaling of the
 // accumulator are all lane-local, plus one exchange with lane ^ 32.  Rows at or beyond lens[b] are
-// replaced by zeros as they are loaded and masked out of phi, so their content is never used.
-// Every chunk writes an un-normalised partial (max, sum, accumulator); a small merge kernel
+// replaced by zeros before they are read and masked out of phi, so their content is never used.
+// The rows go from memory straight to LDS, a step ahead; the TP waves of a block combine their tiles' results in LDS
+// at the end.
+// Every chunk writes an un-normalised partial (base, sum, accumulator); a small merge kernel
 // combines the chunks of a user in a fixed order (deterministic) and writes L^P.
-#include "mfma.hpp"
+#include <algorithm>
+
+#include "history.hpp"
 
 namespace lime {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-struct HistArgs {
-  const bf16_t* E;
-  const int32_t* lens;
-  const bf16x8 *WkA, *WvB, *QB;
-  int64_t qb_user_frags;  // size of one user's query image in bf16x8 units (0 = shared links)
-  float* part_acc;        // [B][chunks][h][m][dh]
-  float* part_ml;         // [B][chunks][h][m][2]  (running max, running sum)
-  int N, chunk_items, chunks;
-  float scale;
+// How a workgroup's waves are laid out: heads x tiles of a step x 32-column blocks of a head.
+template <int DH, int M, int H, int HG_, int TP_>
+struct HistShape {
+  static constexpr int D = DH * H, HG = HG_, TP = TP_;
+  static constexpr int MB = DH / 32, K1 = D / 16, K2 = DH / 16, LB = M / 32;
+  static constexpr int LBW = (LB + MB - 1) / MB;  // 32-link blocks per wave
+  static constexpr int kWaves = HG * TP * MB, kThreads = 64 * kWaves, kRows = 32 * TP;
+  static constexpr int kXBytes = kRows * 2 * D, kExchange = MB > 1 ? kWaves * 4 * 1024 : 0, kQueries = HG * K2 * LB * 1024;
+  // Two buffers for the rows and the exchange (one barrier a step) where a compute unit then still holds eight waves,
+  // otherwise one (two barriers).
+  static constexpr int kLdsPerUnit = 160 * 1024 / (8 / kWaves);
+  static constexpr int NX = 2 * kXBytes + 2 * kExchange + kQueries <= kLdsPerUnit ? 2 : 1;
+  static constexpr int kCombine = (TP - 1) * HG * MB * (MB * LBW * 4096 + LBW * 512);
+  static constexpr int kLds = std::max(NX * (kXBytes + kExchange) + kQueries, kCombine);
 };
 
-// COOP = false: a workgroup is one wave (one head of one chunk; grid.z = heads) that reads its rows
-// straight from memory, one tile ahead.  COOP = true (long histories, d <= 128): a workgroup is h waves
-// (all heads of one chunk) that copy each tile once, cooperatively and several tiles ahead, through a
-// register ring into LDS, as the candidate-side kernel does.
-template <int DH, int M, int H, int PHI, bool WK_LDS, bool COOP>
-__global__ __launch_bounds__(COOP ? 64 * H : 64) void links_over_history_kernel(HistArgs a) {
-  constexpr int D = DH * H;
-  constexpr int K1 = D / 16, MB = DH / 32;  // projections: k-steps over d, blocks over d/h
-  constexpr int K2 = DH / 16, LB = M / 32;  // scores: k-steps over d/h, blocks over links
-  constexpr int P = WK_LDS ? (M >= 128 ? 1 : 2) : 4;  // COOP: tiles in flight per workgroup (registers permitting)
-  constexpr int NXS = COOP ? (WK_LDS ? 1 : 2) : 1;  // COOP: LDS tile buffers (one when W_K^T fills the LDS)
-  constexpr int LW = DH / 16;               // COOP: 1 KiB loads per wave and tile
-  constexpr int CPR = D / 8, PITCH = 2 * D + 16;
-  extern __shared__ bf16x8 lds_wk_all[];
-  __shared__ __attribute__((aligned(16))) unsigned char xs[NXS][COOP ? 32 * PITCH : 16];
-  const int lane = threadIdx.x & 63, head = COOP ? threadIdx.x >> 6 : blockIdx.z;
-  const int n = lane & 31, g = lane >> 5;
+// A 16-byte piece c of row r of a staged tile lies at piece c ^ row_swizzle<D>(r) of the row, so that the 16 lanes that an
+// LDS read serves at once (16 rows, one column) touch all banks.
+template <int D>
+__device__ __forceinline__ int row_swizzle(int r) {
+  constexpr int CPR = D / 8;  // pieces per row
+  return CPR >= 16 ? r & 15 : r / (16 / CPR) & (CPR - 1);
+}
+
+template <int DH, int M, int H, int PHI, int HG, int TP>
+__global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void links_over_history_kernel(HistArgs a) {
+  using S = HistShape<DH, M, H, HG, TP>;
+  constexpr int D = S::D, K1 = S::K1, MB = S::MB, K2 = S::K2, LB = S::LB, LBW = S::LBW, NX = S::NX, kWaves = S::kWaves;
+  constexpr int CPR = D / 8, LW = S::kXBytes / (kWaves * 1024);  // 1 KiB loads per wave and step
+  constexpr float kSlack = 8.f;
+  extern __shared__ unsigned char lds[];
+  unsigned char* const ex_lds = lds + NX * S::kXBytes;
+  bf16x8* const q_lds = reinterpret_cast<bf16x8*>(ex_lds + NX * S::kExchange);
+  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = wave % MB, hl = wave / MB % HG, tp = wave / (MB * HG);  // column block, head of the group, tile of a step
+  const int head = blockIdx.z * HG + hl;
   const int b = blockIdx.y, chunk = blockIdx.x;
-  const int len = a.lens ? min(a.lens[b], a.N) : a.N;
+  const int len = __builtin_amdgcn_readfirstlane(a.lens ? min(a.lens[b], a.N) : a.N);
   const int i_begin = chunk * a.chunk_items;
   if (i_begin >= len) return;  // uniform over the workgroup: nothing for this chunk
   const int i_end = min(len, i_begin + a.chunk_items);
 
   const bf16_t* Eb = a.E + static_cast<int64_t>(b) * a.N * D;
-  // rows at or beyond the end of the chunk are replaced by zeros (their content is never used)
-  auto load_tile = [&](int i0, bf16x8 (&x)[K1]) {
-    const int item = i0 + n;
-    const bf16_t* xrow = Eb + static_cast<int64_t>(min(item, a.N - 1)) * D + 8 * g;
+  auto ask_rows = [&](int i0, int buf) {  // this wave's part of a step; rows past the tensor's end as its last one
+    const int last = a.N - 1 - i0;
+    const bf16_t* base = Eb + static_cast<int64_t>(i0) * D;
+    int q0 = wave * LW * 64 + lane;
+    asm volatile("" : "+v"(q0));  // (what follows from it is formed here, not carried through the loop)
 #pragma unroll
-    for (int kk = 0; kk < K1; ++kk) {
-      bf16x8 v;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(0.f);
-      if (item < i_end) v = *reinterpret_cast<const bf16x8*>(xrow + 16 * kk);
-      x[kk] = v;
+    for (int j = 0; j < LW; ++j) {
+      const int q = q0 + j * 64, r = q / CPR;
+      load_to_lds(lds_offset_of(lds) + buf * S::kXBytes + (wave * LW + j) * 1024,
+                  min(r, last) * (2 * D) + (q % CPR ^ row_swizzle<D>(r)) * 16, base);
     }
   };
-  // The first tile's rows come from HBM and are asked for ahead of the operands, which come from L2: behind them, as
-  // the loop's own order has it, their latency would begin only once the operands had arrived (the W_K^T slice is
-  // waited for on its way into LDS).
-  bf16x8 xnext[COOP ? 1 : K1];
-  if constexpr (!COOP) load_tile(i_begin, xnext);
+  auto clear_tail = [&](int i0, int buf) {  // what this wave asked for past the chunk's end becomes zeros
+    if (i0 + S::kRows <= i_end) return;     // uniform
+    bf16x8 zero;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) zero[t] = static_cast<__bf16>(0.f);
+    int q0 = wave * LW * 64 + lane;
+    asm volatile("" : "+v"(q0));
+#pragma unroll
+    for (int j = 0; j < LW; ++j) {
+      const int q = q0 + j * 64;
+      if (i0 + q / CPR >= i_end) *reinterpret_cast<bf16x8*>(lds + buf * S::kXBytes + q * 16) = zero;
+    }
+  };
 
-  bf16x8* lds_wk = lds_wk_all + (COOP ? head * K1 * MB * 64 : 0);  // this wave's slice
-  bf16x8 wk[WK_LDS ? 1 : K1][WK_LDS ? 1 : MB];
-  if (WK_LDS) {
-    // this head's W_K^T image: the lane moves exactly the K1*MB fragments it will read back itself
-    bf16x8 tmp[K1 * MB];
-#pragma unroll
-    for (int it = 0; it < K1 * MB; ++it) tmp[it] = a.WkA[(head * K1 * MB + it) * 64 + lane];
-#pragma unroll
-    for (int it = 0; it < K1 * MB; ++it) lds_wk[it * 64 + lane] = tmp[it];
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < K1; ++kk)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) wk[kk][mb] = a.WkA[((head * K1 + kk) * MB + mb) * 64 + lane];
-  }
-  bf16x8 wv[K1][MB];
-#pragma unroll
-  for (int kk = 0; kk < K1; ++kk)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) wv[kk][mb] = a.WvB[((head * K1 + kk) * MB + mb) * 64 + lane];
-  bf16x8 qb[K2][LB];
+  // The rows come from HBM and are asked for ahead of the operands, which come from L2.
+  ask_rows(i_begin, 0);
   {
-    const bf16x8* src = a.QB + b * a.qb_user_frags + static_cast<int64_t>(head) * K2 * LB * 64;
+    // the heads' query fragments: kept in LDS, read once per tile
+    const bf16x8* src = a.QB + b * a.qb_user_frags + static_cast<int64_t>(blockIdx.z) * HG * K2 * LB * 64;
+    for (int f = wave; f < HG * K2 * LB; f += kWaves) load_to_lds(lds_offset_of(q_lds) + f * 1024, lane * 16, src + f * 64);
+  }
+  if (NX == 2 && i_begin + S::kRows < i_end) ask_rows(i_begin + S::kRows, 1);
+  bf16x8 wk[K1], wv[K1];
 #pragma unroll
-    for (int kk = 0; kk < K2; ++kk)
-#pragma unroll
-      for (int lb = 0; lb < LB; ++lb) qb[kk][lb] = src[(kk * LB + lb) * 64 + lane];
+  for (int kk = 0; kk < K1; ++kk) {
+    wk[kk] = a.WkA[((head * K1 + kk) * MB + half) * 64 + lane];
+    wv[kk] = a.WvB[((head * K1 + kk) * MB + half) * 64 + lane];
   }
 
-  if constexpr ((!COOP && M < 128) || (COOP && WK_LDS)) {  // (not where the accumulators of 128 links need the room)
-    // W_V only ever feeds the matrix cores, which read AGPRs as readily as VGPRs: pinned there, it leaves the
-    // VGPRs to the values the vector ALUs touch and needs no copies.
+  f32x16 acc[MB][LBW];
+  float run_max[LBW], run_sum[LBW];
 #pragma unroll
-    for (int kk = 0; kk < K1; ++kk)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+a"(wv[kk][mb]));
-  }
-  f32x16 acc[MB][LB];
-  float run_max[LB], run_sum[LB];
-#pragma unroll
-  for (int lb = 0; lb < LB; ++lb) {
-    run_max[lb] = -INFINITY;
-    run_sum[lb] = 0.f;
+  for (int l = 0; l < LBW; ++l) {
+    run_max[l] = -INFINITY;
+    run_sum[l] = 0.f;
 #pragma unroll
     for (int ob = 0; ob < MB; ++ob)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[ob][lb][i] = 0.f;
+      for (int i = 0; i < 16; ++i) acc[ob][l][i] = 0.f;
   }
+  const float c = a.scale * kLog2e;                    // >= 0: a negative scale is folded into the sign of the packed queries
+  const float slack = c > 0.f ? kSlack / c : 0.f;      // how far a logit may pass the base before the base moves
+  const int row = 32 * tp + n, row_base = row * (2 * D) + (g ^ row_swizzle<D>(row)) * 16;
 
-  // COOP: this wave's share of a tile (32 rows = 64 D contiguous bytes), 16 bytes per lane and load
-  auto issue = [&](int i0, bf16x8 (&r)[LW]) {
+  // (the weights are waited for here: left pending, the loop would wait for them, and with them for the rows, every time)
 #pragma unroll
-    for (int j = 0; j < LW; ++j) {
-      const int q = (head * LW + j) * 64 + lane;
-      const int item = i0 + q / CPR;
-      bf16x8 v;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(0.f);
-      if (item < i_end) v = *reinterpret_cast<const bf16x8*>(Eb + static_cast<int64_t>(item) * D + (q % CPR) * 8);
-      r[j] = v;
-    }
-  };
+  for (int kk = 0; kk < K1; ++kk) asm volatile("" : "+v"(wk[kk]), "+v"(wv[kk]));
+  wait_lds_loads<0>();
+  clear_tail(i_begin, 0);
+  lds_barrier();
 
-  auto process_tile = [&](int i0, const bf16x8 (&x)[K1]) {
-    // The LDS copy of W_K^T must be re-read for every tile (that is the point of keeping it in LDS
-    // rather than in registers); an opaque base index stops the compiler from hoisting the reads.
-    int wk_base = lane;
-    asm volatile("" : "+v"(wk_base));
-
-    f32x16 d1[MB], d2[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) d1[mb][i] = d2[mb][i] = 0.f;
-    // the LDS reads run kAhead k-steps ahead of the MFMAs that use them (one wave per SIMD: nobody else
-    // covers the LDS latency)
-    constexpr int kAhead = 3;
-    bf16x8 wkf[WK_LDS ? K1 : 1][MB];
-    auto fetch = [&](int kk) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) wkf[WK_LDS ? kk : 0][mb] = lds_wk[wk_base + (kk * MB + mb) * 64];
-    };
-    if (WK_LDS) {
-#pragma unroll
-      for (int kk = 0; kk < kAhead && kk < K1; ++kk) fetch(kk);
-    }
-#pragma unroll
-    for (int kk = 0; kk < K1; ++kk) {
-      if (WK_LDS && kk + kAhead < K1) fetch(kk + kAhead);
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16x8 w = WK_LDS ? wkf[WK_LDS ? kk : 0][mb] : wk[WK_LDS ? 0 : kk][WK_LDS ? 0 : mb];
-        d1[mb] = mfma32(w, x[kk], d1[mb]);
-        d2[mb] = mfma32(x[kk], wv[kk][mb], d2[mb]);
-      }
-    }
+  int s = 0;
+  for (int i0 = i_begin; i0 < i_end; i0 += S::kRows, ++s) {
+    const int buf = NX == 2 ? s & 1 : 0;
+    const int t0 = i0 + 32 * tp;       // this wave's tile
+    const bool live = t0 < i_end;      // uniform over the wave
     bf16x8 kf[K2], vf[MB][2];
+    unsigned char* const ex = ex_lds + buf * S::kExchange;
+    if (live) {
+      f32x16 d1, d2;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      kf[2 * mb] = pack_half(d1[mb], 0);
-      kf[2 * mb + 1] = pack_half(d1[mb], 1);
-      vf[mb][0] = pack_half(d2[mb], 0);
-      vf[mb][1] = pack_half(d2[mb], 1);
-    }
-
-#pragma unroll
-    for (int lb = 0; lb < LB; ++lb) {
-      f32x16 sc;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sc[i] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < K2; ++kk) sc = mfma32(kf[kk], qb[kk][lb], sc);
-      // register 4j + r of this lane is item i0 + 8j + 4g + r; only a chunk's last tile can be ragged
-      const float c = a.scale * kLog2e;  // >= 0: a negative scale is folded into the sign of the packed queries
-      const bool ragged = i0 + 32 > i_end;  // uniform
-      if (PHI == kPhiSoftmax) {
-        if (ragged) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (i0 + 8 * (i >> 2) + 4 * g + (i & 3) >= i_end) sc[i] = -INFINITY;
-        }
-        float tmax = sc[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sc[i]);
-        tmax = pair_max(tmax);
-        const float new_max = fmaxf(run_max[lb], tmax);  // finite: the tile holds at least one valid item
-        if (__any(new_max > run_max[lb])) {  // uniform; after the first tiles the maximum rarely moves
-          const float alpha = run_max[lb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((run_max[lb] - new_max) * c);
-          run_sum[lb] *= alpha;
-          run_max[lb] = new_max;
-#pragma unroll
-          for (int ob = 0; ob < MB; ++ob)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ob][lb][i] *= alpha;
-        }
-        const float shift = -new_max * c;  // exp2(raw * c + shift) = exp(scale * raw - running maximum)
-        float psum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float raw = sc[i];
-          sc[i] = __builtin_amdgcn_exp2f(fmaf(raw, c, shift));
-          if (ragged && raw == -INFINITY) sc[i] = 0.f;  // (explicit: also right for scale = 0)
-          psum += sc[i];
-        }
-        run_sum[lb] += psum;
-      } else {
-        // SiLU(scale * s) = scale * s * sigmoid(scale * s); the factor `scale` is applied by the merge
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sc[i] = sc[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-sc[i] * c));
-        // (no mask is needed here: rows past the end of the chunk were loaded as zeros, so their projected keys are
-        // zero, their logits are zero and SiLU(0) = 0 exactly)
-      }
-      const bf16x8 p0 = pack_half(sc, 0), p1 = pack_half(sc, 1);
-#pragma unroll
-      for (int ob = 0; ob < MB; ++ob) {
-        acc[ob][lb] = mfma32(vf[ob][0], p0, acc[ob][lb]);
-        acc[ob][lb] = mfma32(vf[ob][1], p1, acc[ob][lb]);
-      }
-    }
-  };
-
-  if constexpr (COOP) {
-    bf16x8 ring[P][LW];
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-      if (i_begin + 32 * p < i_end) issue(i_begin + 32 * p, ring[p]);
-    for (int base = i_begin; base < i_end; base += 32 * P) {
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        const int i0 = base + 32 * p;
-        if (i0 >= i_end) break;  // uniform over the workgroup
-        unsigned char* buf = xs[NXS == 2 ? p & 1 : 0];
-#pragma unroll
-        for (int j = 0; j < LW; ++j) {
-          const int q = (head * LW + j) * 64 + lane;
-          *reinterpret_cast<bf16x8*>(buf + (q / CPR) * PITCH + (q % CPR) * 16) = ring[p][j];
-        }
-        // with two buffers a wave arrives here only after it has finished reading the tile before the
-        // previous one, which is the one this buffer held; with one, a second barrier follows the reads
-        __syncthreads();
-        if (i0 + 32 * P < i_end) issue(i0 + 32 * P, ring[p]);
-        bf16x8 x[K1];
-#pragma unroll
-        for (int kk = 0; kk < K1; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(buf + n * PITCH + 32 * kk + 16 * g);
-        if (NXS == 1) __syncthreads();
-        process_tile(i0, x);
-      }
-    }
-  } else {
-    for (int i0 = i_begin; i0 < i_end; i0 += 32) {
+      for (int i = 0; i < 16; ++i) d1[i] = d2[i] = 0.f;
+      int base = row_base + buf * S::kXBytes;
+      asm volatile("" : "+v"(base));  // (the addresses are formed here, not carried through the loop)
+      // (the reads run kAhead k-steps ahead of their use and, fenced, no further: registers)
+      constexpr int kAhead = K1 < 3 ? K1 : 3;
       bf16x8 x[K1];
 #pragma unroll
-      for (int kk = 0; kk < K1; ++kk) x[kk] = xnext[kk];
-      if (i0 + 32 < i_end) load_tile(i0 + 32, xnext);
-      process_tile(i0, x);
+      for (int kk = 0; kk < K1 + kAhead; ++kk) {
+        if (kk < K1) x[kk] = *reinterpret_cast<const bf16x8*>(lds + ((base ^ (kk % 8 * 32)) + kk / 8 * 256));
+        if (kk >= kAhead) {
+          d1 = mfma32(wk[kk - kAhead], x[kk - kAhead], d1);
+          d2 = mfma32(x[kk - kAhead], wv[kk - kAhead], d2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if constexpr (MB == 1) {
+        kf[0] = pack_half(d1, 0), kf[1] = pack_half(d1, 1);
+        vf[0][0] = pack_half(d2, 0), vf[0][1] = pack_half(d2, 1);
+      } else {
+        bf16x8* dst = reinterpret_cast<bf16x8*>(ex) + (wave * 4) * 64 + lane;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) dst[f * 64] = pack_half(d1, f), dst[(2 + f) * 64] = pack_half(d2, f);
+      }
+    }
+    const int next = i0 + S::kRows;
+    if constexpr (NX == 2) {
+      if (next < i_end) {
+        wait_lds_loads<0>();
+        clear_tail(next, buf ^ 1);
+      }
+    }
+    // publishes the next step's rows (NX == 2) and this step's exchange; everybody has read this step's rows
+    if (MB > 1 || next < i_end) lds_barrier();
+    const int after = NX == 2 ? next + S::kRows : next;
+    if (after < i_end) ask_rows(after, buf);
+
+    // A wave that projects always has a matrix instruction ready: without priority the other wave of its SIMD would wait
+    // for it to finish before each of the few that stand between its vector instructions.
+    __builtin_amdgcn_s_setprio(2);
+    if (live) {
+      if constexpr (MB == 2) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          const bf16x8* src = reinterpret_cast<const bf16x8*>(ex) + ((wave - half + mb) * 4) * 64 + lane;
+#pragma unroll
+          for (int f = 0; f < 2; ++f) kf[2 * mb + f] = src[f * 64];
+        }
+      }
+      const bool ragged = t0 + 32 > i_end;  // uniform; only a chunk's last tile can be
+#pragma unroll
+      for (int l = 0; l < LBW; ++l) {
+        const int lb = half * LBW + l;
+        if (LB % MB != 0 && lb >= LB) break;  // uniform
+        f32x16 sc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < K2; ++kk) sc = mfma32(kf[kk], q_lds[((hl * K2 + kk) * LB + lb) * 64 + lane], sc);
+        // register 4j + r of this lane is item t0 + 8j + 4g + r
+        if (PHI == kPhiSoftmax) {
+          auto mask = [&](float to) {
+            if (!ragged) return;
+            int valid = i_end - t0 - 4 * g;
+            asm volatile("" : "+v"(valid));  // (the comparisons stay in here)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              if (8 * (i >> 2) + (i & 3) >= valid) sc[i] = to;
+          };
+          mask(-INFINITY);
+          float tmax = sc[0];
+#pragma unroll
+          for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sc[i]);
+          // The weights' base follows the maximum at a distance: it moves once a logit passes it by kSlack (in powers of
+          // two), so that most tiles rescale nothing.
+          if (__any(tmax > run_max[l] + slack)) {  // uniform
+            const float new_max = fmaxf(run_max[l], pair_max(tmax));  // finite: the tile holds at least one valid item
+            const float alpha = run_max[l] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((run_max[l] - new_max) * c);
+            run_sum[l] *= alpha;
+            run_max[l] = new_max;
+#pragma unroll
+            for (int ob = 0; ob < MB; ++ob)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) acc[ob][l][i] *= alpha;
+          }
+          const float shift = -run_max[l] * c;  // exp2(raw * c + shift) = exp(scale * raw - base)
+          float psum = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sc[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, shift));
+          mask(0.f);  // (explicit: also right for scale = 0)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) psum += sc[i];
+          run_sum[l] += psum;
+        } else {
+          // SiLU(scale * s) = scale * s * sigmoid(scale * s); the factor `scale` is applied by the merge
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sc[i] = sc[i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-sc[i] * c));
+          // (no mask is needed here: rows past the end of the chunk are zeros, so their projected keys are zero, their
+          // logits are zero and SiLU(0) = 0 exactly)
+        }
+        const bf16x8 p0 = pack_half(sc, 0), p1 = pack_half(sc, 1);
+        if constexpr (MB == 2) {
+          if (LBW > 1) __builtin_amdgcn_sched_barrier(0);  // (fetched no earlier: registers)
+#pragma unroll
+          for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int f = 0; f < 2; ++f) vf[mb][f] = reinterpret_cast<const bf16x8*>(ex)[((wave - half + mb) * 4 + 2 + f) * 64 + lane];
+        }
+#pragma unroll
+        for (int ob = 0; ob < MB; ++ob) {
+          acc[ob][l] = mfma32(vf[ob][0], p0, acc[ob][l]);
+          acc[ob][l] = mfma32(vf[ob][1], p1, acc[ob][l]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if constexpr (NX == 1) {
+      if (next < i_end) {
+        wait_lds_loads<0>();
+        clear_tail(next, 0);
+        lds_barrier();
+      }
+    }
+  }
+
+  // the tiles of a step are combined in ascending order by the waves of the first one
+  if constexpr (TP > 1) {
+    constexpr int kPer = MB * LBW * 4096 + LBW * 512;  // bytes per wave
+    lds_barrier();  // the rows' and the exchange's last readers are done
+    if (tp > 0) {
+      unsigned char* dst = lds + ((tp - 1) * HG * MB + hl * MB + half) * kPer;
+#pragma unroll
+      for (int l = 0; l < LBW; ++l) {
+#pragma unroll
+        for (int ob = 0; ob < MB; ++ob)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<float4*>(dst + ((ob * LBW + l) * 4 + j) * 1024 + lane * 16) =
+                make_float4(acc[ob][l][4 * j], acc[ob][l][4 * j + 1], acc[ob][l][4 * j + 2], acc[ob][l][4 * j + 3]);
+        *reinterpret_cast<float2*>(dst + MB * LBW * 4096 + l * 512 + lane * 8) = make_float2(run_max[l], run_sum[l]);
+      }
+    }
+    lds_barrier();
+    if (tp > 0) return;
+#pragma unroll
+    for (int l = 0; l < LBW; ++l) {
+      float2 ms[TP];
+      float top = run_max[l];
+      ms[0] = make_float2(run_max[l], run_sum[l]);
+#pragma unroll
+      for (int p = 1; p < TP; ++p) {
+        ms[p] = *reinterpret_cast<const float2*>(lds + ((p - 1) * HG * MB + hl * MB + half) * kPer + MB * LBW * 4096 + l * 512 + lane * 8);
+        top = fmaxf(top, ms[p].x);
+      }
+      // (a tile without items has base -inf and weight zero; the first tile of a chunk has one; phi = SiLU has no base)
+      float w[TP];
+#pragma unroll
+      for (int p = 0; p < TP; ++p)
+        w[p] = PHI != kPhiSoftmax ? 1.f : ms[p].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ms[p].x - top) * c);
+      run_max[l] = top, run_sum[l] = ms[0].y * w[0];
+#pragma unroll
+      for (int ob = 0; ob < MB; ++ob)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[ob][l][i] *= w[0];
+#pragma unroll
+      for (int p = 1; p < TP; ++p) {
+        const unsigned char* src = lds + ((p - 1) * HG * MB + hl * MB + half) * kPer;
+        run_sum[l] = fmaf(ms[p].y, w[p], run_sum[l]);
+#pragma unroll
+        for (int ob = 0; ob < MB; ++ob) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float4 v = *reinterpret_cast<const float4*>(src + ((ob * LBW + l) * 4 + j) * 1024 + lane * 16);
+            acc[ob][l][4 * j] = fmaf(v.x, w[p], acc[ob][l][4 * j]), acc[ob][l][4 * j + 1] = fmaf(v.y, w[p], acc[ob][l][4 * j + 1]);
+            acc[ob][l][4 * j + 2] = fmaf(v.z, w[p], acc[ob][l][4 * j + 2]), acc[ob][l][4 * j + 3] = fmaf(v.w, w[p], acc[ob][l][4 * j + 3]);
+          }
+        }
+      }
     }
   }
 
   // partials: lane (link n of block lb) holds head columns 32ob + 8j + 4g + r in register 4j + r
   const int64_t slot = (static_cast<int64_t>(b) * a.chunks + chunk) * H + head;
 #pragma unroll
-  for (int lb = 0; lb < LB; ++lb) {
+  for (int l = 0; l < LBW; ++l) {
+    const int lb = half * LBW + l;
+    if (LB % MB != 0 && lb >= LB) break;  // uniform
     const int link = 32 * lb + n;
     float* dst = a.part_acc + (slot * M + link) * DH + 4 * g;
 #pragma unroll
     for (int ob = 0; ob < MB; ++ob)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        float4 v = make_float4(acc[ob][lb][4 * j], acc[ob][lb][4 * j + 1], acc[ob][lb][4 * j + 2], acc[ob][lb][4 * j + 3]);
+        float4 v = make_float4(acc[ob][l][4 * j], acc[ob][l][4 * j + 1], acc[ob][l][4 * j + 2], acc[ob][l][4 * j + 3]);
         *reinterpret_cast<float4*>(dst + 32 * ob + 8 * j) = v;
       }
-    const float total = pair_sum(run_sum[lb]);
+    const float total = pair_sum(run_sum[l]);
     if (g == 0) {
       float* ml = a.part_ml + (slot * M + link) * 2;
-      ml[0] = run_max[lb] * a.scale;  // the merge works on scaled logits
+      ml[0] = run_max[l] * a.scale;  // the merge works on scaled logits
       ml[1] = total;
     }
   }
@@ -517,89 +566,103 @@ __global__ __launch_bounds__(2 * D) void merge_values_kernel(MergeValuesArgs a) 
   }
 }
 
-template <int DH, int M, int H, int PHI>
-hipError_t launch_phi(const HistArgs& a, int users, bool coop, hipStream_t s) {
-  constexpr bool kWkLds = DH * H >= 256;
-  constexpr size_t slice = kWkLds ? static_cast<size_t>(DH) * H * DH * 2 : 0;  // one head's slice of W_K^T
-  if constexpr (H > 1 && !(kWkLds && H > 4)) {  // (eight waves of d = 256 would not fit the register file)
-    if (coop) {
-      constexpr size_t lds = slice * H;
-      auto kernel = links_over_history_kernel<DH, M, H, PHI, kWkLds, true>;
-      if (lds > 64 * 1024) {
-        static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-        if (attr != hipSuccess) return attr;
-      }
-      launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users), dim3(64 * H), lds, s, a);
-      return hipGetLastError();
-    }
-  }
-  auto kernel = links_over_history_kernel<DH, M, H, PHI, kWkLds, false>;
-  if (slice > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(slice));
+// Forms of a workgroup, by the amount of work (plan()):
+//   kShort   one head, four waves: one step is all there is.  The most compute units share the first loads.
+//   kNarrow  one head, eight waves: a row goes to h workgroups, but a workgroup covers many rows, which leaves few partials.
+//   kWide    several heads, eight waves: for long histories, whose rows cost more than their partials.
+//   kWalk, kWalkTogether  the kernels of mfma_history_walk.hip, one wave or one per head
+enum Form { kShort, kNarrow, kWide, kWalk, kWalkTogether };
+constexpr int waves_per_group(int form) { return form == kShort ? 4 : 8; }
+constexpr int heads_per_group(int dh, int h, int form) { return form != kWide ? 1 : dh == 64 ? std::min(h, 2) : std::min(h, 4); }
+constexpr int tiles_per_step(int dh, int h, int form) { return waves_per_group(form) / (heads_per_group(dh, h, form) * (dh / 32)); }
+
+template <int DH, int M, int H, int PHI, int FORM>
+hipError_t launch_shape(const HistArgs& a, int users, hipStream_t s) {
+  constexpr int HG = heads_per_group(DH, H, FORM), TP = tiles_per_step(DH, H, FORM);
+  using S = HistShape<DH, M, H, HG, TP>;
+  static_assert(S::kLds <= 160 * 1024, "LDS");
+  auto kernel = links_over_history_kernel<DH, M, H, PHI, HG, TP>;
+  if (S::kLds > 64 * 1024) {
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
     if (attr != hipSuccess) return attr;
   }
-  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H), dim3(64), slice, s, a);
+  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H / HG), dim3(S::kThreads), S::kLds, s, a);
   return hipGetLastError();
 }
 
+template <int DH, int M, int H, int PHI>
+hipError_t launch_form(const HistArgs& a, int users, int form, hipStream_t s) {
+  if constexpr (H > 1) {
+    if (form == kWide) return launch_shape<DH, M, H, PHI, kWide>(a, users, s);
+  }
+  return form == kShort ? launch_shape<DH, M, H, PHI, kShort>(a, users, s) : launch_shape<DH, M, H, PHI, kNarrow>(a, users, s);
+}
+
 template <int DH, int M, int H>
-hipError_t launch_main(const HistArgs& a, int phi, int users, bool coop, hipStream_t s) {
-  return phi == kPhiSoftmax ? launch_phi<DH, M, H, kPhiSoftmax>(a, users, coop, s)
-                            : launch_phi<DH, M, H, kPhiSilu>(a, users, coop, s);
+hipError_t launch_main(const HistArgs& a, int phi, int users, int form, hipStream_t s) {
+  return phi == kPhiSoftmax ? launch_form<DH, M, H, kPhiSoftmax>(a, users, form, s) : launch_form<DH, M, H, kPhiSilu>(a, users, form, s);
 }
 
 template <int DH, int H>
-hipError_t dispatch_m(const HistArgs& a, int links, int phi, int users, bool coop, hipStream_t s) {
+hipError_t dispatch_m(const HistArgs& a, int links, int phi, int users, int form, hipStream_t s) {
   switch (links) {
-    case 32: return launch_main<DH, 32, H>(a, phi, users, coop, s);
-    case 64: return launch_main<DH, 64, H>(a, phi, users, coop, s);
-    case 96: return launch_main<DH, 96, H>(a, phi, users, coop, s);
-    case 128: return launch_main<DH, 128, H>(a, phi, users, coop, s);
+    case 32: return launch_main<DH, 32, H>(a, phi, users, form, s);
+    case 64: return launch_main<DH, 64, H>(a, phi, users, form, s);
+    case 96: return launch_main<DH, 96, H>(a, phi, users, form, s);
+    case 128: return launch_main<DH, 128, H>(a, phi, users, form, s);
   }
   return hipErrorInvalidValue;
 }
 
 template <int DH>
-hipError_t dispatch_h(const HistArgs& a, int h, int links, int phi, int users, bool coop, hipStream_t s) {
+hipError_t dispatch_h(const HistArgs& a, int h, int links, int phi, int users, int form, hipStream_t s) {
   switch (h) {
-    case 1: return dispatch_m<DH, 1>(a, links, phi, users, coop, s);
-    case 2: return dispatch_m<DH, 2>(a, links, phi, users, coop, s);
-    case 4: return dispatch_m<DH, 4>(a, links, phi, users, coop, s);
-    case 8: if (DH == 32) return dispatch_m<32, 8>(a, links, phi, users, coop, s);
+    case 1: return dispatch_m<DH, 1>(a, links, phi, users, form, s);
+    case 2: return dispatch_m<DH, 2>(a, links, phi, users, form, s);
+    case 4: return dispatch_m<DH, 4>(a, links, phi, users, form, s);
+    case 8: if (DH == 32) return dispatch_m<32, 8>(a, links, phi, users, form, s);
   }
   return hipErrorInvalidValue;
 }
 
 struct Layout {
-  int chunk_items, chunks;
-  bool coop;  // h-wave workgroups that stage each tile once through LDS (long histories, d <= 128)
+  int chunk_items, chunks, form;
   size_t wk, wv, qb, acc, ml, total;
 };
 
-Layout plan(int B, int N, int d, int h, int m, bool q_per_user) {
+Layout plan(int B, int N, int d, int h, int m, bool q_per_user, bool walk) {
   Layout l{};
+  auto sized = [&] {
+    l.wk = l.wv = align_up(static_cast<size_t>(d) * d * 2);
+    l.qb = align_up(static_cast<size_t>(q_per_user ? B : 1) * m * d * 2);
+    l.acc = align_up(static_cast<size_t>(B) * l.chunks * m * d * sizeof(float));
+    l.ml = align_up(static_cast<size_t>(B) * l.chunks * h * m * 2 * sizeof(float));
+    l.total = l.wk + l.wv + l.qb + l.acc + l.ml;
+    return l;
+  };
+  if (walk) {
+    const WalkPlan w = walk_plan(B, N, d, h);
+    l.chunk_items = w.chunk_items, l.chunks = w.chunks, l.form = w.coop ? kWalkTogether : kWalk;
+    return sized();
+  }
+  // A workgroup per compute unit, and the smallest form that then has one step, or the one for the amount of work.
+  // Measured, history + merge kernel in us, for four-wave, narrow and wide groups:
+  //   B=1 N=2048 d=256: 11.7, 12.9, 13.1     B=32 N=1024 d=128: 15.0, 15.1, 18.1     B=32 N=2048 d=128: 20.2, 18.8, 20.5
+  //   B=8 N=16384 d=128: 31.1, 26.3, 25.5    B=16 N=4096 d=256: 36.4, 34.2, 32.4
+  const int64_t slots = compute_units();
   const int tiles = (N + 31) / 32;
-  // Short histories: every (chunk, head) pair is a one-wave workgroup and a compute unit runs four of
-  // them at once (eight when d/h = 32); aim at one round of workgroups.  Long histories with d <= 128
-  // (at least four tiles per compute unit): h-wave workgroups, two per compute unit.  At least two
-  // tiles per chunk so that the stationary operands are fetched for more than one tile and the merge
-  // stays small.
-  l.coop = h > 1 && !(d >= 256 && h > 4) && static_cast<int64_t>(B) * tiles >= 4 * static_cast<int64_t>(compute_units());
-  // (at d = 256 the cooperative workgroup keeps all of W_K^T in LDS and is alone on its compute unit)
-  const int64_t slots = static_cast<int64_t>(l.coop ? (d >= 256 ? 1 : 2) : (d / h == 32 ? 8 : 4)) * compute_units();
-  int chunk_tiles = static_cast<int>((static_cast<int64_t>(B) * tiles * (l.coop ? 1 : h) + slots - 1) / slots);
-  if (chunk_tiles < 2) chunk_tiles = 2;
-  if (chunk_tiles > tiles) chunk_tiles = tiles;
-  l.chunk_items = chunk_tiles * 32;
-  l.chunks = (tiles + chunk_tiles - 1) / chunk_tiles;
-  l.wk = l.wv = align_up(static_cast<size_t>(d) * d * 2);
-  l.qb = align_up(static_cast<size_t>(q_per_user ? B : 1) * m * d * 2);
-  l.acc = align_up(static_cast<size_t>(B) * l.chunks * m * d * sizeof(float));
-  l.ml = align_up(static_cast<size_t>(B) * l.chunks * h * m * 2 * sizeof(float));
-  l.total = l.wk + l.wv + l.qb + l.acc + l.ml;
-  return l;
+  int tp = 1, groups = 1, steps = tiles;
+  auto shape = [&](int form) {
+    l.form = form;
+    tp = tiles_per_step(d / h, h, form), groups = h / heads_per_group(d / h, h, form), steps = (tiles + tp - 1) / tp;
+  };
+  shape(kShort);
+  if (static_cast<int64_t>(B) * steps * groups > slots) shape(h > 1 && static_cast<int64_t>(B) * tiles * d >= 2048 * slots ? kWide : kNarrow);
+  int chunk_steps = static_cast<int>((static_cast<int64_t>(B) * steps * groups + slots - 1) / slots);
+  if (chunk_steps > steps) chunk_steps = steps;
+  l.chunk_items = chunk_steps * tp * 32;
+  l.chunks = (steps + chunk_steps - 1) / chunk_steps;
+  return sized();
 }
 
 }  // namespace
@@ -607,11 +670,11 @@ Layout plan(int B, int N, int d, int h, int m, bool q_per_user) {
 bool links_over_history_supported(int d, int h, int m) { return queries_over_links_supported(d, h, m); }
 
 size_t links_over_history_workspace(int B, int N, int d, int h, int m, bool q_per_user) {
-  return plan(B, N, d, h, m, q_per_user).total;
+  return std::max(plan(B, N, d, h, m, q_per_user, false).total, plan(B, N, d, h, m, q_per_user, true).total);
 }
 
 void links_over_history_jobs(const LinksOverHistory& q, void* workspace, PackJobs& jobs) {
-  const Layout l = plan(q.B, q.N, q.d, q.h, q.m, q.lc_user_stride != 0);
+  const Layout l = plan(q.B, q.N, q.d, q.h, q.m, q.lc_user_stride != 0, q.walk);
   char* ws = static_cast<char*>(workspace);
   jobs.weights[jobs.n_weights++] = PackWeight{q.Wk, ws};
   jobs.weights[jobs.n_weights++] = PackWeight{q.Wv, ws + l.wk};
@@ -623,7 +686,7 @@ void links_over_history_jobs(const LinksOverHistory& q, void* workspace, PackJob
 hipError_t links_over_history(const LinksOverHistory& q, void* workspace, hipStream_t s) {
   const int d = q.d, h = q.h, m = q.m, dh = d / h;
   const bool per_user = q.lc_user_stride != 0;
-  const Layout l = plan(q.B, q.N, d, h, m, per_user);
+  const Layout l = plan(q.B, q.N, d, h, m, per_user, q.walk);
   char* ws = static_cast<char*>(workspace);
   void* WkA = ws;
   void* WvB = ws + l.wk;
@@ -650,7 +713,10 @@ hipError_t links_over_history(const LinksOverHistory& q, void* workspace, hipStr
   a.qb_user_frags = per_user ? static_cast<int64_t>(m) * d / 8 : 0;
   a.part_acc = part_acc, a.part_ml = part_ml;
   a.N = q.N, a.chunk_items = l.chunk_items, a.chunks = l.chunks, a.scale = fabsf(q.scale);
-  e = dh == 32 ? dispatch_h<32>(a, h, m, q.phi, q.B, l.coop, s) : dispatch_h<64>(a, h, m, q.phi, q.B, l.coop, s);
+  if (q.walk)
+    e = walk_history(a, d, h, m, q.B, l.form == kWalkTogether, s);
+  else
+    e = dh == 32 ? dispatch_h<32>(a, h, m, q.phi, q.B, l.form, s) : dispatch_h<64>(a, h, m, q.phi, q.B, l.form, s);
   if (e != hipSuccess) return e;
 
   MergeArgs g{part_acc, part_ml, q.lens, static_cast<bf16_t*>(q.LP), q.N, l.chunk_items, l.chunks, h, m, dh, fabsf(q.scale)};

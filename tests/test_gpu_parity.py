@@ -642,3 +642,26 @@ def test_general_kernels_at_their_edges(B, N, C, d, h, m, dtype):
     LP, O = binding.lime_request(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, g.T, g.L, g.Wq, g.Wk, g.Wv, h, s, s)
     LP2 = binding.lime_link_history(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, h, s)
     assert torch.equal(LP, LP2) and torch.equal(O, binding.lime_score_candidates(g.T, g.L, LP2, g.Wq, g.Wk, g.Wv, h, s))
+
+
+@pytest.mark.parametrize("B,N,C,d,h,m", [
+    (1, 1, 1, 256, 4, 64),       # one item, one query
+    (2, 65, 257, 256, 4, 96),    # a step of the history kernel and one item; three link blocks over two waves
+    (3, 129, 31, 128, 2, 32),    # one link block over two waves; one query short of a block
+    (5, 1057, 64, 128, 4, 128),  # several steps per workgroup, the last one item long
+    (2, 2049, 33, 256, 8, 64),   # one head per workgroup, eight tiles a step
+    (33, 2017, 40, 256, 4, 32),  # several heads per workgroup, the last step one tile and one item
+    (65, 2080, 20, 128, 4, 64),  # the same with heads of width 32
+])
+def test_history_and_target_attention_at_their_edges(B, N, C, d, h, m):
+    w = _sharp(workload=170 + m, B=B, N=N, C=C, d=d, h=h, m=m, dtype="bf16", len_range=(max(1, N // 3), N), pad_value=np.nan)
+    g = DeviceWorkload(w)
+    for name, got, ref in [
+        ("LP", binding.lime_link_history(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, h, w.softmax_scale),
+         orc.lime_link_history(w.E, w.lens, w.L, w.Wq, w.Wk, w.Wv, h, w.softmax_scale)),
+        ("O[T]", binding.lime_xor_history(g.E, g.lens, g.L, g.Wq, g.Wk, g.Wv, h, 0.1 * w.softmax_scale, want_os=False)[0],
+         orc.lime_xor_history(w.E, w.lens, w.L, w.Wq, w.Wk, w.Wv, h, 0.1 * w.softmax_scale, want_os=False)[0]),
+        ("target attention", binding.mha_target_attention(g.T, g.E, g.lens, g.Wq, g.Wk, g.Wv, h, w.softmax_scale),
+         orc.mha_target_attention(w.T, w.E, w.lens, w.Wq, w.Wk, w.Wv, h, w.softmax_scale)),
+    ]:
+        assert_close(host(got), ref, "bf16", name)
