@@ -294,7 +294,8 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
     };
     auto move_base = [&](int qb, f32x16& s, float mx) {
       const float by = pair_max(mx);  // the query's other items are in the other lane of the pair
-      const float keep = __builtin_amdgcn_exp2f(-by);
+      // (> kSlack except for the first tile, whose logits may be so low that 2^-by is infinite: there is nothing to keep yet)
+      const float keep = by > 0.f ? __builtin_amdgcn_exp2f(-by) : 1.f;
       run_sum[qb][0] *= keep, run_sum[qb][1] *= keep;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {

@@ -665,3 +665,23 @@ def test_history_and_target_attention_at_their_edges(B, N, C, d, h, m):
          orc.mha_target_attention(w.T, w.E, w.lens, w.Wq, w.Wk, w.Wv, h, w.softmax_scale)),
     ]:
         assert_close(host(got), ref, "bf16", name)
+
+
+@pytest.mark.parametrize("d,h", [(128, 4), (256, 4)])
+@pytest.mark.parametrize("scale", [0.1, -0.1])
+def test_logits_far_from_zero_and_scales_near_it(d, h, scale):
+    """All of a head's logits near -64 d/h scale (about -200 and -400, or +200 and +400): the softmax's first base lies
+    below the exponent range."""
+    rng = np.random.default_rng(5)
+    bf = lambda x: torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).float().numpy()  # noqa: E731
+    E = bf(-8 + 0.5 * rng.standard_normal((2, 100, d)))
+    X = np.full((2, 70, d), 8, np.float32)
+    L = np.full((64, d), 8, np.float32)
+    I, V = np.eye(d, dtype=np.float32), np.eye(d, dtype=np.float32) / 16  # outputs near -1/2
+    lens = np.array([100, 37], np.int32)
+    t = lambda x: dev(x, "bf16")  # noqa: E731
+    lens_d = torch.from_numpy(lens).cuda()
+    A = binding.mha_target_attention(t(X), t(E), lens_d, t(I), t(I), t(V), h, scale)
+    assert_close(host(A), orc.mha_target_attention(X, E, lens, I, I, V, h, scale), "bf16", "target attention")
+    LP = binding.lime_link_history(t(E), lens_d, t(L), t(I), t(I), t(V), h, scale)
+    assert_close(host(LP), orc.lime_link_history(E, lens, L, I, I, V, h, scale), "bf16", "LP")
