@@ -122,7 +122,8 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
       for (int i = 0; i < 16; ++i) acc[ob][l][i] = 0.f;
   }
   const float c = a.scale * kLog2e;                    // >= 0: a negative scale is folded into the sign of the packed queries
-  const float slack = c > 0.f ? kSlack / c : 0.f;      // how far a logit may pass the base before the base moves
+  // how far a logit may pass the base before the base moves (finite, so that the first tile always sets it)
+  const float slack = c > 0.f ? fminf(kSlack / c, 3e38f) : 0.f;
   const int row = 32 * tp + n, row_base = row * (2 * D) + (g ^ row_swizzle<D>(row)) * 16;
 
   // (the weights are waited for here: left pending, the loop would wait for them, and with them for the rows, every time)

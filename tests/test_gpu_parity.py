@@ -668,10 +668,10 @@ def test_history_and_target_attention_at_their_edges(B, N, C, d, h, m):
 
 
 @pytest.mark.parametrize("d,h", [(128, 4), (256, 4)])
-@pytest.mark.parametrize("scale", [0.1, -0.1])
+@pytest.mark.parametrize("scale", [0.1, -0.1, 1e-38])
 def test_logits_far_from_zero_and_scales_near_it(d, h, scale):
     """All of a head's logits near -64 d/h scale (about -200 and -400, or +200 and +400): the softmax's first base lies
-    below the exponent range."""
+    below the exponent range; a scale so small that eight powers of two divided by it are infinite: uniform weights."""
     rng = np.random.default_rng(5)
     bf = lambda x: torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).float().numpy()  # noqa: E731
     E = bf(-8 + 0.5 * rng.standard_normal((2, 100, d)))
