@@ -143,7 +143,7 @@ __device__ __forceinline__ void store_through(void* base, int span, int offset, 
 // the compiler makes every read of LDS after its own form of this load wait for the youngest such load.
 __device__ __forceinline__ void load_to_lds(unsigned lds_offset, unsigned lane_offset, const void* base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               : : "s"(__builtin_amdgcn_readfirstlane(lds_offset)), "v"(lane_offset), "s"(base) : "memory");
+               : : "s"(__builtin_amdgcn_readfirstlane(lds_offset)), "v"(lane_offset), "s"(base) : "memory", "m0");
 }
 template <int OUTSTANDING>
 __device__ __forceinline__ void wait_lds_loads() {  // all but the OUTSTANDING youngest loads of this wave have landed

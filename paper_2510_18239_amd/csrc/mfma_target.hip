@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
 #pragma unroll
     for (int j = 0; j < kLoads; ++j)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   : : "s"(__builtin_amdgcn_readfirstlane(dst + j * 1024)), "v"(lane * 16), "s"(src + j * 64) : "memory");
+                   : : "s"(__builtin_amdgcn_readfirstlane(dst + j * 1024)), "v"(lane * 16), "s"(src + j * 64) : "memory", "m0");
   };
   auto publish = [&] {  // this wave's part of the stage about to be read has arrived; so has everybody's
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(kLoads) : "memory");  // all but the youngest stage
