@@ -88,13 +88,65 @@ __device__ void score_wave(const PackArgs& p, int combo) {
   for (int i = 0; i < 16; ++i) store_as(dst + (8 * (i / 4) + 4 * g + i % 4) * 8, acc[i] * p.s_sign);
 }
 
+// Layer normalisation of 32 rows by a workgroup of four wavefronts: eight lanes per row, D / 64 pieces of eight columns
+// per lane, so that a row's statistics are a lane's own sums and three exchanges; mean first, then the centred second
+// moment, in fp32.  `take` asks for what it needs, `finish` leaves the rows, rounded to bf16 where a normalisation pass of
+// its own would have stored them, in LDS, from where every wavefront reads its fragments.
+template <int D>
+struct GroupNorm {
+  static constexpr int J = D / 64, kPitch = D + 8;  // (16 rows of a fragment read then cover all banks)
+  bf16x8 x[J], gamma[J], beta[J];
+  __device__ __forceinline__ void take(const bf16_t* rows, const bf16_t* ga, const bf16_t* be) {
+    const int r = threadIdx.x / 8, c = 8 * (threadIdx.x % 8);
+#pragma unroll
+    for (int j = 0; j < J; ++j) x[j] = *reinterpret_cast<const bf16x8*>(rows + static_cast<int64_t>(r) * D + 64 * j + c);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      gamma[j] = *reinterpret_cast<const bf16x8*>(ga + 64 * j + c);
+      beta[j] = *reinterpret_cast<const bf16x8*>(be + 64 * j + c);
+    }
+  }
+  __device__ __forceinline__ void finish(bf16_t* lds, float eps) {
+    float v[J][8], sum = 0.f, q = 0.f;
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[j][t] = static_cast<float>(x[j][t]), sum += v[j][t];
+    const float mean = group_sum<8>(sum) * (1.f / D);
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[j][t] -= mean, q = fmaf(v[j][t], v[j][t], q);
+    const float inv = 1.f / sqrtf(group_sum<8>(q) * (1.f / D) + eps);
+    bf16_t* dst = lds + threadIdx.x / 8 * kPitch + 8 * (threadIdx.x % 8);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      bf16x8 y;
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        y[t] = static_cast<__bf16>(fmaf(v[j][t] * inv, static_cast<float>(gamma[j][t]), static_cast<float>(beta[j][t])));
+      *reinterpret_cast<bf16x8*>(dst + 64 * j) = y;
+    }
+  }
+};
+
 // One wavefront of a projection job: 32 rows x 32 columns of X_u W on the matrix cores (project_block), written as two
 // fragments of the job's image.
+//
+// Normalised rows: from d = 128 on (a multiple of four column blocks: a workgroup's units then belong to one job) the
+// workgroup takes four column blocks of the same rows and normalises them together.  Below, a wavefront normalises its
+// rows by itself: an element costs it a dozen instructions, 32 of them per lane at d = 64, but 128 at d = 256, which every
+// one of a row's eight column blocks would repeat (pack kernel of a request with normalisations, d = 256: 10.9 us so,
+// 6.0 together).
 template <int D>
 __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int unit) {
   constexpr int NK = D / 16, CB = D / 32;
+  constexpr bool kTogether = CB % 4 == 0;
+  __shared__ __attribute__((aligned(16))) bf16_t normalised[kTogether ? 32 * (D + 8) : 8];
   const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, dh = p.dh, m = p.m;
-  const int lbs = m / 32, lb = unit % lbs, cb = unit / lbs % CB, u = unit / (lbs * CB);
+  const bool together = kTogether && p.p_norm[job];  // uniform over the workgroup
+  const int lbs = m / 32, u = unit / (lbs * CB);
+  const int lb = together ? unit / CB % lbs : unit % lbs, cb = together ? unit % CB : unit / lbs % CB;
   const bf16_t* X = p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(32 * lb + n) * D + 8 * g;  // row 32 lb + n
   const bf16_t* W = p.p_w[job];
   const int a = 32 * cb / dh, hc = 32 * cb % dh / 32;  // head, and 32-column block of the head
@@ -112,24 +164,44 @@ __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int uni
     }
     if (p.p_sign[job] < 0.f) lo = -lo, hi = -hi;
   } else {
-    bf16x8 x[NK];
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
-    bf16x8 gamma[NK], beta[NK];
-    if (p.p_norm[job]) {  // asked for with everything else
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) {
-        gamma[kk] = *reinterpret_cast<const bf16x8*>(p.p_gamma[job] + 16 * kk + 8 * g);
-        beta[kk] = *reinterpret_cast<const bf16x8*>(p.p_beta[job] + 16 * kk + 8 * g);
-      }
-    }
-    bf16x8 w[NK];
     const bf16_t* wcol = W + static_cast<int64_t>(8 * g) * D + 32 * cb + n;
+    bf16x8 x[NK], w[NK];
+    auto take_weights = [&] {
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk)
+      for (int kk = 0; kk < NK; ++kk)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) w[kk][t] = __builtin_bit_cast(__bf16, wcol[(16 * kk + t) * D].bits);
-    if (p.p_norm[job]) normalise_rows<D>(x, gamma, beta, p.p_eps[job]);
+        for (int t = 0; t < 8; ++t) w[kk][t] = __builtin_bit_cast(__bf16, wcol[(16 * kk + t) * D].bits);
+    };
+    auto take_rows = [&] {
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
+    };
+    if constexpr (kTogether) {
+      if (together) {
+        GroupNorm<D> norm;
+        norm.take(p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(32 * lb) * D, p.p_gamma[job], p.p_beta[job]);
+        take_weights();
+        norm.finish(normalised, p.p_eps[job]);
+        lds_barrier();
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(normalised + n * GroupNorm<D>::kPitch + 16 * kk + 8 * g);
+      } else {
+        take_rows();
+        take_weights();
+      }
+    } else {
+      take_rows();
+      bf16x8 gamma[NK], beta[NK];
+      if (p.p_norm[job]) {  // asked for with everything else
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+          gamma[kk] = *reinterpret_cast<const bf16x8*>(p.p_gamma[job] + 16 * kk + 8 * g);
+          beta[kk] = *reinterpret_cast<const bf16x8*>(p.p_beta[job] + 16 * kk + 8 * g);
+        }
+      }
+      take_weights();
+      if (p.p_norm[job]) normalise_rows<D>(x, gamma, beta, p.p_eps[job]);
+    }
     f32x16 acc = keys ? project_block<NK>(w, x) : project_block<NK>(x, w);
     if (p.p_sign[job] < 0.f) acc = -acc;
     lo = pack_half(acc, 0), hi = pack_half(acc, 1);
