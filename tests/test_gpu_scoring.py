@@ -136,3 +136,13 @@ def test_lime_scores_config3_full_size(widths):
     with the industrial interaction network [96] and the largest public one."""
     c = synth.CONFIGS[3]
     _request(3, c["B"], c["N"], c["C"], c["d"], c["h"], c["m"], 64, 256, widths, "bf16", None)
+
+
+@pytest.mark.parametrize("B,d,h,m", [
+    (2, 64, 2, 32),    # two column blocks: each wavefront normalises its rows by itself
+    (3, 128, 2, 96),   # four: one workgroup per 32 rows, an odd number of row blocks
+    (2, 256, 8, 128),  # eight: two workgroups per 32 rows
+])
+def test_lime_scores_normalised_link_rows(B, d, h, m):
+    """The link rows' normalisation inside the pack launch, in both of its forms."""
+    _request(780 + d, B, 70, 45, d, h, m, 8, 40, [96, 1], "bf16", (20, 70))
