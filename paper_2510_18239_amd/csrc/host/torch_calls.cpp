@@ -77,6 +77,7 @@ class Args {
 };
 
 void* ptr(const Tensor* t) { return t == nullptr ? nullptr : t->data_ptr(); }
+const int32_t* ints(const Tensor* t) { return static_cast<const int32_t*>(ptr(t)); }
 
 // Tensors of one call: contiguous, on the GPU, of one dtype and device; the first of them is returned.
 const Tensor& check(std::initializer_list<const Tensor*> tensors) {
@@ -177,12 +178,27 @@ class Scope {
   throw PyFailed{};
 }
 
-template <typename F>
-void call(F&& f) {
+// The interpreter lock given up for the lifetime of the object, taken back also when an exception passes.
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
+// One entry point of the library.  Its arguments are values: a tensor's pointer is taken at the call, under the lock, where
+// a tensor that has none (vmap's and other wrappers) may raise.
+template <typename... P, typename... A>
+void call(int32_t (*entry_point)(P...), A... args) {
   int32_t status;
-  Py_BEGIN_ALLOW_THREADS
-  status = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    status = entry_point(args...);
+  }
   if (status != LIME_OK) lime_failed(status, lime_last_error());
 }
 
@@ -218,12 +234,12 @@ PyObject* history(Args a) {
   Tensor OS;
   if (want_os) OS = Out(OSin, {B, N, d}, *E).t;
   Scope s(*E, a.object(), workspace, lime_workspace_bytes(is_xor ? LIME_OP_XOR_HISTORY : LIME_OP_LINK_HISTORY, B, N, 1, d, h, l.m, code, want_os ? 1 : 0));
-  call([&] {
-    return is_xor ? lime_xor_history(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(&LP.t),
-                                     want_os ? OS.data_ptr() : nullptr, B, N, d, h, l.m, scale, code, s.ws(), s.bytes(), s.stream())
-                  : lime_link_history(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(&LP.t), B, N,
-                                      d, h, l.m, scale, code, s.ws(), s.bytes(), s.stream());
-  });
+  if (is_xor)
+    call(lime_xor_history, ptr(E), ints(lens), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(&LP.t), want_os ? OS.data_ptr() : nullptr,
+         B, N, d, h, l.m, scale, code, s.ws(), s.bytes(), s.stream());
+  else
+    call(lime_link_history, ptr(E), ints(lens), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(&LP.t), B, N, d, h, l.m, scale, code,
+         s.ws(), s.bytes(), s.stream());
   return pair(LP.t, want_os ? &OS : nullptr);
 }
 
@@ -243,10 +259,8 @@ PyObject* xor_layers(Args a) {
   check_lens(lens, B);
   Out LP(LPin, {B, l.m, d}, *E);
   Scope s(*E, a.object(), workspace, lime_workspace_bytes(LIME_OP_XOR_LAYERS, B, N, 1, d, h, l.m, code, 0));
-  call([&] {
-    return lime_xor_layers(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(Wu), ptr(Wo),
-                           dim(*Wu, 0), ptr(&LP.t), B, N, d, h, l.m, scale, code, s.ws(), s.bytes(), s.stream());
-  });
+  call(lime_xor_layers, ptr(E), ints(lens), ptr(LC), l.stride, ptr(Wq), ptr(Wk), ptr(Wv), ptr(Wu), ptr(Wo), dim(*Wu, 0), ptr(&LP.t), B, N,
+       d, h, l.m, scale, code, s.ws(), s.bytes(), s.stream());
   return wrap(LP.t);
 }
 
@@ -261,10 +275,8 @@ PyObject* score_candidates(Args a) {
   const int32_t B = dim(*T, 0), C = dim(*T, 1), d = dim(*T, 2), m = dim(*L, 0), code = dtype_code(like);
   Out O(Oin, T->sizes(), *T);
   Scope s(*T, a.object(), workspace, lime_workspace_bytes(LIME_OP_SCORE_CANDIDATES, B, 1, C, d, h, m, code, 0));
-  call([&] {
-    return lime_score_candidates(ptr(T), ptr(L), ptr(LP), ptr(Wq), ptr(Wk), ptr(Wv), ptr(&O.t), B, C, d, h, m, scale, code, s.ws(),
-                                 s.bytes(), s.stream());
-  });
+  call(lime_score_candidates, ptr(T), ptr(L), ptr(LP), ptr(Wq), ptr(Wk), ptr(Wv), ptr(&O.t), B, C, d, h, m, scale, code, s.ws(), s.bytes(),
+       s.stream());
   return wrap(O.t);
 }
 
@@ -280,10 +292,8 @@ PyObject* target_attention(Args a) {
   check_lens(lens, B);
   Out O(Oin, T->sizes(), *T);
   Scope s(*T, a.object(), workspace, lime_workspace_bytes(LIME_OP_MHA_TARGET, B, N, C, d, h, 1, code, 0));
-  call([&] {
-    return mha_target_attention(ptr(T), ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(Wq), ptr(Wk), ptr(Wv), ptr(&O.t), B, C, N, d, h,
-                                scale, code, s.ws(), s.bytes(), s.stream());
-  });
+  call(mha_target_attention, ptr(T), ptr(E), ints(lens), ptr(Wq), ptr(Wk), ptr(Wv), ptr(&O.t), B, C, N, d, h, scale, code, s.ws(),
+       s.bytes(), s.stream());
   return wrap(O.t);
 }
 
@@ -302,11 +312,11 @@ PyObject* score_cached(Args a) {
   const int32_t h = dim(*W, ids != nullptr ? 1 : 2), m = dim(*W, ids != nullptr ? 2 : 3), d = dim(*LP, 2), code = dtype_code(like);
   Out O(Oin, {B, C, d}, *W);
   Scope s(*W, a.object(), workspace, lime_workspace_bytes(LIME_OP_SCORE_CACHED, B, 1, C, d, h, m, code, 0));
-  call([&] {
-    return ids != nullptr ? lime_score_candidates_gathered(ptr(W), static_cast<int32_t*>(ptr(ids)), dim(*W, 0), ptr(LP), ptr(Wv), ptr(&O.t),
-                                                           B, C, d, h, m, code, s.ws(), s.bytes(), s.stream())
-                          : lime_score_candidates_cached(ptr(W), ptr(LP), ptr(Wv), ptr(&O.t), B, C, d, h, m, code, s.ws(), s.bytes(), s.stream());
-  });
+  if (ids != nullptr)
+    call(lime_score_candidates_gathered, ptr(W), ints(ids), dim(*W, 0), ptr(LP), ptr(Wv), ptr(&O.t), B, C, d, h, m, code, s.ws(), s.bytes(),
+         s.stream());
+  else
+    call(lime_score_candidates_cached, ptr(W), ptr(LP), ptr(Wv), ptr(&O.t), B, C, d, h, m, code, s.ws(), s.bytes(), s.stream());
   return wrap(O.t);
 }
 
@@ -322,10 +332,8 @@ PyObject* history_prepared(Args a) {
   const int32_t B = dim(*E, 0), N = dim(*E, 1), d = dim(*E, 2), code = dtype_code(like);
   Out LP(LPin, {B, m, d}, *E);
   Scope s(*E, a.object(), workspace, lime_workspace_bytes(LIME_OP_LINK_HISTORY, B, N, 1, d, h, m, code, 0));
-  call([&] {
-    return lime_link_history_prepared(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(prepared), ptr(&LP.t), B, N, d, h, m, scale, is_xor, code,
-                                      s.ws(), s.bytes(), s.stream());
-  });
+  call(lime_link_history_prepared, ptr(E), ints(lens), ptr(prepared), ptr(&LP.t), B, N, d, h, m, scale, is_xor, code, s.ws(), s.bytes(),
+       s.stream());
   return wrap(LP.t);
 }
 
@@ -340,10 +348,8 @@ PyObject* candidates_prepared(Args a) {
   const int32_t B = dim(*T, 0), C = dim(*T, 1), d = dim(*T, 2), m = dim(*LP, 1), code = dtype_code(like);
   Out O(Oin, T->sizes(), *T);
   Scope s(*T, a.object(), workspace, lime_workspace_bytes(LIME_OP_SCORE_CANDIDATES, B, 1, C, d, h, m, code, 0));
-  call([&] {
-    return lime_score_candidates_prepared(ptr(T), ptr(LP), ptr(Wv), ptr(prepared), ptr(&O.t), B, C, d, h, m, scale, code, s.ws(), s.bytes(),
-                                          s.stream());
-  });
+  call(lime_score_candidates_prepared, ptr(T), ptr(LP), ptr(Wv), ptr(prepared), ptr(&O.t), B, C, d, h, m, scale, code, s.ws(), s.bytes(),
+       s.stream());
   return wrap(O.t);
 }
 
@@ -367,16 +373,12 @@ PyObject* request(Args a) {
   if (on_static) {
     c10::DeviceGuard guard(E->device());
     void* stream = stream_handle(a.object(), E->device().index());
-    call([&] {
-      return lime_request_static(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(LC), l.stride, ptr(Wqh), ptr(Wkh), ptr(Wvh), ptr(T), ptr(L),
-                                 ptr(Wqc), ptr(Wkc), ptr(Wvc), ptr(&LP.t), ptr(&O.t), B, N, C, d, h, l.m, sh, sc, is_xor, code, stream);
-    });
+    call(lime_request_static, ptr(E), ints(lens), ptr(LC), l.stride, ptr(Wqh), ptr(Wkh), ptr(Wvh), ptr(T), ptr(L), ptr(Wqc), ptr(Wkc),
+         ptr(Wvc), ptr(&LP.t), ptr(&O.t), B, N, C, d, h, l.m, sh, sc, is_xor, code, stream);
   } else {
     Scope s(*E, a.object(), workspace, lime_workspace_bytes(LIME_OP_REQUEST, B, N, C, d, h, l.m, code, 0));
-    call([&] {
-      return lime_request(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(LC), l.stride, ptr(Wqh), ptr(Wkh), ptr(Wvh), ptr(T), ptr(L), ptr(Wqc),
-                          ptr(Wkc), ptr(Wvc), ptr(&LP.t), ptr(&O.t), B, N, C, d, h, l.m, sh, sc, is_xor, code, s.ws(), s.bytes(), s.stream());
-    });
+    call(lime_request, ptr(E), ints(lens), ptr(LC), l.stride, ptr(Wqh), ptr(Wkh), ptr(Wvh), ptr(T), ptr(L), ptr(Wqc), ptr(Wkc), ptr(Wvc),
+         ptr(&LP.t), ptr(&O.t), B, N, C, d, h, l.m, sh, sc, is_xor, code, s.ws(), s.bytes(), s.stream());
   }
   return pair(LP.t, &O.t);
 }
@@ -394,10 +396,8 @@ PyObject* request_prepared(Args a) {
   check_lens(lens, B);
   Out LP(LPin, {B, m, d}, *E), O(Oin, T->sizes(), *T);
   Scope s(*E, a.object(), workspace, lime_workspace_bytes(LIME_OP_REQUEST_PREPARED, B, N, C, d, h, m, code, 0));
-  call([&] {
-    return lime_request_prepared(ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(T), ptr(Wv), ptr(prepared), ptr(&LP.t), ptr(&O.t), B, N, C, d,
-                                 h, m, sh, sc, is_xor, code, s.ws(), s.bytes(), s.stream());
-  });
+  call(lime_request_prepared, ptr(E), ints(lens), ptr(T), ptr(Wv), ptr(prepared), ptr(&LP.t), ptr(&O.t), B, N, C, d, h, m, sh, sc, is_xor,
+       code, s.ws(), s.bytes(), s.stream());
   return pair(LP.t, &O.t);
 }
 
@@ -417,11 +417,8 @@ PyObject* xor_backward(Args a) {
   std::array<Tensor, 6> o;
   for (int i = 0; i < 6; ++i) o[i] = at::empty(i < 3 ? QS->sizes() : QT->sizes(), QS->options());
   Scope s(*QS, a.object(), workspace, lime_workspace_bytes(LIME_OP_XOR_BACKWARD, B, N, 1, d, h, m, code, 0));
-  call([&] {
-    return lime_xor_backward(ptr(QS), ptr(KS), ptr(VS), ptr(QT), ptr(KT), ptr(VT), ptr(dOT), ptr(dOS), static_cast<int32_t*>(ptr(lens)),
-                             ptr(&o[0]), ptr(&o[1]), ptr(&o[2]), ptr(&o[3]), ptr(&o[4]), ptr(&o[5]), B, N, m, d, h, scale, code, s.ws(),
-                             s.bytes(), s.stream());
-  });
+  call(lime_xor_backward, ptr(QS), ptr(KS), ptr(VS), ptr(QT), ptr(KT), ptr(VT), ptr(dOT), ptr(dOS), ints(lens), ptr(&o[0]), ptr(&o[1]),
+       ptr(&o[2]), ptr(&o[3]), ptr(&o[4]), ptr(&o[5]), B, N, m, d, h, scale, code, s.ws(), s.bytes(), s.stream());
   PyObject* t = PyTuple_New(6);
   if (t == nullptr) throw PyFailed{};
   for (int i = 0; i < 6; ++i) PyTuple_SET_ITEM(t, i, wrap(o[i]));
@@ -453,11 +450,8 @@ PyObject* scores(Args a) {
   const size_t need = lime_scores_workspace_bytes(M, B, N, C, code);
   if (need == 0) lime_failed(LIME_INVALID_ARG, "lime_scores: the model or the sizes are not valid");
   Scope s(*E, a.object(), workspace, need);
-  call([&] {
-    return lime_scores(M, ptr(E), static_cast<int32_t*>(ptr(lens)), ptr(EC), ptr(T), want ? LC.data_ptr() : nullptr,
-                       want ? LP.data_ptr() : nullptr, want ? O.data_ptr() : nullptr, static_cast<float*>(out.data_ptr()), B, N, C, code, s.ws(),
-                       s.bytes(), s.stream());
-  });
+  call(lime_scores, M, ptr(E), ints(lens), ptr(EC), ptr(T), want ? LC.data_ptr() : nullptr, want ? LP.data_ptr() : nullptr,
+       want ? O.data_ptr() : nullptr, static_cast<float*>(out.data_ptr()), B, N, C, code, s.ws(), s.bytes(), s.stream());
   if (!want) return wrap(out);
   PyObject* t = PyTuple_New(4);
   if (t == nullptr) throw PyFailed{};

@@ -4,6 +4,8 @@ function include/lime.h declares, and rejects bad arguments before launching any
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -292,3 +294,28 @@ def test_per_request_calls_check_their_tensors_before_anything_else():
         binding.lime_score_candidates(3, x, x, None, None, None, 2, 1.0)
     with pytest.raises(TypeError):
         binding.lime_scores(object(), x, None, x, x)
+
+
+def test_per_request_calls_raise_for_tensors_without_storage():
+    """Under vmap a tensor has no data pointer: the call raises what torch raises.  In a process of its own: the error
+    once passed through the code that had given up the interpreter lock, which ended the process."""
+    script = """
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2510_18239_amd import binding
+
+class Stream:
+    cuda_stream = 16
+
+with FakeTensorMode():
+    bf = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+    E, L, W, LP = bf(3, 2, 40, 64), bf(32, 64), bf(64, 64), bf(2, 32, 64)
+    ws = torch.empty(1 << 22, dtype=torch.uint8, device="cuda")
+    try:
+        torch.func.vmap(lambda e: binding.lime_link_history(e, None, L, W, W, W, 2, 1.0, LP=LP, workspace=ws, stream=Stream()))(E)
+    except RuntimeError as e:
+        print("raised:", e)
+"""
+    r = subprocess.run([sys.executable, "-W", "ignore", "-c", script], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+    assert "raised: Cannot access data pointer" in r.stdout, (r.stdout, r.stderr[-2000:])
