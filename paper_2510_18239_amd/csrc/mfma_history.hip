@@ -9,12 +9,12 @@
 // The MB waves of a head and tile then trade their blocks of K~ and V~ through LDS and share out the links:
 //   S^T  (32 x links) = K~ . Q~_a^T   A operand = accumulators of the first product
 //   L^P^T(d/h x links) += V~^T . phi(S)^T   both operands are accumulators (of the 2nd and 3rd product)
-// Each lane owns one link (column of S^T and of L^P^T): the running softmax base, the running sum and the rescaling of the
+// Each lane owns one link (column of S^T and of L^P^T): the running maximum, the running sum and the rescaling of the
 // accumulator are all lane-local, plus one exchange with lane ^ 32.  Rows at or beyond lens[b] are
 // replaced by zeros before they are read and masked out of phi, so their content is never used.
 // The rows go from memory straight to LDS, a step ahead; the TP waves of a block combine their tiles' results in LDS
 // at the end.
-// Every chunk writes an un-normalised partial (base, sum, accumulator); a small merge kernel
+// Every chunk writes an un-normalised partial (maximum, sum, accumulator); a small merge kernel
 // combines the chunks of a user in a fixed order (deterministic) and writes L^P.
 #include <algorithm>
 
@@ -54,7 +54,6 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
   using S = HistShape<DH, M, H, HG, TP>;
   constexpr int D = S::D, K1 = S::K1, MB = S::MB, K2 = S::K2, LB = S::LB, LBW = S::LBW, NX = S::NX, kWaves = S::kWaves;
   constexpr int CPR = D / 8, LW = S::kXBytes / (kWaves * 1024);  // 1 KiB loads per wave and step
-  constexpr float kSlack = 8.f;
   extern __shared__ unsigned char lds[];
   unsigned char* const ex_lds = lds + NX * S::kXBytes;
   bf16x8* const q_lds = reinterpret_cast<bf16x8*>(ex_lds + NX * S::kExchange);
@@ -122,8 +121,6 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
       for (int i = 0; i < 16; ++i) acc[ob][l][i] = 0.f;
   }
   const float c = a.scale * kLog2e;                    // >= 0: a negative scale is folded into the sign of the packed queries
-  // how far a logit may pass the base before the base moves (finite, so that the first tile always sets it)
-  const float slack = c > 0.f ? fminf(kSlack / c, 3e38f) : 0.f;
   const int row = 32 * tp + n, row_base = row * (2 * D) + (g ^ row_swizzle<D>(row)) * 16;
 
   // (the weights are waited for here: left pending, the loop would wait for them, and with them for the rows, every time)
@@ -215,9 +212,10 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
           float tmax = sc[0];
 #pragma unroll
           for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sc[i]);
-          // The weights' base follows the maximum at a distance: it moves once a logit passes it by kSlack (in powers of
-          // two), so that most tiles rescale nothing.
-          if (__any(tmax > run_max[l] + slack)) {  // uniform
+          // The weights are relative to the running maximum, so that the largest is one exactly.  (A base that moves only
+          // once a logit passes it by eight powers of two saves 1 us of 99 at B=16 N=4096 C=8192 d=256 m=128, but rounds
+          // the largest weight like any other: link states up to 1.3 % further from the exact ones.)
+          if (__any(tmax > run_max[l])) {  // uniform
             const float new_max = fmaxf(run_max[l], pair_max(tmax));  // finite: the tile holds at least one valid item
             const float alpha = run_max[l] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((run_max[l] - new_max) * c);
             run_sum[l] *= alpha;
@@ -227,7 +225,7 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
 #pragma unroll
               for (int i = 0; i < 16; ++i) acc[ob][l][i] *= alpha;
           }
-          const float shift = -run_max[l] * c;  // exp2(raw * c + shift) = exp(scale * raw - base)
+          const float shift = -run_max[l] * c;  // exp2(raw * c + shift) = exp(scale * raw - running maximum)
           float psum = 0.f;
 #pragma unroll
           for (int i = 0; i < 16; ++i) sc[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, shift));
@@ -297,7 +295,7 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
         ms[p] = *reinterpret_cast<const float2*>(lds + ((p - 1) * HG * MB + hl * MB + half) * kPer + MB * LBW * 4096 + l * 512 + lane * 8);
         top = fmaxf(top, ms[p].x);
       }
-      // (a tile without items has base -inf and weight zero; the first tile of a chunk has one; phi = SiLU has no base)
+      // (a tile without items has maximum -inf and weight zero; the first tile of a chunk has one; phi = SiLU has no maximum)
       float w[TP];
 #pragma unroll
       for (int p = 0; p < TP; ++p)

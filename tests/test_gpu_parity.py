@@ -685,3 +685,41 @@ def test_logits_far_from_zero_and_scales_near_it(d, h, scale):
     assert_close(host(A), orc.mha_target_attention(X, E, lens, I, I, V, h, scale), "bf16", "target attention")
     LP = binding.lime_link_history(t(E), lens_d, t(L), t(I), t(I), t(V), h, scale)
     assert_close(host(LP), orc.lime_link_history(E, lens, L, I, I, V, h, scale), "bf16", "LP")
+
+
+@pytest.mark.parametrize("d,h,B,N", [
+    (128, 4, 33, 2017),  # several steps per workgroup of the history kernel, several heads together
+    (256, 4, 3, 1057),   # heads of width 64
+    (256, 8, 6, 2049),   # one head per workgroup, two steps
+])
+def test_largest_softmax_weight_is_not_rounded(d, h, B, N):
+    """One item per user has a logit of its own and is the only one with a value; every other logit is zero.  The weights
+    are kept in bf16 relative to the running maximum, so that this item's is one exactly, and with logits that are exact
+    the output is off by its own rounding only: half a bf16 ulp, at most 2^-8 of the value (beside fp32 sums and the hardware
+    exponential, 2^-20 each at most).  A weight that is rounded like any other would add up to 2^-8 of its own.  Head a
+    takes its keys from column 2a of E and its values from column 2a + 1, spread over the head by W_V."""
+    dh = d // h
+    rng = np.random.default_rng(17)
+    top = rng.integers(N // 2, N, B)  # past the first tiles, whose logits are all zero
+    E = np.zeros((B, N, d), np.float32)
+    Wq, Wk, Wv = (np.zeros((d, d), np.float32) for _ in range(3))
+    for a in range(h):
+        E[np.arange(B), top, 2 * a], E[np.arange(B), top, 2 * a + 1] = 1, 1
+        Wq[a * dh, a * dh] = Wk[2 * a, a * dh] = 1
+        Wv[2 * a + 1, a * dh:(a + 1) * dh] = 1 + np.arange(dh) / 128  # representable
+    m = 64
+    X = np.zeros((m, d), np.float32)
+    X[:, ::dh] = 1 + np.arange(m)[:, None] / 64  # logits of 4 to 8 powers of two
+    scale = float(np.float32(4 * np.log(2)))
+    X, E, Wq, Wk, Wv = (torch.from_numpy(x).to(torch.bfloat16).float().numpy() for x in (X, E, Wq, Wk, Wv))
+    t = lambda x: dev(x, "bf16")  # noqa: E731
+    T = np.broadcast_to(X, (B, m, d)).copy()
+    for name, got, ref in [
+        ("target attention", binding.mha_target_attention(t(T), t(E), None, t(Wq), t(Wk), t(Wv), h, scale),
+         orc.mha_target_attention(T, E, None, Wq, Wk, Wv, h, scale)),
+        ("link states", binding.lime_link_history(t(E), None, t(X), t(Wq), t(Wk), t(Wv), h, scale),
+         orc.lime_link_history(E, None, X, Wq, Wk, Wv, h, scale)),
+    ]:
+        worst = float((np.abs(host(got) - ref) / ref).max())
+        print(f"{name} d={d} h={h}: largest relative error {worst * 256:.4f} x 2^-8", flush=True)
+        assert worst <= 2.0 ** -8 + 2.0 ** -18, name
