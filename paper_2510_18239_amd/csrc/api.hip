@@ -77,8 +77,8 @@ int32_t check_common(const char* fn, int32_t B, int32_t d, int32_t h, int32_t dt
 struct HistoryPlan {
   float *Qt, *Ks, *Vs;        // Q[T] = LC Wq; K[S] = E Wk; V[S] = E Wv
   float *Qs, *Kt, *Vt;        // only for O[S]: Q[S] = E Wq; K[T] = LC Wk; V[T] = LC Wv
-  void* scratch;              // states of the key chunks, where the attention is cut into any; last, and optional:
-  size_t needed, bytes;       // a workspace of `needed` bytes does without it
+  void* scratch;              // states of the key chunks, where chunks have workgroups of their own; last, and optional:
+  size_t needed, bytes;       // a workspace of `needed` bytes does without it (slower, the same bits)
 };
 
 HistoryPlan plan_history(void* ws, int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, bool per_user_links, bool want_os) {
@@ -569,7 +569,8 @@ RequestPlan plan_request(bool on_mfma, bool any_path, bool per_user, int32_t B, 
     p.total = p.hist_bytes + lime::queries_over_links_workspace(B, d, m, false);
   } else {
     // the two stages in turn: each picks its kernels by itself, so each part is sized for either choice
-    // (without the states of key chunks, which an attention does without, where the room is fixed and they do not fit)
+    // (without the states of key chunks, which an attention does without, at the same bits, where the room is fixed and they
+    // do not fit)
     const HistoryPlan hp = plan_history(nullptr, B, N, d, h, m, per_user, false);
     const QueryPlan cp = plan_candidates(nullptr, B, C, d, h, m);
     const bool chunked = hp.bytes + cp.bytes <= kStaticScratchBytes;

@@ -79,7 +79,7 @@ struct GenericAttention {
   float scale;
   int phi;    // kPhiSoftmax: softmax over valid keys; kPhiSilu: SiLU(logit) / (number of valid keys)
   int dtype;  // of O
-  void* scratch;  // generic_attention_scratch bytes; nullptr = the keys are not cut into chunks
+  void* scratch;  // generic_attention_scratch bytes; nullptr = a workgroup takes all chunks of the keys (the same bits)
 };
 size_t generic_attention_scratch(int64_t B, int64_t q_rows, int64_t n_keys, int64_t d, int64_t h);
 hipError_t generic_attention(const GenericAttention& a, hipStream_t s);

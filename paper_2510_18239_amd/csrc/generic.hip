@@ -178,12 +178,16 @@ hipError_t launch_project(const ProjectArgs& a, int tiles, bool vec, hipStream_t
 // 16 of the 32 keys, the other 16 in lane ^ 32: the online softmax is lane-local plus one exchange.  Then
 // O^T += V^T P^T: register i of S^T is the B operand whose two k are the keys that register stands for in the two lane
 // halves, and the A operand is one float of each of those two rows of V: coalesced row reads, no LDS.
-// SPLIT: the four waves of a workgroup share 32 query rows and take every fourth key tile each; their states meet in LDS
-// at the end, added in wave order.  Chosen where the queries alone would leave the compute units idle (the m links
-// over a history); with few workgroups besides, the keys are also cut into chunks of kChunkTiles tiles whose
-// un-normalised states attention_merge_kernel combines in ascending order.  What bounds it: two key tiles per wave are
-// two dependent round trips to the cache, the matrix instruction (64 cycles each, d/h / 2 + 16 per tile at d/h <= 32)
-// from a few thousand tiles up.
+// The order of the sums over the keys is the same however the work is cut, so that a user's result has the same bits in
+// every batch and with every workspace: the keys are taken in chunks of kChunkTiles tiles; of a chunk, tiles 0, 4, 8, ..,
+// then 1, 5, .., up to 3, 7, .. each give a state (running maximum, running sum, sums), which are folded in this order, and
+// the chunks' states in ascending order.
+// SPLIT: the four waves of a workgroup share 32 query rows, a state of every chunk each, folded through LDS.  Chosen where
+// the queries alone would leave the compute units idle (the m links over a history); with few workgroups besides, each
+// chunk has a workgroup of its own and attention_merge_kernel folds the chunks' states.  Without SPLIT a wave forms all
+// four states in turn (one chunk only: the third state that more would need has no registers).  What bounds it: two key
+// tiles per wave are two dependent round trips to the cache, the matrix instruction (64 cycles each, d/h / 2 + 16 per tile
+// at d/h <= 32) from a few thousand tiles up.
 constexpr int kChunkTiles = 32;
 
 struct AttnDev {
@@ -191,10 +195,25 @@ struct AttnDev {
   int64_t qs, ks, vs;
   void* O;
   const int32_t *q_lens, *k_lens;
-  int q_rows, n_keys, d, dh, q_tiles, h, chunks;
+  int q_rows, n_keys, d, dh, q_tiles, h, chunks;  // chunks > 1: a workgroup takes one chunk
   float scale;
   float *part_acc, *part_ml;  // chunks > 1: [B][chunks][q_rows][d], [B][chunks][q_rows][h][2] (running max, running sum)
 };
+
+// The weights of two states that are folded into one: their maxima relative to the common one, which `mx` becomes.  (A
+// maximum is -inf where every logit of the state was.)
+struct FoldWeights {
+  float into, from;
+};
+template <int PHI>
+__device__ __forceinline__ FoldWeights fold_weights(float& mx, float from) {
+  if (PHI != kPhiSoftmax) return {1.f, 1.f};
+  const float top = fmaxf(mx, from);
+  const FoldWeights w{mx == -INFINITY ? 0.f : expf(mx - top), from == -INFINITY ? 0.f : expf(from - top)};
+  mx = top;
+  return w;
+}
+__device__ __forceinline__ float folded(float into, float from, FoldWeights w) { return fmaf(w.from, from, into * w.into); }
 
 // KJ: groups of eight head columns (d/h <= 8 KJ; the columns past d/h are zeros in Q and K).  VEC: d/h is a multiple of 4
 // and the rows are 16-byte aligned.  Loads carry no condition: a test per load costs a branch and the copies of a join
@@ -203,21 +222,19 @@ template <typename OutT, int PHI, int KJ, bool SPLIT, bool VEC>
 __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   constexpr int DB = (KJ + 3) / 4;     // 32-column blocks of the head's output
   constexpr bool kPrefetch = KJ <= 8;  // the next tile's K and V in flight during the current one (registers permitting)
-  __shared__ float red[SPLIT ? 3 * (DB * 16 + 2) * 64 : 1];
+  __shared__ float red[SPLIT ? 4 * (DB * 16 + 2) * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, g = lane >> 5;
   const int b = blockIdx.z, d = a.d, dh = a.dh;
-  const int chunk = SPLIT ? blockIdx.y : 0;
   const int unit = SPLIT ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * 4 + wave;  // (query tile, head), heads innermost
   const int head = unit % a.h, q0 = unit / a.h * 32;
   if (!SPLIT && q0 >= a.q_rows) return;
   const int qlen = a.q_lens ? min(a.q_lens[b], a.q_rows) : a.q_rows;
   const int klen = a.k_lens ? min(a.k_lens[b], a.n_keys) : a.n_keys;
-  const int tile_first = chunk * kChunkTiles + (SPLIT ? wave : 0);
   const int tiles = (klen + 31) / 32;
-  const int tile_last = SPLIT && a.chunks > 1 ? min(tiles, (chunk + 1) * kChunkTiles) : tiles;
-  if (SPLIT && a.chunks > 1 && chunk > 0 && chunk * kChunkTiles >= tiles) return;  // uniform: no key in this chunk
-  constexpr int kStep = SPLIT ? 4 : 1;
-  const bool dead = q0 >= qlen;  // only rows that are written as zeros
+  const int chunk = SPLIT && a.chunks > 1 ? blockIdx.y : 0;
+  if (chunk > 0 && chunk * kChunkTiles >= tiles) return;  // uniform: no key in this chunk
+  const bool dead = q0 >= qlen;                           // only rows that are written as zeros
+  const int tile_last = dead ? 0 : SPLIT && a.chunks > 1 ? min(tiles, (chunk + 1) * kChunkTiles) : tiles;
 
   // head columns 8j + 4g .. + 3 of a row, zeros past the head's width (read from its last columns instead)
   auto load_row = [&](const float* row, float4 (&x)[KJ]) {
@@ -266,22 +283,29 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       }
     }
   };
-  f32x16 acc[DB];
-#pragma unroll
-  for (int ob = 0; ob < DB; ++ob)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[ob][i] = 0.f;
-  float run_max = -INFINITY, run_sum = 0.f;
   float4 kn[kPrefetch ? KJ : 1];
   float vn[kPrefetch ? DB : 1][16];
-  if constexpr (kPrefetch) {
-    if (!dead && tile_first < tile_last) load_k(tile_first * 32, kn), load_v(tile_first * 32, vn);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  auto prefetch = [&](int t) {
+    if constexpr (kPrefetch) load_k(t * 32, kn), load_v(t * 32, vn);
+  };
+  int t = chunk * kChunkTiles + (SPLIT ? wave : 0);
+  if (kPrefetch && t < tile_last) prefetch(t);
+  __builtin_amdgcn_sched_barrier(0);
   if (8 * KJ != dh) zero_past(q);  // uniform; a zero in Q leaves whatever K has there out of the sum
 #pragma unroll
   for (int j = 0; j < KJ; ++j) q[j].x *= a.scale, q[j].y *= a.scale, q[j].z *= a.scale, q[j].w *= a.scale;
-  for (int t = tile_first; t < tile_last && !dead; t += kStep) {
+
+  f32x16 acc[DB];  // the state that is being formed
+  float run_max, run_sum;
+  auto begin_state = [&] {
+#pragma unroll
+    for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[ob][i] = 0.f;
+    run_max = -INFINITY, run_sum = 0.f;
+  };
+  begin_state();
+  auto take_tile = [&](int t, int next) {  // next: the tile after it, or one past tile_last
     const int k0 = t * 32;
     float4 k[KJ];
     float v[DB][16];
@@ -292,7 +316,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       for (int ob = 0; ob < DB; ++ob)
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[ob][i] = vn[ob][i];
-      if (t + kStep < tile_last) load_k(k0 + 32 * kStep, kn), load_v(k0 + 32 * kStep, vn);
+      if (next < tile_last) prefetch(next);
     } else {
       load_k(k0, k);
     }
@@ -320,7 +344,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       float psum = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = expf(s[i] - new_max), psum += s[i];  // masked logits are -inf -> 0
-      run_sum = run_sum * alpha + psum;
+      run_sum = fmaf(run_sum, alpha, psum);
       run_max = new_max;
 #pragma unroll
       for (int ob = 0; ob < DB; ++ob)
@@ -334,45 +358,91 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
     for (int i = 0; i < 16; ++i)
 #pragma unroll
       for (int ob = 0; ob < DB; ++ob) acc[ob] = mfma_f32(v[ob][i], s[i], acc[ob]);
-  }
-  float total = pair_sum(run_sum);
+  };
 
-  if constexpr (SPLIT) {
-    // the four waves' states: the common maximum first, then the sums in wave order
-    constexpr int kState = (DB * 16 + 2) * 64;
-    if (wave > 0) {
-      float* mine = red + (wave - 1) * kState + lane;
-      mine[0] = run_max, mine[64] = total;
-#pragma unroll
-      for (int ob = 0; ob < DB; ++ob)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mine[(2 + ob * 16 + i) * 64] = acc[ob][i];
-    }
-    __syncthreads();
-    if (wave > 0) return;
-    float mx = run_max, w[4];
-    if (PHI == kPhiSoftmax) {
-#pragma unroll
-      for (int o = 0; o < 3; ++o) mx = fmaxf(mx, red[o * kState + lane]);
-      w[0] = run_max == -INFINITY ? 0.f : expf(run_max - mx);
-#pragma unroll
-      for (int o = 0; o < 3; ++o) w[o + 1] = red[o * kState + lane] == -INFINITY ? 0.f : expf(red[o * kState + lane] - mx);
-      total *= w[0];
-#pragma unroll
-      for (int o = 0; o < 3; ++o) total = fmaf(w[o + 1], red[o * kState + 64 + lane], total);
-      run_max = mx;
-    } else {
-#pragma unroll
-      for (int o = 0; o < 4; ++o) w[o] = 1.f;
-    }
+  // the result: acc, run_max and run_sum (the lane pair's), for SPLIT in the first wave
+  if constexpr (!SPLIT) {
+    f32x16 out[DB];  // the states folded so far
+    float out_max = -INFINITY, out_sum = 0.f;
 #pragma unroll
     for (int ob = 0; ob < DB; ++ob)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        acc[ob][i] *= w[0];
+      for (int i = 0; i < 16; ++i) out[ob][i] = 0.f;
+    while (t < tile_last) {  // tiles 0, 4, 8, .., 1, 5, .. (t & 3: the state)
+      const bool ends = t + 4 >= tile_last;
+      const int next = !ends ? t + 4 : (t & 3) < 3 ? (t & 3) + 1 : tile_last;
+      take_tile(t, next);
+      if (ends) {  // uniform
+        run_sum = pair_sum(run_sum);
+        if ((t & 3) == 0) {
+          out_max = run_max, out_sum = run_sum;
 #pragma unroll
-        for (int o = 0; o < 3; ++o) acc[ob][i] = fmaf(w[o + 1], red[o * kState + (2 + ob * 16 + i) * 64 + lane], acc[ob][i]);
+          for (int ob = 0; ob < DB; ++ob) out[ob] = acc[ob];
+        } else {
+          const FoldWeights w = fold_weights<PHI>(out_max, run_max);
+          out_sum = folded(out_sum, run_sum, w);
+#pragma unroll
+          for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) out[ob][i] = folded(out[ob][i], acc[ob][i], w);
+        }
+        begin_state();
       }
+      t = next;
+    }
+    run_max = out_max, run_sum = out_sum;
+#pragma unroll
+    for (int ob = 0; ob < DB; ++ob) acc[ob] = out[ob];
+  } else {
+    constexpr int kState = (DB * 16 + 2) * 64;
+    float* const kept = red + 3 * kState + lane;  // the first wave's: the chunks folded so far
+    for (int c = chunk; c * kChunkTiles < tile_last; ++c) {  // uniform over the workgroup
+      const int end = min(tile_last, (c + 1) * kChunkTiles), states = min(4, end - c * kChunkTiles);
+      if (c > chunk) {
+        __syncthreads();  // the last chunk's states have been read
+        begin_state();
+      }
+      for (t = c * kChunkTiles + wave; t < end; t += 4) take_tile(t, t + 4);  // (a chunk is a multiple of four tiles)
+      run_sum = pair_sum(run_sum);
+      if (wave > 0) {
+        float* mine = red + (wave - 1) * kState + lane;
+        mine[0] = run_max, mine[64] = run_sum;
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) mine[(2 + ob * 16 + i) * 64] = acc[ob][i];
+      }
+      __syncthreads();
+      if (wave > 0) continue;
+#pragma unroll
+      for (int o = 0; o < 3; ++o) {
+        if (o + 1 >= states) break;  // uniform
+        const float* theirs = red + o * kState + lane;
+        const FoldWeights w = fold_weights<PHI>(run_max, theirs[0]);
+        run_sum = folded(run_sum, theirs[64], w);
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[ob][i] = folded(acc[ob][i], theirs[(2 + ob * 16 + i) * 64], w);
+      }
+      if (c > chunk) {
+        float top = kept[0];
+        const FoldWeights w = fold_weights<PHI>(top, run_max);
+        run_max = top, run_sum = folded(kept[64], run_sum, w);
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[ob][i] = folded(kept[(2 + ob * 16 + i) * 64], acc[ob][i], w);
+      }
+      if (end < tile_last) {
+        kept[0] = run_max, kept[64] = run_sum;
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) kept[(2 + ob * 16 + i) * 64] = acc[ob][i];
+      }
+    }
+    if (wave > 0) return;
   }
 
   // lane (query n, g) holds head columns 32 ob + 8 j + 4 g + r in register 4 j + r
@@ -405,12 +475,12 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       for (int j = 0; j < 4; ++j) store4(dst, 32 * ob + 8 * j + 4 * g, acc[ob], j, 1.f);
     if (g == 0) {
       float* ml = a.part_ml + (slot * a.h + head) * 2;
-      ml[0] = run_max, ml[1] = total;
+      ml[0] = run_max, ml[1] = run_sum;
     }
     return;
   }
   const bool live = row < qlen && klen > 0;
-  const float inv = live ? 1.f / (PHI == kPhiSoftmax ? total : static_cast<float>(klen)) : 0.f;
+  const float inv = live ? 1.f / (PHI == kPhiSoftmax ? run_sum : static_cast<float>(klen)) : 0.f;
   OutT* orow = static_cast<OutT*>(a.O) + (static_cast<int64_t>(b) * a.q_rows + row) * d + head * dh;
 #pragma unroll
   for (int ob = 0; ob < DB; ++ob)
@@ -423,7 +493,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
     }
 }
 
-// The chunks' states combined in ascending order, one thread per output element.
+// The chunks' states folded in ascending order, one thread per output element.
 template <typename OutT, int PHI>
 __global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
   const int b = blockIdx.y;
@@ -436,26 +506,22 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
   float out = 0.f;
   if (used > 0 && row < qlen) {
     const int64_t slot0 = static_cast<int64_t>(b) * a.chunks * a.q_rows + row;
-    float mx = -INFINITY, num = 0.f, den = 0.f;
-    if (PHI == kPhiSoftmax)
-      for (int c = 0; c < used; ++c) mx = fmaxf(mx, a.part_ml[((slot0 + static_cast<int64_t>(c) * a.q_rows) * a.h + head) * 2]);
-    for (int c = 0; c < used; ++c) {
-      const int64_t slot = slot0 + static_cast<int64_t>(c) * a.q_rows;
-      const float x = a.part_acc[slot * a.d + col];
-      if (PHI == kPhiSoftmax) {
-        const float w = expf(a.part_ml[(slot * a.h + head) * 2] - mx);
-        num = fmaf(w, x, num), den = fmaf(w, a.part_ml[(slot * a.h + head) * 2 + 1], den);
-      } else {
-        num += x;
-      }
+    const float* ml = a.part_ml + (slot0 * a.h + head) * 2;
+    const float* acc = a.part_acc + slot0 * a.d + col;
+    float mx = ml[0], den = ml[1], num = acc[0];
+#pragma unroll 4
+    for (int c = 1; c < used; ++c) {
+      const int64_t row_c = static_cast<int64_t>(c) * a.q_rows;
+      const float2 theirs = *reinterpret_cast<const float2*>(ml + row_c * a.h * 2);
+      const FoldWeights w = fold_weights<PHI>(mx, theirs.x);
+      num = folded(num, acc[row_c * a.d], w), den = folded(den, theirs.y, w);
     }
-    out = num / (PHI == kPhiSoftmax ? den : static_cast<float>(klen));
+    out = num * (1.f / (PHI == kPhiSoftmax ? den : static_cast<float>(klen)));
   }
   store_as(static_cast<OutT*>(a.O) + static_cast<int64_t>(b) * a.q_rows * a.d + idx, out);
 }
 
-// (split the keys over a workgroup's waves, chunks) of an attention: rules on what fills the compute units, never on
-// the number of keys a user has, so that a user's result does not depend on the others' lengths.
+// (a workgroup's waves share the keys, chunks with workgroups of their own) of an attention: what fills the compute units.
 struct AttnSplit {
   bool split;
   int chunks;
@@ -463,9 +529,10 @@ struct AttnSplit {
 AttnSplit attention_split(int64_t B, int64_t q_rows, int64_t n_keys, int64_t h) {
   const int64_t units = B * h * ((q_rows + 31) / 32);  // (user, head, query tile)
   const int cus = compute_units();
-  if (units >= 4 * static_cast<int64_t>(cus)) return {false, 1};  // a wave per SIMD without splitting
-  if (units >= cus) return {true, 1};                             // a workgroup per compute unit
-  return {true, static_cast<int>((n_keys + 32 * kChunkTiles - 1) / (32 * kChunkTiles))};
+  const int chunks = static_cast<int>((n_keys + 32 * kChunkTiles - 1) / (32 * kChunkTiles));
+  if (units >= 4 * static_cast<int64_t>(cus) && chunks <= 1) return {false, 1};  // a wave per SIMD without splitting
+  if (units >= cus) return {true, 1};                                           // a workgroup per compute unit
+  return {true, chunks};
 }
 
 template <typename OutT, int PHI, int KJ, bool VEC>

@@ -68,6 +68,15 @@ def test_static_request_matches_request_with_a_workspace():
         assert torch.equal(LP0, LP1) and torch.equal(O0, O1)
 
 
+@pytest.mark.parametrize("N,C", [(2048, 11964), (2048, 12000), (2048, 12096)])
+def test_static_request_has_the_same_bits_where_chunk_states_do_not_fit(N, C):
+    """Two chunks of keys: up to C = 11964 their states fit the array, up to 12096 the rest of the scratch does."""
+    w = _sharp(806, B=1, N=N, C=C, d=256, h=4, m=64, dtype="fp32", len_range=(N, N))
+    for xor in (False, True):
+        (LP0, O0), (LP1, O1) = _both(w, xor)
+        assert torch.equal(LP0, LP1) and torch.equal(O0, O1)
+
+
 def test_static_request_rejects_what_does_not_fit():
     w = synth.make_workload(805, B=64, N=2048, C=64, d=256, h=4, m=128, dtype="bf16")
     g = DeviceWorkload(w)
