@@ -215,12 +215,18 @@ __device__ __forceinline__ FoldWeights fold_weights(float& mx, float from) {
 }
 __device__ __forceinline__ float folded(float into, float from, FoldWeights w) { return fmaf(w.from, from, into * w.into); }
 
-// KJ: groups of eight head columns (d/h <= 8 KJ; the columns past d/h are zeros in Q and K).  VEC: d/h is a multiple of 4
-// and the rows are 16-byte aligned.  Loads carry no condition: a test per load costs a branch and the copies of a join
-// (12.9 -> 6 us for the 16 links of a one-user request at d/h = 64).
-template <typename OutT, int PHI, int KJ, bool SPLIT, bool VEC>
-__global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
+// How a head's row is read: kWhole d/h = 8 KJ, kQuads d/h is a multiple of 4 (both from 16-byte aligned rows), kSingly.
+enum Rows { kWhole, kQuads, kSingly };
+
+// KJ: groups of eight head columns (d/h <= 8 KJ; the columns past d/h are zeros in Q and K).  Loads carry no condition: a
+// test per load costs a branch and the copies of a join (12.9 -> 6 us for the 16 links of a one-user request at d/h = 64).
+// Waves per SIMD: as many as the operands' registers leave room for (at d/h = 8 and a wave per query tile the allocator by
+// itself takes 144 registers, three waves instead of four: 29.8 instead of 29.0 us for B=64 N=256 C=501 d=32).
+template <typename OutT, int PHI, int KJ, bool SPLIT, Rows ROWS>
+__global__ __launch_bounds__(256, KJ == 1 ? 4 : KJ == 2 ? 3 : KJ == 4 ? 2 : 1) void attention_kernel(AttnDev a) {
+  constexpr bool VEC = ROWS != kSingly;
   constexpr int DB = (KJ + 3) / 4;     // 32-column blocks of the head's output
+  constexpr int VB = DB < 4 ? DB : 4, KB = KJ < 16 ? KJ : 16;  // blocks of V and column groups of K in registers at a time
   constexpr bool kPrefetch = KJ <= 8;  // the next tile's K and V in flight during the current one (registers permitting)
   __shared__ float red[SPLIT ? 4 * (DB * 16 + 2) * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, g = lane >> 5;
@@ -236,64 +242,74 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   const bool dead = q0 >= qlen;                           // only rows that are written as zeros
   const int tile_last = dead ? 0 : SPLIT && a.chunks > 1 ? min(tiles, (chunk + 1) * kChunkTiles) : tiles;
 
-  // head columns 8j + 4g .. + 3 of a row, zeros past the head's width (read from its last columns instead)
-  auto load_row = [&](const float* row, float4 (&x)[KJ]) {
+  // head columns 8j + 4g .. + 3 of a row, j = j0 ..; past the head's width its last columns (zero_past clears them)
+  // (the lane half through an opaque copy: what follows from it is formed here, not carried through the loop)
+  auto load_row = [&](const float* row, int j0, float4 (&x)[KB]) {
+    int g_ = g;
+    if constexpr (KJ > KB) asm volatile("" : "+v"(g_));
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int k = 8 * j + 4 * g;
+    for (int j = 0; j < KB; ++j) {
+      const int k = 8 * (j0 + j) + 4 * g_;
       if constexpr (VEC) {
-        x[j] = *reinterpret_cast<const float4*>(row + min(k, dh - 4));
+        x[j] = *reinterpret_cast<const float4*>(row + (ROWS == kWhole ? k : min(k, dh - 4)));
       } else {
         x[j] = make_float4(row[min(k, dh - 1)], row[min(k + 1, dh - 1)], row[min(k + 2, dh - 1)], row[min(k + 3, dh - 1)]);
       }
     }
   };
-  auto zero_past = [&](float4 (&x)[KJ]) {
+  auto zero_past = [&](int j0, float4 (&x)[KB]) {
+    if constexpr (ROWS == kWhole) return;
+    int left = dh - 8 * j0 - 4 * g;
+    asm volatile("" : "+v"(left));
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const int k = 8 * j + 4 * g;
-      if (k >= dh) x[j].x = 0.f;
-      if (k + 1 >= dh) x[j].y = 0.f;
-      if (k + 2 >= dh) x[j].z = 0.f;
-      if (k + 3 >= dh) x[j].w = 0.f;
+    for (int j = 0; j < KB; ++j) {
+      x[j].x = left > 8 * j ? x[j].x : 0.f;
+      x[j].y = left > 8 * j + (VEC ? 0 : 1) ? x[j].y : 0.f;  // (VEC: all four or none)
+      x[j].z = left > 8 * j + (VEC ? 0 : 2) ? x[j].z : 0.f;
+      x[j].w = left > 8 * j + (VEC ? 0 : 3) ? x[j].w : 0.f;
     }
   };
-  float4 q[KJ];
-  load_row(a.Q + b * a.qs + static_cast<int64_t>(min(q0 + n, a.q_rows - 1)) * d + head * dh, q);
+  float4 q[KJ / KB][KB];
+#pragma unroll
+  for (int p = 0; p < KJ / KB; ++p)
+    load_row(a.Q + b * a.qs + static_cast<int64_t>(min(q0 + n, a.q_rows - 1)) * d + head * dh, p * KB, q[p]);
   const float* Kb = a.K + b * a.ks + head * dh;
   const float* Vb = a.V + b * a.vs + head * dh;
   // rows past the last valid key are read from it instead: their weights are zero
-  auto load_k = [&](int k0, float4 (&k)[KJ]) { load_row(Kb + static_cast<int64_t>(min(k0 + n, klen - 1)) * d, k); };
+  auto load_k = [&](int k0, int j0, float4 (&k)[KB]) { load_row(Kb + static_cast<int64_t>(min(k0 + n, klen - 1)) * d, j0, k); };
   int vcol[DB];
 #pragma unroll
   for (int ob = 0; ob < DB; ++ob) vcol[ob] = min(32 * ob + n, dh - 1);
-  auto load_v = [&](int k0, float (&v)[DB][16]) {
+  auto load_v = [&](int k0, int ob0, float (&v)[VB][16]) {
     if (k0 + 32 <= klen) {  // uniform: a scalar row base plus a lane offset that never changes
       const float* base = Vb + static_cast<int64_t>(k0) * d;
 #pragma unroll
       for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int ob = 0; ob < DB; ++ob) v[ob][i] = (base + static_cast<int64_t>(8 * (i >> 2) + (i & 3)) * d)[4 * g * d + vcol[ob]];
+        for (int ob = 0; ob < VB; ++ob) v[ob][i] = (base + static_cast<int64_t>(8 * (i >> 2) + (i & 3)) * d)[4 * g * d + vcol[ob0 + ob]];
     } else {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const float* vrow = Vb + static_cast<int64_t>(min(k0 + 8 * (i >> 2) + 4 * g + (i & 3), klen - 1)) * d;
 #pragma unroll
-        for (int ob = 0; ob < DB; ++ob) v[ob][i] = vrow[vcol[ob]];
+        for (int ob = 0; ob < VB; ++ob) v[ob][i] = vrow[vcol[ob0 + ob]];
       }
     }
   };
-  float4 kn[kPrefetch ? KJ : 1];
-  float vn[kPrefetch ? DB : 1][16];
+  float4 kn[KB];
+  float vn[VB][16];
   auto prefetch = [&](int t) {
-    if constexpr (kPrefetch) load_k(t * 32, kn), load_v(t * 32, vn);
+    if constexpr (kPrefetch) load_k(t * 32, 0, kn), load_v(t * 32, 0, vn);
   };
   int t = chunk * kChunkTiles + (SPLIT ? wave : 0);
   if (kPrefetch && t < tile_last) prefetch(t);
   __builtin_amdgcn_sched_barrier(0);
-  if (8 * KJ != dh) zero_past(q);  // uniform; a zero in Q leaves whatever K has there out of the sum
 #pragma unroll
-  for (int j = 0; j < KJ; ++j) q[j].x *= a.scale, q[j].y *= a.scale, q[j].z *= a.scale, q[j].w *= a.scale;
+  for (int p = 0; p < KJ / KB; ++p) {
+    zero_past(p * KB, q[p]);
+#pragma unroll
+    for (int j = 0; j < KB; ++j) q[p][j].x *= a.scale, q[p][j].y *= a.scale, q[p][j].z *= a.scale, q[p][j].w *= a.scale;
+  }
 
   f32x16 acc[DB];  // the state that is being formed
   float run_max, run_sum;
@@ -307,43 +323,54 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
   begin_state();
   auto take_tile = [&](int t, int next) {  // next: the tile after it, or one past tile_last
     const int k0 = t * 32;
-    float4 k[KJ];
-    float v[DB][16];
+    float4 k[KB];
+    float v[VB][16];
     if constexpr (kPrefetch) {
 #pragma unroll
-      for (int j = 0; j < KJ; ++j) k[j] = kn[j];
+      for (int j = 0; j < KB; ++j) k[j] = kn[j];
 #pragma unroll
-      for (int ob = 0; ob < DB; ++ob)
+      for (int ob = 0; ob < VB; ++ob)
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[ob][i] = vn[ob][i];
       if (next < tile_last) prefetch(next);
     } else {
-      load_k(k0, k);
+      load_k(k0, 0, k);
     }
     f32x16 s;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      s = mfma_f32(k[j].x, q[j].x, s), s = mfma_f32(k[j].y, q[j].y, s);
-      s = mfma_f32(k[j].z, q[j].z, s), s = mfma_f32(k[j].w, q[j].w, s);
+    for (int p = 0; p < KJ / KB; ++p) {
+      if (p > 0) {
+        __builtin_amdgcn_sched_barrier(0);  // (fetched no earlier: registers)
+        load_k(k0, p * KB, k);
+      }
+      zero_past(p * KB, k);
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        s = mfma_f32(k[j].x, q[p][j].x, s), s = mfma_f32(k[j].y, q[p][j].y, s);
+        s = mfma_f32(k[j].z, q[p][j].z, s), s = mfma_f32(k[j].w, q[p][j].w, s);
+      }
     }
-    if constexpr (!kPrefetch) load_v(k0, v);
+    if constexpr (!kPrefetch) load_v(k0, 0, v);
     // register i of this lane is key k0 + 8 (i / 4) + 4g + i % 4
-    if (k0 + 32 > klen) {  // uniform
+    const bool ragged = k0 + 32 > klen;  // uniform
+    auto past = [&](int i) { return 8 * (i >> 2) + (i & 3) >= klen - k0 - 4 * g; };
+    if (ragged) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (k0 + 8 * (i >> 2) + 4 * g + (i & 3) >= klen) s[i] = PHI == kPhiSoftmax ? -INFINITY : 0.f;  // (SiLU(0) = 0)
+        if (past(i)) s[i] = PHI == kPhiSoftmax ? -INFINITY : 0.f;  // (SiLU(0) = 0)
     }
     if (PHI == kPhiSoftmax) {
       float tmax = s[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-      const float new_max = fmaxf(run_max, pair_max(tmax));  // finite: the tile holds at least one valid key
-      const float alpha = expf(run_max - new_max);           // run_max = -inf on the first tile -> 0
+      const float new_max = fmaxf(run_max, pair_max(tmax));
+      const float base = new_max == -INFINITY ? 0.f : new_max;  // (every logit so far is -inf: weights of zero)
+      const float alpha = expf(run_max - base);                 // run_max = -inf on the first tile -> 0
       float psum = 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = expf(s[i] - new_max), psum += s[i];  // masked logits are -inf -> 0
+      for (int i = 0; i < 16; ++i) s[i] = expf(s[i] - base), psum += s[i];  // masked logits are -inf -> 0
       run_sum = fmaf(run_sum, alpha, psum);
       run_max = new_max;
 #pragma unroll
@@ -355,9 +382,22 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnDev a) {
       for (int i = 0; i < 16; ++i) s[i] = s[i] / (1.f + expf(-s[i]));
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int ob0 = 0; ob0 < DB; ob0 += VB) {
+      if (ob0 > 0) {
+        __builtin_amdgcn_sched_barrier(0);  // (fetched no earlier: registers)
+        load_v(k0, ob0, v);
+      }
+      if (ragged) {
 #pragma unroll
-      for (int ob = 0; ob < DB; ++ob) acc[ob] = mfma_f32(v[ob][i], s[i], acc[ob]);
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int ob = 0; ob < VB; ++ob) v[ob][i] = past(i) ? 0.f : v[ob][i];  // (what was read in its place may be infinite)
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int ob = 0; ob < VB; ++ob) acc[ob0 + ob] = mfma_f32(v[ob][i], s[i], acc[ob0 + ob]);
+    }
   };
 
   // the result: acc, run_max and run_sum (the lane pair's), for SPLIT in the first wave
@@ -535,13 +575,13 @@ AttnSplit attention_split(int64_t B, int64_t q_rows, int64_t n_keys, int64_t h) 
   return {true, chunks};
 }
 
-template <typename OutT, int PHI, int KJ, bool VEC>
+template <typename OutT, int PHI, int KJ, Rows ROWS>
 hipError_t launch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
   const int units = dev.q_tiles * dev.h;
   if (split)
-    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, true, VEC>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, true, ROWS>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
   else
-    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, false, VEC>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
+    hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, false, ROWS>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
   if (dev.chunks > 1) {
     const int64_t total = static_cast<int64_t>(dev.q_rows) * dev.d;
     hipLaunchKernelGGL((attention_merge_kernel<OutT, PHI>), dim3(static_cast<unsigned>((total + 255) / 256), B), dim3(256), 0, s, dev);
@@ -553,14 +593,12 @@ template <typename OutT, int PHI>
 hipError_t dispatch_attention(const AttnDev& dev, int B, bool split, hipStream_t s) {
   const bool vec = dev.dh % 4 == 0 &&
                    ((reinterpret_cast<uintptr_t>(dev.Q) | reinterpret_cast<uintptr_t>(dev.K) | reinterpret_cast<uintptr_t>(dev.O)) & 15u) == 0;
-#define LIME_ATTN_CASE(KJ, VEC) \
-  if (dev.dh <= 8 * KJ) return launch_attention<OutT, PHI, KJ, VEC>(dev, B, split, s);
-  if (vec) {
-    LIME_ATTN_CASE(1, true) LIME_ATTN_CASE(2, true) LIME_ATTN_CASE(4, true)
-    LIME_ATTN_CASE(8, true) LIME_ATTN_CASE(16, true) LIME_ATTN_CASE(32, true)
-  } else {
-    LIME_ATTN_CASE(4, false) LIME_ATTN_CASE(32, false)
-  }
+#define LIME_ATTN_CASE(KJ)                                                                              \
+  if (vec && dev.dh == 8 * KJ) return launch_attention<OutT, PHI, KJ, kWhole>(dev, B, split, s); \
+  if (vec && dev.dh < 8 * KJ) return launch_attention<OutT, PHI, KJ, kQuads>(dev, B, split, s);
+  LIME_ATTN_CASE(1) LIME_ATTN_CASE(2) LIME_ATTN_CASE(4) LIME_ATTN_CASE(8) LIME_ATTN_CASE(16) LIME_ATTN_CASE(32)
+  if (dev.dh <= 32) return launch_attention<OutT, PHI, 4, kSingly>(dev, B, split, s);
+  if (dev.dh <= 256) return launch_attention<OutT, PHI, 32, kSingly>(dev, B, split, s);
 #undef LIME_ATTN_CASE
   return hipErrorInvalidValue;
 }

@@ -66,3 +66,25 @@ def test_bits_do_not_depend_on_the_workspace():
         least = int(re.search(r"workspace of (\d+) bytes needed", str(e.value)).group(1))
         small = call(workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
         assert torch.equal(small, call())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,h,m", [(48, 2, 20), (50, 2, 45), (40, 1, 7), (96, 1, 150), (300, 2, 33), (32, 2, 16), (64, 1, 70)])
+def test_infinite_links(d, h, m, dtype):
+    """An infinite key entry makes its logit infinite and nothing else (weight zero where it is -inf, also where that are all
+    logits of 32 keys in a row); an infinite value stays infinite in its own column.  Keys and values are the links as they
+    are, odd counts and head widths among them."""
+    dh, C = d // h, 37
+    g = torch.Generator(device="cuda").manual_seed(d)
+    rand = lambda *shape: (torch.rand(shape, generator=g, device="cuda") + 0.25).to(dtype)  # noqa: E731
+    T, L, LP = rand(1, C, d), rand(m, d), rand(1, m, d)
+    L[0, dh - 1] = -torch.inf   # the first head's last column
+    if m > 64:
+        L[:32, d - dh] = -torch.inf  # a whole tile of the last head's logits
+    LP[0, m - 1, d - dh] = torch.inf  # the last key's value, in the last head's first column
+    O = binding.lime_score_candidates(T, L, LP, None, None, None, h, 0.1).double().cpu()
+    q, k, v = (x.double().cpu().reshape(-1, h, dh).transpose(0, 1) for x in (T[0], L, LP[0]))
+    ref = (torch.softmax(q @ k.transpose(1, 2) * 0.1, dim=-1) @ v).transpose(0, 1).reshape(1, C, d)
+    finite = torch.isfinite(ref)
+    assert (~finite).sum() == C and torch.equal(O[~finite], ref[~finite])
+    assert (O - ref)[finite].abs().max() <= (1e-4 if dtype == torch.float32 else 2e-2)
