@@ -175,7 +175,7 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
                      int64_t lc_user_stride, const void* Wq, const void* Wk, const void* Wv, void* LP, void* OS,
                      int32_t B, int32_t N, int32_t d, int32_t h, int32_t m, float scale, int32_t dtype,
                      void* workspace, size_t ws_bytes, void* stream, const lime::PackWeight* extra = nullptr,
-                     int n_extra = 0) {
+                     int n_extra = 0, bool walk = false) {
   if (int32_t st = check_common(fn, B, d, h, dtype)) return st;
   if (N <= 0 || m <= 0) return fail(LIME_INVALID_ARG, "%s: N and m must be positive (N=%d m=%d)", fn, N, m);
   if (!E || !LC || !Wq || !Wk || !Wv || !LP) return fail(LIME_INVALID_ARG, "%s: a required pointer is NULL", fn);
@@ -202,7 +202,7 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
                   workspace ? ws_bytes : 0);
     lime::LinksOverHistory q{};
     q.E = E, q.lens = lens, q.LC = LC, q.lc_user_stride = link_stride, q.Wq = Wq, q.Wk = Wk, q.Wv = Wv, q.LP = LP;
-    q.B = B, q.N = N, q.d = d, q.h = h, q.m = m, q.scale = scale, q.phi = phi;
+    q.B = B, q.N = N, q.d = d, q.h = h, q.m = m, q.scale = scale, q.phi = phi, q.walk = walk;
     // one pack launch for everything this call needs on the matrix cores: the operands of both kernels and `extra`
     lime::PackJobs jobs;
     lime::links_over_history_jobs(q, workspace, jobs);
@@ -1052,7 +1052,8 @@ int32_t lime_scores(const lime_scoring_model* model, const void* E, const int32_
   } else {
     LIME_HIP(lime::layer_norm_rows(lc, M.ln_hist_q[0], M.ln_hist_q[1], M.ln_eps, ws + p.LCn, static_cast<int64_t>(B) * m, d, nullptr, 1, dtype, s));
     if (int32_t st = history_impl(fn, lime::kPhiSoftmax, ws + p.En, lens, ws + p.LCn, link_stride, M.hist_Wq, M.hist_Wk,
-                                  M.hist_Wv, lp, nullptr, B, N, d, M.h, m, M.scale_hist, dtype, ws + p.hist, p.hist_bytes, stream))
+                                  M.hist_Wv, lp, nullptr, B, N, d, M.h, m, M.scale_hist, dtype, ws + p.hist, p.hist_bytes, stream, nullptr, 0,
+                                  /*walk=*/true))
       return st;
     // Eq. 4 on normalised inputs: keys from the raw links, values from the personalised links
     LIME_HIP(lime::layer_norm_rows(T, M.ln_cand_q[0], M.ln_cand_q[1], M.ln_eps, ws + p.Tn, static_cast<int64_t>(B) * C, d, nullptr, 1, dtype, s));

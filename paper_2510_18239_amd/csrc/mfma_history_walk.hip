@@ -1,10 +1,13 @@
 // The history-side softmax with a chunk walked by one wave per head (mfma_history.hip is the faster form).
 //
-// lime_scores runs on this one.  Behind the link states its pipeline has two layer normalisations and the interaction
-// network, and a score may come out near zero, where the bf16 rounding of the softmax weights shows: rounded relative to
-// another base, two results that are equally far from the exact one differ by several per mille of a typical score.  Here
-// a weight is rounded relative to the running maximum of its chunk, tile after tile, and scores stay what they have been;
-// the faster form would take 2 us of a 75 us call (B=1 N=2048 C=32768 d=256).
+// Every lime_scores call runs on this one.  Behind the link states its pipeline has two layer normalisations and the
+// interaction network, and a score may come out near zero, where the bf16 rounding of the softmax weights shows.  A weight
+// is rounded relative to the running maximum of its chunk; the other kernel's chunks and tiles are others, and with them
+// the roundings.  Both are equally far from the exact scores (2-norm, relative: 0.0025 and 0.0025 at N=2048 C=32768 d=256,
+// 0.024 and 0.024 at N=16384 C=512, 0.037 and 0.039 at N=50 C=16), but apart from each other they are as far: 0.0025,
+// 0.021, 0.023: a program that holds scores against recorded ones, or splits its users over two builds, would see the
+// larger of these.  What keeping them costs, whole calls on this kernel and on the other: 77.4 and 75.0 us, 96.9 and 77.4 us,
+// 60.0 and 57.9 us.
 //
 // A wave owns one head of a chunk of one user's history, keeps the head's slices of W_K^T and W_V and the projected link
 // queries in fragment form (W_K^T in LDS when d = 256, otherwise in registers) and walks its chunk in tiles of 32 items,

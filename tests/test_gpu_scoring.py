@@ -68,9 +68,14 @@ def test_interaction_mlp(dtype, rows, d, widths):
     assert_close(scores.double().cpu().numpy(), orc.interaction_mlp(O, Ws, [np.zeros_like(b) for b in bs]), dtype, "scores without biases")
 
 
-def _request(idx, B, N, C, d, h, m, dc, dhid, widths, dtype, len_range, plain_norm=None):
+def _request(idx, B, N, C, d, h, m, dc, dhid, widths, dtype, len_range, plain_norm=None, lens=None):
     w = synth.make_workload(idx, B=B, N=N, C=C, d=d, h=h, m=m, dtype=dtype, gain=4.0, len_range=len_range,
                             pad_value=np.nan if len_range else None)
+    if lens is not None:  # of the first users
+        w.lens[:len(lens)] = lens
+        for b, n in enumerate(lens):
+            w.E[b, n:] = np.nan
+            w.E[b, :n] = np.nan_to_num(w.E[b, :n], nan=0.0)  # rows that became valid after the length change
     p = synth.scoring_params(idx, B, m, d, dc, dhid, widths, dtype)
     if plain_norm is not None:  # this normalisation without scale and shift
         p[plain_norm] = (None, None)
@@ -146,3 +151,34 @@ def test_lime_scores_config3_full_size(widths):
 def test_lime_scores_normalised_link_rows(B, d, h, m):
     """The link rows' normalisation inside the pack launch, in both of its forms."""
     _request(780 + d, B, 70, 45, d, h, m, 8, 40, [96, 1], "bf16", (20, 70))
+
+
+@pytest.mark.parametrize("d,h,m,B,N", [(256, 4, 64, 40, 1024), (256, 4, 32, 36, 1000), (256, 2, 128, 36, 1000), (128, 2, 64, 70, 600),
+                                       (128, 4, 96, 70, 600), (64, 2, 32, 70, 600)])
+def test_lime_scores_cooperative_history_walk_on_edge_lengths(d, h, m, B, N):
+    """Enough users x tiles (four per compute unit) for the scoring call's cooperative history kernels (at d = 256 the variant
+    with all W_K slices in LDS and one tile buffer), with the lengths that stress them: empty users, one item, one short of /
+    exactly / one past a tile, a chunk boundary, the full history; padding rows hold NaN."""
+    _request(790 + d + m, B, N, 5, d, h, m, 8, 40, [16, 1], "bf16", (1, N), lens=[0, 1, 31, 32, 33, 255, 256, 257, N - 1, N, 0, N])
+
+
+@pytest.mark.parametrize("d,h,m,B,N", [(256, 4, 64, 3, 777), (128, 4, 64, 70, 600)])
+def test_lime_scores_runs_one_history_kernel(d, h, m, B, N):
+    """Without scale and shift for the candidates' normalisation the scoring call takes the separate passes, but the same
+    history kernel, so that the link states differ only in rows with a normalised element that the other pass rounds the other
+    way (its sums run in another order): a few in ten thousand.  Another kernel rounds its softmax weights relative to other
+    maxima, which changed 4 and 9 % of all elements."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    W = lambda: [(rn(d, d).float() * d ** -0.5).to(torch.bfloat16) for _ in range(3)]  # noqa: E731
+    hist, cand = W(), W()
+    norms = [((rn(d).float() * 0.2 + 1).to(torch.bfloat16), rn(d)) for _ in range(5)]
+    L, E, T, EC, ctx, mlp = rn(m, d), rn(B, N, d), rn(B, 16, d), rn(B, 8), (rn(d + 8, 40), rn(40), rn(40, d), rn(d)), ([rn(d, 1)], [rn(1)])
+    s = (d // h) ** -0.5
+    LP = []
+    for cand_q in (norms[2], (None, None)):
+        model = binding.scoring_model(L, ctx, hist, cand, *norms[:2], cand_q, *norms[3:], mlp, h, s, s)
+        LP.append(binding.lime_scores(model, E, None, EC, T, want_intermediates=True)[2])
+    share = float((LP[0] != LP[1]).float().mean())
+    print(f"d={d}: {share:.2e} of the link states' elements differ", flush=True)
+    assert share <= 0.01
