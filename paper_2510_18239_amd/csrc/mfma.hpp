@@ -119,7 +119,7 @@ __device__ __forceinline__ void normalise_rows(bf16x8 (&x)[D / 16], const bf16x8
       const float c = static_cast<float>(x[kk][t]) - mean;
       q = fmaf(c, c, q);
     }
-  const float inv = __builtin_amdgcn_rsqf(pair_sum(q) * (1.f / D) + eps);
+  const float inv = 1.f / sqrtf(pair_sum(q) * (1.f / D) + eps);
 #pragma unroll
   for (int kk = 0; kk < D / 16; ++kk)
 #pragma unroll

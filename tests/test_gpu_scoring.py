@@ -182,3 +182,29 @@ def test_lime_scores_runs_one_history_kernel(d, h, m, B, N):
     share = float((LP[0] != LP[1]).float().mean())
     print(f"d={d}: {share:.2e} of the link states' elements differ", flush=True)
     assert share <= 0.01
+
+
+@pytest.mark.parametrize("d,h", [(64, 2), (32, 1), (128, 4), (256, 8)])
+def test_link_rows_are_normalised_as_by_the_separate_pass(d, h):
+    """On rows whose sums are exact in fp32 (entries 0 .. 3: mean, centred squares and their sum have at most 24 bits) the
+    order of the sums does not matter: the pack launch's normalisation gives the separate pass's bits, and with it the whole
+    scoring call those of the call that takes the separate passes.  (Without scale and shift for the candidates'
+    normalisation, that is; the link states do not depend on it.)"""
+    B, m, N, dc = 512 * 64 // d, 128, 8, 8
+    g = torch.Generator(device="cuda").manual_seed(d)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    ints = lambda hi, *s: torch.randint(0, hi + 1, s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    W = lambda: [(rn(d, d).float() * d ** -0.5).to(torch.bfloat16) for _ in range(3)]  # noqa: E731
+    hist, cand = W(), W()
+    norms = [((rn(d).float() * 0.2 + 1).to(torch.bfloat16), rn(d)) for _ in range(5)]
+    zero = torch.zeros(d, dtype=torch.bfloat16, device="cuda")
+    eye = torch.eye(d, device="cuda", dtype=torch.bfloat16)
+    spread = torch.nn.functional.one_hot(torch.arange(d, device="cuda") % dc, dc).t().to(torch.bfloat16)  # [dc, d]: L^C = L + E^C spread
+    L, E, T, EC = ints(2, m, d), rn(B, N, d), rn(B, 1, d), ints(1, B, dc)
+    ctx = (torch.cat([eye, spread]).contiguous(), zero, eye, zero)
+    s = 3.0 * (d // h) ** -0.5
+    LP = []
+    for cand_q in (norms[2], (None, None)):
+        model = binding.scoring_model(L, ctx, hist, cand, *norms[:2], cand_q, *norms[3:], ([rn(d, 1)], [rn(1)]), h, s, s)
+        LP.append(binding.lime_scores(model, E, None, EC, T, want_intermediates=True)[2])
+    assert torch.equal(LP[0], LP[1]), f"{int((LP[0] != LP[1]).sum())} of {LP[0].numel()} elements differ"
