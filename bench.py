@@ -278,7 +278,7 @@ def main():
         "vs_baseline": None,
         "dtype": "bf16",
         "data": "synthetic",
-        "config": {"workload": f"BASELINE.json configs[2] (synth.CONFIGS[3]), the candidate sweep at its largest point: B={B} user, N={N}, C={C}, d={d}, h={h}, m={m}, "
+        "config": {"workload": f"configuration 3 (synth.CONFIGS[3]), the candidate sweep at its largest point: B={B} user, N={N}, C={C}, d={d}, h={h}, m={m}, "
                                "bf16, embeddings and weights ~N(0,1/d); step = "
                                + ("lime_request (link states, then candidate scores, packing everything per call)" if one_call
                                   else "lime_link_history + lime_score_candidates"),
@@ -485,7 +485,7 @@ def curves(binding, synth, torch, dev, timed, pct):
         req = pct(timed(lambda i: binding.lime_request(E, None, L, Wq, Wk, Wv, Tc, L, Wq, Wk, Wv, w.h, s, s, LP=LP, O=O,
                                                        workspace=wsc), 60), 0.5)
         sweep[C] = {"lime_score_candidates_p50_ms": cand, "lime_request_p50_ms": req}
-    res["latency_vs_candidates"] = {"workload": "BASELINE.json configs[2]: B=1, N=2048, d=256, h=4, m=64, bf16 (warm buffers)",
+    res["latency_vs_candidates"] = {"workload": "configuration 3: B=1, N=2048, d=256, h=4, m=64, bf16 (warm buffers)",
                                     "points": sweep}
     # ... and the same request from embeddings to scores (lime_scores: Eq. 2, layer normalisation before the projections,
     # Eq. 3, Eq. 4, the interaction network of Section 3.3) with Appendix C's industrial network [96] and its largest one
@@ -543,7 +543,7 @@ def curves(binding, synth, torch, dev, timed, pct):
     for key in ("lime_xor_history_p50_ms", "with_OS_p50_ms", "lime_link_history_p50_ms"):
         slope, floor = np.polyfit(np.array(ns, dtype=np.float64) / 1024.0, np.array([xs[n][key] for n in ns]) * 1e3, 1)
         fits[key] = {"us_per_1024_items": float(slope), "floor_us": float(floor)}
-    res["latency_vs_history_length"] = {"workload": "BASELINE.json configs[3]: B=8, d=128, h=4, m=64, bf16; XORA (Eq. 6-7) and "
+    res["latency_vs_history_length"] = {"workload": "configuration 4: B=8, d=128, h=4, m=64, bf16; XORA (Eq. 6-7) and "
                                                     "softmax (Eq. 3); 32768 and 65536 are beyond the paper's sweep",
                                         "points": xs, "least_squares_line": fits}
     # (c) LIME against full target attention on identical inputs
@@ -556,9 +556,9 @@ def curves(binding, synth, torch, dev, timed, pct):
     lat_lime = pct(timed(lambda i: binding.lime_request(E5, lens5, L5, q5, k5, v5, T5, L5, q5, k5, v5, w5.h, s5, s5), 20), 0.5)
     lat_mha = pct(timed(lambda i: binding.mha_target_attention(T5, E5, lens5, q5, k5, v5, w5.h, s5), 6), 0.5)
     res["lime_vs_target_attention"] = {
-        "workload": "BASELINE.json configs[4]: B=16, N=4096 ragged in [2048, 4096], C=8192, m=128, d=256, h=4, bf16",
+        "workload": "configuration 5: B=16, N=4096 ragged in [2048, 4096], C=8192, m=128, d=256, h=4, bf16",
         "lime_request_p50_ms": lat_lime, "mha_target_attention_p50_ms": lat_mha, "speedup": lat_mha / lat_lime,
-        "note": "the baseline is a fair matrix-core kernel, not a tuned one: the ratio flatters LIME by that much"}
+        "note": "both tuned for this card; the baseline keeps its matrix cores busy, the request is mostly latency and phi"}
     return res
 
 
@@ -778,7 +778,7 @@ def extras(binding, synth, torch, dev, timed, pct):
                    "frac_of_two_pass_bound": two_pass / (HBM_PEAK_GBS * 1e9) / (pct(lat, 0.5) * 1e-3)}
         del gb
     res["lime_xor_backward_vs_N"] = back
-    # the batched block of configs[1]: 32 users, ragged histories of 512..1024 items, d = 128, 1024 candidates each
+    # the batched block of configuration 2: 32 users, ragged histories of 512..1024 items, d = 128, 1024 candidates each
     c2 = dict(synth.CONFIGS[2])
     c2["pad_value"] = 0.0
     w2 = synth.make_workload(2, **c2)

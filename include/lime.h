@@ -351,7 +351,7 @@ size_t lime_workspace_bytes(int32_t op, int32_t B, int32_t N, int32_t C, int32_t
  * stop event of its own (hipExtLaunchKernel), which the runtime fills with the dispatch's begin and end time stamps:
  * the kernel's own duration as a kernel trace reports it.  Kernel ids: 0 = the candidate-side kernel of
  * lime_score_candidates and of O[S]; 1 = the links-over-history kernel of lime_link_history / lime_xor_history;
- * 2 = the attention kernel of mha_target_attention; 3 = its three row projections (one duration each); 4 = the kernel
+ * 2 = the attention kernel of mha_target_attention; 3 = its projection of the history's keys and values; 4 = the kernel
  * of lime_score_candidates_cached and lime_score_candidates_gathered; 5, 6 = the two probes below.
  * lime_profile_collect(kernel, ms, capacity): waits for the recorded launches of that kernel,
  * writes up to `capacity` durations in milliseconds to the HOST array `ms` in launch order,

@@ -78,8 +78,9 @@ __device__ __forceinline__ float group_sum(float x) {
 
 __device__ __forceinline__ float wave_sum(float x) { return pair_sum(group_sum<32>(x)); }
 
-// A 32 x 32 block of a product over 16 NK: one accumulator, k ascending.  Every projection of link rows goes through it,
-// so that an operand has the same bits wherever it is projected.
+// A 32 x 32 block of a product over 16 NK: one accumulator, k ascending.  Every projection of the pack kernel goes through
+// it, so that an operand has the same bits in whatever launch it is packed.  (Link states that the merge step projects are
+// summed in another order, see merge_values_kernel.)
 template <int NK>
 __device__ __forceinline__ f32x16 project_block(const bf16x8 (&a)[NK], const bf16x8 (&b)[NK]) {
   f32x16 acc;

@@ -441,9 +441,10 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeArgs a) {
 
 // Merge and the candidate stage's value projection in one kernel: a block finishes kMvRows link states of one user
 // (four adjacent elements per thread, as the merge kernel does), stores them, and projects their bf16-rounded values onto Wv:
-// V~ = LP Wv, written as the value image (kPackValues) that the candidate-side kernel loads.  Same split of the sum
-// over d as the pack kernel's projections: thread (cg, kc) owns 8 adjacent columns and every nkc-th k; the partial
-// sums meet in LDS.  Every partial state is read once, as in the merge kernel: those reads miss the local L2
+// V~ = LP Wv, written as the value image (kPackValues) that the candidate-side kernel loads.  On the vector ALUs:
+// thread (cg, kc) owns 8 adjacent columns and every nkc-th k; the partial sums meet in LDS.  (The pack kernel sums the
+// same projection on the matrix cores, k ascending: V~ of a request and of lime_score_candidates on its link states agree
+// to the last bits of fp32, before their rounding to bf16.)  Every partial state is read once, as in the merge kernel: those reads miss the local L2
 // (other compute units wrote them) and set the kernel's time.
 // The workgroup has 2 d threads: d / 8 column groups x 16 k-groups (d / 16 k-steps per thread), of which d / 2
 // threads do the merge.
@@ -648,6 +649,14 @@ Layout plan(int B, int N, int d, int h, int m, bool q_per_user, bool walk) {
   // Measured, history + merge kernel in us, for four-wave, narrow and wide groups:
   //   B=1 N=2048 d=256: 11.7, 12.9, 13.1     B=32 N=1024 d=128: 15.0, 15.1, 18.1     B=32 N=2048 d=128: 20.2, 18.8, 20.5
   //   B=8 N=16384 d=128: 31.1, 26.3, 25.5    B=16 N=4096 d=256: 36.4, 34.2, 32.4
+  // The line between narrow and wide, at B tiles d = 2048 slots: where they cross depends on the shape.  lime_link_history
+  // on prepared operands in us, narrow | wide, at 1434, 1741, 2048, 2458 and 3072 slots (SiLU crosses at the same places):
+  //   B=8 d=128 h=4 m=64:  20.2|22.5  22.3|23.6  24.2|24.8  28.1|27.9  32.1|31.1
+  //   B=32 d=128 h=4 m=64: 20.5|21.9  22.2|22.6  24.5|24.1  28.0|27.4  32.0|30.4
+  //   B=8 d=256 h=4 m=64:  24.7|24.1  27.1|26.5  29.9|28.7  34.1|32.6  39.7|37.7
+  //   B=8 d=256 h=4 m=128: 33.7|32.2  37.1|35.6  41.1|39.3  47.1|43.9  54.5|50.8
+  // With h = 8 wide is ahead from 1000 slots on (30.3|27.1 at 1741), with h = 2 from 4096, for one user later still
+  // (36.6|37.2 at 1741, 33.7|38.8 at 2048, d=256).  One line for all, where four heads of width 32 cross.
   const int64_t slots = compute_units();
   const int tiles = (N + 31) / 32;
   int tp = 1, groups = 1, steps = tiles;

@@ -223,9 +223,8 @@ __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int uni
 
 // D: embedding width.  SDH, SM: shape of the score job (d/h, m) this instance can run after its other jobs; 0 = none.
 // A block is four wavefronts: 256 slots of a weight image, or four units of the projection jobs, or four of the score
-// job.  What bounds it is latency (a few KiB per compute unit): every load of a unit is independent of every other.  A
-// projection unit used to be 4 rows x 32 columns in fp32 on the vector ALUs with the sum over k split over a block and
-// combined through LDS; on the matrix cores a wavefront does 32 x 32 without LDS or barriers.
+// job.  What bounds it is latency (a few KiB per compute unit): every load of a unit is independent of every other, and a
+// projection's wavefront needs neither LDS nor a barrier.
 template <int D, int SDH, int SM>
 __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
   constexpr int d = D;

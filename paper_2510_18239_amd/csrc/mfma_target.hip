@@ -204,15 +204,11 @@ __global__ __launch_bounds__(256, 2) void target_attention_kernel(AttnArgs a) {
   const bf16x8* kv = a.KV + (static_cast<int64_t>(b) * H + head) * ((a.tiles + 1) & ~1) * Img::kFrags * 64;
   const int last_stage = (tiles - 1) / 2;
   // (a stage past the last is the last one again: the number of outstanding loads is then the same at every wait)
-  // (assembly: the compiler would make every later read of LDS wait for the youngest of these loads)
   auto load_stage = [&](int stage, int slot) {
     const bf16x8* src = kv + (static_cast<int64_t>(min(stage, last_stage)) * kStageFrags + wave * kLoads) * 64;
-    const unsigned dst = static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)kv_lds)) +
-                         (slot * kStageFrags + wave * kLoads) * 1024;
+    const unsigned dst = lds_offset_of(kv_lds) + (slot * kStageFrags + wave * kLoads) * 1024;
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   : : "s"(__builtin_amdgcn_readfirstlane(dst + j * 1024)), "v"(lane * 16), "s"(src + j * 64) : "memory", "m0");
+    for (int j = 0; j < kLoads; ++j) load_to_lds(dst + j * 1024, lane * 16, src + j * 64);
   };
   auto publish = [&] {  // this wave's part of the stage about to be read has arrived; so has everybody's
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(kLoads) : "memory");  // all but the youngest stage

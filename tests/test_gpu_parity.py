@@ -514,10 +514,10 @@ def test_prepared_candidate_stage_with_folded_scores(d, h, m, identity):
 
 
 @pytest.mark.parametrize("d,h,m,B,N", [(256, 4, 64, 40, 1024), (256, 4, 128, 36, 1000), (128, 4, 64, 70, 600)])
-def test_cooperative_history_kernels_on_edge_lengths(d, h, m, B, N):
-    """Enough users x tiles for the cooperative history kernels (at d = 256 the variant with all W_K slices in
-    LDS and one tile buffer), with the lengths that stress them: empty users, one item, one short of / exactly /
-    one past a tile, a chunk boundary, the full history; padding rows hold NaN."""
+def test_history_kernel_on_edge_lengths(d, h, m, B, N):
+    """Enough users x tiles for workgroups of eight waves and several steps, with the lengths that stress them: empty users,
+    one item, one short of / exactly / one past a tile, a step's and a chunk's boundary, the full history; padding rows hold
+    NaN."""
     w = _sharp(workload=90 + m, B=B, N=N, C=8, d=d, h=h, m=m, dtype="bf16", len_range=(1, N), pad_value=np.nan,
                value_gain=TINY_HISTORY_VALUE_GAIN)
     special = [0, 1, 31, 32, 33, 255, 256, 257, N - 1, N, 0, N]
@@ -575,7 +575,7 @@ def test_xor_layers_on_general_kernels(dtype, B, N, d, h, m, n_layers, per_user)
     (2, 257, 256, 4, 128, 3, False),
     (2, 190, 64, 2, 32, 2, True),        # per-user contextualised links from the start
     (1, 100, 256, 8, 96, 1, False),      # one layer: the gated block on top of lime_xor_history
-    (40, 1024, 128, 4, 64, 3, False),    # enough rows for the cooperative history kernel
+    (40, 1024, 128, 4, 64, 3, False),    # several steps per workgroup of the history kernel
 ])
 def test_xor_layers(B, N, d, h, m, n_layers, per_user):
     """lime_xor_layers against the oracle's Eq. 8 on sharp inputs (gate pre-activations and XORA logits of order
@@ -648,8 +648,10 @@ def test_general_kernels_at_their_edges(B, N, C, d, h, m, dtype):
     (1, 1, 1, 256, 4, 64),       # one item, one query
     (2, 65, 257, 256, 4, 96),    # a step of the history kernel and one item; three link blocks over two waves
     (3, 129, 31, 128, 2, 32),    # one link block over two waves; one query short of a block
-    (5, 1057, 64, 128, 4, 128),  # several steps per workgroup, the last one item long
-    (2, 2049, 33, 256, 8, 64),   # one head per workgroup, eight tiles a step
+    (5, 1057, 64, 128, 4, 128),  # four waves and one step per workgroup, the last workgroup's of two tiles, one item in the second
+    (2, 2049, 33, 256, 8, 64),   # eight waves, one head and one step per workgroup, the last one's of one item
+    (16, 1281, 40, 128, 4, 128), # the same with two steps, the last one item long (two buffers for the rows)
+    (6, 2049, 33, 256, 8, 64),   # and without a second buffer: the refill between two barriers
     (33, 2017, 40, 256, 4, 32),  # several heads per workgroup, the last step one tile and one item
     (65, 2080, 20, 128, 4, 64),  # the same with heads of width 32
 ])
