@@ -45,7 +45,8 @@ class Args {
   Args(PyObject* const* args, Py_ssize_t n, Py_ssize_t want) : a_(args) {
     if (n != want) raise(PyExc_TypeError, "wrong number of arguments");
   }
-  const Tensor* tensor(bool required = true) {  // nullptr for None
+  // nullptr for None: `required` where the call's sizes come from the tensor, otherwise the library says what it needs.
+  const Tensor* tensor(bool required = true) {
     PyObject* o = a_[i_++];
     if (o == Py_None) {
       if (required) raise(PyExc_ValueError, "a required tensor is None");
@@ -220,7 +221,7 @@ PyObject* pair(const Tensor& a, const Tensor* b) {
 // ------------------------------------------------------------------------------------------------- the calls
 // (E, lens, LC, Wq, Wk, Wv, h, scale, LP, OS, want_os, xor, workspace, stream) -> (LP, OS or None)
 PyObject* history(Args a) {
-  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wq = a.tensor(), *Wk = a.tensor(), *Wv = a.tensor();
+  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wq = a.tensor(false), *Wk = a.tensor(false), *Wv = a.tensor(false);
   const int32_t h = a.integer();
   const float scale = a.number();
   const Tensor *LPin = a.tensor(false), *OSin = a.tensor(false);
@@ -246,7 +247,7 @@ PyObject* history(Args a) {
 
 // (E, lens, LC, Wq, Wk, Wv, Wu, Wo, h, scale, LP, workspace, stream) -> LP
 PyObject* xor_layers(Args a) {
-  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wq = a.tensor(), *Wk = a.tensor(), *Wv = a.tensor(),
+  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wq = a.tensor(false), *Wk = a.tensor(false), *Wv = a.tensor(false),
                *Wu = a.tensor(), *Wo = a.tensor();
   const int32_t h = a.integer();
   const float scale = a.number();
@@ -283,7 +284,7 @@ PyObject* score_candidates(Args a) {
 
 // (T, E, lens, Wq, Wk, Wv, h, scale, O, workspace, stream) -> O
 PyObject* target_attention(Args a) {
-  const Tensor *T = a.tensor(), *E = a.tensor(), *lens = a.tensor(false), *Wq = a.tensor(), *Wk = a.tensor(), *Wv = a.tensor();
+  const Tensor *T = a.tensor(), *E = a.tensor(), *lens = a.tensor(false), *Wq = a.tensor(false), *Wk = a.tensor(false), *Wv = a.tensor(false);
   const int32_t h = a.integer();
   const float scale = a.number();
   const Tensor *Oin = a.tensor(false), *workspace = a.tensor(false);
@@ -323,7 +324,7 @@ PyObject* score_cached(Args a) {
 
 // (E, lens, prepared, h, m, scale, xor, LP, workspace, stream) -> LP
 PyObject* history_prepared(Args a) {
-  const Tensor *E = a.tensor(), *lens = a.tensor(false), *prepared = a.tensor();
+  const Tensor *E = a.tensor(), *lens = a.tensor(false), *prepared = a.tensor(false);
   const int32_t h = a.integer(), m = a.integer();
   const float scale = a.number();
   const bool is_xor = a.truth();
@@ -340,7 +341,7 @@ PyObject* history_prepared(Args a) {
 
 // (T, LP, Wv, prepared, h, scale, O, workspace, stream) -> O
 PyObject* candidates_prepared(Args a) {
-  const Tensor *T = a.tensor(), *LP = a.tensor(), *Wv = a.tensor(false), *prepared = a.tensor();
+  const Tensor *T = a.tensor(), *LP = a.tensor(), *Wv = a.tensor(false), *prepared = a.tensor(false);
   const int32_t h = a.integer();
   const float scale = a.number();
   const Tensor *Oin = a.tensor(false), *workspace = a.tensor(false);
@@ -357,7 +358,7 @@ PyObject* candidates_prepared(Args a) {
 // (E, lens, LC, Wq_hist, Wk_hist, Wv_hist, T, L, Wq_cand, Wk_cand, Wv_cand, h, scale_hist, scale_cand, xor, LP, O, on_static,
 //  workspace, stream) -> (LP, O)
 PyObject* request(Args a) {
-  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wqh = a.tensor(), *Wkh = a.tensor(), *Wvh = a.tensor();
+  const Tensor *E = a.tensor(), *lens = a.tensor(false), *LC = a.tensor(), *Wqh = a.tensor(false), *Wkh = a.tensor(false), *Wvh = a.tensor(false);
   const Tensor *T = a.tensor(), *L = a.tensor(), *Wqc = a.tensor(false), *Wkc = a.tensor(false), *Wvc = a.tensor(false);
   const int32_t h = a.integer();
   const float sh = a.number(), sc = a.number();
@@ -386,7 +387,7 @@ PyObject* request(Args a) {
 
 // (E, lens, T, Wv, prepared, h, m, scale_hist, scale_cand, xor, LP, O, workspace, stream) -> (LP, O)
 PyObject* request_prepared(Args a) {
-  const Tensor *E = a.tensor(), *lens = a.tensor(false), *T = a.tensor(), *Wv = a.tensor(false), *prepared = a.tensor();
+  const Tensor *E = a.tensor(), *lens = a.tensor(false), *T = a.tensor(), *Wv = a.tensor(false), *prepared = a.tensor(false);
   const int32_t h = a.integer(), m = a.integer();
   const float sh = a.number(), sc = a.number();
   const bool is_xor = a.truth();

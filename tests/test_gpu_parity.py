@@ -725,3 +725,25 @@ def test_largest_softmax_weight_is_not_rounded(d, h, B, N):
         worst = float((np.abs(host(got) - ref) / ref).max())
         print(f"{name} d={d} h={h}: largest relative error {worst * 256:.4f} x 2^-8", flush=True)
         assert worst <= 2.0 ** -8 + 2.0 ** -18, name
+
+
+def test_a_missing_weight_is_refused_by_the_library():
+    """None for a weight that a call needs, or for the prepared operands, is the library's error (LIME_INVALID_ARG), as it is
+    through the C symbols."""
+    bf = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    E, L, W, T = bf(2, 40, 64), bf(32, 64), bf(64, 64), bf(2, 5, 64)
+    Wu = bf(1, 64, 64)
+    for call in [
+        lambda: binding.lime_link_history(E, None, L, W, None, W, 2, 1.0),
+        lambda: binding.lime_xor_history(E, None, L, None, W, W, 2, 1.0),
+        lambda: binding.lime_xor_layers(E, None, L, W, W, None, Wu, Wu, 2, 1.0),
+        lambda: binding.mha_target_attention(T, E, None, W, W, None, 2, 1.0),
+        lambda: binding.lime_request(E, None, L, W, W, None, T, L, W, W, W, 2, 1.0, 1.0),
+        lambda: binding.lime_request_static(E, None, L, None, W, W, T, L, W, W, W, 2, 1.0, 1.0),
+        lambda: binding.lime_link_history_prepared(E, None, None, 2, 32, 1.0),
+        lambda: binding.lime_score_candidates_prepared(T, bf(2, 32, 64), W, None, 2, 1.0),
+        lambda: binding.lime_request_prepared(E, None, T, W, None, 2, 32, 1.0, 1.0),
+    ]:
+        with pytest.raises(binding.LimeError, match="NULL") as e:
+            call()
+        assert e.value.status == 1
