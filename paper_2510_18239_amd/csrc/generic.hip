@@ -552,9 +552,8 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
 #pragma unroll 4
     for (int c = 1; c < used; ++c) {
       const int64_t row_c = static_cast<int64_t>(c) * a.q_rows;
-      const float2 theirs = *reinterpret_cast<const float2*>(ml + row_c * a.h * 2);
-      const FoldWeights w = fold_weights<PHI>(mx, theirs.x);
-      num = folded(num, acc[row_c * a.d], w), den = folded(den, theirs.y, w);
+      const FoldWeights w = fold_weights<PHI>(mx, ml[row_c * a.h * 2]);
+      num = folded(num, acc[row_c * a.d], w), den = folded(den, ml[row_c * a.h * 2 + 1], w);
     }
     out = num * (1.f / (PHI == kPhiSoftmax ? den : static_cast<float>(klen)));
   }
