@@ -156,6 +156,24 @@ __device__ __forceinline__ unsigned lds_offset_of(const void* p) {
 // A workgroup barrier that waits for this wave's LDS accesses but, unlike __syncthreads, for no load from memory.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
+// A fragment whose summed index runs down the columns of a row-major matrix, from a tile of it in LDS: lane (n, g), slot t =
+// tile[row 8g + t][column n], rows `pitch` bytes apart, `tile` the first of 16 rows and 32 columns.  ds_read_b64_tr_b16 hands
+// each lane of a group of 16 a column of the 4 x 16 block whose rows the group's lanes point at, four lanes a row.
+// (At a pitch of 64 bytes the 32 lanes that are served at once read 256 consecutive bytes.)
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 column_fragment(const unsigned char* tile, int pitch, int lane) {
+  const unsigned char* p = tile + (8 * (lane >> 5) + (lane % 16) / 4) * pitch + ((lane >> 4) & 1) * 32 + lane % 4 * 8;
+  auto at = [&](const unsigned char* q) {
+    return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(q)));
+  };
+  const bf16x4 lo = at(p), hi = at(p + 4 * pitch);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Between a wave's writes to LDS and its own lanes' reads of what other lanes wrote (and back): the accesses are served in
+// order, so only the compiler has to keep them.
+__device__ __forceinline__ void wave_lds_fence() { asm volatile("" : : : "memory"); }
+
 // Output-row permutation that makes a lane's 16 accumulator registers 16 consecutive columns:
 // the A-operand row `rho` of an output block carries column out_col(rho); lane-half g then holds
 // columns 16g .. 16g+15 of the 32-wide block in register order.

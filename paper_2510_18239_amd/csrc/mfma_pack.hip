@@ -22,7 +22,8 @@ struct PackArgs {
   const bf16_t* p_beta[kMaxJobs];
   float p_eps[kMaxJobs];
   int p_norm[kMaxJobs];
-  int p_first_unit[kMaxJobs + 1];   // ranges of the projection jobs' units (a wavefront each), after the weight jobs
+  int p_first_unit[kMaxJobs + 1];   // ranges of the projection jobs' units, after the weight jobs
+  int units_per_block;              // of the projection jobs: 1 or 4
   const bf16_t *s_wq, *s_k, *s_wk;  // the score job (at most one), after the projection jobs
   bf16_t* s_img;
   float s_sign;
@@ -88,74 +89,80 @@ __device__ void score_wave(const PackArgs& p, int combo) {
   for (int i = 0; i < 16; ++i) store_as(dst + (8 * (i / 4) + 4 * g + i % 4) * 8, acc[i] * p.s_sign);
 }
 
-// Layer normalisation of 32 rows by a workgroup of four wavefronts: eight lanes per row, D / 64 pieces of eight columns
-// per lane, so that a row's statistics are a lane's own sums and three exchanges; mean first, then the centred second
-// moment, in fp32.  `take` asks for what it needs, `finish` leaves the rows, rounded to bf16 where a normalisation pass of
-// its own would have stored them, in LDS, from where every wavefront reads its fragments.
+// 32 rows taken by a workgroup of four wavefronts into LDS, from where every wavefront reads its fragments: eight lanes per
+// row, D / 64 pieces of eight columns per lane.  With a normalisation a row's statistics are a lane's own sums and three
+// exchanges; mean first, then the centred second moment, in fp32, the rows rounded to bf16 where a normalisation pass of its
+// own would have stored them.  `take` asks for what is needed, `finish` leaves the rows in LDS.
 template <int D>
-struct GroupNorm {
+struct GroupRows {
   static constexpr int J = D / 64, kPitch = D + 8;  // (16 rows of a fragment read then cover all banks)
   bf16x8 x[J], gamma[J], beta[J];
-  __device__ __forceinline__ void take(const bf16_t* rows, const bf16_t* ga, const bf16_t* be) {
+  __device__ __forceinline__ void take(const bf16_t* rows, bool norm, const bf16_t* ga, const bf16_t* be) {
     const int r = threadIdx.x / 8, c = 8 * (threadIdx.x % 8);
 #pragma unroll
     for (int j = 0; j < J; ++j) x[j] = *reinterpret_cast<const bf16x8*>(rows + static_cast<int64_t>(r) * D + 64 * j + c);
+    if (!norm) return;  // uniform
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       gamma[j] = *reinterpret_cast<const bf16x8*>(ga + 64 * j + c);
       beta[j] = *reinterpret_cast<const bf16x8*>(be + 64 * j + c);
     }
   }
-  __device__ __forceinline__ void finish(bf16_t* lds, float eps) {
-    float v[J][8], sum = 0.f, q = 0.f;
-#pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[j][t] = static_cast<float>(x[j][t]), sum += v[j][t];
-    const float mean = group_sum<8>(sum) * (1.f / D);
-#pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[j][t] -= mean, q = fmaf(v[j][t], v[j][t], q);
-    const float inv = 1.f / sqrtf(group_sum<8>(q) * (1.f / D) + eps);
+  __device__ __forceinline__ void finish(bf16_t* lds, bool norm, float eps) {
     bf16_t* dst = lds + threadIdx.x / 8 * kPitch + 8 * (threadIdx.x % 8);
+    if (norm) {  // uniform
+      float v[J][8], sum = 0.f, q = 0.f;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      bf16x8 y;
+      for (int j = 0; j < J; ++j)
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
-        y[t] = static_cast<__bf16>(fmaf(v[j][t] * inv, static_cast<float>(gamma[j][t]), static_cast<float>(beta[j][t])));
-      *reinterpret_cast<bf16x8*>(dst + 64 * j) = y;
+        for (int t = 0; t < 8; ++t) v[j][t] = static_cast<float>(x[j][t]), sum += v[j][t];
+      const float mean = group_sum<8>(sum) * (1.f / D);
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[j][t] -= mean, q = fmaf(v[j][t], v[j][t], q);
+      const float inv = 1.f / sqrtf(group_sum<8>(q) * (1.f / D) + eps);
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          x[j][t] = static_cast<__bf16>(fmaf(v[j][t] * inv, static_cast<float>(gamma[j][t]), static_cast<float>(beta[j][t])));
     }
+#pragma unroll
+    for (int j = 0; j < J; ++j) *reinterpret_cast<bf16x8*>(dst + 64 * j) = x[j];
   }
 };
 
-// One wavefront of a projection job: 32 rows x 32 columns of X_u W on the matrix cores (project_block), written as two
-// fragments of the job's image.
+// A projection job's unit: 32 rows x 32 columns of X_u W on the matrix cores (project_block), written as two fragments of
+// the job's image.  The unit's columns of W are read along its rows, 16 rows of 64 bytes per load, and turned in LDS.
 //
-// Normalised rows: from d = 128 on (a multiple of four column blocks: a workgroup's units then belong to one job) the
-// workgroup takes four column blocks of the same rows and normalises them together.  Below, a wavefront normalises its
-// rows by itself: an element costs it a dozen instructions, 32 of them per lane at d = 64, but 128 at d = 256, which every
-// one of a row's eight column blocks would repeat (pack kernel of a request with normalisations, d = 256: 10.9 us so,
-// 6.0 together).
+// Up to d = 64 a wavefront does a unit by itself.  From d = 128 on (a multiple of four column blocks: a workgroup's units
+// then belong to one job and to the same rows) the workgroup takes the rows together, and normalises them where that is
+// asked for; with few units (one per workgroup) its wavefronts also share the loads of W, and the first does the product.
+// What counts is the bytes a compute unit asks for, 64 a cycle: with four units a workgroup, each wavefront fetching its
+// rows as fragments (32 lines a load), the loads of the request's 32 units at d = 256 took 2.1 us to be issued.
 template <int D>
-__device__ __forceinline__ void project_wave(const PackArgs& p, int job, int unit) {
+__device__ __forceinline__ void project_unit(const PackArgs& p, int job, int unit) {
   constexpr int NK = D / 16, CB = D / 32;
   constexpr bool kTogether = CB % 4 == 0;
-  __shared__ __attribute__((aligned(16))) bf16_t normalised[kTogether ? 32 * (D + 8) : 8];
+  constexpr int kTurn = NK < 8 ? NK : 8;  // k-steps of W that a wavefront has in LDS at a time
+  __shared__ __attribute__((aligned(16))) bf16_t rows_lds[kTogether ? 32 * (D + 8) : 8];
+  __shared__ __attribute__((aligned(16))) unsigned char turned[4 * kTurn * 1024];
+  static_assert(!kTogether || NK <= 4 * kTurn, "a unit's columns of W fit the workgroup's part of LDS");
   const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, dh = p.dh, m = p.m;
-  const bool together = kTogether && p.p_norm[job];  // uniform over the workgroup
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lbs = m / 32, u = unit / (lbs * CB);
-  const int lb = together ? unit / CB % lbs : unit % lbs, cb = together ? unit % CB : unit / lbs % CB;
-  const bf16_t* X = p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(32 * lb + n) * D + 8 * g;  // row 32 lb + n
+  const int lb = kTogether ? unit / CB % lbs : unit % lbs, cb = kTogether ? unit % CB : unit / lbs % CB;
+  const bf16_t* Xu = p.p_x[job] + u * p.p_stride[job];
   const bf16_t* W = p.p_w[job];
+  const bool alone = kTogether && p.units_per_block == 1;  // uniform
   const int a = 32 * cb / dh, hc = 32 * cb % dh / 32;  // head, and 32-column block of the head
   const bool keys = p.p_layout[job] == kPackKeys;
   bf16x8* img = reinterpret_cast<bf16x8*>(p.p_img[job]);
   bf16x8 lo, hi;  // the block's accumulators, or what they would be
   if (W == nullptr) {
     // the identity: the rows as they are (normalised rows always come with a weight)
-    const bf16_t* Xu = p.p_x[job] + u * p.p_stride[job];
+    if (alone && wave > 0) return;
     auto element = [&](int k) { return keys ? Xu[static_cast<int64_t>(32 * lb + n) * D + 32 * cb + k] : Xu[static_cast<int64_t>(32 * lb + k) * D + 32 * cb + n]; };
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -164,33 +171,51 @@ __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int uni
     }
     if (p.p_sign[job] < 0.f) lo = -lo, hi = -hi;
   } else {
-    const bf16_t* wcol = W + static_cast<int64_t>(8 * g) * D + 32 * cb + n;
-    bf16x8 x[NK], w[NK];
+    const bf16_t* wrow = W + static_cast<int64_t>(lane / 4) * D + 32 * cb + 8 * (lane % 4);
+    bf16x8 x[NK], w[NK], raw[NK];
     auto take_weights = [&] {
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk)
-#pragma unroll
-        for (int t = 0; t < 8; ++t) w[kk][t] = __builtin_bit_cast(__bf16, wcol[(16 * kk + t) * D].bits);
+      for (int kk = 0; kk < NK; ++kk) raw[kk] = *reinterpret_cast<const bf16x8*>(wrow + 16 * kk * D);
     };
-    auto take_rows = [&] {
+    auto turn_weights = [&] {  // (a wavefront's LDS accesses are served in order, so its part needs no barrier)
+      unsigned char* mine = turned + wave * kTurn * 1024;
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
+      for (int k0 = 0; k0 < NK; k0 += kTurn) {
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) *reinterpret_cast<bf16x8*>(mine + k * 1024 + lane * 16) = raw[k0 + k];
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) w[k0 + k] = column_fragment(mine + k * 1024, 64, lane);
+      }
     };
     if constexpr (kTogether) {
-      if (together) {
-        GroupNorm<D> norm;
-        norm.take(p.p_x[job] + u * p.p_stride[job] + static_cast<int64_t>(32 * lb) * D, p.p_gamma[job], p.p_beta[job]);
-        take_weights();
-        norm.finish(normalised, p.p_eps[job]);
-        lds_barrier();
+      const bool norm = p.p_norm[job];
+      GroupRows<D> group;
+      group.take(Xu + static_cast<int64_t>(32 * lb) * D, norm, p.p_gamma[job], p.p_beta[job]);
+      if (alone) {
+        bf16x8 part[NK / 4];
 #pragma unroll
-        for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(normalised + n * GroupNorm<D>::kPitch + 16 * kk + 8 * g);
+        for (int k = 0; k < NK / 4; ++k) part[k] = *reinterpret_cast<const bf16x8*>(wrow + 16 * (NK / 4 * wave + k) * D);
+        group.finish(rows_lds, norm, p.p_eps[job]);
+#pragma unroll
+        for (int k = 0; k < NK / 4; ++k) *reinterpret_cast<bf16x8*>(turned + (NK / 4 * wave + k) * 1024 + lane * 16) = part[k];
+        lds_barrier();
+        if (wave > 0) return;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) w[kk] = column_fragment(turned + kk * 1024, 64, lane);
       } else {
-        take_rows();
         take_weights();
+        group.finish(rows_lds, norm, p.p_eps[job]);
+        lds_barrier();
+        turn_weights();
       }
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(rows_lds + n * GroupRows<D>::kPitch + 16 * kk + 8 * g);
     } else {
-      take_rows();
+      const bf16_t* X = Xu + static_cast<int64_t>(32 * lb + n) * D + 8 * g;  // row 32 lb + n
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
       bf16x8 gamma[NK], beta[NK];
       if (p.p_norm[job]) {  // asked for with everything else
 #pragma unroll
@@ -201,6 +226,7 @@ __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int uni
       }
       take_weights();
       if (p.p_norm[job]) normalise_rows<D>(x, gamma, beta, p.p_eps[job]);
+      turn_weights();
     }
     f32x16 acc = keys ? project_block<NK>(w, x) : project_block<NK>(x, w);
     if (p.p_sign[job] < 0.f) acc = -acc;
@@ -222,9 +248,8 @@ __device__ __forceinline__ void project_wave(const PackArgs& p, int job, int uni
 }
 
 // D: embedding width.  SDH, SM: shape of the score job (d/h, m) this instance can run after its other jobs; 0 = none.
-// A block is four wavefronts: 256 slots of a weight image, or four units of the projection jobs, or four of the score
-// job.  What bounds it is latency (a few KiB per compute unit): every load of a unit is independent of every other, and a
-// projection's wavefront needs neither LDS nor a barrier.
+// A block is four wavefronts: 256 slots of a weight image, or one or four units of the projection jobs, or four of the
+// score job.  What bounds it is latency (a few KiB per compute unit): every load of a unit is independent of every other.
 template <int D, int SDH, int SM>
 __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
   constexpr int d = D;
@@ -259,18 +284,18 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     return;
   }
   blk -= p.n_weights * p.blocks_per_weight;
-  const int projection_blocks = (p.p_first_unit[kMaxJobs] + 3) / 4;
+  const int projection_blocks = (p.p_first_unit[kMaxJobs] + p.units_per_block - 1) / p.units_per_block;
   if constexpr (SDH != 0) {
     if (blk >= projection_blocks) {  // uniform
       score_wave<SDH, SM, D / 32>(p, (blk - projection_blocks) * 4 + tid / 64);
       return;
     }
   }
-  int unit = __builtin_amdgcn_readfirstlane(blk * 4 + tid / 64);
+  int unit = p.units_per_block == 1 ? blk : __builtin_amdgcn_readfirstlane(blk * 4 + tid / 64);
   if (unit >= p.p_first_unit[kMaxJobs]) return;
   int job = 0;
   while (job + 1 < kMaxJobs && unit >= p.p_first_unit[job + 1]) ++job;
-  project_wave<D>(p, job, unit - p.p_first_unit[job]);
+  project_unit<D>(p, job, unit - p.p_first_unit[job]);
 }
 
 }  // namespace
@@ -306,7 +331,9 @@ hipError_t pack_operands(const PackWeight* weights, int n_weights, const PackPro
     }
   }
   p.p_first_unit[kMaxJobs] = units;
-  int grid = n_weights * p.blocks_per_weight + (units + 3) / 4;
+  // A unit per workgroup as long as every workgroup then has a compute unit to itself; project_unit takes four from there on.
+  p.units_per_block = d >= 128 && units <= compute_units() ? 1 : 4;
+  int grid = n_weights * p.blocks_per_weight + (units + p.units_per_block - 1) / p.units_per_block;
   const int dh = d / h, nkb = d / 32;
   if (score == nullptr) {
     if (grid == 0) return hipSuccess;
