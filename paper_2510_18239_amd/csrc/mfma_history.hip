@@ -356,65 +356,123 @@ struct MergeArgs {
   float scale;  // |logit scale|: the factor the SiLU partials still lack
 };
 
-// The merged values LP[b][link][a dh + t .. t + 3] of a user's chunks, combined in ascending order (t is a multiple
-// of four: one 16-byte load per chunk serves four outputs, and the load path of a compute unit, not the arithmetic,
-// is what this step keeps busy).
-template <int PHI>
-__device__ __forceinline__ float4 merged_values(const MergeArgs& a, int b, int link, int head, int t, int len) {
-  const int used = (len + a.chunk_items - 1) / a.chunk_items;  // chunks that hold at least one valid item
-  float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (used > 0) {
-    const int64_t stride = static_cast<int64_t>(a.h) * a.m;  // (head, link) slots per chunk
-    const int64_t first = (static_cast<int64_t>(b) * a.chunks * a.h + head) * a.m + link;
-    // all loads of a batch of chunks are issued before any is used: the partials were written by
-    // other compute units and every access is a long-latency miss
-    constexpr int kBatch = 16;
+// The merged link states of a user's chunks, one row LP[b][link] at a time by a workgroup of 2 d threads: thread
+// (quad, group) has four adjacent columns and every eighth chunk, kMergeBatch chunks at a time.  The sum over the chunks is
+// eight sums (chunk c in sum c % 8, ascending), added in pairs: the same in every kernel, so that a link state has the same
+// bits whichever of them finishes it.
+// The partials were written by other compute units and every read of them is a long-latency miss: all reads of a batch are
+// asked for before any is used, whether or not a user has that many chunks (what lies past its last one is left out of the
+// sums, and need not have been written), and the chunks' maxima and sums are read once per row and handed round in LDS.
+// (With two batches of 16 chunks one after the other in 128 threads, this took 3.5 of a merge_values_kernel's 5.9 us between
+// its first and last instruction, at B=1 N=2048 d=256 m=64; 1.2 of 3.6 so.)
+constexpr int kMergeBatch = 32, kMergeGroups = 8;
+template <int PHI, int D>
+struct MergeRow {
+  static constexpr int kThreads = 2 * D, kQuads = D / 4, kLoads = kMergeBatch / kMergeGroups, kMaxHeads = D / 32;
+  static constexpr int kMlPitch = kMergeBatch + 4;
+  struct Lds {
+    float top[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];  // the chunks' maxima, by head
+    float sum[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];
+    float4 num[(kMergeGroups - 1) * kQuads];
+    float den[PHI == kPhiSoftmax ? (kMergeGroups - 1) * kQuads : 1];
+  };
+  float4 ac[kLoads];
+  float2 ml;
+  int quad, group, head;
+  int64_t first, stride;  // (head, link) slots: of the row in the user's first chunk, per chunk
+
+  // asks for the first batch
+  __device__ __forceinline__ void begin(const MergeArgs& a, int b, int link) {
+    quad = threadIdx.x % kQuads, group = threadIdx.x / kQuads, head = 4 * quad / a.dh;
+    stride = static_cast<int64_t>(a.h) * a.m;
+    first = static_cast<int64_t>(b) * a.chunks * stride + link;
+    ask(a, 0);
+  }
+  __device__ __forceinline__ void ask(const MergeArgs& a, int c0) {
     if (PHI == kPhiSoftmax) {
-      float gmax = -INFINITY, den = 0.f;
-      float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int c0 = 0; c0 < used; c0 += kBatch) {
-        float2 ml[kBatch];  // (scaled maximum, sum)
-        float4 ac[kBatch];
+      // thread (head, chunk of the batch); the threads past the last head's repeat it
+      const int hd = min(static_cast<int>(threadIdx.x) / kMergeBatch, a.h - 1), c = c0 + threadIdx.x % kMergeBatch;
+      ml = *reinterpret_cast<const float2*>(a.part_ml + (first + hd * a.m + min(c, a.chunks - 1) * stride) * 2);
+    }
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int64_t s = first + static_cast<int64_t>(min(c0 + i, used - 1)) * stride;
-          ml[i] = *reinterpret_cast<const float2*>(a.part_ml + s * 2);
-          ac[i] = *reinterpret_cast<const float4*>(a.part_acc + s * a.dh + t);
+    for (int i = 0; i < kLoads; ++i)
+      ac[i] = *reinterpret_cast<const float4*>(
+          a.part_acc + (first + head * a.m + min(c0 + group + kMergeGroups * i, a.chunks - 1) * stride) * a.dh + 4 * quad % a.dh);
+  }
+  // the finished values, in the threads of the first group
+  __device__ __forceinline__ float4 finish(const MergeArgs& a, int len, Lds& lds) {
+    const int used = (len + a.chunk_items - 1) / a.chunk_items;  // chunks that hold at least one valid item
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    float top = -INFINITY, den = 0.f;
+    for (int c0 = 0; c0 < used; c0 += kMergeBatch) {  // uniform
+      if (c0 > 0) ask(a, c0);
+      float w[kLoads];
+      if (PHI == kPhiSoftmax) {
+        if (c0 > 0) lds_barrier();  // the last batch's have been read
+        const int hd = threadIdx.x / kMergeBatch, c = threadIdx.x % kMergeBatch;
+        if (hd < a.h) {
+          lds.top[hd * kMlPitch + c] = c0 + c < used ? ml.x : -INFINITY;
+          lds.sum[hd * kMlPitch + c] = c0 + c < used ? ml.y : 0.f;
         }
-        float bmax = gmax;
+        lds_barrier();
+        float batch_top = top;
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) bmax = fmaxf(bmax, ml[i].x);
-        const float keep = __builtin_amdgcn_exp2f((gmax - bmax) * kLog2e);  // 0 on the first batch
+        for (int i = 0; i < kMergeBatch; i += 4) {
+          const float4 v = *reinterpret_cast<const float4*>(&lds.top[head * kMlPitch + i]);
+          batch_top = fmaxf(batch_top, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+        }
+        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
         num.x *= keep, num.y *= keep, num.z *= keep, num.w *= keep;
         den *= keep;
-        gmax = bmax;
+        top = batch_top;
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const float w = c0 + i < used ? __builtin_amdgcn_exp2f((ml[i].x - gmax) * kLog2e) : 0.f;
-          num.x = fmaf(w, ac[i].x, num.x), num.y = fmaf(w, ac[i].y, num.y);
-          num.z = fmaf(w, ac[i].z, num.z), num.w = fmaf(w, ac[i].w, num.w);
-          den = fmaf(w, ml[i].y, den);
+        for (int i = 0; i < kLoads; ++i) {
+          const int at = head * kMlPitch + group + kMergeGroups * i;
+          w[i] = c0 + group + kMergeGroups * i < used ? __builtin_amdgcn_exp2f((lds.top[at] - top) * kLog2e) : 0.f;
+          den = fmaf(w[i], lds.sum[at], den);
         }
       }
-      out = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
-    } else {
-      float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int c0 = 0; c0 < used; c0 += kBatch) {
-        float4 ac[kBatch];
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-          ac[i] = *reinterpret_cast<const float4*>(
-              a.part_acc + (first + static_cast<int64_t>(min(c0 + i, used - 1)) * stride) * a.dh + t);
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-          if (c0 + i < used) num.x += ac[i].x, num.y += ac[i].y, num.z += ac[i].z, num.w += ac[i].w;
+      for (int i = 0; i < kLoads; ++i) {
+        if (c0 + group + kMergeGroups * i >= used) continue;
+        if (PHI == kPhiSoftmax) {
+          num.x = fmaf(w[i], ac[i].x, num.x), num.y = fmaf(w[i], ac[i].y, num.y);
+          num.z = fmaf(w[i], ac[i].z, num.z), num.w = fmaf(w[i], ac[i].w, num.w);
+        } else {
+          num.x += ac[i].x, num.y += ac[i].y, num.z += ac[i].z, num.w += ac[i].w;
+        }
       }
-      const float f = a.scale / static_cast<float>(len);
-      out = make_float4(num.x * f, num.y * f, num.z * f, num.w * f);
     }
+    if (group > 0) {
+      lds.num[(group - 1) * kQuads + quad] = num;
+      if (PHI == kPhiSoftmax) lds.den[(group - 1) * kQuads + quad] = den;
+    }
+    lds_barrier();
+    if (group > 0 || used <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 n[kMergeGroups];
+    float d[kMergeGroups];
+    n[0] = num, d[0] = den;
+#pragma unroll
+    for (int q = 1; q < kMergeGroups; ++q) {
+      n[q] = lds.num[(q - 1) * kQuads + quad];
+      d[q] = PHI == kPhiSoftmax ? lds.den[(q - 1) * kQuads + quad] : 0.f;
+    }
+    return total(n, d, a.scale, len);
   }
-  return out;
-}
+  // the eight sums added in pairs, and normalised
+  static __device__ __forceinline__ float4 total(float4 (&n)[kMergeGroups], float (&d)[kMergeGroups], float scale, int len) {
+#pragma unroll
+    for (int o = 1; o < kMergeGroups; o *= 2)
+#pragma unroll
+      for (int q = 0; q < kMergeGroups; q += 2 * o) {
+        n[q].x += n[q + o].x, n[q].y += n[q + o].y, n[q].z += n[q + o].z, n[q].w += n[q + o].w;
+        d[q] += d[q + o];
+      }
+    if (PHI == kPhiSoftmax) return make_float4(n[0].x / d[0], n[0].y / d[0], n[0].z / d[0], n[0].w / d[0]);
+    const float f = scale / static_cast<float>(len);
+    return make_float4(n[0].x * f, n[0].y * f, n[0].z * f, n[0].w * f);
+  }
+};
 
 // Four rounded link-state values as one 8-byte store.
 __device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, float* rounded = nullptr) {
@@ -424,146 +482,234 @@ __device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, floa
   if (rounded != nullptr)
     *reinterpret_cast<float4*>(rounded) = make_float4(to_float(r[0]), to_float(r[1]), to_float(r[2]), to_float(r[3]));
 }
-
-// One thread per four adjacent output elements LP[b][link][a dh + t .. t + 3], one wave per workgroup: the
-// workgroups spread over as many compute units as there are.
-constexpr int kMergeThreads = 64;
-template <int PHI>
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeArgs a) {
-  const int b = blockIdx.y;
-  const int idx = (blockIdx.x * kMergeThreads + threadIdx.x) * 4;
-  const int d = a.h * a.dh;
-  if (idx >= a.m * d) return;
-  const int link = idx / d, col = idx % d, head = col / a.dh, t = col % a.dh;
-  const int len = a.lens ? min(a.lens[b], a.N) : a.N;
-  store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + link) * d + col, merged_values<PHI>(a, b, link, head, t, len));
+__device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, bf16_t* again) {
+  alignas(8) bf16_t r[4];
+  store_as(&r[0], v.x), store_as(&r[1], v.y), store_as(&r[2], v.z), store_as(&r[3], v.w);
+  *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<uint2*>(again) = *reinterpret_cast<const uint2*>(r);
 }
 
-// Merge and the candidate stage's value projection in one kernel: a block finishes kMvRows link states of one user
-// (four adjacent elements per thread, as the merge kernel does), stores them, and projects their bf16-rounded values onto Wv:
-// V~ = LP Wv, written as the value image (kPackValues) that the candidate-side kernel loads.  On the vector ALUs:
-// thread (cg, kc) owns 8 adjacent columns and every nkc-th k; the partial sums meet in LDS.  (The pack kernel sums the
-// same projection on the matrix cores, k ascending: V~ of a request and of lime_score_candidates on its link states agree
-// to the last bits of fp32, before their rounding to bf16.)  Every partial state is read once, as in the merge kernel: those reads miss the local L2
-// (other compute units wrote them) and set the kernel's time.
-// The workgroup has 2 d threads: d / 8 column groups x 16 k-groups (d / 16 k-steps per thread), of which d / 2
-// threads do the merge.
-constexpr int kMvRows = 2, kMvKGroups = 16;
+// A workgroup per link state.
+template <int PHI, int D>
+__global__ __launch_bounds__(2 * D) void merge_kernel(MergeArgs a) {
+  __shared__ typename MergeRow<PHI, D>::Lds lds;
+  const int b = blockIdx.y, link = blockIdx.x;
+  MergeRow<PHI, D> row;
+  row.begin(a, b, link);
+  const int len = a.lens ? min(a.lens[b], a.N) : a.N;
+  const float4 v = row.finish(a, len, lds);
+  if (row.group == 0) store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + link) * D + 4 * row.quad, v);
+}
+
+// Layer normalisation of a finished link state by a wavefront, from x(k) to put(k, value): mean, centred second moment, then
+// the normalised row rounded to bf16, as a normalisation pass of its own would have stored it.
+// (the lane through an opaque copy: what is derived from it - addresses, the scale and the shift - is then computed and
+// fetched here, not ahead of the merge, which has no registers to carry it; the fetches are in flight during the two
+// reductions)
+template <int D, typename X, typename Put>
+__device__ __forceinline__ void normalise_state(const bf16_t* gamma, const bf16_t* beta, float eps, X x, Put put) {
+  constexpr int kPerLane = (D + 63) / 64;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  bf16_t ga[kPerLane], be[kPerLane];
+#pragma unroll
+  for (int i = 0; i < kPerLane; ++i) {
+    const int k = min(lane + 64 * i, D - 1);
+    ga[i] = gamma[k], be[i] = beta[k];
+  }
+  float v[kPerLane], sum = 0.f, q = 0.f;
+#pragma unroll
+  for (int i = 0; i < kPerLane; ++i) v[i] = lane + 64 * i < D ? x(lane + 64 * i) : 0.f, sum += v[i];
+  const float mean = wave_sum(sum) * (1.f / D);
+#pragma unroll
+  for (int i = 0; i < kPerLane; ++i) {
+    v[i] = lane + 64 * i < D ? v[i] - mean : 0.f;
+    q = fmaf(v[i], v[i], q);
+  }
+  const float inv = 1.f / sqrtf(wave_sum(q) * (1.f / D) + eps);
+#pragma unroll
+  for (int i = 0; i < kPerLane; ++i)
+    if (lane + 64 * i < D) put(lane + 64 * i, static_cast<__bf16>(fmaf(v[i] * inv, to_float(ga[i]), to_float(be[i]))));
+}
+
+// Merge and the candidate stage's value projection in one kernel: a workgroup finishes link states of one user, stores them,
+// and projects their bf16-rounded values onto Wv: V~ = LP Wv, written as the value image (kPackValues) that the
+// candidate-side kernel loads.  (The sums of the projection are in another order than the pack kernel's: V~ of a request and
+// of lime_score_candidates on its link states agree to the last bits of fp32, before their rounding to bf16.)
 struct MergeValuesArgs {
   MergeArgs m;
   const bf16_t* Wv;  // [d][d], nullable = identity
   bf16_t* VA;        // [B] value images
-  int passes;        // row pairs a workgroup handles one after the other with the same W_V registers
   // layer normalisation of the finished link states before the projection (ln_on; LP is stored un-normalised)
   const bf16_t *ln_gamma, *ln_beta;
   float ln_eps;
   int ln_on;
 };
 
+// A link state per workgroup, for calls whose workgroups then all run at once.  The projection is on the vector ALUs: thread
+// (cg, kc) owns 8 adjacent columns and every sixteenth k; the partial sums meet in LDS.
 template <int PHI, int D>
 __global__ __launch_bounds__(2 * D) void merge_values_kernel(MergeValuesArgs a) {
-  constexpr int d = D, kMvThreads = 2 * D, CG = D / 8, nkc = kMvKGroups, kMvMaxK = D / kMvKGroups;
-  static_assert(CG * nkc == kMvThreads, "one thread per (column group, k-group)");
-  // rounded link states + output rows + one partial output per k-group (36 KiB at d = 256)
-  __shared__ float lp[kMvRows * D];         // bf16-rounded values
-  __shared__ float out[kMvRows * D];
+  constexpr int kThreads = 2 * D, CG = D / 8, nkc = 16, kMaxK = D / nkc;
+  static_assert(CG * nkc == kThreads, "one thread per (column group, k-group)");
+  __shared__ typename MergeRow<PHI, D>::Lds lds;
+  __shared__ __attribute__((aligned(16))) float lp[D];  // bf16-rounded values
   // (a column c sits at c + c / 32: the writers' columns are 8 apart, which would otherwise share four banks)
   constexpr int kRedRow = D + D / 32;
-  __shared__ float red[nkc * kMvRows * kRedRow];
-  const int tid = threadIdx.x, b = blockIdx.y;
+  __shared__ float red[nkc * kRedRow];
+  const int tid = threadIdx.x, b = blockIdx.y, link = blockIdx.x;
   const int cg = tid % CG, kc = tid / CG;
-  bf16x8 wreg[kMvMaxK];
-  if (a.Wv != nullptr) {  // asked for before the merge, used after it
+  MergeRow<PHI, D> merge;
+  merge.begin(a.m, b, link);
+  bf16x8 wreg[kMaxK];
+  if (a.Wv != nullptr) {  // asked for behind the partials, used after them
 #pragma unroll
-    for (int it = 0; it < kMvMaxK; ++it)
-      wreg[it] = *reinterpret_cast<const bf16x8*>(a.Wv + static_cast<int64_t>(kc + it * nkc) * d + 8 * cg);
+    for (int it = 0; it < kMaxK; ++it)
+      wreg[it] = *reinterpret_cast<const bf16x8*>(a.Wv + static_cast<int64_t>(kc + it * nkc) * D + 8 * cg);
   }
-  constexpr int kLnWaves = kMvThreads / 64, kLnPerLane = (D + 63) / 64;
   const int len = a.m.lens ? min(a.m.lens[b], a.m.N) : a.m.N;
-  // (no barrier is needed between two passes: whoever writes lp, red or out again has passed two barriers since
-  // the last read of it)
-  const int passes = D >= 256 ? a.passes : 1;  // (a compile-time 1 keeps the small shapes' register count low)
-  for (int pass = 0; pass < passes; ++pass) {
-    const int row0 = (blockIdx.x * passes + pass) * kMvRows;
-    for (int i = 4 * tid; i < kMvRows * d; i += 4 * kMvThreads) {
-      const int link = row0 + i / d, col = i % d;
-      store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link) * d + col,
-                    merged_values<PHI>(a.m, b, link, col / a.m.dh, col % a.m.dh, len), lp + i);
-    }
+  const float4 v = merge.finish(a.m, len, lds);
+  if (merge.group == 0) store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link) * D + 4 * merge.quad, v, lp + 4 * merge.quad);
+  __syncthreads();
+  if (a.ln_on) {  // uniform
+    if (tid < 64) normalise_state<D>(a.ln_gamma, a.ln_beta, a.ln_eps, [&](int k) { return lp[k]; }, [&](int k, __bf16 y) { lp[k] = static_cast<float>(y); });
     __syncthreads();
-    if (a.ln_on) {  // uniform
-      // a wavefront per row: mean, centred second moment, then the normalised row rounded to bf16, as a
-      // normalisation pass of its own would have stored it
-      // (the thread index through an opaque copy: what is derived from it here - addresses, the scale and the shift -
-      // is then computed and fetched here, not ahead of the merge, which has no registers to carry it and would
-      // spill; the fetches are in flight during the two reductions)
-      int t_ln = tid;
-      asm volatile("" : "+v"(t_ln));
-      for (int r = t_ln / 64; r < kMvRows; r += kLnWaves) {
-        float* xr = lp + r * d;
-        bf16_t ln_g[kLnPerLane], ln_b[kLnPerLane];
-#pragma unroll
-        for (int i = 0; i < kLnPerLane; ++i) {
-          const int k = min(t_ln % 64 + 64 * i, d - 1);
-          ln_g[i] = a.ln_gamma[k], ln_b[i] = a.ln_beta[k];
-        }
-        float x[kLnPerLane], sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < kLnPerLane; ++i) {
-          const int k = t_ln % 64 + 64 * i;
-          x[i] = k < d ? xr[k] : 0.f;
-          sum += x[i];
-        }
-        const float mean = wave_sum(sum) * (1.f / d);
-        float q = 0.f;
-#pragma unroll
-        for (int i = 0; i < kLnPerLane; ++i) {
-          const int k = t_ln % 64 + 64 * i;
-          x[i] = k < d ? x[i] - mean : 0.f;
-          q = fmaf(x[i], x[i], q);
-        }
-        const float inv = 1.f / sqrtf(wave_sum(q) * (1.f / d) + a.ln_eps);
-#pragma unroll
-        for (int i = 0; i < kLnPerLane; ++i) {
-          const int k = t_ln % 64 + 64 * i;
-          if (k < d) xr[k] = static_cast<float>(static_cast<__bf16>(fmaf(x[i] * inv, to_float(ln_g[i]), to_float(ln_b[i]))));
-        }
-      }
-      __syncthreads();
-    }
-    if (a.Wv == nullptr) {
-      for (int i = tid; i < kMvRows * d; i += kMvThreads) out[i] = lp[i];
-    } else {
-      float acc[kMvRows][8];
-#pragma unroll
-      for (int r = 0; r < kMvRows; ++r)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[r][j] = 0.f;
-#pragma unroll
-      for (int it = 0; it < kMvMaxK; ++it) {
-#pragma unroll
-        for (int r = 0; r < kMvRows; ++r) {
-          const float x = lp[r * d + kc + it * nkc];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[r][j] = fmaf(x, static_cast<float>(wreg[it][j]), acc[r][j]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kMvRows; ++r)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) red[(kc * kMvRows + r) * kRedRow + 8 * cg + j + (cg >> 2)] = acc[r][j];
-      __syncthreads();
-      for (int i = tid; i < kMvRows * d; i += kMvThreads) {
-        float sum = 0.f;
-#pragma unroll 8
-        for (int c = 0; c < nkc; ++c) sum += red[(c * kMvRows + i / d) * kRedRow + i % d + (i % d) / 32];
-        out[i] = sum;
-      }
-    }
-    __syncthreads();
-    for (int i = tid; i < kMvRows * d; i += kMvThreads)
-      store_as(a.VA + values_slot(b, row0 + i / d, i % d, d, a.m.dh, a.m.m, true), out[i]);
   }
+  float out = 0.f;
+  if (a.Wv == nullptr) {
+    if (tid < D) out = lp[tid];
+  } else {
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+#pragma unroll
+    for (int it = 0; it < kMaxK; ++it) {
+      const float x = lp[kc + it * nkc];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] = fmaf(x, static_cast<float>(wreg[it][j]), acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) red[kc * kRedRow + 8 * cg + j + (cg >> 2)] = acc[j];
+    __syncthreads();
+    if (tid < D)
+#pragma unroll
+      for (int c = 0; c < nkc; ++c) out += red[c * kRedRow + tid + tid / 32];
+  }
+  if (tid < D) store_as(a.VA + values_slot(b, link, tid, D, a.m.dh, a.m.m, true), out);
+}
+
+// Sixteen link states per workgroup, for calls with many: the projection is on the matrix cores (the upper half of a 32-row
+// block repeats the lower), W_V goes straight to LDS and is turned on its way out, a wavefront's 32 columns in its own part.
+// A thread takes all chunks of its columns, kMergeGroups at a time, in the same order of sums as MergeRow.
+template <int PHI, int D>
+struct MergeTile {
+  static constexpr int kRows = 16, NK = D / 16, kWaves = D / 32, kPitch = D + 8, kTasks = kRows * (D / 4) / (2 * D);
+  static constexpr int kLds = kWaves * NK * 1024 + kRows * kPitch * 2;
+};
+template <int PHI, int D>
+__global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArgs a) {
+  using T = MergeTile<PHI, D>;
+  constexpr int NK = T::NK, kTasks = T::kTasks, kQuads = D / 4;
+  extern __shared__ unsigned char lds[];
+  bf16_t* const rows = reinterpret_cast<bf16_t*>(lds + T::kWaves * NK * 1024);
+  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.y, link0 = blockIdx.x * T::kRows, dh = a.m.dh;
+  const int64_t stride = static_cast<int64_t>(a.m.h) * a.m.m;  // (head, link) slots per chunk
+  unsigned char* const mine = lds + wave * NK * 1024;
+  int64_t first[kTasks];
+  int row[kTasks], quad[kTasks];
+  float2 ml[kTasks][kMergeGroups];
+  float4 ac[kTasks][kMergeGroups];
+#pragma unroll
+  for (int i = 0; i < kTasks; ++i) {
+    const int idx = threadIdx.x + i * 2 * D;
+    row[i] = idx / kQuads, quad[i] = idx % kQuads;
+    first[i] = (static_cast<int64_t>(b) * a.m.chunks * a.m.h + 4 * quad[i] / dh) * a.m.m + link0 + row[i];
+  }
+  auto ask_ml = [&](int i, int c0) {
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q) ml[i][q] = *reinterpret_cast<const float2*>(a.m.part_ml + (first[i] + min(c0 + q, a.m.chunks - 1) * stride) * 2);
+  };
+  auto ask = [&](int i, int c0) {
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q)
+      ac[i][q] = *reinterpret_cast<const float4*>(a.m.part_acc + (first[i] + min(c0 + q, a.m.chunks - 1) * stride) * dh + 4 * quad[i] % dh);
+  };
+#pragma unroll
+  for (int i = 0; i < kTasks; ++i) {
+    if (PHI == kPhiSoftmax) ask_ml(i, 0);
+    ask(i, 0);
+  }
+  if (a.Wv != nullptr) {
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+      load_to_lds(lds_offset_of(mine) + kk * 1024, (lane / 4) * (2 * D) + lane % 4 * 16, a.Wv + static_cast<int64_t>(16 * kk) * D + 32 * wave);
+  }
+  const int len = a.m.lens ? min(a.m.lens[b], a.m.N) : a.m.N;
+  const int used = (len + a.m.chunk_items - 1) / a.m.chunk_items;
+#pragma unroll
+  for (int i = 0; i < kTasks; ++i) {
+    float4 num[kMergeGroups], v = make_float4(0.f, 0.f, 0.f, 0.f);
+    float den[kMergeGroups], top = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q) num[q] = v, den[q] = 0.f;
+    for (int c0 = 0; c0 < used; c0 += kMergeGroups) {  // uniform
+      if (PHI == kPhiSoftmax && c0 % kMergeBatch == 0) {
+        float batch_top = top;
+        for (int c1 = c0; c1 < min(used, c0 + kMergeBatch); c1 += kMergeGroups) {
+          if (c1 > 0) ask_ml(i, c1);
+#pragma unroll
+          for (int q = 0; q < kMergeGroups; ++q) batch_top = fmaxf(batch_top, c1 + q < used ? ml[i][q].x : -INFINITY);
+        }
+        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
+#pragma unroll
+        for (int q = 0; q < kMergeGroups; ++q) num[q].x *= keep, num[q].y *= keep, num[q].z *= keep, num[q].w *= keep, den[q] *= keep;
+        top = batch_top;
+        if (used - c0 > kMergeGroups) ask_ml(i, c0);  // (the maxima of the batch's other chunks were read over them)
+      } else if (PHI == kPhiSoftmax) {
+        ask_ml(i, c0);
+      }
+      if (c0 > 0) ask(i, c0);
+#pragma unroll
+      for (int q = 0; q < kMergeGroups; ++q) {
+        if (c0 + q >= used) continue;  // uniform
+        if (PHI == kPhiSoftmax) {
+          const float w = __builtin_amdgcn_exp2f((ml[i][q].x - top) * kLog2e);
+          num[q].x = fmaf(w, ac[i][q].x, num[q].x), num[q].y = fmaf(w, ac[i][q].y, num[q].y);
+          num[q].z = fmaf(w, ac[i][q].z, num[q].z), num[q].w = fmaf(w, ac[i][q].w, num[q].w);
+          den[q] = fmaf(w, ml[i][q].y, den[q]);
+        } else {
+          num[q].x += ac[i][q].x, num[q].y += ac[i][q].y, num[q].z += ac[i][q].z, num[q].w += ac[i][q].w;
+        }
+      }
+    }
+    if (used > 0) v = MergeRow<PHI, D>::total(num, den, a.m.scale, len);
+    store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link0 + row[i]) * D + 4 * quad[i], v, rows + row[i] * T::kPitch + 4 * quad[i]);
+  }
+  wait_lds_loads<0>();  // W_V's part of this wave
+  __syncthreads();
+  if (a.ln_on) {  // uniform
+    for (int r = wave; r < T::kRows; r += T::kWaves) {
+      bf16_t* x = rows + r * T::kPitch;
+      normalise_state<D>(a.ln_gamma, a.ln_beta, a.ln_eps, [&](int k) { return to_float(x[k]); },
+                         [&](int k, __bf16 y) { x[k].bits = __builtin_bit_cast(uint16_t, y); });
+    }
+    __syncthreads();
+  }
+  bf16x8 values;  // lane (column 32 wave + n, g), slot t = link chain_k(g, t) of the sixteen
+  if (a.Wv == nullptr) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) values[t] = __builtin_bit_cast(__bf16, rows[chain_k(g, t) * T::kPitch + 32 * wave + n].bits);
+  } else {
+    bf16x8 x[NK], w[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      x[kk] = *reinterpret_cast<const bf16x8*>(rows + n % 16 * T::kPitch + 16 * kk + 8 * g);
+      w[kk] = column_fragment(mine + kk * 1024, 64, lane);
+    }
+    values = pack_half(project_block<NK>(x, w), 0);
+  }
+  const int64_t frag = ((static_cast<int64_t>(b) * a.m.h + 32 * wave / dh) * (a.m.m / 16) + link0 / 16) * (dh / 32) + 32 * wave % dh / 32;
+  reinterpret_cast<bf16x8*>(a.VA)[frag * 64 + out_rho(n) + 32 * g] = values;
 }
 
 // Forms of a workgroup, by the amount of work (plan()):
@@ -623,6 +769,22 @@ hipError_t dispatch_h(const HistArgs& a, int h, int links, int phi, int users, i
     case 8: if (DH == 32) return dispatch_m<32, 8>(a, links, phi, users, form, s);
   }
   return hipErrorInvalidValue;
+}
+
+// One link state per workgroup where all of them run at once (eight waves a compute unit: its registers).
+template <int PHI, int D>
+hipError_t launch_merge_values(const MergeValuesArgs& a, int users, hipStream_t s) {
+  using T = MergeTile<PHI, D>;
+  if (static_cast<int64_t>(users) * a.m.m <= static_cast<int64_t>(compute_units()) * (256 / D)) {
+    hipLaunchKernelGGL((merge_values_kernel<PHI, D>), dim3(a.m.m, users), dim3(2 * D), 0, s, a);
+    return hipGetLastError();
+  }
+  if (T::kLds > 64 * 1024) {
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_values_tile_kernel<PHI, D>), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
+    if (attr != hipSuccess) return attr;
+  }
+  hipLaunchKernelGGL((merge_values_tile_kernel<PHI, D>), dim3(a.m.m / T::kRows, users), dim3(2 * D), T::kLds, s, a);
+  return hipGetLastError();
 }
 
 struct Layout {
@@ -728,41 +890,36 @@ hipError_t links_over_history(const LinksOverHistory& q, void* workspace, hipStr
   if (e != hipSuccess) return e;
 
   MergeArgs g{part_acc, part_ml, q.lens, static_cast<bf16_t*>(q.LP), q.N, l.chunk_items, l.chunks, h, m, dh, fabsf(q.scale)};
+  const bool softmax = q.phi == kPhiSoftmax;
   if (q.values_image != nullptr) {
-    // With many users and the largest W_V a workgroup takes several row pairs in turn, as long as every compute
-    // unit still has a workgroup: each workgroup reads all of W_V (128 KiB at d = 256; at d = 128 the shorter
-    // chain per workgroup is worth more than the 32 KiB: measured).
-    int passes = 1;
-    while (d >= 256 && passes < 16 && static_cast<int64_t>(q.B) * (m / kMvRows) / (2 * passes) >= compute_units())
-      passes *= 2;
-    MergeValuesArgs mv{g, static_cast<const bf16_t*>(q.Wv_values), static_cast<bf16_t*>(q.values_image), passes,
+    MergeValuesArgs mv{g, static_cast<const bf16_t*>(q.Wv_values), static_cast<bf16_t*>(q.values_image),
                        static_cast<const bf16_t*>(q.values_norm.gamma), static_cast<const bf16_t*>(q.values_norm.beta),
                        q.values_norm.eps, q.values_norm.on ? 1 : 0};
-    const dim3 vgrid(m / (kMvRows * passes), q.B);  // (m / 2 is a multiple of 16)
-    const bool softmax = q.phi == kPhiSoftmax;
-#define LIME_MV_CASE(D)                                                                                      \
-  case D:                                                                                                    \
-    if (softmax)                                                                                             \
-      hipLaunchKernelGGL((merge_values_kernel<kPhiSoftmax, D>), vgrid, dim3(2 * D), 0, s, mv);               \
-    else                                                                                                     \
-      hipLaunchKernelGGL((merge_values_kernel<kPhiSilu, D>), vgrid, dim3(2 * D), 0, s, mv);                  \
-    break;
     switch (d) {  // every d the matrix-core kernels take
-      LIME_MV_CASE(32)
-      LIME_MV_CASE(64)
-      LIME_MV_CASE(128)
-      LIME_MV_CASE(256)
-      default:
-        return hipErrorInvalidValue;
+      case 32: return softmax ? launch_merge_values<kPhiSoftmax, 32>(mv, q.B, s) : launch_merge_values<kPhiSilu, 32>(mv, q.B, s);
+      case 64: return softmax ? launch_merge_values<kPhiSoftmax, 64>(mv, q.B, s) : launch_merge_values<kPhiSilu, 64>(mv, q.B, s);
+      case 128: return softmax ? launch_merge_values<kPhiSoftmax, 128>(mv, q.B, s) : launch_merge_values<kPhiSilu, 128>(mv, q.B, s);
+      case 256: return softmax ? launch_merge_values<kPhiSoftmax, 256>(mv, q.B, s) : launch_merge_values<kPhiSilu, 256>(mv, q.B, s);
     }
-#undef LIME_MV_CASE
-    return hipGetLastError();
+    return hipErrorInvalidValue;
   }
-  const dim3 mgrid((m * d / 4 + kMergeThreads - 1) / kMergeThreads, q.B);
-  if (q.phi == kPhiSoftmax)
-    hipLaunchKernelGGL(merge_kernel<kPhiSoftmax>, mgrid, dim3(kMergeThreads), 0, s, g);
-  else
-    hipLaunchKernelGGL(merge_kernel<kPhiSilu>, mgrid, dim3(kMergeThreads), 0, s, g);
+  const dim3 mgrid(m, q.B);
+#define LIME_MERGE_CASE(D)                                                                    \
+  case D:                                                                                     \
+    if (softmax)                                                                              \
+      hipLaunchKernelGGL((merge_kernel<kPhiSoftmax, D>), mgrid, dim3(2 * D), 0, s, g);        \
+    else                                                                                      \
+      hipLaunchKernelGGL((merge_kernel<kPhiSilu, D>), mgrid, dim3(2 * D), 0, s, g);           \
+    break;
+  switch (d) {
+    LIME_MERGE_CASE(32)
+    LIME_MERGE_CASE(64)
+    LIME_MERGE_CASE(128)
+    LIME_MERGE_CASE(256)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef LIME_MERGE_CASE
   return hipGetLastError();
 }
 

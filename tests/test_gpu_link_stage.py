@@ -1,5 +1,5 @@
 """The small kernels around the two attention stages, at the edges of their dispatch: the pack kernel's projections (one or
-four 32 x 32 blocks per workgroup)."""
+four 32 x 32 blocks per workgroup) and the merge of a history's chunks, with and without the value projection."""
 
 import pytest
 import torch
@@ -28,3 +28,37 @@ def test_projected_links_do_not_depend_on_the_batch(B, d, h, m):
     ref = (W[b].double().transpose(0, 1) @ V).transpose(0, 1).reshape(C, d)
     # V~ and the output are rounded to bf16 (2^-9 each), fp32 sums of m and d terms besides
     assert ((O[b].double() - ref).abs() <= 2 ** -7 * ref.abs().max()).all()
+
+
+# rows of link states up to and past what runs at once with a workgroup each; up to 8, 32 and more chunks of a history
+@pytest.mark.parametrize("B,N,d,h,m", [
+    (4, 300, 256, 4, 64), (5, 300, 256, 4, 64), (8, 129, 128, 4, 64), (9, 129, 128, 4, 64), (33, 70, 64, 2, 32), (65, 70, 32, 1, 32),
+    (3, 12000, 256, 4, 128), (5, 26240, 128, 2, 128), (1, 16384, 64, 1, 32), (1, 2048, 256, 8, 96)])
+@pytest.mark.parametrize("xor", [False, True])
+def test_merged_link_states(B, N, d, h, m, xor):
+    C = 40
+    E, T, L, Wq, Wk, Wv, Wv2 = _tensors(N + m, (B, N, d), (B, C, d), (m, d), (d, d), (d, d), (d, d), (d, d))
+    lens = torch.randint(1, N + 1, (B,), device="cuda", dtype=torch.int32, generator=torch.Generator(device="cuda").manual_seed(B))
+    lens[0] = N
+    if B > 1:
+        lens[1] = 0
+    s = (d // h) ** -0.5
+    LP, O = binding.lime_request(E, lens, L, Wq, Wk, Wv, T, L, Wq, Wk, Wv2, h, s, s, xor_attention=xor)
+    alone = binding.lime_xor_history(E, lens, L, Wq, Wk, Wv, h, s)[0] if xor else binding.lime_link_history(E, lens, L, Wq, Wk, Wv, h, s)
+    assert torch.equal(LP, alone)  # the merge kernel's sums, whichever kernel merges
+    O2 = binding.lime_score_candidates(T, L, LP, Wq, Wk, Wv2, h, s)
+    # V~ summed in another order: at most a bf16 step apart, weighted by probabilities, and the output's rounding
+    assert ((O.float() - O2.float()).abs() <= 2 ** -7 * (O2.float().abs().amax(dim=(1, 2), keepdim=True) + 1e-30)).all()
+    heads = lambda x: x.float().reshape(-1, h, d // h).transpose(0, 1).contiguous()  # noqa: E731
+    for b in sorted({0, 1, B - 1} & set(range(B))):
+        n = int(lens[b])
+        if n == 0:
+            assert not LP[b].any()
+            continue
+        Eb, q = E[b, :n].float(), heads(L.float() @ Wq.float())
+        k, v = heads(Eb @ Wk.float()), heads(Eb @ Wv.float())
+        logits = (q @ k.transpose(1, 2).contiguous()) * s
+        w = torch.nn.functional.silu(logits) / n if xor else torch.softmax(logits, -1)
+        ref = (w @ v).transpose(0, 1).reshape(m, d)
+        err = (LP[b].float() - ref).abs().max()
+        assert err <= 2e-2 and err <= 2e-2 * ref.abs().max(), (b, float(err))
