@@ -12,7 +12,9 @@
 //    after bias and ReLU, are as they stand the B operand of the next layer (chained k order, see mfma.hpp) and the
 //    hidden activations never leave registers; the last affine map to one logit is a dot product over the lane's
 //    registers plus one exchange with lane ^ 32.
+#include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "scoring.hpp"
 
@@ -297,28 +299,71 @@ hipError_t launch_dense(const DenseArgs& a, hipStream_t s) {
 //   layer i (d_in x d_out, d_out a multiple of 32): fragment (cb, kk), lane (n, g), slot t = W_i[16kk + k(g, t)][32cb + n],
 //   k(g, t) = 8g + t for the first layer (its B operand is read from memory in natural order) and chain_k(g, t) for the
 //   others (their B operand is the previous layer's accumulators).
+//   The layers' images follow each other without a gap: one stream of fragments.
 struct MlpArgs {
   const bf16_t* O;        // [rows][D]
   float* scores;          // [rows]
-  const bf16x8* img[3];   // hidden layers' weight images
+  const bf16x8* img;      // hidden layers' weight images
   const bf16_t* bias[3];  // hidden layers' biases
   const bf16_t* w_last;   // [HL] weights of the last affine map
   const bf16_t* b_last;   // [1], nullable
   int64_t rows;
 };
 
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_of(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Where fragment f of the stream belongs.
+template <int D, int H1, int H2, int H3>
+struct MlpStream {
+  static constexpr int kF1 = D / 16 * (H1 / 32), kF2 = H1 / 16 * (H2 / 32), kF3 = H2 / 16 * (H3 / 32);
+  static constexpr int kFrags = kF1 + kF2 + kF3;
+  static constexpr int HL = H3 > 0 ? H3 : (H2 > 0 ? H2 : H1);  // width of the last hidden layer
+  static constexpr int kLast = H3 > 0 ? 2 : H2 > 0 ? 1 : 0;    // its number
+  static constexpr int layer(int f) { return f < kF1 ? 0 : f < kF1 + kF2 ? 1 : 2; }
+  static constexpr int in_layer(int f) { return f < kF1 ? f : f < kF1 + kF2 ? f - kF1 : f - kF1 - kF2; }
+  static constexpr int k_steps(int f) { return (layer(f) == 0 ? D : layer(f) == 1 ? H1 : H2) / 16; }
+  static constexpr int block(int f) { return in_layer(f) / k_steps(f); }  // 32-column block of the layer's output
+  static constexpr int k(int f) { return in_layer(f) % k_steps(f); }
+  static constexpr int nth(int f) { return block(f) + (layer(f) > 0 ? H1 / 32 : 0) + (layer(f) > 1 ? H2 / 32 : 0); }  // of all blocks
+  static constexpr int bias_at(int f) { return (layer(f) == 0 ? 0 : layer(f) == 1 ? H1 : H1 + H2) + 32 * block(f); }
+  // The stream travels in chunks of kChunk fragments through kBuffers parts of LDS.
+  static constexpr int kChunk = 16, kChunks = (kFrags + kChunk - 1) / kChunk, kBuffers = 6;
+  static constexpr int kTable = H1 + H2 + H3 + HL;  // biases of the hidden layers, then the last map's weights
+  static constexpr int kLds = kBuffers * kChunk * 1024 + kTable * 4;
+};
+
+// A 32-column block of a layer's weight image is the A operand of all four wavefronts, a wavefront's 32 rows the B operand.
+// The fragments go from L2 straight to LDS, a quarter of a chunk per wavefront, kBuffers chunks ahead of their products
+// (a chunk's products are 0.3 us, a fetch from L2 several times that), and from LDS to registers one chunk ahead, a read
+// between every two products.  Products alternate between two accumulators (into one, each waits for the one before: 51
+// instead of 37 cycles), and a finished block is rounded and packed between the next block's products.
+// What bounds it: one wavefront per SIMD (registers), so matrix cores and everything else take turns; LDS reads, 4 KiB per
+// product of the four wavefronts, take as long as the product.  32 768 rows of 256 -> 512 -> 128 -> 64 -> 1: 16 us (13.4
+// GFLOP, 0.84 PFLOP/s), 22 us with a chunk's fragments all read before the first of its products, into one accumulator.
 template <int D, int H1, int H2, int H3>
 __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
-  constexpr int HL = H3 > 0 ? H3 : (H2 > 0 ? H2 : H1);  // width of the last hidden layer
-  constexpr int NB = H1 + H2 + H3 + HL;
-  // A 32-column block of a layer's weight image (K/16 fragments of 1 KiB) is the A operand of all four wavefronts.
-  // It travels in chunks of at most 16 fragments (16 KiB: a block of the widest layer is two of them): the waves fetch
-  // a chunk together, a quarter each, kAhead chunks before its products (one chunk's products are 0.2 us, a fetch
-  // from L2 several times that), park it in one of two LDS buffers and read it back from there.
-  constexpr int kChunkFrags = 16, kAhead = 3;
-  __shared__ bf16x8 stage[2 * kChunkFrags * 64];
-  __shared__ __attribute__((aligned(16))) float tab[NB];  // biases of the hidden layers, then the last map's weights
-  for (int i = threadIdx.x; i < NB; i += 256) {
+  using S = MlpStream<D, H1, H2, H3>;
+  constexpr int HL = S::HL, kChunk = S::kChunk, PER = kChunk / 4, kBuffers = S::kBuffers;
+  extern __shared__ bf16x8 stage[];
+  float* const tab = reinterpret_cast<float*>(stage + kBuffers * kChunk * 64);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, g = lane >> 5;
+  auto fetch = [&](int c) {  // this wavefront's quarter of a chunk (past the stream's end its last fragment)
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      load_to_lds(lds_offset_of(stage) + ((c % kBuffers) * kChunk + wave * PER + i) * 1024, lane * 16,
+                  a.img + min(c * kChunk + wave * PER + i, S::kFrags - 1) * 64);
+  };
+  const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * 32 + n;
+  // rows past the end are read from the last row and not stored (every wave stays for the barriers)
+  const bf16_t* xrow = a.O + (row < a.rows ? row : a.rows - 1) * D + 8 * g;
+  bf16x8 xb[D / 16];
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) xb[kk] = *reinterpret_cast<const bf16x8*>(xrow + 16 * kk);
+  for (int i = threadIdx.x; i < S::kTable; i += 256) {
     float v;
     if (i < H1) v = a.bias[0] ? to_float(a.bias[0][i]) : 0.f;
     else if (i < H1 + H2) v = a.bias[1] ? to_float(a.bias[1][i - H1]) : 0.f;
@@ -326,87 +371,53 @@ __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
     else v = to_float(a.w_last[i - H1 - H2 - H3]);
     tab[i] = v;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 31, g = lane >> 5;
-  const int64_t row = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * 32 + n;
-  // rows past the end are read from the last row and not stored (every wave stays for the barriers)
-  const bf16_t* xrow = a.O + (row < a.rows ? row : a.rows - 1) * D + 8 * g;
-  bf16x8 xb[D / 16];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) xb[kk] = *reinterpret_cast<const bf16x8*>(xrow + 16 * kk);
+  for (int c = 0; c < kBuffers && c < S::kChunks; ++c) fetch(c);
 
-  // one layer: Y^T = W^T X^T block by block; bias and ReLU on the accumulators; the rounded result is the next B operand
-  auto layer = [&](auto k_tag, auto out_tag, const bf16x8* img, const bf16x8* in, int bias_at, bf16x8* out, f32x16* keep) {
-    constexpr int K = decltype(k_tag)::value, OUT = decltype(out_tag)::value;
-    constexpr int KF = K / 16, NCB = OUT / 32;                    // fragments per block, blocks
-    constexpr int CH = (KF + kChunkFrags - 1) / kChunkFrags;      // chunks per block
-    constexpr int CF = KF / CH;                                   // fragments per chunk (KF is 2, 4, 8, 16 or 32)
-    static_assert(CF * CH == KF, "a block is a whole number of equal chunks");
-    constexpr int NCH = NCB * CH;                                 // chunks of the layer: chunk c holds fragments c CF ..
-    constexpr int PER = (CF + 3) / 4;                             // fragments a wave fetches per chunk
-    bf16x8 pre[kAhead][PER];
-    auto fetch = [&](int c) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (wave + 4 * i < CF) pre[c % kAhead][i] = img[(c * CF + wave + 4 * i) * 64 + lane];
-    };
-#pragma unroll
-    for (int c = 0; c < kAhead && c < NCH; ++c) fetch(c);
-    __syncthreads();  // the previous layer's last chunks have been read by everyone (and tab is written)
-    f32x16 acc;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int cb = c / CH, part = c % CH;
-      // (the buffer written here was last read two chunks ago, and every wave has passed a barrier since)
-      bf16x8* buf = stage + (c & 1) * kChunkFrags * 64;
-#pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (wave + 4 * i < CF) buf[(wave + 4 * i) * 64 + lane] = pre[c % kAhead][i];
-      __syncthreads();
-      if (c + kAhead < NCH) fetch(c + kAhead);
-      if (part == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {  // registers 4j .. 4j+3 are columns 32cb + 8j + 4g + 0..3
-          const float4 b4 = *reinterpret_cast<const float4*>(&tab[bias_at + 32 * cb + 8 * j + 4 * g]);
-          acc[4 * j] = b4.x, acc[4 * j + 1] = b4.y, acc[4 * j + 2] = b4.z, acc[4 * j + 3] = b4.w;
-        }
-      }
-      // every fragment of the chunk is asked for before the first product (one wave per SIMD: nobody else covers the
-      // LDS latency, and left alone the compiler reads two fragments ahead and waits for them)
-      bf16x8 af[CF];
-#pragma unroll
-      for (int kk = 0; kk < CF; ++kk) af[kk] = buf[kk * 64 + lane];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int kk = 0; kk < CF; ++kk) acc = mfma32(af[kk], in[part * CF + kk], acc);
-      __builtin_amdgcn_sched_barrier(0);
-      if (part == CH - 1) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = fmaxf(acc[i], 0.f);
-        if (keep != nullptr) {
-          keep[cb] = acc;
-        } else {
-          out[2 * cb] = pack_half(acc, 0);
-          out[2 * cb + 1] = pack_half(acc, 1);
-        }
-      }
-    }
-  };
+  bf16x8 h1[H1 / 16], h2[H2 > 0 ? H2 / 16 : 1], af[2][kChunk];
   f32x16 last[HL / 32];  // the last hidden layer stays in fp32: one accumulator block per 32 columns
-  bf16x8 h1[H1 / 16];
-  using std::integral_constant;
-  if constexpr (H2 == 0) {
-    layer(integral_constant<int, D>{}, integral_constant<int, H1>{}, a.img[0], xb, 0, nullptr, last);
-  } else {
-    layer(integral_constant<int, D>{}, integral_constant<int, H1>{}, a.img[0], xb, 0, h1, nullptr);
-    if constexpr (H3 == 0) {
-      layer(integral_constant<int, H1>{}, integral_constant<int, H2>{}, a.img[1], h1, H1, nullptr, last);
-    } else {
-      bf16x8 h2[H2 / 16];
-      layer(integral_constant<int, H1>{}, integral_constant<int, H2>{}, a.img[1], h1, H1, h2, nullptr);
-      layer(integral_constant<int, H2>{}, integral_constant<int, H3>{}, a.img[2], h2, H1 + H2, nullptr, last);
+  f32x16 acc[2][2];
+  auto publish = [&](auto c_tag) {  // chunk c has landed everywhere, and every wavefront has read chunk c - 1
+    constexpr int c = decltype(c_tag)::value, asked = std::min(c + kBuffers - (c > 0 ? 2 : 1), S::kChunks - 1);
+    wait_lds_loads<(asked - c) * PER>();  // all but the chunks behind it
+    lds_barrier();
+  };
+  publish(std::integral_constant<int, 0>{});
+#pragma unroll
+  for (int i = 0; i < kChunk; ++i) af[0][i] = stage[i * 64 + lane];
+  auto finish = [&](auto f_tag) {  // f: the block's last fragment
+    constexpr int f = decltype(f_tag)::value, layer = S::layer(f), block = S::block(f);
+    f32x16 done = acc[S::nth(f) & 1][0] + acc[S::nth(f) & 1][1];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) done[j] = fmaxf(done[j], 0.f);
+    if constexpr (layer == S::kLast) last[block] = done;
+    else if constexpr (layer == 0) h1[2 * block] = pack_half(done, 0), h1[2 * block + 1] = pack_half(done, 1);
+    else h2[2 * block] = pack_half(done, 0), h2[2 * block + 1] = pack_half(done, 1);
+  };
+  for_each_of(std::make_integer_sequence<int, S::kFrags>{}, [&](auto f_tag) {
+    constexpr int f = decltype(f_tag)::value, c = f / kChunk, i = f % kChunk, layer = S::layer(f), k = S::k(f);
+    f32x16(&sum)[2] = acc[S::nth(f) & 1];
+    if constexpr (i == 0 && c + 1 < S::kChunks) {
+      publish(std::integral_constant<int, c + 1>{});
+      if constexpr (c + kBuffers < S::kChunks) fetch(c + kBuffers);  // over chunk c, which is in registers
     }
-  }
+    if constexpr (k == 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // registers 4j .. 4j+3 are columns 32 block + 8j + 4g + 0..3
+        const float4 b4 = *reinterpret_cast<const float4*>(&tab[S::bias_at(f) + 8 * j + 4 * g]);
+        sum[0][4 * j] = b4.x, sum[0][4 * j + 1] = b4.y, sum[0][4 * j + 2] = b4.z, sum[0][4 * j + 3] = b4.w;
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) sum[1][j] = 0.f;
+    }
+    if constexpr (layer == 0) sum[k & 1] = mfma32(af[c & 1][i], xb[k], sum[k & 1]);
+    else if constexpr (layer == 1) sum[k & 1] = mfma32(af[c & 1][i], h1[k], sum[k & 1]);
+    else sum[k & 1] = mfma32(af[c & 1][i], h2[k], sum[k & 1]);
+    if constexpr (c + 1 < S::kChunks) af[(c + 1) & 1][i] = stage[((c + 1) % kBuffers * kChunk + i) * 64 + lane];
+    if constexpr (S::nth(f) > 0 && k == (S::k_steps(f) > 4 ? 3 : 1)) finish(std::integral_constant<int, f - k - 1>{});
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  finish(std::integral_constant<int, S::kFrags - 1>{});
   // the logit: a dot product over the last hidden layer (this lane holds the columns 32cb + 8j + 4g + r)
   float s = 0.f;
 #pragma unroll
@@ -448,8 +459,12 @@ __global__ __launch_bounds__(256) void mlp_pack_kernel(MlpPackArgs p) {
 
 template <int D, int H1, int H2, int H3>
 hipError_t launch_mlp(const MlpArgs& a, hipStream_t s) {
+  using S = MlpStream<D, H1, H2, H3>;
   const unsigned grid = static_cast<unsigned>((a.rows + 127) / 128);
-  hipLaunchKernelGGL((interaction_mlp_kernel<D, H1, H2, H3>), dim3(grid), dim3(256), 0, s, a);
+  auto kernel = interaction_mlp_kernel<D, H1, H2, H3>;
+  static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), S::kLds, s, a);
   return hipGetLastError();
 }
 
@@ -482,6 +497,7 @@ hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, 
   MlpPackArgs p{};
   MlpArgs a{};
   a.O = static_cast<const bf16_t*>(O), a.scores = scores, a.rows = rows;
+  a.img = static_cast<const bf16x8*>(images);
   char* at = static_cast<char*>(images);
   int din = d, blocks = 0;
   for (int i = 0; i < 3; ++i) {
@@ -489,7 +505,7 @@ hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, 
     if (i + 1 < n_maps) {
       p.W[i] = static_cast<const bf16_t*>(W[i]), p.img[i] = reinterpret_cast<bf16x8*>(at);
       p.din[i] = din, p.dout[i] = widths[i];
-      a.img[i] = reinterpret_cast<const bf16x8*>(at), a.bias[i] = static_cast<const bf16_t*>(b[i]);
+      a.bias[i] = static_cast<const bf16_t*>(b[i]);
       at += align_up(static_cast<size_t>(din) * widths[i] * 2);
       blocks += (din * widths[i] / 8 + 255) / 256;
       din = widths[i];

@@ -49,6 +49,7 @@ def test_contextualize_links(dtype, B, m, d, dc, dhid):
     ("bf16", 129, 128, [512, 128, 64, 1]),
     ("bf16", 257, 128, [96, 1]),
     ("bf16", 64, 32, [512, 256, 128, 1]),
+    ("bf16", 1, 64, [96, 1]),                 # one chunk and no next one to read ahead
     ("bf16", 31, 32, [96, 1]),
     ("bf16", 200, 64, [40, 8, 1]),            # widths the matrix-core kernel is not built for: fp32 arithmetic
     ("bf16", 100, 256, [1]),                  # no hidden layer: a dot product
