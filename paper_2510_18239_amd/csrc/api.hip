@@ -863,13 +863,13 @@ size_t mlp_workspace(int64_t rows, int32_t d, const int32_t* widths, int32_t n_m
 }
 
 int32_t mlp_impl(const char* fn, const void* O, const void* const* W, const void* const* b, const int32_t* widths, int32_t n_maps,
-                 float* scores, int64_t rows, int32_t d, int32_t dtype, void* workspace, size_t ws_bytes, void* stream) {
+                 float* scores, int64_t rows, int32_t d, int32_t dtype, void* workspace, size_t ws_bytes, void* stream, bool packed = false) {
   const size_t need = mlp_workspace(rows, d, widths, n_maps, dtype);
   if (!workspace || ws_bytes < need)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace ? ws_bytes : 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (mlp_on_mfma(O, W, b, widths, n_maps, d, dtype, workspace)) {
-    LIME_HIP(lime::interaction_mlp_mfma(O, rows, d, n_maps, widths, W, b, scores, workspace, s));
+    LIME_HIP(lime::interaction_mlp_mfma(O, rows, d, n_maps, widths, W, b, scores, workspace, packed, s));
     return LIME_OK;
   }
   int widest = 1;
@@ -890,6 +890,22 @@ int32_t mlp_impl(const char* fn, const void* O, const void* const* W, const void
   return LIME_OK;
 }
 
+// Eq. 2: hidden = ReLU([L | E^C_b] W1 + b1), L^C = hidden W2 + b2 (hidden in fp32)
+lime::Dense hidden_layer(const void* L, const void* EC, const void* W1, const void* b1, void* hidden, int32_t B, int32_t m, int32_t d,
+                         int32_t dc, int32_t dhid, int32_t dtype) {
+  lime::Dense h{};
+  h.X1 = L, h.x1_rows = m, h.X2 = EC, h.x2_rows_per = m, h.W = W1, h.b = b1, h.Y = hidden;
+  h.rows = static_cast<int64_t>(B) * m, h.d1 = d, h.d2 = dc, h.dout = dhid, h.relu = true, h.x_dtype = dtype, h.w_dtype = dtype, h.y_dtype = LIME_F32;
+  return h;
+}
+lime::Dense output_layer(const void* hidden, const void* W2, const void* b2, void* LC, int32_t B, int32_t m, int32_t d, int32_t dhid,
+                         int32_t dtype) {
+  lime::Dense o{};
+  o.X1 = hidden, o.W = W2, o.b = b2, o.Y = LC;
+  o.rows = static_cast<int64_t>(B) * m, o.d1 = dhid, o.dout = d, o.relu = false, o.x_dtype = LIME_F32, o.w_dtype = dtype, o.y_dtype = dtype;
+  return o;
+}
+
 int32_t contextualize_impl(const char* fn, const void* L, const void* EC, const void* W1, const void* b1, const void* W2,
                            const void* b2, void* LC, int32_t B, int32_t m, int32_t d, int32_t dc, int32_t dhid, int32_t dtype,
                            void* workspace, size_t ws_bytes, void* stream) {
@@ -897,15 +913,8 @@ int32_t contextualize_impl(const char* fn, const void* L, const void* EC, const 
   if (!workspace || ws_bytes < need)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace ? ws_bytes : 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t rows = static_cast<int64_t>(B) * m;
-  lime::Dense h{};  // hidden = ReLU([L | E^C_b] W1 + b1)
-  h.X1 = L, h.x1_rows = m, h.X2 = EC, h.x2_rows_per = m, h.W = W1, h.b = b1, h.Y = workspace;
-  h.rows = rows, h.d1 = d, h.d2 = dc, h.dout = dhid, h.relu = true, h.x_dtype = dtype, h.w_dtype = dtype, h.y_dtype = LIME_F32;
-  LIME_HIP(lime::dense_rows(h, s));
-  lime::Dense o{};  // L^C = hidden W2 + b2
-  o.X1 = workspace, o.W = W2, o.b = b2, o.Y = LC;
-  o.rows = rows, o.d1 = dhid, o.dout = d, o.relu = false, o.x_dtype = LIME_F32, o.w_dtype = dtype, o.y_dtype = dtype;
-  LIME_HIP(lime::dense_rows(o, s));
+  LIME_HIP(lime::dense_rows(hidden_layer(L, EC, W1, b1, workspace, B, m, d, dc, dhid, dtype), s));
+  LIME_HIP(lime::dense_rows(output_layer(workspace, W2, b2, LC, B, m, d, dhid, dtype), s));
   return LIME_OK;
 }
 
@@ -1021,12 +1030,17 @@ int32_t lime_scores(const lime_scoring_model* model, const void* E, const int32_
   void* lc = LC ? LC : ws + p.LC;
   void* lp = LP ? LP : ws + p.LP;
   void* o = O ? O : ws + p.O;
-  // Eq. 2
-  if (int32_t st = contextualize_impl(fn, M.L, EC, M.ctx_W1, M.ctx_b1, M.ctx_W2, M.ctx_b2, lc, B, m, d, M.dc, M.dhid, dtype,
-                                      ws + p.hid, p.hid_bytes, stream))
-    return st;
-  // Eq. 3 on normalised inputs (history rows past lens[b] are skipped: nothing reads them)
-  LIME_HIP(lime::layer_norm_rows(E, M.ln_hist_kv[0], M.ln_hist_kv[1], M.ln_eps, ws + p.En, static_cast<int64_t>(B) * N, d, lens, N, dtype, s));
+  // Eq. 2; Eq. 3's normalised history rows (those past lens[b] are skipped: nothing reads them); the network's weight images
+  const lime::Dense hidden = hidden_layer(M.L, EC, M.ctx_W1, M.ctx_b1, ws + p.hid, B, m, d, M.dc, M.dhid, dtype);
+  const lime::LayerNorm rows{E, M.ln_hist_kv[0], M.ln_hist_kv[1], M.ln_eps, ws + p.En, static_cast<int64_t>(B) * N, lens, N};
+  bool together = false;
+  if (mlp_on_mfma(o, M.mlp_W, M.mlp_b, M.mlp_width, M.n_mlp, d, dtype, ws + p.mlp))
+    LIME_HIP(lime::scores_prologue(hidden, rows, d, M.n_mlp, M.mlp_width, M.mlp_W, ws + p.mlp, &together, s));
+  if (!together) {
+    LIME_HIP(lime::dense_rows(hidden, s));
+    LIME_HIP(lime::layer_norm_rows(rows.X, rows.gamma, rows.beta, rows.eps, rows.Y, rows.rows, d, lens, N, dtype, s));
+  }
+  LIME_HIP(lime::dense_rows(output_layer(ws + p.hid, M.ctx_W2, M.ctx_b2, lc, B, m, d, M.dhid, dtype), s));
   const int64_t link_stride = static_cast<int64_t>(m) * d;
   const bool on_mfma = dtype == LIME_BF16 && lime::links_over_history_supported(d, M.h, m) && fits_tiles(B, N) && fits_tiles(B, C) &&
                        all_aligned16(E, T, M.L, lc, lp, o, M.hist_Wq, M.hist_Wk, M.hist_Wv, M.cand_Wq, M.cand_Wk, M.cand_Wv) &&
@@ -1064,7 +1078,7 @@ int32_t lime_scores(const lime_scoring_model* model, const void* E, const int32_
       return st;
   }
   // Section 3.3: the interaction network
-  return mlp_impl(fn, o, M.mlp_W, M.mlp_b, M.mlp_width, M.n_mlp, scores, static_cast<int64_t>(B) * C, d, dtype, ws + p.mlp, p.mlp_bytes, stream);
+  return mlp_impl(fn, o, M.mlp_W, M.mlp_b, M.mlp_width, M.n_mlp, scores, static_cast<int64_t>(B) * C, d, dtype, ws + p.mlp, p.mlp_bytes, stream, together);
 }
 
 size_t lime_workspace_bytes(int32_t op, int32_t B, int32_t N, int32_t C, int32_t d, int32_t h, int32_t m,

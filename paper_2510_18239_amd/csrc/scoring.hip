@@ -34,10 +34,10 @@ struct LnArgs {
 
 // bf16, d = 8 G with G a power of two up to 64: G lanes per row, one 16-byte piece each.
 template <int G>
-__global__ __launch_bounds__(256) void layer_norm_bf16_kernel(LnArgs a) {
+__device__ __forceinline__ void layer_norm_bf16(const LnArgs& a, int block) {
   constexpr int D = 8 * G;
   const int sub = threadIdx.x % G;
-  const int64_t row = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / G;
+  const int64_t row = (static_cast<int64_t>(block) * 256 + threadIdx.x) / G;
   const bool live = row < a.rows && (a.lens == nullptr || static_cast<int>(row % a.rows_per_user) < a.lens[row / a.rows_per_user]);
   bf16x8 v;
 #pragma unroll
@@ -63,6 +63,10 @@ __global__ __launch_bounds__(256) void layer_norm_bf16_kernel(LnArgs a) {
 #pragma unroll
   for (int t = 0; t < 8; ++t) y[t] = static_cast<__bf16>(fmaf(x[t] * inv, static_cast<float>(gv[t]), static_cast<float>(bv[t])));
   if (live) *reinterpret_cast<bf16x8*>(static_cast<bf16_t*>(a.Y) + row * D + 8 * sub) = y;
+}
+template <int G>
+__global__ __launch_bounds__(256) void layer_norm_bf16_kernel(LnArgs a) {
+  layer_norm_bf16<G>(a, blockIdx.x);
 }
 
 // any width and storage type: one wavefront per row
@@ -206,32 +210,36 @@ __global__ __launch_bounds__(256) void dense_few_rows_kernel(DenseArgs a) {
 // weights in batches of 16 loads with the index clamped and the out-of-range terms zeroed on the X side.
 constexpr int kVecKGroups = 32, kVecBatch = 16;
 template <typename TX, typename TY>
-__global__ __launch_bounds__(256) void dense_few_rows_vec_kernel(DenseArgs a) {
+__device__ __forceinline__ void dense_few_rows_vec(const DenseArgs& a, int row_block, int col_block) {
   __shared__ float Xs[kFewRows][kFewMaxDin];
   __shared__ float red[kVecKGroups][kFewRows * kDenseCols + 1];  // (odd pitch: the k-groups spread over the banks)
   const int tid = threadIdx.x, cg = tid % 8, kq = tid / 8;
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kFewRows;
-  const int c0 = blockIdx.y * kDenseCols + 8 * cg, din = a.d1 + a.d2;
+  const int64_t r0 = static_cast<int64_t>(row_block) * kFewRows;
+  const int c0 = col_block * kDenseCols + 8 * cg, din = a.d1 + a.d2;
   const int cc = min(c0, a.dout - 8);  // columns past d_out are computed on the last valid ones and not stored
   const bf16_t* W = static_cast<const bf16_t*>(a.W);
   bf16x8 w[kVecBatch];
 #pragma unroll
   for (int j = 0; j < kVecBatch; ++j)
     w[j] = *reinterpret_cast<const bf16x8*>(W + static_cast<int64_t>(min(kq + kVecKGroups * j, din - 1)) * a.dout + cc);
-  for (int base = 0; base < kFewRows * din; base += 4 * 256) {
-    TX v[4];
+  {
+    // a wavefront per row, 64 columns at a time
+    const int r = tid / 64;
+    const int64_t row = min(r0 + r, a.rows - 1);
+    const TX* x1 = static_cast<const TX*>(a.X1) + (row % a.x1_rows) * a.d1;
+    const TX* x2 = a.d2 > 0 ? static_cast<const TX*>(a.X2) + (row / a.x2_rows_per) * a.d2 : x1;
+    for (int base = 0; base < din; base += 8 * 64) {
+      TX v[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = min(base + j * 256 + tid, kFewRows * din - 1), k = i % din;
-      const int64_t row = min(r0 + i / din, a.rows - 1);
-      const TX* src = k < a.d1 ? static_cast<const TX*>(a.X1) + (row % a.x1_rows) * a.d1 + k
-                               : static_cast<const TX*>(a.X2) + (row / a.x2_rows_per) * a.d2 + (k - a.d1);
-      v[j] = *src;
-    }
+      for (int j = 0; j < 8; ++j) {
+        const int k = min(base + 64 * j + tid % 64, din - 1);
+        v[j] = *(k < a.d1 ? x1 + k : x2 + (k - a.d1));
+      }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = base + j * 256 + tid;
-      if (i < kFewRows * din) Xs[i / din][i % din] = r0 + i / din < a.rows ? to_float(v[j]) : 0.f;
+      for (int j = 0; j < 8; ++j) {
+        const int k = base + 64 * j + tid % 64;
+        if (k < din) Xs[r][k] = r0 + r < a.rows ? to_float(v[j]) : 0.f;
+      }
     }
   }
   __syncthreads();
@@ -264,7 +272,7 @@ __global__ __launch_bounds__(256) void dense_few_rows_vec_kernel(DenseArgs a) {
     for (int t = 0; t < 8; ++t) red[kq][r * kDenseCols + 8 * cg + t] = acc[r][t];
   __syncthreads();
   // thread (r, col) finishes one output
-  const int r = tid / kDenseCols, col = blockIdx.y * kDenseCols + tid % kDenseCols;
+  const int r = tid / kDenseCols, col = col_block * kDenseCols + tid % kDenseCols;
   if (col >= a.dout || r0 + r >= a.rows) return;
   float y = 0.f;
 #pragma unroll 8
@@ -274,19 +282,27 @@ __global__ __launch_bounds__(256) void dense_few_rows_vec_kernel(DenseArgs a) {
   store_as(static_cast<TY*>(a.Y) + (r0 + r) * a.dout + col, y);
 }
 
+template <typename TX, typename TY>
+__global__ __launch_bounds__(256) void dense_few_rows_vec_kernel(DenseArgs a) {
+  dense_few_rows_vec<TX, TY>(a, blockIdx.x, blockIdx.y);
+}
+bool few_rows_vec(const DenseArgs& a) {
+  return a.rows <= 2048 && a.d1 + a.d2 <= kFewMaxDin && a.dout >= 8 && a.dout % 8 == 0 && (reinterpret_cast<uintptr_t>(a.W) & 15u) == 0;
+}
+dim3 few_rows_grid(const DenseArgs& a) {
+  return dim3(static_cast<unsigned>((a.rows + kFewRows - 1) / kFewRows), (a.dout + kDenseCols - 1) / kDenseCols);
+}
+
 template <typename TX, typename TW, typename TY>
 hipError_t launch_dense(const DenseArgs& a, hipStream_t s) {
   if constexpr (std::is_same<TW, bf16_t>::value) {
-    if (a.rows <= 2048 && a.d1 + a.d2 <= kFewMaxDin && a.dout >= 8 && a.dout % 8 == 0 &&
-        (reinterpret_cast<uintptr_t>(a.W) & 15u) == 0) {
-      const dim3 few(static_cast<unsigned>((a.rows + kFewRows - 1) / kFewRows), (a.dout + kDenseCols - 1) / kDenseCols);
-      hipLaunchKernelGGL((dense_few_rows_vec_kernel<TX, TY>), few, dim3(256), 0, s, a);
+    if (few_rows_vec(a)) {
+      hipLaunchKernelGGL((dense_few_rows_vec_kernel<TX, TY>), few_rows_grid(a), dim3(256), 0, s, a);
       return hipGetLastError();
     }
   }
   if (a.rows <= 2048 && a.d1 + a.d2 <= kFewMaxDin) {
-    const dim3 few(static_cast<unsigned>((a.rows + kFewRows - 1) / kFewRows), (a.dout + kDenseCols - 1) / kDenseCols);
-    hipLaunchKernelGGL((dense_few_rows_kernel<TX, TW, TY>), few, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((dense_few_rows_kernel<TX, TW, TY>), few_rows_grid(a), dim3(256), 0, s, a);
     return hipGetLastError();
   }
   const dim3 grid(static_cast<unsigned>((a.rows + kDenseRows - 1) / kDenseRows), (a.dout + kDenseCols - 1) / kDenseCols);
@@ -439,8 +455,7 @@ struct MlpPackArgs {
   int first_block[4];
 };
 
-__global__ __launch_bounds__(256) void mlp_pack_kernel(MlpPackArgs p) {
-  int blk = blockIdx.x;
+__device__ __forceinline__ void mlp_pack(const MlpPackArgs& p, int blk) {
   const int layer = blk >= p.first_block[2] ? 2 : (blk >= p.first_block[1] ? 1 : 0);
   blk -= p.first_block[layer];
   const int din = p.din[layer], dout = p.dout[layer];
@@ -455,6 +470,31 @@ __global__ __launch_bounds__(256) void mlp_pack_kernel(MlpPackArgs p) {
     v[t] = __builtin_bit_cast(__bf16, p.W[layer][static_cast<int64_t>(k) * dout + 32 * cb + n].bits);
   }
   p.img[layer][idx] = v;
+}
+__global__ __launch_bounds__(256) void mlp_pack_kernel(MlpPackArgs p) { mlp_pack(p, blockIdx.x); }
+
+// What a scoring call can do before anything else, in one launch: the hidden layer of Eq. 2 (which the chain of kernels
+// waits for: its workgroups come first), the network's weight images and the normalisation of the history rows.  As three
+// launches the latter two cost 3.1 and 4.9 us each.
+struct PrologueArgs {
+  DenseArgs hidden;
+  MlpPackArgs images;
+  LnArgs rows;
+  int dense_blocks, dense_cols, image_blocks;
+};
+template <int G>
+__global__ __launch_bounds__(256) void scores_prologue_kernel(PrologueArgs a) {
+  int blk = blockIdx.x;
+  if (blk < a.dense_blocks) {
+    dense_few_rows_vec<bf16_t, float>(a.hidden, blk / a.dense_cols, blk % a.dense_cols);
+    return;
+  }
+  blk -= a.dense_blocks;
+  if (blk < a.image_blocks) {
+    mlp_pack(a.images, blk);
+    return;
+  }
+  layer_norm_bf16<G>(a.rows, blk - a.image_blocks);
 }
 
 template <int D, int H1, int H2, int H3>
@@ -492,12 +532,10 @@ size_t interaction_mlp_image_bytes(int d, int n_maps, const int32_t* widths) {
   return total;
 }
 
-hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, const int32_t* widths, const void* const* W,
-                                const void* const* b, float* scores, void* images, hipStream_t s) {
-  MlpPackArgs p{};
-  MlpArgs a{};
-  a.O = static_cast<const bf16_t*>(O), a.scores = scores, a.rows = rows;
-  a.img = static_cast<const bf16x8*>(images);
+namespace {
+
+// the images' places (one after the other) and the pack kernel's arguments; returns its workgroups
+int plan_images(int d, int n_maps, const int32_t* widths, const void* const* W, void* images, MlpPackArgs& p) {
   char* at = static_cast<char*>(images);
   int din = d, blocks = 0;
   for (int i = 0; i < 3; ++i) {
@@ -505,7 +543,6 @@ hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, 
     if (i + 1 < n_maps) {
       p.W[i] = static_cast<const bf16_t*>(W[i]), p.img[i] = reinterpret_cast<bf16x8*>(at);
       p.din[i] = din, p.dout[i] = widths[i];
-      a.bias[i] = static_cast<const bf16_t*>(b[i]);
       at += align_up(static_cast<size_t>(din) * widths[i] * 2);
       blocks += (din * widths[i] / 8 + 255) / 256;
       din = widths[i];
@@ -514,10 +551,38 @@ hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, 
     }
   }
   p.first_block[0] = 0;
+  return blocks;
+}
+
+DenseArgs dense_args(const Dense& q) {
+  return {q.X1, q.X2, q.W, q.b, q.Y, q.rows, q.x1_rows > 0 ? q.x1_rows : q.rows, q.x2_rows_per > 0 ? q.x2_rows_per : 1,
+          q.d1, q.X2 != nullptr ? q.d2 : 0, q.dout, q.relu ? 1 : 0};
+}
+
+// lanes per row of the 16-byte normalisation kernel, 0 where it does not apply
+int layer_norm_lanes(const LnArgs& a, int dtype) {
+  const bool aligned = ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.Y) | reinterpret_cast<uintptr_t>(a.gamma) |
+                         reinterpret_cast<uintptr_t>(a.beta)) & 15u) == 0;
+  const int G = a.d / 8;
+  return dtype == 1 && aligned && a.d % 8 == 0 && (G == 4 || G == 8 || G == 16 || G == 32 || G == 64) ? G : 0;
+}
+
+}  // namespace
+
+hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, const int32_t* widths, const void* const* W,
+                                const void* const* b, float* scores, void* images, bool packed, hipStream_t s) {
+  MlpArgs a{};
+  a.O = static_cast<const bf16_t*>(O), a.scores = scores, a.rows = rows;
+  a.img = static_cast<const bf16x8*>(images);
+  for (int i = 0; i + 1 < n_maps; ++i) a.bias[i] = static_cast<const bf16_t*>(b[i]);
   a.w_last = static_cast<const bf16_t*>(W[n_maps - 1]), a.b_last = static_cast<const bf16_t*>(b[n_maps - 1]);
-  hipLaunchKernelGGL(mlp_pack_kernel, dim3(blocks), dim3(256), 0, s, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!packed) {
+    MlpPackArgs p{};
+    const int blocks = plan_images(d, n_maps, widths, W, images, p);
+    hipLaunchKernelGGL(mlp_pack_kernel, dim3(blocks), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const int h1 = widths[0], h2 = n_maps > 2 ? widths[1] : 0, h3 = n_maps > 3 ? widths[2] : 0;
 #define LIME_MLP_LAUNCH(D_, A_, B_, C_) if (d == D_ && h1 == A_ && h2 == B_ && h3 == C_) return launch_mlp<D_, A_, B_, C_>(a, s);
   LIME_MLP_SHAPES(LIME_MLP_LAUNCH)
@@ -525,14 +590,37 @@ hipError_t interaction_mlp_mfma(const void* O, int64_t rows, int d, int n_maps, 
   return hipErrorInvalidValue;
 }
 
+hipError_t scores_prologue(const Dense& hidden, const LayerNorm& rows, int d, int n_maps, const int32_t* widths, const void* const* W,
+                           void* images, bool* done, hipStream_t s) {
+  PrologueArgs a{};
+  a.hidden = dense_args(hidden);
+  a.rows = LnArgs{rows.X, rows.Y, rows.gamma, rows.beta, rows.lens, rows.rows, rows.rows_per_user, d, rows.eps};
+  const int G = layer_norm_lanes(a.rows, 1);
+  *done = few_rows_vec(a.hidden) && G != 0;
+  if (!*done) return hipSuccess;
+  const dim3 dense = few_rows_grid(a.hidden);
+  a.dense_blocks = static_cast<int>(dense.x * dense.y), a.dense_cols = static_cast<int>(dense.y);
+  a.image_blocks = plan_images(d, n_maps, widths, W, images, a.images);
+  const int64_t blocks = a.dense_blocks + a.image_blocks + (rows.rows * G + 255) / 256;
+  if (blocks > 0x7fffffff) {
+    *done = false;
+    return hipSuccess;
+  }
+  const dim3 grid(static_cast<unsigned>(blocks));
+  switch (G) {
+#define LIME_PROLOGUE_CASE(G_) case G_: hipLaunchKernelGGL(scores_prologue_kernel<G_>, grid, dim3(256), 0, s, a); break;
+    LIME_PROLOGUE_CASE(4) LIME_PROLOGUE_CASE(8) LIME_PROLOGUE_CASE(16) LIME_PROLOGUE_CASE(32)
+#undef LIME_PROLOGUE_CASE
+    default: *done = false;
+  }
+  return hipGetLastError();
+}
+
 hipError_t layer_norm_rows(const void* X, const void* gamma, const void* beta, float eps, void* Y, int64_t rows, int d,
                            const int32_t* lens, int rows_per_user, int dtype, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   LnArgs a{X, Y, gamma, beta, lens, rows, rows_per_user > 0 ? rows_per_user : 1, d, eps};
-  const bool aligned = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(gamma) |
-                         reinterpret_cast<uintptr_t>(beta)) & 15u) == 0;
-  if (dtype == 1 && aligned && d % 8 == 0) {
-    const int G = d / 8;
+  if (const int G = layer_norm_lanes(a, dtype)) {
     const unsigned grid = static_cast<unsigned>((rows * G + 255) / 256);
     switch (G) {
 #define LIME_LN_CASE(G_) case G_: hipLaunchKernelGGL(layer_norm_bf16_kernel<G_>, dim3(grid), dim3(256), 0, s, a); return hipGetLastError();
@@ -551,8 +639,7 @@ hipError_t layer_norm_rows(const void* X, const void* gamma, const void* beta, f
 
 hipError_t dense_rows(const Dense& q, hipStream_t s) {
   if (q.rows <= 0) return hipSuccess;
-  DenseArgs a{q.X1, q.X2, q.W, q.b, q.Y, q.rows, q.x1_rows > 0 ? q.x1_rows : q.rows, q.x2_rows_per > 0 ? q.x2_rows_per : 1,
-              q.d1, q.X2 != nullptr ? q.d2 : 0, q.dout, q.relu ? 1 : 0};
+  const DenseArgs a = dense_args(q);
   // (x, w, y) storage: 0 = fp32, 1 = bf16
   const int key = q.x_dtype * 4 + q.w_dtype * 2 + q.y_dtype;
   switch (key) {
