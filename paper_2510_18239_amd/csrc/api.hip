@@ -170,12 +170,13 @@ lime::QueriesOverLinks os_query(const void* E, const int32_t* lens, const void* 
   return q;
 }
 
-// `extra`: weight images that the call's pack launch writes as well (matrix-core path only).
+// `extra`: weight images that the call's pack launch writes as well (matrix-core path only).  os_packed_only: O[S]'s operands
+// are packed behind the history stage's workspace, and O[S] itself is the caller's business.
 int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens, const void* LC,
                      int64_t lc_user_stride, const void* Wq, const void* Wk, const void* Wv, void* LP, void* OS,
                      int32_t B, int32_t N, int32_t d, int32_t h, int32_t m, float scale, int32_t dtype,
                      void* workspace, size_t ws_bytes, void* stream, const lime::PackWeight* extra = nullptr,
-                     int n_extra = 0, bool walk = false) {
+                     int n_extra = 0, bool walk = false, bool os_packed_only = false) {
   if (int32_t st = check_common(fn, B, d, h, dtype)) return st;
   if (N <= 0 || m <= 0) return fail(LIME_INVALID_ARG, "%s: N and m must be positive (N=%d m=%d)", fn, N, m);
   if (!E || !LC || !Wq || !Wk || !Wv || !LP) return fail(LIME_INVALID_ARG, "%s: a required pointer is NULL", fn);
@@ -233,7 +234,7 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     }
     return LIME_OK;
   }
-  if (os_on_mfma) {
+  if (os_on_mfma && !os_packed_only) {
     lime::QueriesOverLinks q = os_query(E, lens, LC, link_stride, Wq, Wk, Wv, OS, B, N, d, h, m, scale);
     q.packed = true;
     LIME_HIP(lime::queries_over_links(q, static_cast<char*>(workspace) + p.bytes, s));
@@ -541,7 +542,7 @@ int32_t lime_request_prepared(const void* E, const int32_t* lens, const void* T,
   q.phi = xor_attention ? lime::kPhiSilu : lime::kPhiSoftmax;
   // three kernels: the merge step of the history side also projects the finished link states and writes the value
   // image where the candidate-side kernel of this request expects it
-  q.Wv_values = Wv, q.values_image = lime::queries_over_links_values(c, cand_ws);
+  q.Wv_values = Wv, q.values_image = lime::queries_over_links_operands(c, cand_ws).values;
   c.packed = true;
   LIME_HIP(lime::links_over_history(q, workspace, s));
   LIME_HIP(lime::queries_over_links(c, cand_ws, s));
@@ -661,7 +662,7 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   lime::queries_over_links_jobs(c, cand_ws, jobs, /*values=*/false);
   LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
   q.packed = c.packed = true;
-  q.Wv_values = Wv_cand, q.values_image = lime::queries_over_links_values(c, cand_ws);
+  q.Wv_values = Wv_cand, q.values_image = lime::queries_over_links_operands(c, cand_ws).values;
   LIME_HIP(lime::links_over_history(q, workspace, s));
   LIME_HIP(lime::queries_over_links(c, cand_ws, s));
   return LIME_OK;
@@ -770,8 +771,10 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
     // (the layer's pack launch also writes the images of the gated block's two weights)
     const void *Wu_j = Wu_all + j * weight_bytes, *Wo_j = Wo_all + j * weight_bytes;
     lime::PackWeight images[2] = {{Wu_j, p.Wu_image}, {Wo_j, p.Wo_image}};
+    // On the matrix cores O[S] and the gated block of the history rows are one kernel where its operands fit the registers.
+    const bool rows_in_one = on_mfma && lime::xor_rows_supported(d, h, m);
     if (int32_t st = history_impl(fn, lime::kPhiSilu, Ej, lens, Lj, lj_stride, Wq, Wk, Wv, p.OT, last ? nullptr : p.OS, B, N,
-                                  d, h, m, scale, dtype, p.hist_ws, p.hist_bytes, stream, images, on_mfma ? 2 : 0))
+                                  d, h, m, scale, dtype, p.hist_ws, p.hist_bytes, stream, images, on_mfma ? 2 : 0, false, rows_in_one))
       return st;
     if (!on_mfma) {
       lime::GenericGatedBlock links{};
@@ -796,6 +799,15 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
     LIME_HIP(lime::gated_block(links, s));
     if (last) break;
     // history rows: the same block with O[S]; rows at or past lens[b] stay zero
+    if (rows_in_one) {
+      const bool per_user = lj_stride != 0;
+      const lime::QueriesOverLinksOperands o = lime::queries_over_links_operands(
+          os_query(Ej, lens, Lj, lj_stride, Wq, Wk, Wv, p.OS, B, N, d, h, m, scale),
+          static_cast<char*>(p.hist_ws) + lime::links_over_history_workspace(B, N, d, h, m, per_user));
+      lime::XorRows rows{Ej, lens, o.queries, p.Wu_image, p.Wo_image, o.keys, o.values, per_user, p.Xs[(j + 1) & 1], B, N, d, h, m, scale};
+      LIME_HIP(lime::xor_rows(rows, s));
+      continue;
+    }
     lime::GatedBlock rows{};
     rows.X = Ej, rows.x_user_stride = hist_stride, rows.lens = lens, rows.Wu_image = p.Wu_image, rows.Wo_image = p.Wo_image;
     rows.A = p.OS, rows.Y = p.Xs[(j + 1) & 1], rows.B = B, rows.rows = N, rows.d = d, rows.h = h;

@@ -304,8 +304,11 @@ struct QueriesOverLinks {
   RowNorm x_norm;       // applied to the query rows as their tiles are loaded (softmax, O output, per-call operands)
   RowNorm k_norm, v_norm;  // applied to the key / value rows by the pack step
 };
-// where the value image of a call lives in its workspace
-void* queries_over_links_values(const QueriesOverLinks& a, void* workspace);
+// where the images of a call live in its workspace (without `prepared`)
+struct QueriesOverLinksOperands {
+  void *queries, *keys, *values;
+};
+QueriesOverLinksOperands queries_over_links_operands(const QueriesOverLinks& a, void* workspace);
 // The pack jobs of a call, appended to `jobs` instead of being launched by queries_over_links (not with `prepared`);
 // without `values` when someone else writes the value image (the history side's merge step).
 void queries_over_links_jobs(const QueriesOverLinks& a, void* workspace, PackJobs& jobs, bool values = true);
@@ -357,6 +360,21 @@ struct GatedBlock {
   int B, rows, d, h;
 };
 hipError_t gated_block(const GatedBlock& q, hipStream_t s);
+
+// The history rows' part of an XOR layer in one kernel: O[S] over the m links and the gated block, Y = X + (O[S] * SiLU(X Wu)) Wo
+// (rows >= lens[b] are zeros).
+struct XorRows {
+  const void* X;        // [B][N][d] bf16
+  const int32_t* lens;  // nullable
+  const void *Wq_image, *Wu_image, *Wo_image;  // weight images
+  const void *keys, *values;                   // the links' kPackKeys and kPackValues images
+  bool per_user;                               // of these two
+  void* Y;              // [B][N][d]
+  int B, N, d, h, m;
+  float scale;
+};
+bool xor_rows_supported(int d, int h, int m);
+hipError_t xor_rows(const XorRows& q, hipStream_t s);
 
 // ----------------------------------------------------------------------------- history-side kernel family
 // Fused "few queries x many keys" attention: the m links attend over one user's N history rows;

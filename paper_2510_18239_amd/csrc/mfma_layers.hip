@@ -1,5 +1,4 @@
-// The gated block of the stacked XOR layers (Eq. 8): rows streamed past two stationary weight slices, the two
-// products chained through LDS.
+// The stacked XOR layers (Eq. 8): rows streamed past stationary weight slices, the products chained through LDS.
 #include "mfma.hpp"
 
 namespace lime {
@@ -163,7 +162,251 @@ hipError_t launch_gated(const GatedArgs& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+
+// The history rows' part of an XOR layer in one pass (Eq. 7's O[S], then Eq. 8's gated block):
+//   O[S] = SiLU(scale X W_Q K~^T) V~ / m per head,  Y = X + (O[S] * SiLU(X W_U)) W_O,
+// each rounded where the kernels it takes the place of (queries_over_links_kernel, gated_block_kernel) store it, so with
+// their bits.  One wave per head, all five stationary operands in registers; a tile of 32 rows goes through LDS for the
+// first two products (which share its fragments), the gated rows and the output rows go through LDS once each.
+// Two barriers a tile: the one that publishes a tile's rows also publishes the last tile's output rows, which the waves
+// store during the next tile's products.
+// What bounds it: memory traffic (one read and one write of the rows) and the vector ALUs (48 SiLUs per row and head at
+// d/h = 32, m = 64) about equally.  B=8 N=16384 d=128 m=64, 67 MB: 17.5 + 21.3 us as two kernels, which also write and read
+// O[S] and read the rows twice.
+struct RowsArgs {
+  const bf16_t* X;                 // [B][rows][d]
+  const int32_t* lens;             // nullable; rows >= lens[b] count as zeros and are written as zeros
+  const bf16x8 *Wq, *Wu, *Wo;      // weight images
+  const bf16x8 *KA, *VA;           // key and value images of the links
+  int64_t ka_user_frags, va_user_frags;
+  bf16_t* Y;                       // [B][rows][d]
+  int rows, tiles_per_user, total_tiles;
+  float scale, inv_norm;           // scale >= 0 (a negative one is folded into the keys)
+};
+
+template <int DH, int M, int H>
+__global__ __launch_bounds__(64 * H, DH * H == 128 && DH == 32 ? 2 : 1) void xor_rows_kernel(RowsArgs a) {
+  constexpr int D = DH * H, K1 = D / 16, MB = DH / 32, K2 = DH / 16, LB = M / 32, K3 = M / 16;
+  constexpr int PITCH = 2 * D + 16;  // bytes; the padding keeps the fragment reads free of bank conflicts
+  constexpr int CPR = D / 8, LW = DH / 16;
+  __shared__ __attribute__((aligned(16))) unsigned char xs[2][32 * PITCH], zs[32 * PITCH], ys[32 * PITCH];
+  const int lane = threadIdx.x & 63, head = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, g = lane >> 5;
+  const int per_wg = (a.total_tiles + gridDim.x - 1) / gridDim.x;  // a contiguous run of tiles: few changes of user
+  const int first = blockIdx.x * per_wg, last = min(first + per_wg, a.total_tiles);
+  if (first >= last) return;  // uniform
+
+  int lds_at[LW], row_of[LW];
+  int64_t at[LW];
+#pragma unroll
+  for (int j = 0; j < LW; ++j) {
+    const int q = (head * LW + j) * 64 + lane;
+    row_of[j] = q / CPR, lds_at[j] = q / CPR * PITCH + q % CPR * 16, at[j] = static_cast<int64_t>(q) * 8;
+  }
+  bf16x8 rx[LW];
+  auto request = [&](int tile) {  // rows at or past the user's length arrive as zeros
+    const int b = tile / a.tiles_per_user, r0 = (tile - b * a.tiles_per_user) * 32;
+    const int len = a.lens ? min(a.lens[b], a.rows) : a.rows;
+    const bf16_t* base = a.X + (static_cast<int64_t>(b) * a.rows + r0) * D;
+    if (r0 + 32 <= len) {  // uniform
+#pragma unroll
+      for (int j = 0; j < LW; ++j) rx[j] = *reinterpret_cast<const bf16x8*>(base + at[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < LW; ++j) {
+        bf16x8 v;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(0.f);
+        if (r0 + row_of[j] < len) v = *reinterpret_cast<const bf16x8*>(base + at[j]);
+        rx[j] = v;
+      }
+    }
+  };
+  request(first);
+  bf16x8 wq[K1][MB], wu[K1][MB], wo[K1][MB], ka[K2][LB], va[K3][MB];
+#pragma unroll
+  for (int kk = 0; kk < K1; ++kk)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int f = ((head * K1 + kk) * MB + mb) * 64 + lane;
+      // (W_U and W_O with their columns in the order of the value image, so that a lane gets 16 consecutive columns of a
+      // block: out_col in place of the lane)
+      const int fo = ((head * K1 + kk) * MB + mb) * 64 + out_col(n) + 32 * g;
+      wq[kk][mb] = a.Wq[f], wu[kk][mb] = a.Wu[fo], wo[kk][mb] = a.Wo[fo];
+    }
+  auto load_user = [&](int b) {
+    const bf16x8* k = a.KA + b * a.ka_user_frags + static_cast<int64_t>(head) * K2 * LB * 64 + lane;
+    const bf16x8* v = a.VA + b * a.va_user_frags + static_cast<int64_t>(head) * K3 * MB * 64 + lane;
+#pragma unroll
+    for (int kk = 0; kk < K2; ++kk)
+#pragma unroll
+      for (int lb = 0; lb < LB; ++lb) ka[kk][lb] = k[(kk * LB + lb) * 64];
+#pragma unroll
+    for (int kk = 0; kk < K3; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) va[kk][mb] = v[(kk * MB + mb) * 64];
+  };
+  int cur_user = first / a.tiles_per_user;
+  load_user(cur_user);
+
+  auto store_rows = [&](int tile) {
+    const int b = tile / a.tiles_per_user, r0 = (tile - b * a.tiles_per_user) * 32;
+    bf16_t* base = a.Y + (static_cast<int64_t>(b) * a.rows + r0) * D;
+    bf16x8 v[LW];
+#pragma unroll
+    for (int j = 0; j < LW; ++j) v[j] = *reinterpret_cast<const bf16x8*>(ys + lds_at[j]);
+    if (r0 + 32 <= a.rows) {  // uniform
+#pragma unroll
+      for (int j = 0; j < LW; ++j) store_through(base, 32 * 2 * D, static_cast<int>(at[j]) * 2, v[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < LW; ++j)
+        if (r0 + row_of[j] < a.rows) *reinterpret_cast<bf16x8*>(base + at[j]) = v[j];
+    }
+  };
+  const float c = a.scale * kLog2e, factor = a.inv_norm * a.scale;
+  for (int tile = first; tile < last; ++tile) {
+    const unsigned char* x_lds = xs[tile & 1];
+#pragma unroll
+    for (int j = 0; j < LW; ++j) *reinterpret_cast<bf16x8*>(xs[tile & 1] + lds_at[j]) = rx[j];
+    lds_barrier();  // the tile's rows; the last tile's output rows
+    if (tile + 1 < last) request(tile + 1);
+    if (tile > first) store_rows(tile - 1);
+    const int b = tile / a.tiles_per_user;
+    if (b != cur_user) {  // uniform, rare: waited for right here, so that no other tile waits for its loads and stores
+      load_user(b), cur_user = b;
+#pragma unroll
+      for (int kk = 0; kk < K2; ++kk)
+#pragma unroll
+        for (int lb = 0; lb < LB; ++lb) asm volatile("" : "+v"(ka[kk][lb]));
+#pragma unroll
+      for (int kk = 0; kk < K3; ++kk)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(va[kk][mb]));
+    }
+    // Q~^T = Wq_a^T X^T and P^T = Wu_a^T X^T
+    f32x16 q[MB], p[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) q[mb][i] = p[mb][i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < K1; ++kk) {
+      const bf16x8 x = *reinterpret_cast<const bf16x8*>(x_lds + n * PITCH + (16 * kk + 8 * g) * 2);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) q[mb] = mfma32(wq[kk][mb], x, q[mb]), p[mb] = mfma32(wu[kk][mb], x, p[mb]);
+    }
+    bf16x8 qf[K2];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) qf[2 * mb] = pack_half(q[mb], 0), qf[2 * mb + 1] = pack_half(q[mb], 1);
+    // S^T = K~_a Q~^T, SiLU, O^T = V~_a^T SiLU(S)^T
+    f32x16 s[LB], o[MB];
+#pragma unroll
+    for (int lb = 0; lb < LB; ++lb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[lb][i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < K2; ++kk)
+#pragma unroll
+      for (int lb = 0; lb < LB; ++lb) s[lb] = mfma32(ka[kk][lb], qf[kk], s[lb]);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
+#pragma unroll
+    for (int lb = 0; lb < LB; ++lb) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[lb][i] = s[lb][i] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-s[lb][i] * c));
+      const bf16x8 p0 = pack_half(s[lb], 0), p1 = pack_half(s[lb], 1);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        o[mb] = mfma32(va[2 * lb][mb], p0, o[mb]);
+        o[mb] = mfma32(va[2 * lb + 1][mb], p1, o[mb]);
+      }
+    }
+    // register i of a block is column 16 g + i of it, in o, p and y
+    const int own = n * PITCH + (head * DH + 16 * g) * 2;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        bf16x8 z;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const float u = p[mb][8 * f + t], att = static_cast<float>(static_cast<__bf16>(o[mb][8 * f + t] * factor));
+          z[t] = static_cast<__bf16>(att * u * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-u * kLog2e)));
+        }
+        *reinterpret_cast<bf16x8*>(zs + own + mb * 64 + f * 16) = z;
+      }
+    lds_barrier();  // Z complete; everybody has stored the last tile's output rows
+    f32x16 y[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) y[mb][i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < K1; ++kk) {
+      const bf16x8 z = *reinterpret_cast<const bf16x8*>(zs + n * PITCH + (16 * kk + 8 * g) * 2);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) y[mb] = mfma32(wo[kk][mb], z, y[mb]);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x_lds + own + mb * 64 + f * 16);
+        bf16x8 v;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(static_cast<float>(xr[t]) + y[mb][8 * f + t]);
+        *reinterpret_cast<bf16x8*>(ys + own + mb * 64 + f * 16) = v;
+      }
+  }
+  lds_barrier();
+  store_rows(last - 1);
+}
+
+template <int DH, int M, int H>
+hipError_t launch_rows(const RowsArgs& p, hipStream_t s) {
+  const int resident = (DH == 32 ? 2 : 1) * compute_units();
+  hipLaunchKernelGGL((xor_rows_kernel<DH, M, H>), dim3(p.total_tiles < resident ? p.total_tiles : resident), dim3(64 * H), 0, s, p);
+  return hipGetLastError();
+}
+template <int DH, int H>
+hipError_t launch_rows(const RowsArgs& p, int m, hipStream_t s) {
+  switch (m) {
+    case 32: return launch_rows<DH, 32, H>(p, s);
+    case 64: return launch_rows<DH, 64, H>(p, s);
+    case 96: return launch_rows<DH, 96, H>(p, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+// (five stationary operands: with d = 256, or with 128 links at d = 128, they do not fit the registers)
+bool xor_rows_supported(int d, int h, int m) { return queries_over_links_supported(d, h, m) && d <= 128 && m <= 96; }
+
+hipError_t xor_rows(const XorRows& q, hipStream_t s) {
+  const int tiles = (q.N + 31) / 32, dh = q.d / q.h;
+  const int64_t frags = static_cast<int64_t>(q.m) * q.d / 8;
+  RowsArgs p{static_cast<const bf16_t*>(q.X), q.lens, static_cast<const bf16x8*>(q.Wq_image), static_cast<const bf16x8*>(q.Wu_image),
+             static_cast<const bf16x8*>(q.Wo_image), static_cast<const bf16x8*>(q.keys), static_cast<const bf16x8*>(q.values),
+             q.per_user ? frags : 0, q.per_user ? frags : 0, static_cast<bf16_t*>(q.Y), q.N, tiles, tiles * q.B, fabsf(q.scale),
+             1.f / static_cast<float>(q.m)};
+  if (dh == 32) {
+    switch (q.h) {
+      case 1: return launch_rows<32, 1>(p, q.m, s);
+      case 2: return launch_rows<32, 2>(p, q.m, s);
+      case 4: return launch_rows<32, 4>(p, q.m, s);
+    }
+  } else if (dh == 64) {
+    switch (q.h) {
+      case 1: return launch_rows<64, 1>(p, q.m, s);
+      case 2: return launch_rows<64, 2>(p, q.m, s);
+    }
+  }
+  return hipErrorInvalidValue;
+}
 
 hipError_t gated_block(const GatedBlock& q, hipStream_t s) {
   if (q.B <= 0 || q.rows <= 0) return hipSuccess;
