@@ -140,11 +140,34 @@ XorLayersPlan plan_xor_layers(void* ws, int64_t B, int64_t N, int64_t d, int64_t
   return p;
 }
 
+// The same for the shapes whose layers are four kernels (history, merge, history rows, link rows).
+struct XorRegistersPlan {
+  void* hist_ws;
+  void *Wk, *Wv, *Wq, *Wu[2], *Wo[2];  // weight images; W_U and W_O of the current and the next layer
+  void *Q, *K, *V;                     // images of the current layer's links
+  void *Xs[2], *Xt[2], *OT;            // as in XorLayersPlan
+  float* sum;
+  size_t bytes;
+};
+
+XorRegistersPlan plan_xor_registers(void* ws, int64_t B, int64_t N, int64_t d, int64_t h, int64_t m) {
+  Arena a(ws);
+  XorRegistersPlan p{};
+  p.hist_ws = a.take<char>(lime::links_over_history_workspace(B, N, d, h, m, true));
+  for (void** t : {&p.Wk, &p.Wv, &p.Wq, &p.Wu[0], &p.Wu[1], &p.Wo[0], &p.Wo[1]}) *t = a.take<uint16_t>(d * d);
+  for (void** t : {&p.Q, &p.K, &p.V, &p.Xt[0], &p.Xt[1], &p.OT}) *t = a.take<uint16_t>(B * m * d);
+  for (void** t : {&p.Xs[0], &p.Xs[1]}) *t = a.take<uint16_t>(B * N * d);
+  p.sum = a.take<float>(B * m * d);
+  p.bytes = a.used;
+  return p;
+}
+
 // large enough for either path (a bf16 call whose pointers are not 16-byte aligned runs on the general kernels)
 size_t xor_layers_workspace(int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, int32_t dtype) {
   size_t need = plan_xor_layers(nullptr, B, N, d, h, m, dtype, false).bytes;
   if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m))
     need = std::max(need, plan_xor_layers(nullptr, B, N, d, h, m, dtype, true).bytes);
+  if (dtype == LIME_BF16 && lime::xor_rows_supported(d, h, m)) need = std::max(need, plan_xor_registers(nullptr, B, N, d, h, m).bytes);
   return need;
 }
 
@@ -170,13 +193,12 @@ lime::QueriesOverLinks os_query(const void* E, const int32_t* lens, const void* 
   return q;
 }
 
-// `extra`: weight images that the call's pack launch writes as well (matrix-core path only).  os_packed_only: O[S]'s operands
-// are packed behind the history stage's workspace, and O[S] itself is the caller's business.
+// `extra`: weight images that the call's pack launch writes as well (matrix-core path only).
 int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens, const void* LC,
                      int64_t lc_user_stride, const void* Wq, const void* Wk, const void* Wv, void* LP, void* OS,
                      int32_t B, int32_t N, int32_t d, int32_t h, int32_t m, float scale, int32_t dtype,
                      void* workspace, size_t ws_bytes, void* stream, const lime::PackWeight* extra = nullptr,
-                     int n_extra = 0, bool walk = false, bool os_packed_only = false) {
+                     int n_extra = 0, bool walk = false) {
   if (int32_t st = check_common(fn, B, d, h, dtype)) return st;
   if (N <= 0 || m <= 0) return fail(LIME_INVALID_ARG, "%s: N and m must be positive (N=%d m=%d)", fn, N, m);
   if (!E || !LC || !Wq || !Wk || !Wv || !LP) return fail(LIME_INVALID_ARG, "%s: a required pointer is NULL", fn);
@@ -234,7 +256,7 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     }
     return LIME_OK;
   }
-  if (os_on_mfma && !os_packed_only) {
+  if (os_on_mfma) {
     lime::QueriesOverLinks q = os_query(E, lens, LC, link_stride, Wq, Wk, Wv, OS, B, N, d, h, m, scale);
     q.packed = true;
     LIME_HIP(lime::queries_over_links(q, static_cast<char*>(workspace) + p.bytes, s));
@@ -279,6 +301,52 @@ lime::GenericAttention candidate_attention(const QueryPlan& p, void* O, int32_t 
   a.O = O, a.q_lens = nullptr, a.k_lens = nullptr, a.scratch = p.scratch;
   a.B = B, a.q_rows = C, a.n_keys = m, a.d = d, a.h = h, a.scale = scale, a.phi = lime::kPhiSoftmax, a.dtype = dtype;
   return a;
+}
+
+// lime_xor_layers where a layer's stationary operands fit the registers.  The weights' images and the first layer's link
+// images come from one pack launch; every later layer's from the link kernel of the layer before.
+int32_t xor_layers_in_registers(const XorRegistersPlan& p, const void* E, const int32_t* lens, const void* LC, int64_t lc_user_stride,
+                                const void* Wq, const void* Wk, const void* Wv, const void* Wu, const void* Wo, int32_t n_layers, void* LP,
+                                int32_t B, int32_t N, int32_t d, int32_t h, int32_t m, float scale, hipStream_t s) {
+  const char* fn = "lime_xor_layers";
+  const int64_t link_stride = static_cast<int64_t>(m) * d;
+  const size_t weight_bytes = static_cast<size_t>(d) * d * 2;
+  const float sign = scale < 0.f ? -1.f : 1.f;  // folded into Q~ and K~, so that the kernels see scale >= 0
+  auto of_layer = [&](const void* W, int j) { return j < n_layers ? static_cast<const char*>(W) + j * weight_bytes : nullptr; };
+  lime::PackJobs jobs;
+  for (const lime::PackWeight& w : {lime::PackWeight{Wk, p.Wk}, lime::PackWeight{Wv, p.Wv}, lime::PackWeight{Wq, p.Wq},
+                                    lime::PackWeight{Wu, p.Wu[0]}, lime::PackWeight{Wo, p.Wo[0]}})
+    jobs.weights[jobs.n_weights++] = w;
+  const int users = lc_user_stride != 0 ? B : 1;
+  jobs.projections[jobs.n_projections++] = lime::PackProject{LC, Wq, p.Q, lc_user_stride, users, lime::kPackKeys, sign};
+  if (n_layers > 1) {
+    jobs.projections[jobs.n_projections++] = lime::PackProject{LC, Wk, p.K, lc_user_stride, users, lime::kPackKeys, sign};
+    jobs.projections[jobs.n_projections++] = lime::PackProject{LC, Wv, p.V, lc_user_stride, users, lime::kPackValues, 1.f};
+  }
+  LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
+  for (int j = 0; j < n_layers; ++j) {
+    const bool first = j == 0, last = j + 1 == n_layers;
+    const void *Ej = first ? E : p.Xs[j & 1], *Lj = first ? LC : p.Xt[j & 1];
+    const int64_t lj_stride = first ? lc_user_stride : link_stride;
+    lime::LinksOverHistory q{};
+    q.E = Ej, q.lens = lens, q.lc_user_stride = lj_stride, q.LP = p.OT, q.B = B, q.N = N, q.d = d, q.h = h, q.m = m, q.scale = scale;
+    q.phi = lime::kPhiSilu, q.images[0] = p.Wk, q.images[1] = p.Wv, q.images[2] = p.Q;
+    LIME_HIP(lime::links_over_history(q, p.hist_ws, s));
+    if (!last) {  // (ahead of the link kernel, which writes the next layer's keys and values over this one's)
+      const lime::XorRows rows{Ej, lens, p.Wq, p.Wu[j & 1], p.Wo[j & 1], p.K, p.V, lj_stride != 0, p.Xs[(j + 1) & 1], B, N, d, h, m, scale};
+      LIME_HIP(lime::xor_rows(rows, s));
+    }
+    lime::XorLinks l{};
+    l.X = Lj, l.x_user_stride = lj_stride, l.A = p.OT;
+    l.Wu_image = p.Wu[j & 1], l.Wo_image = p.Wo[j & 1], l.Wq_image = p.Wq, l.Wk_image = p.Wk, l.Wv_image = p.Wv;
+    l.Y = last ? nullptr : p.Xt[(j + 1) & 1];
+    l.sum_in = first ? nullptr : p.sum, l.sum_out = last ? nullptr : p.sum, l.sum_rounded = last ? LP : nullptr;
+    l.queries = p.Q, l.keys = p.K, l.values = p.V;
+    l.next_Wu = of_layer(Wu, j + 1), l.next_Wo = of_layer(Wo, j + 1), l.next_Wu_image = p.Wu[(j + 1) & 1], l.next_Wo_image = p.Wo[(j + 1) & 1];
+    l.B = B, l.m = m, l.d = d, l.h = h, l.scale = scale;
+    LIME_HIP(lime::xor_links(l, s));
+  }
+  return LIME_OK;
 }
 
 }  // namespace
@@ -755,6 +823,9 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
   const size_t need = xor_layers_workspace(B, N, d, h, m, dtype);
   if (!workspace || ws_bytes < need)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace ? ws_bytes : 0);
+  if (on_mfma && lime::xor_rows_supported(d, h, m))
+    return xor_layers_in_registers(plan_xor_registers(workspace, B, N, d, h, m), E, lens, LC, lc_user_stride, Wq, Wk, Wv, Wu, Wo, n_layers, LP,
+                                   B, N, d, h, m, scale, static_cast<hipStream_t>(stream));
   const XorLayersPlan p = plan_xor_layers(workspace, B, N, d, h, m, dtype, on_mfma);
   const size_t es = dtype == LIME_BF16 ? 2 : 4;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -771,10 +842,8 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
     // (the layer's pack launch also writes the images of the gated block's two weights)
     const void *Wu_j = Wu_all + j * weight_bytes, *Wo_j = Wo_all + j * weight_bytes;
     lime::PackWeight images[2] = {{Wu_j, p.Wu_image}, {Wo_j, p.Wo_image}};
-    // On the matrix cores O[S] and the gated block of the history rows are one kernel where its operands fit the registers.
-    const bool rows_in_one = on_mfma && lime::xor_rows_supported(d, h, m);
     if (int32_t st = history_impl(fn, lime::kPhiSilu, Ej, lens, Lj, lj_stride, Wq, Wk, Wv, p.OT, last ? nullptr : p.OS, B, N,
-                                  d, h, m, scale, dtype, p.hist_ws, p.hist_bytes, stream, images, on_mfma ? 2 : 0, false, rows_in_one))
+                                  d, h, m, scale, dtype, p.hist_ws, p.hist_bytes, stream, images, on_mfma ? 2 : 0))
       return st;
     if (!on_mfma) {
       lime::GenericGatedBlock links{};
@@ -799,15 +868,6 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
     LIME_HIP(lime::gated_block(links, s));
     if (last) break;
     // history rows: the same block with O[S]; rows at or past lens[b] stay zero
-    if (rows_in_one) {
-      const bool per_user = lj_stride != 0;
-      const lime::QueriesOverLinksOperands o = lime::queries_over_links_operands(
-          os_query(Ej, lens, Lj, lj_stride, Wq, Wk, Wv, p.OS, B, N, d, h, m, scale),
-          static_cast<char*>(p.hist_ws) + lime::links_over_history_workspace(B, N, d, h, m, per_user));
-      lime::XorRows rows{Ej, lens, o.queries, p.Wu_image, p.Wo_image, o.keys, o.values, per_user, p.Xs[(j + 1) & 1], B, N, d, h, m, scale};
-      LIME_HIP(lime::xor_rows(rows, s));
-      continue;
-    }
     lime::GatedBlock rows{};
     rows.X = Ej, rows.x_user_stride = hist_stride, rows.lens = lens, rows.Wu_image = p.Wu_image, rows.Wo_image = p.Wo_image;
     rows.A = p.OS, rows.Y = p.Xs[(j + 1) & 1], rows.B = B, rows.rows = N, rows.d = d, rows.h = h;

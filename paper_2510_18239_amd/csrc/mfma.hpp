@@ -202,6 +202,18 @@ __device__ __forceinline__ int64_t values_slot(int u, int row, int col, int d, i
   return (frag * 64 + 32 * g + out_rho(c % 32)) * 8 + t;
 }
 
+// Fragment f of the image of a weight matrix of d columns, a lane's part of it.
+template <int DH>
+__device__ __forceinline__ void weight_fragment(const bf16_t* W, bf16x8* image, int d, int f, int lane) {
+  constexpr int MB = DH / 32;
+  const int mb = f % MB, kk = f / MB % (d / 16), a = f / MB / (d / 16);
+  const bf16_t* src = W + static_cast<int64_t>(16 * kk + 8 * (lane >> 5)) * d + a * DH + 32 * mb + (lane & 31);
+  bf16x8 v;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = __builtin_bit_cast(__bf16, src[t * d].bits);
+  image[f * 64 + lane] = v;
+}
+
 // Fragments (1 KiB each) left free between the head slices of the candidate side's query-weight image (and of the
 // score image that replaces it).  Zero: starting the heads' slices at different cache-channel phases was measured
 // and changed nothing.
@@ -376,6 +388,26 @@ struct XorRows {
 bool xor_rows_supported(int d, int h, int m);
 hipError_t xor_rows(const XorRows& q, hipStream_t s);
 
+// The link rows' part in one kernel (for the shapes of xor_rows): the gated block and the running sum as in GatedBlock, and
+// with Y (all but the last layer) the images that the next layer's kernels want of the new rows, Q~ and K~ with the sign of
+// `scale`, and the next layer's images of W_U and W_O.
+struct XorLinks {
+  const void* X;          // [.][m][d] bf16
+  int64_t x_user_stride;  // 0 = one block for all users
+  const void* A;          // [B][m][d]
+  void *Wu_image, *Wo_image, *Wq_image, *Wk_image, *Wv_image;
+  void* Y;                // nullable
+  const float* sum_in;
+  float* sum_out;
+  void* sum_rounded;
+  void *queries, *keys, *values;  // [B] images
+  const void *next_Wu, *next_Wo;  // [d][d]
+  void *next_Wu_image, *next_Wo_image;
+  int B, m, d, h;
+  float scale;
+};
+hipError_t xor_links(const XorLinks& q, hipStream_t s);
+
 // ----------------------------------------------------------------------------- history-side kernel family
 // Fused "few queries x many keys" attention: the m links attend over one user's N history rows;
 // keys and values are projected on the fly (K~ = E Wk, V~ = E Wv), queries are Q~ = LC Wq.
@@ -398,6 +430,7 @@ struct LinksOverHistory {
   RowNorm values_norm;  // applied to the finished link states before that projection (LP itself is stored as it is)
   RowNorm q_norm;       // applied to the link rows LC by the pack step
   bool walk;            // run on the kernel of mfma_history_walk.hip (softmax only)
+  const void* images[3];  // when set: W_K^T, W_V and Q~ (per user where lc_user_stride is set) come from here
 };
 void links_over_history_jobs(const LinksOverHistory& a, void* workspace, PackJobs& jobs);
 bool links_over_history_supported(int d, int h, int m);

@@ -869,6 +869,8 @@ hipError_t links_over_history(const LinksOverHistory& q, void* workspace, hipStr
     const PreparedLayout pl = prepared_layout(d, m);
     char* base = const_cast<char*>(static_cast<const char*>(q.prepared));
     WkA = base + pl.wk, WvB = base + pl.wv, QB = base + pl.qb;
+  } else if (q.images[0] != nullptr) {
+    WkA = const_cast<void*>(q.images[0]), WvB = const_cast<void*>(q.images[1]), QB = const_cast<void*>(q.images[2]);
   } else if (!q.packed) {
     PackJobs jobs;
     links_over_history_jobs(q, workspace, jobs);

@@ -62,3 +62,14 @@ def test_merged_link_states(B, N, d, h, m, xor):
         ref = (w @ v).transpose(0, 1).reshape(m, d)
         err = (LP[b].float() - ref).abs().max()
         assert err <= 2e-2 and err <= 2e-2 * ref.abs().max(), (b, float(err))
+
+
+@pytest.mark.parametrize("d,h,m", [(128, 4, 64), (128, 2, 32), (32, 1, 96)])
+def test_xor_layers_with_a_negative_scale(d, h, m):
+    """SiLU(-s x) with the sign folded into Q~ and K~: negating W_Q as well gives the same logits, bit for bit."""
+    E, L, Wq, Wk, Wv = _tensors(d, (3, 75, d), (m, d), (d, d), (d, d), (d, d))
+    Wu, Wo = (torch.stack(_tensors(d + i, (d, d), (d, d), (d, d))) for i in (1, 2))
+    lens = torch.tensor([75, 0, 33], dtype=torch.int32, device="cuda")
+    a = binding.lime_xor_layers(E, lens, L, Wq, Wk, Wv, Wu, Wo, h, 0.4)
+    assert torch.isfinite(a).all() and a[0].any() and not a[1].any()
+    assert torch.equal(a, binding.lime_xor_layers(E, lens, L, -Wq, Wk, Wv, Wu, Wo, h, -0.4))

@@ -576,6 +576,11 @@ def test_xor_layers_on_general_kernels(dtype, B, N, d, h, m, n_layers, per_user)
     (2, 190, 64, 2, 32, 2, True),        # per-user contextualised links from the start
     (1, 100, 256, 8, 96, 1, False),      # one layer: the gated block on top of lime_xor_history
     (40, 1024, 128, 4, 64, 3, False),    # several steps per workgroup of the history kernel
+    # layers whose operands stay in registers: every head count and width, an odd number of link blocks, less than a tile of
+    # rows, and 128 links at d = 128, where they do not fit.  (Not one row: the sharp inputs' states are then of size 20, of
+    # which bf16 keeps 2^-9, twice the absolute bar.)
+    (3, 131, 128, 2, 96, 3, False), (2, 65, 64, 1, 32, 2, False), (5, 33, 32, 1, 64, 3, True), (2, 31, 64, 2, 32, 2, False),
+    (2, 97, 128, 4, 128, 2, False),
 ])
 def test_xor_layers(B, N, d, h, m, n_layers, per_user):
     """lime_xor_layers against the oracle's Eq. 8 on sharp inputs (gate pre-activations and XORA logits of order
