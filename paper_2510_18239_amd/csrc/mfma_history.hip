@@ -37,7 +37,7 @@ struct HistShape {
   // otherwise one (two barriers).
   static constexpr int kLdsPerUnit = 160 * 1024 / (8 / kWaves);
   static constexpr int NX = 2 * kXBytes + 2 * kExchange + kQueries <= kLdsPerUnit ? 2 : 1;
-  static constexpr int kCombine = (TP - 1) * HG * MB * (MB * LBW * 4096 + LBW * 512);
+  static constexpr int kPerWave = MB * LBW * 4096 + LBW * 512, kCombine = TP > 1 ? TP * HG * MB * kPerWave : 0;
   static constexpr int kLds = std::max(NX * (kXBytes + kExchange) + kQueries, kCombine);
 };
 
@@ -266,12 +266,26 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
     }
   }
 
-  // the tiles of a step are combined in ascending order by the waves of the first one
+  // The tiles of a step are combined in ascending order, through LDS: the TP waves of a block share out its pieces, a piece
+  // being what a lane stores at once: four head columns 32 ob + 8 j + 4 g .. + 3 of its link.  (By the first tile's waves alone
+  // this took 1.6 us with eight tiles, and their stores 2.0, at B=32 N=1024 d=128 m=64; 0.5 and 1.1 so.)
+  const int64_t slot = (static_cast<int64_t>(b) * a.chunks + chunk) * H + head;
+  auto store_piece = [&](int l, int ob, int j, float4 v) {
+    const int link = 32 * (half * LBW + l) + n;
+    *reinterpret_cast<float4*>(a.part_acc + (slot * M + link) * DH + 4 * g + 32 * ob + 8 * j) = v;
+  };
+  auto store_sums = [&](int l, float top, float sum) {
+    const int link = 32 * (half * LBW + l) + n;
+    const float total = pair_sum(sum);
+    if (g == 0) *reinterpret_cast<float2*>(a.part_ml + (slot * M + link) * 2) = make_float2(top * a.scale, total);  // (the merge works on scaled logits)
+  };
+  auto past_links = [&](int l) { return LB % MB != 0 && half * LBW + l >= LB; };  // uniform
   if constexpr (TP > 1) {
-    constexpr int kPer = MB * LBW * 4096 + LBW * 512;  // bytes per wave
+    constexpr int kPer = S::kPerWave;
     lds_barrier();  // the rows' and the exchange's last readers are done
-    if (tp > 0) {
-      unsigned char* dst = lds + ((tp - 1) * HG * MB + hl * MB + half) * kPer;
+    unsigned char* const block = lds + (hl * MB + half) * kPer;  // a tile's part, HG MB kPer apart
+    {
+      unsigned char* dst = block + tp * HG * MB * kPer;
 #pragma unroll
       for (int l = 0; l < LBW; ++l) {
 #pragma unroll
@@ -284,65 +298,50 @@ __global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void li
       }
     }
     lds_barrier();
-    if (tp > 0) return;
 #pragma unroll
     for (int l = 0; l < LBW; ++l) {
+      if (past_links(l)) break;
       float2 ms[TP];
-      float top = run_max[l];
-      ms[0] = make_float2(run_max[l], run_sum[l]);
 #pragma unroll
-      for (int p = 1; p < TP; ++p) {
-        ms[p] = *reinterpret_cast<const float2*>(lds + ((p - 1) * HG * MB + hl * MB + half) * kPer + MB * LBW * 4096 + l * 512 + lane * 8);
-        top = fmaxf(top, ms[p].x);
-      }
+      for (int p = 0; p < TP; ++p) ms[p] = *reinterpret_cast<const float2*>(block + p * HG * MB * kPer + MB * LBW * 4096 + l * 512 + lane * 8);
+      float top = ms[0].x;
+#pragma unroll
+      for (int p = 1; p < TP; ++p) top = fmaxf(top, ms[p].x);
       // (a tile without items has maximum -inf and weight zero; the first tile of a chunk has one; phi = SiLU has no maximum)
       float w[TP];
 #pragma unroll
       for (int p = 0; p < TP; ++p)
         w[p] = PHI != kPhiSoftmax ? 1.f : ms[p].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ms[p].x - top) * c);
-      run_max[l] = top, run_sum[l] = ms[0].y * w[0];
+      if (tp == l % TP) {
+        float sum = ms[0].y * w[0];
+#pragma unroll
+        for (int p = 1; p < TP; ++p) sum = fmaf(ms[p].y, w[p], sum);
+        store_sums(l, top, sum);
+      }
+#pragma unroll
+      for (int piece = 0; piece < MB * 4; ++piece) {
+        const int ob = piece / 4, j = piece % 4;
+        if ((l * MB * 4 + piece) % TP != tp) continue;  // uniform
+        float4 v[TP];
+#pragma unroll
+        for (int p = 0; p < TP; ++p) v[p] = *reinterpret_cast<const float4*>(block + p * HG * MB * kPer + ((ob * LBW + l) * 4 + j) * 1024 + lane * 16);
+        float4 sum = make_float4(v[0].x * w[0], v[0].y * w[0], v[0].z * w[0], v[0].w * w[0]);
+#pragma unroll
+        for (int p = 1; p < TP; ++p)
+          sum.x = fmaf(v[p].x, w[p], sum.x), sum.y = fmaf(v[p].y, w[p], sum.y), sum.z = fmaf(v[p].z, w[p], sum.z), sum.w = fmaf(v[p].w, w[p], sum.w);
+        store_piece(l, ob, j, sum);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int l = 0; l < LBW; ++l) {
+      if (past_links(l)) break;
 #pragma unroll
       for (int ob = 0; ob < MB; ++ob)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[ob][l][i] *= w[0];
-#pragma unroll
-      for (int p = 1; p < TP; ++p) {
-        const unsigned char* src = lds + ((p - 1) * HG * MB + hl * MB + half) * kPer;
-        run_sum[l] = fmaf(ms[p].y, w[p], run_sum[l]);
-#pragma unroll
-        for (int ob = 0; ob < MB; ++ob) {
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float4 v = *reinterpret_cast<const float4*>(src + ((ob * LBW + l) * 4 + j) * 1024 + lane * 16);
-            acc[ob][l][4 * j] = fmaf(v.x, w[p], acc[ob][l][4 * j]), acc[ob][l][4 * j + 1] = fmaf(v.y, w[p], acc[ob][l][4 * j + 1]);
-            acc[ob][l][4 * j + 2] = fmaf(v.z, w[p], acc[ob][l][4 * j + 2]), acc[ob][l][4 * j + 3] = fmaf(v.w, w[p], acc[ob][l][4 * j + 3]);
-          }
-        }
-      }
-    }
-  }
-
-  // partials: lane (link n of block lb) holds head columns 32ob + 8j + 4g + r in register 4j + r
-  const int64_t slot = (static_cast<int64_t>(b) * a.chunks + chunk) * H + head;
-#pragma unroll
-  for (int l = 0; l < LBW; ++l) {
-    const int lb = half * LBW + l;
-    if (LB % MB != 0 && lb >= LB) break;  // uniform
-    const int link = 32 * lb + n;
-    float* dst = a.part_acc + (slot * M + link) * DH + 4 * g;
-#pragma unroll
-    for (int ob = 0; ob < MB; ++ob)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float4 v = make_float4(acc[ob][l][4 * j], acc[ob][l][4 * j + 1], acc[ob][l][4 * j + 2], acc[ob][l][4 * j + 3]);
-        *reinterpret_cast<float4*>(dst + 32 * ob + 8 * j) = v;
-      }
-    const float total = pair_sum(run_sum[l]);
-    if (g == 0) {
-      float* ml = a.part_ml + (slot * M + link) * 2;
-      ml[0] = run_max[l] * a.scale;  // the merge works on scaled logits
-      ml[1] = total;
+        for (int j = 0; j < 4; ++j)
+          store_piece(l, ob, j, make_float4(acc[ob][l][4 * j], acc[ob][l][4 * j + 1], acc[ob][l][4 * j + 2], acc[ob][l][4 * j + 3]));
+      store_sums(l, run_max[l], run_sum[l]);
     }
   }
 }
@@ -474,6 +473,69 @@ struct MergeRow {
   }
 };
 
+// The same by one thread for its four columns, kMergeGroups chunks at a time: for calls with many rows, whose threads have
+// few chunks each.
+template <int PHI, int D>
+struct MergeQuad {
+  int64_t first, stride;
+  int link, quad;
+  float2 ml[kMergeGroups];
+  float4 ac[kMergeGroups];
+  __device__ __forceinline__ void ask_ml(const MergeArgs& a, int c0) {
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q) ml[q] = *reinterpret_cast<const float2*>(a.part_ml + (first + min(c0 + q, a.chunks - 1) * stride) * 2);
+  }
+  __device__ __forceinline__ void ask(const MergeArgs& a, int c0) {
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q)
+      ac[q] = *reinterpret_cast<const float4*>(a.part_acc + (first + min(c0 + q, a.chunks - 1) * stride) * a.dh + 4 * quad % a.dh);
+  }
+  __device__ __forceinline__ void begin(const MergeArgs& a, int b, int link_, int quad_) {
+    link = link_, quad = quad_, stride = static_cast<int64_t>(a.h) * a.m;
+    first = (static_cast<int64_t>(b) * a.chunks * a.h + 4 * quad / a.dh) * a.m + link;
+    if (PHI == kPhiSoftmax) ask_ml(a, 0);
+    ask(a, 0);
+  }
+  __device__ __forceinline__ float4 finish(const MergeArgs& a, int len) {
+    const int used = (len + a.chunk_items - 1) / a.chunk_items;
+    float4 num[kMergeGroups];
+    float den[kMergeGroups], top = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < kMergeGroups; ++q) num[q] = make_float4(0.f, 0.f, 0.f, 0.f), den[q] = 0.f;
+    for (int c0 = 0; c0 < used; c0 += kMergeGroups) {  // uniform
+      if (PHI == kPhiSoftmax && c0 % kMergeBatch == 0) {
+        float batch_top = top;
+        for (int c1 = c0; c1 < min(used, c0 + kMergeBatch); c1 += kMergeGroups) {
+          if (c1 > 0) ask_ml(a, c1);
+#pragma unroll
+          for (int q = 0; q < kMergeGroups; ++q) batch_top = fmaxf(batch_top, c1 + q < used ? ml[q].x : -INFINITY);
+        }
+        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
+#pragma unroll
+        for (int q = 0; q < kMergeGroups; ++q) num[q].x *= keep, num[q].y *= keep, num[q].z *= keep, num[q].w *= keep, den[q] *= keep;
+        top = batch_top;
+        if (used - c0 > kMergeGroups) ask_ml(a, c0);  // (the maxima of the batch's other chunks were read over them)
+      } else if (PHI == kPhiSoftmax) {
+        ask_ml(a, c0);
+      }
+      if (c0 > 0) ask(a, c0);
+#pragma unroll
+      for (int q = 0; q < kMergeGroups; ++q) {
+        if (c0 + q >= used) continue;  // uniform
+        if (PHI == kPhiSoftmax) {
+          const float w = __builtin_amdgcn_exp2f((ml[q].x - top) * kLog2e);
+          num[q].x = fmaf(w, ac[q].x, num[q].x), num[q].y = fmaf(w, ac[q].y, num[q].y);
+          num[q].z = fmaf(w, ac[q].z, num[q].z), num[q].w = fmaf(w, ac[q].w, num[q].w);
+          den[q] = fmaf(w, ml[q].y, den[q]);
+        } else {
+          num[q].x += ac[q].x, num[q].y += ac[q].y, num[q].z += ac[q].z, num[q].w += ac[q].w;
+        }
+      }
+    }
+    return used > 0 ? MergeRow<PHI, D>::total(num, den, a.scale, len) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+};
+
 // Four rounded link-state values as one 8-byte store.
 __device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, float* rounded = nullptr) {
   alignas(8) bf16_t r[4];
@@ -498,6 +560,17 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(MergeArgs a) {
   const int len = a.lens ? min(a.lens[b], a.N) : a.N;
   const float4 v = row.finish(a, len, lds);
   if (row.group == 0) store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + link) * D + 4 * row.quad, v);
+}
+
+// A thread per four columns of a link state.
+constexpr int kMergeManyThreads = 64;
+template <int PHI, int D>
+__global__ __launch_bounds__(kMergeManyThreads) void merge_many_kernel(MergeArgs a) {
+  const int b = blockIdx.y, idx = blockIdx.x * kMergeManyThreads + threadIdx.x;  // (m d / 4 is a multiple of 64)
+  MergeQuad<PHI, D> task;
+  task.begin(a, b, idx / (D / 4), idx % (D / 4));
+  const int len = a.lens ? min(a.lens[b], a.N) : a.N;
+  store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + task.link) * D + 4 * task.quad, task.finish(a, len));
 }
 
 // Layer normalisation of a finished link state by a wavefront, from x(k) to put(k, value): mean, centred second moment, then
@@ -597,47 +670,27 @@ __global__ __launch_bounds__(2 * D) void merge_values_kernel(MergeValuesArgs a) 
   if (tid < D) store_as(a.VA + values_slot(b, link, tid, D, a.m.dh, a.m.m, true), out);
 }
 
-// Sixteen link states per workgroup, for calls with many: the projection is on the matrix cores (the upper half of a 32-row
-// block repeats the lower), W_V goes straight to LDS and is turned on its way out, a wavefront's 32 columns in its own part.
-// A thread takes all chunks of its columns, kMergeGroups at a time, in the same order of sums as MergeRow.
-template <int PHI, int D>
+// ROWS (8 or 16) link states per workgroup, for calls with many: the projection is on the matrix cores (a 32-row block repeats
+// them), W_V goes straight to LDS and is turned on its way out, a wavefront's 32 columns in its own part.
+template <int PHI, int D, int ROWS>
 struct MergeTile {
-  static constexpr int kRows = 16, NK = D / 16, kWaves = D / 32, kPitch = D + 8, kTasks = kRows * (D / 4) / (2 * D);
+  static constexpr int kRows = ROWS, NK = D / 16, kWaves = D / 32, kPitch = D + 8, kTasks = kRows * (D / 4) / (2 * D);
   static constexpr int kLds = kWaves * NK * 1024 + kRows * kPitch * 2;
 };
-template <int PHI, int D>
+template <int PHI, int D, int ROWS>
 __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArgs a) {
-  using T = MergeTile<PHI, D>;
+  using T = MergeTile<PHI, D, ROWS>;
   constexpr int NK = T::NK, kTasks = T::kTasks, kQuads = D / 4;
   extern __shared__ unsigned char lds[];
   bf16_t* const rows = reinterpret_cast<bf16_t*>(lds + T::kWaves * NK * 1024);
   const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = blockIdx.y, link0 = blockIdx.x * T::kRows, dh = a.m.dh;
-  const int64_t stride = static_cast<int64_t>(a.m.h) * a.m.m;  // (head, link) slots per chunk
   unsigned char* const mine = lds + wave * NK * 1024;
-  int64_t first[kTasks];
-  int row[kTasks], quad[kTasks];
-  float2 ml[kTasks][kMergeGroups];
-  float4 ac[kTasks][kMergeGroups];
+  MergeQuad<PHI, D> task[kTasks];
 #pragma unroll
   for (int i = 0; i < kTasks; ++i) {
     const int idx = threadIdx.x + i * 2 * D;
-    row[i] = idx / kQuads, quad[i] = idx % kQuads;
-    first[i] = (static_cast<int64_t>(b) * a.m.chunks * a.m.h + 4 * quad[i] / dh) * a.m.m + link0 + row[i];
-  }
-  auto ask_ml = [&](int i, int c0) {
-#pragma unroll
-    for (int q = 0; q < kMergeGroups; ++q) ml[i][q] = *reinterpret_cast<const float2*>(a.m.part_ml + (first[i] + min(c0 + q, a.m.chunks - 1) * stride) * 2);
-  };
-  auto ask = [&](int i, int c0) {
-#pragma unroll
-    for (int q = 0; q < kMergeGroups; ++q)
-      ac[i][q] = *reinterpret_cast<const float4*>(a.m.part_acc + (first[i] + min(c0 + q, a.m.chunks - 1) * stride) * dh + 4 * quad[i] % dh);
-  };
-#pragma unroll
-  for (int i = 0; i < kTasks; ++i) {
-    if (PHI == kPhiSoftmax) ask_ml(i, 0);
-    ask(i, 0);
+    task[i].begin(a.m, b, link0 + idx / kQuads, idx % kQuads);
   }
   if (a.Wv != nullptr) {
 #pragma unroll
@@ -645,45 +698,10 @@ __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArg
       load_to_lds(lds_offset_of(mine) + kk * 1024, (lane / 4) * (2 * D) + lane % 4 * 16, a.Wv + static_cast<int64_t>(16 * kk) * D + 32 * wave);
   }
   const int len = a.m.lens ? min(a.m.lens[b], a.m.N) : a.m.N;
-  const int used = (len + a.m.chunk_items - 1) / a.m.chunk_items;
 #pragma unroll
   for (int i = 0; i < kTasks; ++i) {
-    float4 num[kMergeGroups], v = make_float4(0.f, 0.f, 0.f, 0.f);
-    float den[kMergeGroups], top = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < kMergeGroups; ++q) num[q] = v, den[q] = 0.f;
-    for (int c0 = 0; c0 < used; c0 += kMergeGroups) {  // uniform
-      if (PHI == kPhiSoftmax && c0 % kMergeBatch == 0) {
-        float batch_top = top;
-        for (int c1 = c0; c1 < min(used, c0 + kMergeBatch); c1 += kMergeGroups) {
-          if (c1 > 0) ask_ml(i, c1);
-#pragma unroll
-          for (int q = 0; q < kMergeGroups; ++q) batch_top = fmaxf(batch_top, c1 + q < used ? ml[i][q].x : -INFINITY);
-        }
-        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
-#pragma unroll
-        for (int q = 0; q < kMergeGroups; ++q) num[q].x *= keep, num[q].y *= keep, num[q].z *= keep, num[q].w *= keep, den[q] *= keep;
-        top = batch_top;
-        if (used - c0 > kMergeGroups) ask_ml(i, c0);  // (the maxima of the batch's other chunks were read over them)
-      } else if (PHI == kPhiSoftmax) {
-        ask_ml(i, c0);
-      }
-      if (c0 > 0) ask(i, c0);
-#pragma unroll
-      for (int q = 0; q < kMergeGroups; ++q) {
-        if (c0 + q >= used) continue;  // uniform
-        if (PHI == kPhiSoftmax) {
-          const float w = __builtin_amdgcn_exp2f((ml[i][q].x - top) * kLog2e);
-          num[q].x = fmaf(w, ac[i][q].x, num[q].x), num[q].y = fmaf(w, ac[i][q].y, num[q].y);
-          num[q].z = fmaf(w, ac[i][q].z, num[q].z), num[q].w = fmaf(w, ac[i][q].w, num[q].w);
-          den[q] = fmaf(w, ml[i][q].y, den[q]);
-        } else {
-          num[q].x += ac[i][q].x, num[q].y += ac[i][q].y, num[q].z += ac[i][q].z, num[q].w += ac[i][q].w;
-        }
-      }
-    }
-    if (used > 0) v = MergeRow<PHI, D>::total(num, den, a.m.scale, len);
-    store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link0 + row[i]) * D + 4 * quad[i], v, rows + row[i] * T::kPitch + 4 * quad[i]);
+    const int link = task[i].link, quad = task[i].quad;
+    store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link) * D + 4 * quad, task[i].finish(a.m, len), rows + (link - link0) * T::kPitch + 4 * quad);
   }
   wait_lds_loads<0>();  // W_V's part of this wave
   __syncthreads();
@@ -695,21 +713,25 @@ __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArg
     }
     __syncthreads();
   }
-  bf16x8 values;  // lane (column 32 wave + n, g), slot t = link chain_k(g, t) of the sixteen
+  bf16x8 values;  // lane (column 32 wave + n, g), slot t = link chain_k(g, t) of sixteen (of eight: the first four slots)
   if (a.Wv == nullptr) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) values[t] = __builtin_bit_cast(__bf16, rows[chain_k(g, t) * T::kPitch + 32 * wave + n].bits);
+    for (int t = 0; t < 8; ++t) values[t] = __builtin_bit_cast(__bf16, rows[chain_k(g, t) % ROWS * T::kPitch + 32 * wave + n].bits);
   } else {
     bf16x8 x[NK], w[NK];
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      x[kk] = *reinterpret_cast<const bf16x8*>(rows + n % 16 * T::kPitch + 16 * kk + 8 * g);
+      x[kk] = *reinterpret_cast<const bf16x8*>(rows + n % ROWS * T::kPitch + 16 * kk + 8 * g);
       w[kk] = column_fragment(mine + kk * 1024, 64, lane);
     }
     values = pack_half(project_block<NK>(x, w), 0);
   }
   const int64_t frag = ((static_cast<int64_t>(b) * a.m.h + 32 * wave / dh) * (a.m.m / 16) + link0 / 16) * (dh / 32) + 32 * wave % dh / 32;
-  reinterpret_cast<bf16x8*>(a.VA)[frag * 64 + out_rho(n) + 32 * g] = values;
+  bf16_t* dst = a.VA + (frag * 64 + out_rho(n) + 32 * g) * 8;
+  if constexpr (ROWS == 16)
+    *reinterpret_cast<bf16x8*>(dst) = values;
+  else  // (links 8 .. 15 of the sixteen are the last four slots)
+    *reinterpret_cast<bf16x4*>(dst + link0 % 16 / 2) = __builtin_shufflevector(values, values, 0, 1, 2, 3);
 }
 
 // Forms of a workgroup, by the amount of work (plan()):
@@ -771,20 +793,39 @@ hipError_t dispatch_h(const HistArgs& a, int h, int links, int phi, int users, i
   return hipErrorInvalidValue;
 }
 
-// One link state per workgroup where all of them run at once (eight waves a compute unit: its registers).
+// One link state per workgroup where all of them run at once with eight waves a compute unit (what the registers of the value
+// projection leave room for; without it four times as many do, but a thread per four columns is then ahead all the same:
+// history + merge at 2048 rows 15.5 us so and 14.1 us by thread at B=32 N=1024 d=128 m=64).
+bool few_rows(int64_t rows, int d) { return rows <= static_cast<int64_t>(compute_units()) * (256 / d); }
+
+template <int PHI, int D>
+hipError_t launch_merge(const MergeArgs& a, int users, hipStream_t s) {
+  if (few_rows(static_cast<int64_t>(users) * a.m, D))
+    hipLaunchKernelGGL((merge_kernel<PHI, D>), dim3(a.m, users), dim3(2 * D), 0, s, a);
+  else
+    hipLaunchKernelGGL((merge_many_kernel<PHI, D>), dim3(a.m * (D / 4) / kMergeManyThreads, users), dim3(kMergeManyThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+template <int PHI, int D, int ROWS>
+hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStream_t s) {
+  using T = MergeTile<PHI, D, ROWS>;
+  if (T::kLds > 64 * 1024) {
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_values_tile_kernel<PHI, D, ROWS>), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
+    if (attr != hipSuccess) return attr;
+  }
+  hipLaunchKernelGGL((merge_values_tile_kernel<PHI, D, ROWS>), dim3(a.m.m / ROWS, users), dim3(2 * D), T::kLds, s, a);
+  return hipGetLastError();
+}
 template <int PHI, int D>
 hipError_t launch_merge_values(const MergeValuesArgs& a, int users, hipStream_t s) {
-  using T = MergeTile<PHI, D>;
-  if (static_cast<int64_t>(users) * a.m.m <= static_cast<int64_t>(compute_units()) * (256 / D)) {
+  const int64_t rows = static_cast<int64_t>(users) * a.m.m;
+  if (few_rows(rows, D)) {
     hipLaunchKernelGGL((merge_values_kernel<PHI, D>), dim3(a.m.m, users), dim3(2 * D), 0, s, a);
     return hipGetLastError();
   }
-  if (T::kLds > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_values_tile_kernel<PHI, D>), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
-    if (attr != hipSuccess) return attr;
-  }
-  hipLaunchKernelGGL((merge_values_tile_kernel<PHI, D>), dim3(a.m.m / T::kRows, users), dim3(2 * D), T::kLds, s, a);
-  return hipGetLastError();
+  // eight rows each as long as the workgroups then all run at once
+  return few_rows(rows / 8, D) ? launch_merge_values_tile<PHI, D, 8>(a, users, s) : launch_merge_values_tile<PHI, D, 16>(a, users, s);
 }
 
 struct Layout {
@@ -905,24 +946,13 @@ hipError_t links_over_history(const LinksOverHistory& q, void* workspace, hipStr
     }
     return hipErrorInvalidValue;
   }
-  const dim3 mgrid(m, q.B);
-#define LIME_MERGE_CASE(D)                                                                    \
-  case D:                                                                                     \
-    if (softmax)                                                                              \
-      hipLaunchKernelGGL((merge_kernel<kPhiSoftmax, D>), mgrid, dim3(2 * D), 0, s, g);        \
-    else                                                                                      \
-      hipLaunchKernelGGL((merge_kernel<kPhiSilu, D>), mgrid, dim3(2 * D), 0, s, g);           \
-    break;
   switch (d) {
-    LIME_MERGE_CASE(32)
-    LIME_MERGE_CASE(64)
-    LIME_MERGE_CASE(128)
-    LIME_MERGE_CASE(256)
-    default:
-      return hipErrorInvalidValue;
+    case 32: return softmax ? launch_merge<kPhiSoftmax, 32>(g, q.B, s) : launch_merge<kPhiSilu, 32>(g, q.B, s);
+    case 64: return softmax ? launch_merge<kPhiSoftmax, 64>(g, q.B, s) : launch_merge<kPhiSilu, 64>(g, q.B, s);
+    case 128: return softmax ? launch_merge<kPhiSoftmax, 128>(g, q.B, s) : launch_merge<kPhiSilu, 128>(g, q.B, s);
+    case 256: return softmax ? launch_merge<kPhiSoftmax, 256>(g, q.B, s) : launch_merge<kPhiSilu, 256>(g, q.B, s);
   }
-#undef LIME_MERGE_CASE
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lime

@@ -30,9 +30,11 @@ def test_projected_links_do_not_depend_on_the_batch(B, d, h, m):
     assert ((O[b].double() - ref).abs() <= 2 ** -7 * ref.abs().max()).all()
 
 
-# rows of link states up to and past what runs at once with a workgroup each; up to 8, 32 and more chunks of a history
+# rows of link states up to and past what runs at once with a workgroup each, and with one per eight of them; up to 8, 32 and
+# more chunks of a history
 @pytest.mark.parametrize("B,N,d,h,m", [
     (4, 300, 256, 4, 64), (5, 300, 256, 4, 64), (8, 129, 128, 4, 64), (9, 129, 128, 4, 64), (33, 70, 64, 2, 32), (65, 70, 32, 1, 32),
+    (17, 200, 256, 4, 128), (129, 33, 32, 1, 128), (33, 400, 128, 4, 128),
     (3, 12000, 256, 4, 128), (5, 26240, 128, 2, 128), (1, 16384, 64, 1, 32), (1, 2048, 256, 8, 96)])
 @pytest.mark.parametrize("xor", [False, True])
 def test_merged_link_states(B, N, d, h, m, xor):
