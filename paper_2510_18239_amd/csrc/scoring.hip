@@ -601,12 +601,16 @@ hipError_t scores_prologue(const Dense& hidden, const LayerNorm& rows, int d, in
   const dim3 dense = few_rows_grid(a.hidden);
   a.dense_blocks = static_cast<int>(dense.x * dense.y), a.dense_cols = static_cast<int>(dense.y);
   a.image_blocks = plan_images(d, n_maps, widths, W, images, a.images);
-  const int64_t blocks = a.dense_blocks + a.image_blocks + (rows.rows * G + 255) / 256;
-  if (blocks > 0x7fffffff) {
-    *done = false;
-    return hipSuccess;
+  // Many rows keep a launch of their own: beside the hidden layer's LDS (three workgroups a compute unit) the normalisation
+  // does not reach the memory's rate.  Whole calls (64 candidates), with the rows inside | apart, us: 2048 workgroups of
+  // rows 59.2|61.4 (d = 256) and 50.1|50.5 (d = 128), 4096 64.1|63.0 and 55.7|53.2, 8192 85.7|78.7.
+  const int64_t row_blocks = (rows.rows * G + 255) / 256;
+  const bool apart = row_blocks > 8 * static_cast<int64_t>(compute_units());
+  if (apart) {
+    hipError_t e = layer_norm_rows(rows.X, rows.gamma, rows.beta, rows.eps, rows.Y, rows.rows, d, rows.lens, rows.rows_per_user, 1, s);
+    if (e != hipSuccess) return e;
   }
-  const dim3 grid(static_cast<unsigned>(blocks));
+  const dim3 grid(static_cast<unsigned>(a.dense_blocks + a.image_blocks + (apart ? 0 : row_blocks)));
   switch (G) {
 #define LIME_PROLOGUE_CASE(G_) case G_: hipLaunchKernelGGL(scores_prologue_kernel<G_>, grid, dim3(256), 0, s, a); break;
     LIME_PROLOGUE_CASE(4) LIME_PROLOGUE_CASE(8) LIME_PROLOGUE_CASE(16) LIME_PROLOGUE_CASE(32)

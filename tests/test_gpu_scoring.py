@@ -117,6 +117,7 @@ def _request(idx, B, N, C, d, h, m, dc, dhid, widths, dtype, len_range, plain_no
 @pytest.mark.parametrize("B,N,C,d,h,m,dc,dhid,widths,dtype", [
     (3, 333, 517, 128, 4, 64, 24, 96, [512, 128, 64, 1], "bf16"),
     (2, 257, 130, 256, 4, 32, 16, 128, [96, 1], "bf16"),
+    (3, 9000, 40, 256, 4, 32, 16, 64, [96, 1], "bf16"),   # history rows enough for a normalisation launch of their own
     (2, 100, 70, 48, 2, 20, 5, 30, [24, 1], "bf16"),      # everything on the general kernels
     (2, 150, 90, 64, 2, 16, 8, 40, [32, 16, 1], "fp32"),
 ])
