@@ -30,15 +30,18 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return 
 // 4-byte reads of a row of W (pitch TN + 8: the lane halves, four rows apart, fall on different banks).
 // What bounds it: at 16016 x 128 fp32 rows the matrix instruction (64 cycles per 32 x 32 x 2); at a few rows the launch.
 constexpr int kProjK = 32;
+struct ProjectJob {
+  const void* X;
+  const void* W;  // nullable = identity: X is copied
+  float* Y;
+  const int32_t* lens;  // nullable; rows of a user at or past its length need not be computed
+  int64_t rows;
+  int64_t rows_per_user;
+};
 struct ProjectArgs {
-  const void* X[kMaxProjections];
-  const void* W[kMaxProjections];  // nullable = identity: X is copied
-  float* Y[kMaxProjections];
-  const int32_t* lens[kMaxProjections];  // nullable; rows of a user at or past its length need not be computed
-  int64_t rows[kMaxProjections];
-  int rows_per_user[kMaxProjections];
-  int first_tile[kMaxProjections + 1];
-  int n, d;
+  int first_tile[kMaxProjections];  // of each job; past the last job the largest int
+  int d;
+  ProjectJob job[kMaxProjections];  // (a workgroup reads the first tiles and then its job: two scalar loads, one after the other)
 };
 
 template <typename T>
@@ -66,18 +69,21 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
   __shared__ __attribute__((aligned(16))) float ws[2][kProjK * WP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g = lane >> 5, d = a.d;
   int job = 0;
-  while (job + 1 < a.n && static_cast<int>(blockIdx.x) >= a.first_tile[job + 1]) ++job;  // uniform
+#pragma unroll
+  for (int i = 1; i < kMaxProjections; ++i) job += static_cast<int>(blockIdx.x) >= a.first_tile[i];
+  const ProjectJob j = a.job[job];
   const int tile = blockIdx.x - a.first_tile[job], col_tiles = (d + TN - 1) / TN;
-  const int64_t r0 = static_cast<int64_t>(tile / col_tiles) * TM, rows = a.rows[job];
+  const int64_t r0 = static_cast<int64_t>(tile / col_tiles) * TM, rows = j.rows;
   const int c0 = (tile % col_tiles) * TN;
-  if (a.lens[job] != nullptr) {  // a tile that holds one user's padding only is skipped: nothing reads it
-    const int64_t b = r0 / a.rows_per_user[job];
-    const int first = static_cast<int>(r0 - b * a.rows_per_user[job]);
-    if (first >= a.lens[job][b] && first + TM <= a.rows_per_user[job]) return;
+  if (j.lens != nullptr) {  // a tile that holds one user's padding only is skipped: nothing reads it
+    // (32-bit divisions where they do: a 64-bit one is a hundred instructions)
+    const int64_t b = rows <= 0x7fffffff ? static_cast<int64_t>(static_cast<int>(r0) / static_cast<int>(j.rows_per_user)) : r0 / j.rows_per_user;
+    const int first = static_cast<int>(r0 - b * j.rows_per_user);
+    if (first >= j.lens[b] && first + TM <= j.rows_per_user) return;
   }
-  const T* X = static_cast<const T*>(a.X[job]);
-  const T* W = static_cast<const T*>(a.W[job]);
-  float* Y = a.Y[job];
+  const T* X = static_cast<const T*>(j.X);
+  const T* W = static_cast<const T*>(j.W);
+  float* Y = j.Y;
   if (W == nullptr) {
     for (int i = tid; i < TM * TN; i += 256) {
       const int64_t row = r0 + i / TN;
@@ -698,17 +704,16 @@ hipError_t generic_project(const Projection* jobs, int n, int d, int dtype, hipS
   const int tn = d <= 32 ? 32 : 64, tm = 4096 / tn;
   bool vec = d % 8 == 0;
   int64_t tiles = 0;
+  int used = 0;
+  for (int i = 0; i < kMaxProjections; ++i) a.first_tile[i] = 0x7fffffff;
   for (int i = 0; i < n; ++i) {
     const Projection& j = jobs[i];
     if (j.rows <= 0) continue;
-    const int k = a.n++;
-    a.X[k] = j.X, a.W[k] = j.W, a.Y[k] = j.Y, a.lens[k] = j.lens, a.rows[k] = j.rows;
-    a.rows_per_user[k] = j.rows_per_user > 0 ? j.rows_per_user : 1;
-    a.first_tile[k] = static_cast<int>(tiles);
+    a.first_tile[used] = static_cast<int>(tiles);
+    a.job[used++] = ProjectJob{j.X, j.W, j.Y, j.lens, j.rows, j.rows_per_user > 0 ? j.rows_per_user : 1};
     vec = vec && ((reinterpret_cast<uintptr_t>(j.X) | reinterpret_cast<uintptr_t>(j.W)) & 15u) == 0;
     tiles += (j.rows + tm - 1) / tm * ((d + tn - 1) / tn);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    a.first_tile[k + 1] = static_cast<int>(tiles);
+    if (tiles >= 0x7fffffff) return hipErrorInvalidValue;
   }
   if (tiles == 0) return hipSuccess;
   return dtype == 0 ? launch_project<float>(a, static_cast<int>(tiles), vec, s) : launch_project<bf16_t>(a, static_cast<int>(tiles), vec, s);

@@ -7,28 +7,30 @@ namespace {
 
 constexpr int kMaxJobs = kMaxPackProjections, kMaxWeights = kMaxPackWeights;
 
+struct WeightJob {
+  const bf16_t* src;
+  bf16x8* img;
+  float sign;
+  int pad;
+};
+struct ProjectJob {
+  const bf16_t *x, *w, *gamma, *beta;  // gamma, beta: of the layer normalisation of a job's rows (norm set)
+  bf16_t* img;
+  int64_t stride;
+  int layout, norm;
+  float sign, eps;
+};
+// (a workgroup reads the numbers and then its job: two scalar loads, one after the other)
 struct PackArgs {
-  const bf16_t* w_src[kMaxWeights];
-  bf16x8* w_img[kMaxWeights];
-  float w_sign[kMaxWeights];
-  int w_pad[kMaxWeights];
-  const bf16_t* p_x[kMaxJobs];
-  const bf16_t* p_w[kMaxJobs];
-  bf16_t* p_img[kMaxJobs];
-  int64_t p_stride[kMaxJobs];
-  int p_layout[kMaxJobs];
-  float p_sign[kMaxJobs];
-  const bf16_t* p_gamma[kMaxJobs];  // layer normalisation of a job's rows before its projection (p_norm set)
-  const bf16_t* p_beta[kMaxJobs];
-  float p_eps[kMaxJobs];
-  int p_norm[kMaxJobs];
-  int p_first_unit[kMaxJobs + 1];   // ranges of the projection jobs' units, after the weight jobs
+  int n_weights, blocks_per_weight;
+  int d, dh, m;
+  int first_unit[kMaxJobs + 1];     // ranges of the projection jobs' units, after the weight jobs
   int units_per_block;              // of the projection jobs: 1 or 4
   const bf16_t *s_wq, *s_k, *s_wk;  // the score job (at most one), after the projection jobs
   bf16_t* s_img;
   float s_sign;
-  int n_weights, blocks_per_weight;
-  int d, dh, m;
+  WeightJob weight[kMaxWeights];
+  ProjectJob job[kMaxJobs];
 };
 
 // One wavefront of a score job: the 32 x 32 block (links 32lb.., rows j = 32jb..) of head a's
@@ -142,7 +144,7 @@ struct GroupRows {
 // What counts is the bytes a compute unit asks for, 64 a cycle: with four units a workgroup, each wavefront fetching its
 // rows as fragments (32 lines a load), the loads of the request's 32 units at d = 256 took 2.1 us to be issued.
 template <int D>
-__device__ __forceinline__ void project_unit(const PackArgs& p, int job, int unit) {
+__device__ __forceinline__ void project_unit(const PackArgs& p, const ProjectJob& job, int unit) {
   constexpr int NK = D / 16, CB = D / 32;
   constexpr bool kTogether = CB % 4 == 0;
   constexpr int kTurn = NK < 8 ? NK : 8;  // k-steps of W that a wavefront has in LDS at a time
@@ -153,12 +155,12 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lbs = m / 32, u = unit / (lbs * CB);
   const int lb = kTogether ? unit / CB % lbs : unit % lbs, cb = kTogether ? unit % CB : unit / lbs % CB;
-  const bf16_t* Xu = p.p_x[job] + u * p.p_stride[job];
-  const bf16_t* W = p.p_w[job];
+  const bf16_t* Xu = job.x + u * job.stride;
+  const bf16_t* W = job.w;
   const bool alone = kTogether && p.units_per_block == 1;  // uniform
   const int a = 32 * cb / dh, hc = 32 * cb % dh / 32;  // head, and 32-column block of the head
-  const bool keys = p.p_layout[job] == kPackKeys;
-  bf16x8* img = reinterpret_cast<bf16x8*>(p.p_img[job]);
+  const bool keys = job.layout == kPackKeys;
+  bf16x8* img = reinterpret_cast<bf16x8*>(job.img);
   bf16x8 lo, hi;  // the block's accumulators, or what they would be
   if (W == nullptr) {
     // the identity: the rows as they are (normalised rows always come with a weight)
@@ -169,7 +171,7 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
       lo[t] = __builtin_bit_cast(__bf16, element(chain_k(g, t)).bits);
       hi[t] = __builtin_bit_cast(__bf16, element(16 + chain_k(g, t)).bits);
     }
-    if (p.p_sign[job] < 0.f) lo = -lo, hi = -hi;
+    if (job.sign < 0.f) lo = -lo, hi = -hi;
   } else {
     const bf16_t* wrow = W + static_cast<int64_t>(lane / 4) * D + 32 * cb + 8 * (lane % 4);
     bf16x8 x[NK], w[NK], raw[NK];
@@ -190,14 +192,14 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
       }
     };
     if constexpr (kTogether) {
-      const bool norm = p.p_norm[job];
+      const bool norm = job.norm;
       GroupRows<D> group;
-      group.take(Xu + static_cast<int64_t>(32 * lb) * D, norm, p.p_gamma[job], p.p_beta[job]);
+      group.take(Xu + static_cast<int64_t>(32 * lb) * D, norm, job.gamma, job.beta);
       if (alone) {
         bf16x8 part[NK / 4];
 #pragma unroll
         for (int k = 0; k < NK / 4; ++k) part[k] = *reinterpret_cast<const bf16x8*>(wrow + 16 * (NK / 4 * wave + k) * D);
-        group.finish(rows_lds, norm, p.p_eps[job]);
+        group.finish(rows_lds, norm, job.eps);
 #pragma unroll
         for (int k = 0; k < NK / 4; ++k) *reinterpret_cast<bf16x8*>(turned + (NK / 4 * wave + k) * 1024 + lane * 16) = part[k];
         lds_barrier();
@@ -206,7 +208,7 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
         for (int kk = 0; kk < NK; ++kk) w[kk] = column_fragment(turned + kk * 1024, 64, lane);
       } else {
         take_weights();
-        group.finish(rows_lds, norm, p.p_eps[job]);
+        group.finish(rows_lds, norm, job.eps);
         lds_barrier();
         turn_weights();
       }
@@ -217,19 +219,19 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) x[kk] = *reinterpret_cast<const bf16x8*>(X + 16 * kk);
       bf16x8 gamma[NK], beta[NK];
-      if (p.p_norm[job]) {  // asked for with everything else
+      if (job.norm) {  // asked for with everything else
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
-          gamma[kk] = *reinterpret_cast<const bf16x8*>(p.p_gamma[job] + 16 * kk + 8 * g);
-          beta[kk] = *reinterpret_cast<const bf16x8*>(p.p_beta[job] + 16 * kk + 8 * g);
+          gamma[kk] = *reinterpret_cast<const bf16x8*>(job.gamma + 16 * kk + 8 * g);
+          beta[kk] = *reinterpret_cast<const bf16x8*>(job.beta + 16 * kk + 8 * g);
         }
       }
       take_weights();
-      if (p.p_norm[job]) normalise_rows<D>(x, gamma, beta, p.p_eps[job]);
+      if (job.norm) normalise_rows<D>(x, gamma, beta, job.eps);
       turn_weights();
     }
     f32x16 acc = keys ? project_block<NK>(w, x) : project_block<NK>(x, w);
-    if (p.p_sign[job] < 0.f) acc = -acc;
+    if (job.sign < 0.f) acc = -acc;
     lo = pack_half(acc, 0), hi = pack_half(acc, 1);
   }
   if (keys) {
@@ -241,7 +243,7 @@ __device__ __forceinline__ void project_unit(const PackArgs& p, int job, int uni
     // lane (column 32 cb + n, g), registers = the block's rows in chained order: k-steps 2 lb and 2 lb + 1
     const int64_t frag = ((static_cast<int64_t>(u) * (D / dh) + a) * (m / 16) + 2 * lb) * (dh / 32) + hc;
     const int slot = out_rho(n) + 32 * g;
-    const bool natural = p.p_layout[job] == kPackValuesNatural;
+    const bool natural = job.layout == kPackValuesNatural;
     img[frag * 64 + slot] = natural ? natural_from_chained(lo) : lo;
     img[(frag + dh / 32) * 64 + slot] = natural ? natural_from_chained(hi) : hi;
   }
@@ -260,7 +262,8 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     const int job = blk / p.blocks_per_weight;
     const int idx = (blk % p.blocks_per_weight) * 256 + tid;
     if (idx >= d * d / 8) return;
-    const bf16_t* W = p.w_src[job];
+    const WeightJob w = p.weight[job];
+    const bf16_t* W = w.src;
     const int col = idx % d, k0 = (idx / d) * 8;
     // (one uniform branch around all eight loads: a test per element would make each load wait for the one before)
     float x[8];
@@ -276,15 +279,15 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     }
     bf16x8 v;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(x[t] * p.w_sign[job]);
+    for (int t = 0; t < 8; ++t) v[t] = static_cast<__bf16>(x[t] * w.sign);
     const int a = col / dh, c = col % dh, mb = c / 32, n = c % 32;
     const int kk = k0 / 16, g = (k0 % 16) / 8;
     const int64_t frag = (static_cast<int64_t>(a) * (d / 16) + kk) * (dh / 32) + mb;
-    p.w_img[job][(frag + a * p.w_pad[job]) * 64 + 32 * g + n] = v;
+    w.img[(frag + a * w.pad) * 64 + 32 * g + n] = v;
     return;
   }
   blk -= p.n_weights * p.blocks_per_weight;
-  const int projection_blocks = (p.p_first_unit[kMaxJobs] + p.units_per_block - 1) / p.units_per_block;
+  const int projection_blocks = (p.first_unit[kMaxJobs] + p.units_per_block - 1) / p.units_per_block;
   if constexpr (SDH != 0) {
     if (blk >= projection_blocks) {  // uniform
       score_wave<SDH, SM, D / 32>(p, (blk - projection_blocks) * 4 + tid / 64);
@@ -292,10 +295,12 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     }
   }
   int unit = p.units_per_block == 1 ? blk : __builtin_amdgcn_readfirstlane(blk * 4 + tid / 64);
-  if (unit >= p.p_first_unit[kMaxJobs]) return;
+  if (unit >= p.first_unit[kMaxJobs]) return;
   int job = 0;
-  while (job + 1 < kMaxJobs && unit >= p.p_first_unit[job + 1]) ++job;
-  project_unit<D>(p, job, unit - p.p_first_unit[job]);
+#pragma unroll
+  for (int i = 1; i < kMaxJobs; ++i) job += unit >= p.first_unit[i];
+  const ProjectJob j = p.job[job];
+  project_unit<D>(p, j, unit - p.first_unit[job]);
 }
 
 }  // namespace
@@ -308,29 +313,20 @@ hipError_t pack_operands(const PackWeight* weights, int n_weights, const PackPro
   p.n_weights = n_weights;
   p.blocks_per_weight = (d * d / 8 + 255) / 256;
   for (int i = 0; i < n_weights; ++i) {
-    p.w_src[i] = static_cast<const bf16_t*>(weights[i].W);
-    p.w_img[i] = static_cast<bf16x8*>(weights[i].image);
-    p.w_sign[i] = weights[i].sign;
-    p.w_pad[i] = weights[i].head_pad;
+    p.weight[i] = WeightJob{static_cast<const bf16_t*>(weights[i].W), static_cast<bf16x8*>(weights[i].image), weights[i].sign, weights[i].head_pad};
   }
   int units = 0;
   for (int i = 0; i < kMaxJobs; ++i) {
-    p.p_first_unit[i] = units;
+    p.first_unit[i] = units;
     if (i < n_projections) {
-      p.p_x[i] = static_cast<const bf16_t*>(projections[i].X);
-      p.p_w[i] = static_cast<const bf16_t*>(projections[i].W);
-      p.p_img[i] = static_cast<bf16_t*>(projections[i].image);
-      p.p_stride[i] = projections[i].user_stride;
-      p.p_layout[i] = projections[i].layout;
-      p.p_sign[i] = projections[i].sign;
-      p.p_norm[i] = projections[i].norm.on ? 1 : 0;
-      p.p_gamma[i] = static_cast<const bf16_t*>(projections[i].norm.gamma);
-      p.p_beta[i] = static_cast<const bf16_t*>(projections[i].norm.beta);
-      p.p_eps[i] = projections[i].norm.eps;
-      units += projections[i].users * (m / 32) * (d / 32);
+      const PackProject& q = projections[i];
+      p.job[i] = ProjectJob{static_cast<const bf16_t*>(q.X), static_cast<const bf16_t*>(q.W), static_cast<const bf16_t*>(q.norm.gamma),
+                            static_cast<const bf16_t*>(q.norm.beta), static_cast<bf16_t*>(q.image), q.user_stride, q.layout, q.norm.on ? 1 : 0,
+                            q.sign, q.norm.eps};
+      units += q.users * (m / 32) * (d / 32);
     }
   }
-  p.p_first_unit[kMaxJobs] = units;
+  p.first_unit[kMaxJobs] = units;
   // A unit per workgroup as long as every workgroup then has a compute unit to itself; project_unit takes four from there on.
   p.units_per_block = d >= 128 && units <= compute_units() ? 1 : 4;
   int grid = n_weights * p.blocks_per_weight + (units + p.units_per_block - 1) / p.units_per_block;
