@@ -283,7 +283,8 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
     const int a = col / dh, c = col % dh, mb = c / 32, n = c % 32;
     const int kk = k0 / 16, g = (k0 % 16) / 8;
     const int64_t frag = (static_cast<int64_t>(a) * (d / 16) + kk) * (dh / 32) + mb;
-    w.img[(frag + a * w.pad) * 64 + 32 * g + n] = v;
+    // (768 KiB of a request's images at d = 256: written through, 19.6 -> 19.4 us a pass with 16 candidates)
+    store_through(w.img, d * d * 2 + (d / dh) * w.pad * 1024, static_cast<int>(((frag + a * w.pad) * 64 + 32 * g + n) * 16), v);
     return;
   }
   blk -= p.n_weights * p.blocks_per_weight;
