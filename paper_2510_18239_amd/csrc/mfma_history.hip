@@ -474,27 +474,33 @@ struct MergeRow {
 };
 
 // The same by one thread for its four columns, kMergeGroups chunks at a time: for calls with many rows, whose threads have
-// few chunks each.
-template <int PHI, int D>
+// few chunks each.  The maxima and sums of a batch are asked for together and stay in registers, and a group's partials are
+// asked for during the group before (lime_request_prepared, 512 candidates, against reading the maxima group by group and
+// again: 41.5 -> 39.6 us at B=5 N=13000 d=128 h=2 m=128, 36.7 -> 35.8 at B=3 N=8000 d=256 m=96, 31.9 -> 31.4 at B=4 N=4096
+// d=256 m=128).  GROUPS: of a batch; 1 where a history has no more than kMergeGroups chunks, which the registers of the
+// general form would slow (16.6 | 17.1 us at B=5 N=300 d=256 m=64, 15.1 | 15.7 at B=16 N=1024 d=128).
+template <int PHI, int D, int GROUPS>
 struct MergeQuad {
+  static constexpr int kBatch = GROUPS * kMergeGroups;
+  static_assert(kBatch == kMergeBatch || GROUPS == 1, "batches as in MergeRow, or one group and no other");
   int64_t first, stride;
   int link, quad;
-  float2 ml[kMergeGroups];
+  float2 ml[kMergeGroups];  // of the first group of a batch
   float4 ac[kMergeGroups];
-  __device__ __forceinline__ void ask_ml(const MergeArgs& a, int c0) {
+  __device__ __forceinline__ void ask_ml(const MergeArgs& a, int c0, float2* to) {
 #pragma unroll
-    for (int q = 0; q < kMergeGroups; ++q) ml[q] = *reinterpret_cast<const float2*>(a.part_ml + (first + min(c0 + q, a.chunks - 1) * stride) * 2);
+    for (int q = 0; q < kMergeGroups; ++q) to[q] = *reinterpret_cast<const float2*>(a.part_ml + (first + min(c0 + q, a.chunks - 1) * stride) * 2);
   }
-  __device__ __forceinline__ void ask(const MergeArgs& a, int c0) {
+  __device__ __forceinline__ void ask(const MergeArgs& a, int c0, float4* to) {
 #pragma unroll
     for (int q = 0; q < kMergeGroups; ++q)
-      ac[q] = *reinterpret_cast<const float4*>(a.part_acc + (first + min(c0 + q, a.chunks - 1) * stride) * a.dh + 4 * quad % a.dh);
+      to[q] = *reinterpret_cast<const float4*>(a.part_acc + (first + min(c0 + q, a.chunks - 1) * stride) * a.dh + 4 * quad % a.dh);
   }
   __device__ __forceinline__ void begin(const MergeArgs& a, int b, int link_, int quad_) {
     link = link_, quad = quad_, stride = static_cast<int64_t>(a.h) * a.m;
     first = (static_cast<int64_t>(b) * a.chunks * a.h + 4 * quad / a.dh) * a.m + link;
-    if (PHI == kPhiSoftmax) ask_ml(a, 0);
-    ask(a, 0);
+    if (PHI == kPhiSoftmax) ask_ml(a, 0, ml);
+    ask(a, 0, ac);
   }
   __device__ __forceinline__ float4 finish(const MergeArgs& a, int len) {
     const int used = (len + a.chunk_items - 1) / a.chunk_items;
@@ -502,33 +508,49 @@ struct MergeQuad {
     float den[kMergeGroups], top = -INFINITY;
 #pragma unroll
     for (int q = 0; q < kMergeGroups; ++q) num[q] = make_float4(0.f, 0.f, 0.f, 0.f), den[q] = 0.f;
-    for (int c0 = 0; c0 < used; c0 += kMergeGroups) {  // uniform
-      if (PHI == kPhiSoftmax && c0 % kMergeBatch == 0) {
-        float batch_top = top;
-        for (int c1 = c0; c1 < min(used, c0 + kMergeBatch); c1 += kMergeGroups) {
-          if (c1 > 0) ask_ml(a, c1);
+    for (int c0 = 0; c0 < (GROUPS > 1 ? used : min(used, 1)); c0 += kBatch) {  // uniform, as every branch on `used` below
+      float2 m[kBatch];
+      if (c0 > 0) {
+        if (PHI == kPhiSoftmax) ask_ml(a, c0, ml);
+        ask(a, c0, ac);
+      }
+      float4 next[kMergeGroups];
+      if (PHI == kPhiSoftmax) {
 #pragma unroll
-          for (int q = 0; q < kMergeGroups; ++q) batch_top = fmaxf(batch_top, c1 + q < used ? ml[q].x : -INFINITY);
-        }
+        for (int q = 0; q < kBatch; ++q) m[q] = q < kMergeGroups ? ml[q % kMergeGroups] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+        for (int c = kMergeGroups; c < kBatch; c += kMergeGroups)
+          if (c0 + c < used) ask_ml(a, c0 + c, m + c);
+      }
+      if (GROUPS > 1 && c0 + kMergeGroups < used) ask(a, c0 + kMergeGroups, next);
+      if (PHI == kPhiSoftmax) {
+        float batch_top = top;
+#pragma unroll
+        for (int c = 0; c < kBatch; ++c) batch_top = fmaxf(batch_top, c0 + c < used ? m[c].x : -INFINITY);
         const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
 #pragma unroll
         for (int q = 0; q < kMergeGroups; ++q) num[q].x *= keep, num[q].y *= keep, num[q].z *= keep, num[q].w *= keep, den[q] *= keep;
         top = batch_top;
-        if (used - c0 > kMergeGroups) ask_ml(a, c0);  // (the maxima of the batch's other chunks were read over them)
-      } else if (PHI == kPhiSoftmax) {
-        ask_ml(a, c0);
       }
-      if (c0 > 0) ask(a, c0);
 #pragma unroll
-      for (int q = 0; q < kMergeGroups; ++q) {
-        if (c0 + q >= used) continue;  // uniform
-        if (PHI == kPhiSoftmax) {
-          const float w = __builtin_amdgcn_exp2f((ml[q].x - top) * kLog2e);
-          num[q].x = fmaf(w, ac[q].x, num[q].x), num[q].y = fmaf(w, ac[q].y, num[q].y);
-          num[q].z = fmaf(w, ac[q].z, num[q].z), num[q].w = fmaf(w, ac[q].w, num[q].w);
-          den[q] = fmaf(w, ml[q].y, den[q]);
-        } else {
-          num[q].x += ac[q].x, num[q].y += ac[q].y, num[q].z += ac[q].z, num[q].w += ac[q].w;
+      for (int c = 0; c < kBatch; c += kMergeGroups) {
+        if (c0 + c >= used) break;
+        if (c > 0) {
+#pragma unroll
+          for (int q = 0; q < kMergeGroups; ++q) ac[q] = next[q];
+          if (c + kMergeGroups < kBatch && c0 + c + kMergeGroups < used) ask(a, c0 + c + kMergeGroups, next);
+        }
+#pragma unroll
+        for (int q = 0; q < kMergeGroups; ++q) {
+          if (c0 + c + q >= used) continue;
+          if (PHI == kPhiSoftmax) {
+            const float w = __builtin_amdgcn_exp2f((m[c + q].x - top) * kLog2e);
+            num[q].x = fmaf(w, ac[q].x, num[q].x), num[q].y = fmaf(w, ac[q].y, num[q].y);
+            num[q].z = fmaf(w, ac[q].z, num[q].z), num[q].w = fmaf(w, ac[q].w, num[q].w);
+            den[q] = fmaf(w, m[c + q].y, den[q]);
+          } else {
+            num[q].x += ac[q].x, num[q].y += ac[q].y, num[q].z += ac[q].z, num[q].w += ac[q].w;
+          }
         }
       }
     }
@@ -564,10 +586,10 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(MergeArgs a) {
 
 // A thread per four columns of a link state.
 constexpr int kMergeManyThreads = 64;
-template <int PHI, int D>
+template <int PHI, int D, int GROUPS>
 __global__ __launch_bounds__(kMergeManyThreads) void merge_many_kernel(MergeArgs a) {
   const int b = blockIdx.y, idx = blockIdx.x * kMergeManyThreads + threadIdx.x;  // (m d / 4 is a multiple of 64)
-  MergeQuad<PHI, D> task;
+  MergeQuad<PHI, D, GROUPS> task;
   task.begin(a, b, idx / (D / 4), idx % (D / 4));
   const int len = a.lens ? min(a.lens[b], a.N) : a.N;
   store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + task.link) * D + 4 * task.quad, task.finish(a, len));
@@ -677,7 +699,7 @@ struct MergeTile {
   static constexpr int kRows = ROWS, NK = D / 16, kWaves = D / 32, kPitch = D + 8, kTasks = kRows * (D / 4) / (2 * D);
   static constexpr int kLds = kWaves * NK * 1024 + kRows * kPitch * 2;
 };
-template <int PHI, int D, int ROWS>
+template <int PHI, int D, int ROWS, int GROUPS>
 __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArgs a) {
   using T = MergeTile<PHI, D, ROWS>;
   constexpr int NK = T::NK, kTasks = T::kTasks, kQuads = D / 4;
@@ -686,7 +708,7 @@ __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArg
   const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = blockIdx.y, link0 = blockIdx.x * T::kRows, dh = a.m.dh;
   unsigned char* const mine = lds + wave * NK * 1024;
-  MergeQuad<PHI, D> task[kTasks];
+  MergeQuad<PHI, D, GROUPS> task[kTasks];
 #pragma unroll
   for (int i = 0; i < kTasks; ++i) {
     const int idx = threadIdx.x + i * 2 * D;
@@ -802,20 +824,28 @@ template <int PHI, int D>
 hipError_t launch_merge(const MergeArgs& a, int users, hipStream_t s) {
   if (few_rows(static_cast<int64_t>(users) * a.m, D))
     hipLaunchKernelGGL((merge_kernel<PHI, D>), dim3(a.m, users), dim3(2 * D), 0, s, a);
+  else if (a.chunks <= kMergeGroups)
+    hipLaunchKernelGGL((merge_many_kernel<PHI, D, 1>), dim3(a.m * (D / 4) / kMergeManyThreads, users), dim3(kMergeManyThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((merge_many_kernel<PHI, D>), dim3(a.m * (D / 4) / kMergeManyThreads, users), dim3(kMergeManyThreads), 0, s, a);
+    hipLaunchKernelGGL((merge_many_kernel<PHI, D, kMergeBatch / kMergeGroups>), dim3(a.m * (D / 4) / kMergeManyThreads, users), dim3(kMergeManyThreads), 0, s, a);
   return hipGetLastError();
 }
 
-template <int PHI, int D, int ROWS>
+template <int PHI, int D, int ROWS, int GROUPS>
 hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStream_t s) {
   using T = MergeTile<PHI, D, ROWS>;
+  auto kernel = merge_values_tile_kernel<PHI, D, ROWS, GROUPS>;
   if (T::kLds > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_values_tile_kernel<PHI, D, ROWS>), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
     if (attr != hipSuccess) return attr;
   }
-  hipLaunchKernelGGL((merge_values_tile_kernel<PHI, D, ROWS>), dim3(a.m.m / ROWS, users), dim3(2 * D), T::kLds, s, a);
+  hipLaunchKernelGGL(kernel, dim3(a.m.m / ROWS, users), dim3(2 * D), T::kLds, s, a);
   return hipGetLastError();
+}
+template <int PHI, int D, int ROWS>
+hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStream_t s) {
+  return a.m.chunks <= kMergeGroups ? launch_merge_values_tile<PHI, D, ROWS, 1>(a, users, s)
+                                    : launch_merge_values_tile<PHI, D, ROWS, kMergeBatch / kMergeGroups>(a, users, s);
 }
 template <int PHI, int D>
 hipError_t launch_merge_values(const MergeValuesArgs& a, int users, hipStream_t s) {
