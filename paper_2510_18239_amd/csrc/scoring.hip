@@ -315,7 +315,7 @@ hipError_t launch_dense(const DenseArgs& a, hipStream_t s) {
 //   layer i (d_in x d_out, d_out a multiple of 32): fragment (cb, kk), lane (n, g), slot t = W_i[16kk + k(g, t)][32cb + n],
 //   k(g, t) = 8g + t for the first layer (its B operand is read from memory in natural order) and chain_k(g, t) for the
 //   others (their B operand is the previous layer's accumulators).
-//   The layers' images follow each other without a gap: one stream of fragments.
+//   The layers' images follow each other without a gap: one stream of fragments, in the order of their products (MlpStream).
 struct MlpArgs {
   const bf16_t* O;        // [rows][D]
   float* scores;          // [rows]
@@ -331,6 +331,9 @@ __device__ __forceinline__ void for_each_of(std::integer_sequence<int, I...>, F 
   (f(std::integral_constant<int, I>{}), ...);
 }
 
+// Blocks of a layer of this width whose products alternate: two, three where the number of blocks is odd.
+__host__ __device__ constexpr int mlp_group(int width) { return width / 32 % 2 == 0 ? 2 : 3; }
+
 // Where fragment f of the stream belongs.
 template <int D, int H1, int H2, int H3>
 struct MlpStream {
@@ -340,11 +343,19 @@ struct MlpStream {
   static constexpr int kLast = H3 > 0 ? 2 : H2 > 0 ? 1 : 0;    // its number
   static constexpr int layer(int f) { return f < kF1 ? 0 : f < kF1 + kF2 ? 1 : 2; }
   static constexpr int in_layer(int f) { return f < kF1 ? f : f < kF1 + kF2 ? f - kF1 : f - kF1 - kF2; }
+  static constexpr int width(int l) { return l == 0 ? H1 : l == 1 ? H2 : H3; }
   static constexpr int k_steps(int f) { return (layer(f) == 0 ? D : layer(f) == 1 ? H1 : H2) / 16; }
-  static constexpr int block(int f) { return in_layer(f) / k_steps(f); }  // 32-column block of the layer's output
-  static constexpr int k(int f) { return in_layer(f) % k_steps(f); }
-  static constexpr int nth(int f) { return block(f) + (layer(f) > 0 ? H1 / 32 : 0) + (layer(f) > 1 ? H2 / 32 : 0); }  // of all blocks
+  // A layer's 32-column blocks are taken in groups, and within a group in turn, k-step by k-step (mlp_group).
+  static constexpr int members(int f) { return mlp_group(width(layer(f))); }
+  static constexpr int group(int f) { return in_layer(f) / (k_steps(f) * members(f)); }
+  static constexpr int in_group(int f) { return in_layer(f) % (k_steps(f) * members(f)); }
+  static constexpr int k(int f) { return in_group(f) / members(f); }
+  static constexpr int member(int f) { return in_group(f) % members(f); }
+  static constexpr int block(int f) { return group(f) * members(f) + member(f); }  // 32-column block of the layer's output
+  static constexpr int groups(int l) { return width(l) > 0 ? width(l) / 32 / mlp_group(width(l)) : 0; }
+  static constexpr int nth(int f) { return group(f) + (layer(f) > 0 ? groups(0) : 0) + (layer(f) > 1 ? groups(1) : 0); }  // of all groups
   static constexpr int bias_at(int f) { return (layer(f) == 0 ? 0 : layer(f) == 1 ? H1 : H1 + H2) + 32 * block(f); }
+  static_assert(H1 / 32 % mlp_group(H1) == 0 && H2 / 32 % mlp_group(H2) == 0 && H3 / 32 % mlp_group(H3) == 0, "whole groups");
   // The stream travels in chunks of kChunk fragments through kBuffers parts of LDS.
   static constexpr int kChunk = 16, kChunks = (kFrags + kChunk - 1) / kChunk, kBuffers = 6;
   static constexpr int kTable = H1 + H2 + H3 + HL;  // biases of the hidden layers, then the last map's weights
@@ -354,8 +365,9 @@ struct MlpStream {
 // A 32-column block of a layer's weight image is the A operand of all four wavefronts, a wavefront's 32 rows the B operand.
 // The fragments go from L2 straight to LDS, a quarter of a chunk per wavefront, kBuffers chunks ahead of their products
 // (a chunk's products are 0.3 us, a fetch from L2 several times that), and from LDS to registers one chunk ahead, a read
-// between every two products.  Products alternate between two accumulators (into one, each waits for the one before: 51
-// instead of 37 cycles), and a finished block is rounded and packed between the next block's products.
+// between every two products.  Products alternate between two blocks (into one accumulator, each would wait for the one
+// before: 51 instead of 37 cycles; a block's sums still start at the bias and take their k-steps in ascending order, in one
+// accumulator), and a finished block is rounded and packed between the next blocks' products.
 // What bounds it: one wavefront per SIMD (registers), so matrix cores and everything else take turns; LDS reads, 4 KiB per
 // product of the four wavefronts, take as long as the product.  32 768 rows of 256 -> 512 -> 128 -> 64 -> 1: 16 us (13.4
 // GFLOP, 0.84 PFLOP/s), 22 us with a chunk's fragments all read before the first of its products, into one accumulator.
@@ -392,7 +404,7 @@ __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
 
   bf16x8 h1[H1 / 16], h2[H2 > 0 ? H2 / 16 : 1], af[2][kChunk];
   f32x16 last[HL / 32];  // the last hidden layer stays in fp32: one accumulator block per 32 columns
-  f32x16 acc[2][2];
+  f32x16 acc[2][3];      // of a group of blocks, and of the one before; [group][member]
   auto publish = [&](auto c_tag) {  // chunk c has landed everywhere, and every wavefront has read chunk c - 1
     constexpr int c = decltype(c_tag)::value, asked = std::min(c + kBuffers - (c > 0 ? 2 : 1), S::kChunks - 1);
     wait_lds_loads<(asked - c) * PER>();  // all but the chunks behind it
@@ -403,7 +415,7 @@ __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
   for (int i = 0; i < kChunk; ++i) af[0][i] = stage[i * 64 + lane];
   auto finish = [&](auto f_tag) {  // f: the block's last fragment
     constexpr int f = decltype(f_tag)::value, layer = S::layer(f), block = S::block(f);
-    f32x16 done = acc[S::nth(f) & 1][0] + acc[S::nth(f) & 1][1];
+    f32x16 done = acc[S::nth(f) & 1][S::member(f)];
 #pragma unroll
     for (int j = 0; j < 16; ++j) done[j] = fmaxf(done[j], 0.f);
     if constexpr (layer == S::kLast) last[block] = done;
@@ -412,7 +424,7 @@ __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
   };
   for_each_of(std::make_integer_sequence<int, S::kFrags>{}, [&](auto f_tag) {
     constexpr int f = decltype(f_tag)::value, c = f / kChunk, i = f % kChunk, layer = S::layer(f), k = S::k(f);
-    f32x16(&sum)[2] = acc[S::nth(f) & 1];
+    f32x16& sum = acc[S::nth(f) & 1][S::member(f)];
     if constexpr (i == 0 && c + 1 < S::kChunks) {
       publish(std::integral_constant<int, c + 1>{});
       if constexpr (c + kBuffers < S::kChunks) fetch(c + kBuffers);  // over chunk c, which is in registers
@@ -421,19 +433,24 @@ __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {  // registers 4j .. 4j+3 are columns 32 block + 8j + 4g + 0..3
         const float4 b4 = *reinterpret_cast<const float4*>(&tab[S::bias_at(f) + 8 * j + 4 * g]);
-        sum[0][4 * j] = b4.x, sum[0][4 * j + 1] = b4.y, sum[0][4 * j + 2] = b4.z, sum[0][4 * j + 3] = b4.w;
+        sum[4 * j] = b4.x, sum[4 * j + 1] = b4.y, sum[4 * j + 2] = b4.z, sum[4 * j + 3] = b4.w;
       }
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sum[1][j] = 0.f;
     }
-    if constexpr (layer == 0) sum[k & 1] = mfma32(af[c & 1][i], xb[k], sum[k & 1]);
-    else if constexpr (layer == 1) sum[k & 1] = mfma32(af[c & 1][i], h1[k], sum[k & 1]);
-    else sum[k & 1] = mfma32(af[c & 1][i], h2[k], sum[k & 1]);
+    if constexpr (layer == 0) sum = mfma32(af[c & 1][i], xb[k], sum);
+    else if constexpr (layer == 1) sum = mfma32(af[c & 1][i], h1[k], sum);
+    else sum = mfma32(af[c & 1][i], h2[k], sum);
     if constexpr (c + 1 < S::kChunks) af[(c + 1) & 1][i] = stage[((c + 1) % kBuffers * kChunk + i) * 64 + lane];
-    if constexpr (S::nth(f) > 0 && k == (S::k_steps(f) > 4 ? 3 : 1)) finish(std::integral_constant<int, f - k - 1>{});
+    // the group before: its first block a k-step into this one, its second a step later (no layer's first k-steps need either)
+    if constexpr (S::nth(f) > 0 && S::member(f) + 1 == S::members(f)) {
+      constexpr int end = f - S::in_group(f) - 1, steps = S::k_steps(f);  // end: its last fragment
+      static_assert(S::members(end) == 2, "only a network's last group has three blocks");
+      if constexpr (k == 1) finish(std::integral_constant<int, end - 1>{});
+      if constexpr (k == (steps > 2 ? 2 : 1)) finish(std::integral_constant<int, end>{});
+    }
     __builtin_amdgcn_sched_barrier(0);
   });
-  finish(std::integral_constant<int, S::kFrags - 1>{});
+  for_each_of(std::make_integer_sequence<int, S::members(S::kFrags - 1)>{},
+              [&](auto j_tag) { finish(std::integral_constant<int, S::kFrags - S::members(S::kFrags - 1) + decltype(j_tag)::value>{}); });
   // the logit: a dot product over the last hidden layer (this lane holds the columns 32cb + 8j + 4g + r)
   float s = 0.f;
 #pragma unroll
@@ -462,7 +479,8 @@ __device__ __forceinline__ void mlp_pack(const MlpPackArgs& p, int blk) {
   const int idx = blk * 256 + threadIdx.x;  // one 16-byte slot of the image
   if (idx >= din * dout / 8) return;
   const int lane = idx % 64, frag = idx / 64, n = lane & 31, g = lane >> 5;
-  const int kk = frag % (din / 16), cb = frag / (din / 16);
+  const int members = mlp_group(dout), group = frag / (din / 16 * members), in_group = frag % (din / 16 * members);
+  const int kk = in_group / members, cb = group * members + in_group % members;
   bf16x8 v;
 #pragma unroll
   for (int t = 0; t < 8; ++t) {

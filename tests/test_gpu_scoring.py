@@ -69,6 +69,40 @@ def test_interaction_mlp(dtype, rows, d, widths):
     assert_close(scores.double().cpu().numpy(), orc.interaction_mlp(O, Ws, [np.zeros_like(b) for b in bs]), dtype, "scores without biases")
 
 
+@pytest.mark.parametrize("d,widths", [(256, [512, 128, 64, 1]), (128, [512, 256, 128, 1]), (32, [512, 256, 128, 1]), (256, [96, 1]), (64, [96, 1])])
+def test_interaction_mlp_sums_a_unit_in_one_chain(d, widths):
+    """A hidden unit's sum takes its k-steps of 16 in ascending order into one accumulator: 2^24, which absorbs the ones of the
+    steps between, minus 2^24 is zero.  (In two accumulators the ones of every other step would be left over.)  Every product and
+    every sum is exact in fp32 but the absorbed ones, so the score is the last bias, exactly."""
+    dims = [d] + widths
+    for layer in range(len(widths) - 1):
+        K = dims[layer]
+        x, w = torch.zeros(K), torch.zeros(K)
+        x[::16] = w[::16] = 1.0
+        x[0] = x[K - 16] = w[0] = 4096.0
+        w[K - 16] = -4096.0
+        Ws = []
+        for i in range(len(widths)):
+            W = torch.zeros(dims[i], dims[i + 1])
+            if i + 1 == layer:
+                W[0] = x         # the first unit, which is one, on to the inputs of the layer in question
+            elif i == layer:
+                W[:] = w[:, None]
+            elif i > layer:
+                W[:] = 1.0
+            else:
+                W[0, 0] = 1.0
+            Ws.append(W.bfloat16().cuda())
+        O = torch.zeros(130, d)
+        if layer == 0:
+            O[:] = x
+        else:
+            O[:, 0] = 1.0
+        bias = [None] * (len(widths) - 1) + [torch.tensor([3.0], device="cuda").bfloat16()]
+        scores = binding.lime_interaction_mlp(O.bfloat16().cuda(), Ws, bias)
+        assert (scores == 3.0).all(), (layer, scores.unique())
+
+
 def _request(idx, B, N, C, d, h, m, dc, dhid, widths, dtype, len_range, plain_norm=None, lens=None):
     w = synth.make_workload(idx, B=B, N=N, C=C, d=d, h=h, m=m, dtype=dtype, gain=4.0, len_range=len_range,
                             pad_value=np.nan if len_range else None)
