@@ -75,6 +75,13 @@ __device__ __forceinline__ float group_sum(float x) {
   }
   return x;
 }
+// The largest value of a 16-lane row, in every lane of it.
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_rotated<8>(x));
+  x = fmaxf(x, row_rotated<4>(x));
+  x = fmaxf(x, row_rotated<2>(x));
+  return fmaxf(x, row_rotated<1>(x));
+}
 
 __device__ __forceinline__ float wave_sum(float x) { return pair_sum(group_sum<32>(x)); }
 

@@ -355,25 +355,26 @@ struct MergeArgs {
   float scale;  // |logit scale|: the factor the SiLU partials still lack
 };
 
-// The merged link states of a user's chunks, one row LP[b][link] at a time by a workgroup of 2 d threads: thread
-// (quad, group) has four adjacent columns and every eighth chunk, kMergeBatch chunks at a time.  The sum over the chunks is
-// eight sums (chunk c in sum c % 8, ascending), added in pairs: the same in every kernel, so that a link state has the same
-// bits whichever of them finishes it.
-// The partials were written by other compute units and every read of them is a long-latency miss: all reads of a batch are
-// asked for before any is used, whether or not a user has that many chunks (what lies past its last one is left out of the
-// sums, and need not have been written), and the chunks' maxima and sums are read once per row and handed round in LDS.
-// (With two batches of 16 chunks one after the other in 128 threads, this took 3.5 of a merge_values_kernel's 5.9 us between
-// its first and last instruction, at B=1 N=2048 d=256 m=64; 1.2 of 3.6 so.)
-constexpr int kMergeBatch = 32, kMergeGroups = 8;
+// The merged link states of a user's chunks, one row LP[b][link] at a time by a workgroup of 2 d threads.  The sum over the
+// chunks is one chain in ascending order per column, relative to a maximum that moves once per kMergeSpan chunks: the same in
+// every kernel, so that a link state has the same bits whichever of them finishes it.
+// The partials were written by other compute units and every read of them is a long-latency miss: thread (quad, group) asks
+// for four adjacent columns of every eighth chunk, all reads of a batch of kMergeBatch before any is used, whether or not a
+// user has that many chunks (what lies past its last one counts as zero, and need not have been written).  They meet in LDS,
+// where thread (head, chunk) has left the chunk's weight, and a thread per column takes the chain.
+// (With two batches of 16 chunks one after the other in 128 threads, each reading its columns of every chunk from memory, this
+// took 3.5 of a merge_values_kernel's 5.9 us between its first and last instruction, at B=1 N=2048 d=256 m=64.)
+constexpr int kMergeBatch = 32, kMergeSpan = 16, kMergeGroups = 8;
 template <int PHI, int D>
 struct MergeRow {
   static constexpr int kThreads = 2 * D, kQuads = D / 4, kLoads = kMergeBatch / kMergeGroups, kMaxHeads = D / 32;
   static constexpr int kMlPitch = kMergeBatch + 4;
+  static_assert(kThreads == kQuads * kMergeGroups && 32 * kMaxHeads <= kThreads, "every chunk and every (head, chunk) has its thread");
   struct Lds {
-    float top[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];  // the chunks' maxima, by head
+    float part[kMergeBatch * D];
+    float w[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];  // the chunks' weights and sums, by head
     float sum[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];
-    float4 num[(kMergeGroups - 1) * kQuads];
-    float den[PHI == kPhiSoftmax ? (kMergeGroups - 1) * kQuads : 1];
+    float keep[PHI == kPhiSoftmax ? kMaxHeads * 2 : 1];      // what a span leaves of the sums before it
   };
   float4 ac[kLoads];
   float2 ml;
@@ -398,78 +399,62 @@ struct MergeRow {
       ac[i] = *reinterpret_cast<const float4*>(
           a.part_acc + (first + head * a.m + min(c0 + group + kMergeGroups * i, a.chunks - 1) * stride) * a.dh + 4 * quad % a.dh);
   }
-  // the finished values, in the threads of the first group
-  __device__ __forceinline__ float4 finish(const MergeArgs& a, int len, Lds& lds) {
+  // the finished value of column threadIdx.x, in the first D threads
+  __device__ __forceinline__ float finish(const MergeArgs& a, int len, Lds& lds) {
     const int used = (len + a.chunk_items - 1) / a.chunk_items;  // chunks that hold at least one valid item
-    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    float top = -INFINITY, den = 0.f;
+    const int col = threadIdx.x, col_head = min(col, D - 1) / a.dh;
+    float num = 0.f, den = 0.f, top = -INFINITY;
     for (int c0 = 0; c0 < used; c0 += kMergeBatch) {  // uniform
-      if (c0 > 0) ask(a, c0);
-      float w[kLoads];
-      if (PHI == kPhiSoftmax) {
-        if (c0 > 0) lds_barrier();  // the last batch's have been read
-        const int hd = threadIdx.x / kMergeBatch, c = threadIdx.x % kMergeBatch;
-        if (hd < a.h) {
-          lds.top[hd * kMlPitch + c] = c0 + c < used ? ml.x : -INFINITY;
-          lds.sum[hd * kMlPitch + c] = c0 + c < used ? ml.y : 0.f;
-        }
-        lds_barrier();
-        float batch_top = top;
-#pragma unroll
-        for (int i = 0; i < kMergeBatch; i += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(&lds.top[head * kMlPitch + i]);
-          batch_top = fmaxf(batch_top, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
-        }
-        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
-        num.x *= keep, num.y *= keep, num.z *= keep, num.w *= keep;
-        den *= keep;
-        top = batch_top;
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-          const int at = head * kMlPitch + group + kMergeGroups * i;
-          w[i] = c0 + group + kMergeGroups * i < used ? __builtin_amdgcn_exp2f((lds.top[at] - top) * kLog2e) : 0.f;
-          den = fmaf(w[i], lds.sum[at], den);
-        }
+      if (c0 > 0) {
+        ask(a, c0);
+        lds_barrier();  // the last batch's have been read
       }
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        if (c0 + group + kMergeGroups * i >= used) continue;
+        const int c = group + kMergeGroups * i;
+        *reinterpret_cast<float4*>(&lds.part[c * D + 4 * quad]) = c0 + c < used ? ac[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      if (PHI == kPhiSoftmax) {
+        const int hd = threadIdx.x / kMergeBatch, c = threadIdx.x % kMergeBatch;  // (a head's two spans are two 16-lane rows)
+        const bool live = c0 + c < used;
+        const float x = live ? ml.x : -INFINITY, span = row_max(x);
+        const u32x2 rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(span), __float_as_uint(span), false, false);
+        const float top0 = fmaxf(top, __uint_as_float(rows[0])), top1 = fmaxf(top0, __uint_as_float(rows[1]));
+        const float before = c < kMergeSpan ? top : top0, now = c < kMergeSpan ? top0 : top1;
+        if (hd < a.h) {
+          lds.w[hd * kMlPitch + c] = live ? __builtin_amdgcn_exp2f((x - now) * kLog2e) : 0.f;
+          lds.sum[hd * kMlPitch + c] = live ? ml.y : 0.f;
+          if (c % kMergeSpan == 0) lds.keep[hd * 2 + c / kMergeSpan] = __builtin_amdgcn_exp2f((before - now) * kLog2e);  // 0 on the first
+        }
+        top = top1;
+      }
+      lds_barrier();
+      if (col >= D) continue;
+#pragma unroll
+      for (int s = 0; s < kMergeBatch; s += kMergeSpan) {
+        if (c0 + s >= used) break;  // uniform
         if (PHI == kPhiSoftmax) {
-          num.x = fmaf(w[i], ac[i].x, num.x), num.y = fmaf(w[i], ac[i].y, num.y);
-          num.z = fmaf(w[i], ac[i].z, num.z), num.w = fmaf(w[i], ac[i].w, num.w);
-        } else {
-          num.x += ac[i].x, num.y += ac[i].y, num.z += ac[i].z, num.w += ac[i].w;
+          const float keep = lds.keep[col_head * 2 + s / kMergeSpan];
+          num *= keep, den *= keep;
+        }
+#pragma unroll
+        for (int c = s; c < s + kMergeSpan; c += 4) {
+          float p[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) p[j] = lds.part[(c + j) * D + col];
+          if (PHI == kPhiSoftmax) {
+            const float4 w = *reinterpret_cast<const float4*>(&lds.w[col_head * kMlPitch + c]);
+            const float4 l = *reinterpret_cast<const float4*>(&lds.sum[col_head * kMlPitch + c]);
+            num = fmaf(w.w, p[3], fmaf(w.z, p[2], fmaf(w.y, p[1], fmaf(w.x, p[0], num))));
+            den = fmaf(w.w, l.w, fmaf(w.z, l.z, fmaf(w.y, l.y, fmaf(w.x, l.x, den))));
+          } else {
+            num = (((num + p[0]) + p[1]) + p[2]) + p[3];
+          }
         }
       }
     }
-    if (group > 0) {
-      lds.num[(group - 1) * kQuads + quad] = num;
-      if (PHI == kPhiSoftmax) lds.den[(group - 1) * kQuads + quad] = den;
-    }
-    lds_barrier();
-    if (group > 0 || used <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 n[kMergeGroups];
-    float d[kMergeGroups];
-    n[0] = num, d[0] = den;
-#pragma unroll
-    for (int q = 1; q < kMergeGroups; ++q) {
-      n[q] = lds.num[(q - 1) * kQuads + quad];
-      d[q] = PHI == kPhiSoftmax ? lds.den[(q - 1) * kQuads + quad] : 0.f;
-    }
-    return total(n, d, a.scale, len);
-  }
-  // the eight sums added in pairs, and normalised
-  static __device__ __forceinline__ float4 total(float4 (&n)[kMergeGroups], float (&d)[kMergeGroups], float scale, int len) {
-#pragma unroll
-    for (int o = 1; o < kMergeGroups; o *= 2)
-#pragma unroll
-      for (int q = 0; q < kMergeGroups; q += 2 * o) {
-        n[q].x += n[q + o].x, n[q].y += n[q + o].y, n[q].z += n[q + o].z, n[q].w += n[q + o].w;
-        d[q] += d[q + o];
-      }
-    if (PHI == kPhiSoftmax) return make_float4(n[0].x / d[0], n[0].y / d[0], n[0].z / d[0], n[0].w / d[0]);
-    const float f = scale / static_cast<float>(len);
-    return make_float4(n[0].x * f, n[0].y * f, n[0].z * f, n[0].w * f);
+    if (used <= 0) return 0.f;
+    return PHI == kPhiSoftmax ? num / den : num * (a.scale / static_cast<float>(len));
   }
 };
 
@@ -504,10 +489,8 @@ struct MergeQuad {
   }
   __device__ __forceinline__ float4 finish(const MergeArgs& a, int len) {
     const int used = (len + a.chunk_items - 1) / a.chunk_items;
-    float4 num[kMergeGroups];
-    float den[kMergeGroups], top = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < kMergeGroups; ++q) num[q] = make_float4(0.f, 0.f, 0.f, 0.f), den[q] = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    float den = 0.f, top = -INFINITY;
     for (int c0 = 0; c0 < (GROUPS > 1 ? used : min(used, 1)); c0 += kBatch) {  // uniform, as every branch on `used` below
       float2 m[kBatch];
       if (c0 > 0) {
@@ -523,15 +506,6 @@ struct MergeQuad {
           if (c0 + c < used) ask_ml(a, c0 + c, m + c);
       }
       if (GROUPS > 1 && c0 + kMergeGroups < used) ask(a, c0 + kMergeGroups, next);
-      if (PHI == kPhiSoftmax) {
-        float batch_top = top;
-#pragma unroll
-        for (int c = 0; c < kBatch; ++c) batch_top = fmaxf(batch_top, c0 + c < used ? m[c].x : -INFINITY);
-        const float keep = __builtin_amdgcn_exp2f((top - batch_top) * kLog2e);  // 0 on the first batch
-#pragma unroll
-        for (int q = 0; q < kMergeGroups; ++q) num[q].x *= keep, num[q].y *= keep, num[q].z *= keep, num[q].w *= keep, den[q] *= keep;
-        top = batch_top;
-      }
 #pragma unroll
       for (int c = 0; c < kBatch; c += kMergeGroups) {
         if (c0 + c >= used) break;
@@ -540,36 +514,41 @@ struct MergeQuad {
           for (int q = 0; q < kMergeGroups; ++q) ac[q] = next[q];
           if (c + kMergeGroups < kBatch && c0 + c + kMergeGroups < used) ask(a, c0 + c + kMergeGroups, next);
         }
+        if (PHI == kPhiSoftmax && c % kMergeSpan == 0) {
+          float span_top = top;
+#pragma unroll
+          for (int q = c; q < c + kMergeSpan && q < kBatch; ++q) span_top = fmaxf(span_top, c0 + q < used ? m[q].x : -INFINITY);
+          const float keep = __builtin_amdgcn_exp2f((top - span_top) * kLog2e);  // 0 on the first span
+          num.x *= keep, num.y *= keep, num.z *= keep, num.w *= keep, den *= keep;
+          top = span_top;
+        }
 #pragma unroll
         for (int q = 0; q < kMergeGroups; ++q) {
           if (c0 + c + q >= used) continue;
           if (PHI == kPhiSoftmax) {
             const float w = __builtin_amdgcn_exp2f((m[c + q].x - top) * kLog2e);
-            num[q].x = fmaf(w, ac[q].x, num[q].x), num[q].y = fmaf(w, ac[q].y, num[q].y);
-            num[q].z = fmaf(w, ac[q].z, num[q].z), num[q].w = fmaf(w, ac[q].w, num[q].w);
-            den[q] = fmaf(w, m[c + q].y, den[q]);
+            num.x = fmaf(w, ac[q].x, num.x), num.y = fmaf(w, ac[q].y, num.y);
+            num.z = fmaf(w, ac[q].z, num.z), num.w = fmaf(w, ac[q].w, num.w);
+            den = fmaf(w, m[c + q].y, den);
           } else {
-            num[q].x += ac[q].x, num[q].y += ac[q].y, num[q].z += ac[q].z, num[q].w += ac[q].w;
+            num.x += ac[q].x, num.y += ac[q].y, num.z += ac[q].z, num.w += ac[q].w;
           }
         }
       }
     }
-    return used > 0 ? MergeRow<PHI, D>::total(num, den, a.scale, len) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (used <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
+    if (PHI == kPhiSoftmax) return make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+    const float f = a.scale / static_cast<float>(len);
+    return make_float4(num.x * f, num.y * f, num.z * f, num.w * f);
   }
 };
 
 // Four rounded link-state values as one 8-byte store.
-__device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, float* rounded = nullptr) {
+__device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, bf16_t* again = nullptr) {
   alignas(8) bf16_t r[4];
   store_as(&r[0], v.x), store_as(&r[1], v.y), store_as(&r[2], v.z), store_as(&r[3], v.w);
   *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(r);
-  if (rounded != nullptr)
-    *reinterpret_cast<float4*>(rounded) = make_float4(to_float(r[0]), to_float(r[1]), to_float(r[2]), to_float(r[3]));
-}
-__device__ __forceinline__ void store_rounded(bf16_t* dst, const float4& v, bf16_t* again) {
-  alignas(8) bf16_t r[4];
-  store_as(&r[0], v.x), store_as(&r[1], v.y), store_as(&r[2], v.z), store_as(&r[3], v.w);
-  *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<uint2*>(again) = *reinterpret_cast<const uint2*>(r);
+  if (again != nullptr) *reinterpret_cast<uint2*>(again) = *reinterpret_cast<const uint2*>(r);
 }
 
 // A workgroup per link state.
@@ -580,8 +559,8 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(MergeArgs a) {
   MergeRow<PHI, D> row;
   row.begin(a, b, link);
   const int len = a.lens ? min(a.lens[b], a.N) : a.N;
-  const float4 v = row.finish(a, len, lds);
-  if (row.group == 0) store_rounded(a.LP + (static_cast<int64_t>(b) * a.m + link) * D + 4 * row.quad, v);
+  const float v = row.finish(a, len, lds);
+  if (threadIdx.x < D) store_as(a.LP + (static_cast<int64_t>(b) * a.m + link) * D + threadIdx.x, v);
 }
 
 // A thread per four columns of a link state.
@@ -662,8 +641,13 @@ __global__ __launch_bounds__(2 * D) void merge_values_kernel(MergeValuesArgs a) 
       wreg[it] = *reinterpret_cast<const bf16x8*>(a.Wv + static_cast<int64_t>(kc + it * nkc) * D + 8 * cg);
   }
   const int len = a.m.lens ? min(a.m.lens[b], a.m.N) : a.m.N;
-  const float4 v = merge.finish(a.m, len, lds);
-  if (merge.group == 0) store_rounded(a.m.LP + (static_cast<int64_t>(b) * a.m.m + link) * D + 4 * merge.quad, v, lp + 4 * merge.quad);
+  const float v = merge.finish(a.m, len, lds);
+  if (tid < D) {
+    bf16_t r;
+    store_as(&r, v);
+    a.m.LP[(static_cast<int64_t>(b) * a.m.m + link) * D + tid] = r;
+    lp[tid] = to_float(r);
+  }
   __syncthreads();
   if (a.ln_on) {  // uniform
     if (tid < 64) normalise_state<D>(a.ln_gamma, a.ln_beta, a.ln_eps, [&](int k) { return lp[k]; }, [&](int k, __bf16 y) { lp[k] = static_cast<float>(y); });

@@ -75,3 +75,46 @@ def test_xor_layers_with_a_negative_scale(d, h, m):
     a = binding.lime_xor_layers(E, lens, L, Wq, Wk, Wv, Wu, Wo, h, 0.4)
     assert torch.isfinite(a).all() and a[0].any() and not a[1].any()
     assert torch.equal(a, binding.lime_xor_layers(E, lens, L, -Wq, Wk, Wv, Wu, Wo, h, -0.4))
+
+
+# one user's history in 10, 12, 20, 26 and 41 chunks, its link states by a workgroup each (MergeRow) or by thread (MergeQuad)
+@pytest.mark.parametrize("B,N,d,h,m", [
+    (2, 640, 256, 4, 128), (1, 768, 256, 4, 32), (2, 1280, 256, 4, 128), (2, 1664, 256, 4, 128), (1, 2624, 256, 4, 64),
+    (3, 640, 256, 4, 128), (3, 1280, 256, 4, 128), (9, 1664, 64, 1, 128), (1, 5248, 128, 2, 64)])
+@pytest.mark.parametrize("xor", [False, True])
+def test_chunks_are_merged_in_one_ascending_chain(B, N, d, h, m, xor):
+    """Every logit is the same, and the values of a user's first and last rows are 2^60 and -2^60, those between one: in
+    ascending order the first absorbs the ones (2^60 has steps of 2^37), and the last leaves zero, exactly.  (Several sums of
+    chunks, added at the end, would keep the ones of those without the first row.)"""
+    E = torch.zeros(B, N, d)
+    E[:, :, :2] = 1.0
+    E[:, 0, 1], E[:, -1, 1] = 2.0 ** 60, -2.0 ** 60
+    L, Wq, Wv = torch.zeros(m, d), torch.zeros(d, d), torch.zeros(d, d)
+    L[:, 0] = 1.0
+    Wq[0, ::d // h] = 1.0  # (also W_K)
+    Wv[1] = 1.0
+    T = torch.zeros(B, 3, d)
+    E, L, Wq, Wv, T = (x.bfloat16().cuda() for x in (E, L, Wq, Wv, T))
+    LP = binding.lime_xor_history(E, None, L, Wq, Wq, Wv, h, 1.0)[0] if xor else binding.lime_link_history(E, None, L, Wq, Wq, Wv, h, 1.0)
+    assert (LP == 0).all()
+    LP, O = binding.lime_request(E, None, L, Wq, Wq, Wv, T, L, Wq, Wq, Wv, h, 1.0, 1.0, xor_attention=xor)
+    assert (LP == 0).all() and (O == 0).all()
+
+
+# batches on either side of the line between a workgroup and a thread per link state, with histories in the same chunks
+@pytest.mark.parametrize("B,N,d,h,m", [(2, 1300, 256, 4, 128), (2, 500, 256, 4, 128), (4, 1500, 128, 4, 128), (8, 129, 128, 4, 64)])
+@pytest.mark.parametrize("xor", [False, True])
+def test_a_link_state_has_the_same_bits_in_either_merge(B, N, d, h, m, xor):
+    E, T, L, Wq, Wk, Wv = _tensors(N + m, (B + 1, N, d), (B + 1, 5, d), (m, d), (d, d), (d, d), (d, d))
+    lens = torch.randint(1, N + 1, (B + 1,), device="cuda", dtype=torch.int32, generator=torch.Generator(device="cuda").manual_seed(B))
+    lens[0], lens[1] = N, 0
+    s = (d // h) ** -0.5
+
+    def states(n):
+        LP, _ = binding.lime_request(E[:n], lens[:n], L, Wq, Wk, Wv, T[:n], L, Wq, Wk, Wv, h, s, s, xor_attention=xor)
+        alone = binding.lime_xor_history(E[:n], lens[:n], L, Wq, Wk, Wv, h, s)[0] if xor else binding.lime_link_history(E[:n], lens[:n], L, Wq, Wk, Wv, h, s)
+        return LP, alone
+
+    few, many = states(B), states(B + 1)
+    for a, b in zip(few, many):
+        assert torch.equal(a, few[0]) and torch.equal(b[:B], a)
