@@ -162,13 +162,19 @@ XorRegistersPlan plan_xor_registers(void* ws, int64_t B, int64_t N, int64_t d, i
   return p;
 }
 
-// large enough for either path (a bf16 call whose pointers are not 16-byte aligned runs on the general kernels)
-size_t xor_layers_workspace(int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, int32_t dtype) {
+// what a call needs: large enough for either way of six kernels a layer (a bf16 call whose pointers are not 16-byte aligned
+// runs on the general kernels)
+size_t xor_layers_needed(int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, int32_t dtype) {
   size_t need = plan_xor_layers(nullptr, B, N, d, h, m, dtype, false).bytes;
   if (dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m))
     need = std::max(need, plan_xor_layers(nullptr, B, N, d, h, m, dtype, true).bytes);
-  if (dtype == LIME_BF16 && lime::xor_rows_supported(d, h, m)) need = std::max(need, plan_xor_registers(nullptr, B, N, d, h, m).bytes);
   return need;
+}
+// what it makes use of: four kernels a layer take more where the history is no longer than the links (with less they are six,
+// and the same bits)
+size_t xor_layers_workspace(int64_t B, int64_t N, int64_t d, int64_t h, int64_t m, int32_t dtype) {
+  const size_t need = xor_layers_needed(B, N, d, h, m, dtype);
+  return dtype == LIME_BF16 && lime::xor_rows_supported(d, h, m) ? std::max(need, plan_xor_registers(nullptr, B, N, d, h, m).bytes) : need;
 }
 
 // The m links over the history on the general kernels (the projections of `p` done).
@@ -820,10 +826,10 @@ int32_t lime_xor_layers(const void* E, const int32_t* lens, const void* LC, int6
   // handed to it below are 256-byte aligned)
   const bool on_mfma = dtype == LIME_BF16 && lime::links_over_history_supported(d, h, m) && fits_tiles(B, N) &&
                        all_aligned16(E, LC, Wq, Wk, Wv, Wu, Wo, LP, workspace);
-  const size_t need = xor_layers_workspace(B, N, d, h, m, dtype);
+  const size_t need = xor_layers_needed(B, N, d, h, m, dtype);
   if (!workspace || ws_bytes < need)
     return fail(LIME_WORKSPACE_TOO_SMALL, "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace ? ws_bytes : 0);
-  if (on_mfma && lime::xor_rows_supported(d, h, m))
+  if (on_mfma && lime::xor_rows_supported(d, h, m) && ws_bytes >= plan_xor_registers(nullptr, B, N, d, h, m).bytes)
     return xor_layers_in_registers(plan_xor_registers(workspace, B, N, d, h, m), E, lens, LC, lc_user_stride, Wq, Wk, Wv, Wu, Wo, n_layers, LP,
                                    B, N, d, h, m, scale, static_cast<hipStream_t>(stream));
   const XorLayersPlan p = plan_xor_layers(workspace, B, N, d, h, m, dtype, on_mfma);

@@ -1,6 +1,8 @@
 """The small kernels around the two attention stages, at the edges of their dispatch: the pack kernel's projections (one or
 four 32 x 32 blocks per workgroup) and the merge of a history's chunks, with and without the value projection."""
 
+import re
+
 import pytest
 import torch
 
@@ -118,3 +120,24 @@ def test_a_link_state_has_the_same_bits_in_either_merge(B, N, d, h, m, xor):
     few, many = states(B), states(B + 1)
     for a, b in zip(few, many):
         assert torch.equal(a, few[0]) and torch.equal(b[:B], a)
+
+
+@pytest.mark.parametrize("B,N,d,h,m,layers", [(1, 31, 128, 4, 96, 3), (3, 31, 128, 2, 32, 2), (1, 1, 128, 4, 64, 3), (1, 31, 64, 2, 64, 3), (1, 1, 32, 1, 32, 2)])
+@pytest.mark.parametrize("scale", [0.4, -0.4])
+def test_xor_layers_in_the_least_workspace(B, N, d, h, m, layers, scale):
+    """Histories no longer than the links: the kernels that hold a layer's operands in registers ask for more workspace than a
+    call needs.  With what it needs it runs on the others, to the same bits."""
+    E, L, Wq, Wk, Wv = _tensors(d + N, (B, N, d), (B, m, d), (d, d), (d, d), (d, d))
+    Wu, Wo = (torch.stack(_tensors(d + i, *[(d, d)] * layers)) for i in (1, 2))
+    lens = torch.tensor([N, 0, N // 2][:B], dtype=torch.int32, device="cuda")
+
+    def call(bytes_):
+        ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+        return binding.lime_xor_layers(E, lens, L, Wq, Wk, Wv, Wu, Wo, h, scale, workspace=ws)
+
+    with pytest.raises(RuntimeError, match="bytes needed") as e:
+        call(256)
+    needed, full = int(re.search(r"(\d+) bytes needed", str(e.value))[1]), binding.workspace_bytes(binding.OP_XOR_LAYERS, B=B, N=N, d=d, h=h, m=m)
+    assert needed < full
+    a, b = call(needed), call(full)
+    assert a.any() and torch.equal(a, b)
