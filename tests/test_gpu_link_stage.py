@@ -141,3 +141,39 @@ def test_xor_layers_in_the_least_workspace(B, N, d, h, m, layers, scale):
     assert needed < full
     a, b = call(needed), call(full)
     assert a.any() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d,h,m", [(128, 4, 64), (64, 2, 96), (128, 4, 128)])
+def test_xor_layers_keep_a_users_infinities(d, h, m):
+    """A user with an infinite and a NaN entry in its history leaves the others' link states as they are."""
+    B, N = 5, 90
+    E, L, Wq, Wk, Wv = _tensors(d + m, (B, N, d), (m, d), (d, d), (d, d), (d, d))
+    Wu, Wo = (torch.stack(_tensors(d + i, (d, d), (d, d), (d, d))) for i in (3, 4))
+    lens = torch.tensor([90, 33, 64, 0, 90], dtype=torch.int32, device="cuda")
+    clean = binding.lime_xor_layers(E, lens, L, Wq, Wk, Wv, Wu, Wo, h, 0.4)
+    E[1, 5, 3], E[4, 89, 0] = float("inf"), float("nan")
+    E[2, 64:] = float("nan")  # padding
+    LP = binding.lime_xor_layers(E, lens, L, Wq, Wk, Wv, Wu, Wo, h, 0.4)
+    for b in (0, 2, 3):
+        assert torch.equal(LP[b], clean[b]), b
+    assert not torch.isfinite(LP[1]).all() and not torch.isfinite(LP[4]).all()
+
+
+@pytest.mark.parametrize("B,N,d,h,m", [(3, 640, 256, 4, 32), (9, 129, 128, 4, 64), (17, 200, 256, 4, 128)])
+@pytest.mark.parametrize("xor", [False, True])
+def test_merges_keep_a_users_infinities(B, N, d, h, m, xor):
+    E, T, L, Wq, Wk, Wv = _tensors(B, (B, N, d), (B, 5, d), (m, d), (d, d), (d, d), (d, d))
+    lens = torch.full((B,), N, device="cuda", dtype=torch.int32)
+    lens[0], lens[2] = N - 31, 1
+    s = (d // h) ** -0.5
+
+    def request():
+        return binding.lime_request(E, lens, L, Wq, Wk, Wv, T, L, Wq, Wk, Wv, h, s, s, xor_attention=xor)
+
+    clean = request()
+    E[1, N // 2, 3] = float("inf")
+    for b in range(B):
+        E[b, int(lens[b]):] = float("nan")  # padding
+    for x, y in zip(request(), clean):
+        others = [b for b in range(B) if b != 1]
+        assert torch.equal(x[others], y[others]) and not torch.isfinite(x[1]).all()
