@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "per_device.hpp"
+
 namespace lime {
 
 // ----------------------------------------------------------------------------- storage types
@@ -34,6 +36,9 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // Compute units of the current device (256 when the query fails): what the launchers size their grids by.
 int compute_units();
+// Lets `kernel` have `bytes` of dynamic LDS, more than the 64 KiB that need no leave, on the current device.  `granted` is the
+// kernel's own.
+hipError_t allow_lds(PerDevice& granted, const void* kernel, int bytes);
 // Sets the calling thread's error text (what lime_last_error returns) and hands the status back.
 int32_t set_error(int32_t status, const char* text);
 

@@ -14,4 +14,10 @@ int compute_units() {
   return n;
 }
 
+hipError_t allow_lds(PerDevice& granted, const void* kernel, int bytes) {
+  int device = -1;
+  if (hipError_t e = hipGetDevice(&device); e != hipSuccess) return e;
+  return granted.ensure(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
+
 }  // namespace lime

@@ -204,22 +204,13 @@ template <int DH, int M, int H>
 hipError_t launch(const CachedArgs& a, int grid, hipStream_t s) {
   constexpr size_t kPitch = 2 * H * M + 16;
   constexpr size_t kLds = (2 * H * M <= 512 ? 2 : 1) * 32 * kPitch + static_cast<size_t>(H) * 32 * (2 * DH + 16);
-  auto gathered = cached_candidates_kernel<DH, M, H, true>;
-  auto direct = cached_candidates_kernel<DH, M, H, false>;
+  const bool gathered = a.ids != nullptr;
+  auto kernel = gathered ? cached_candidates_kernel<DH, M, H, true> : cached_candidates_kernel<DH, M, H, false>;
   if (kLds > 64 * 1024) {
-    static hipError_t attr = [&]() {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gathered), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(kLds));
-      if (e != hipSuccess) return e;
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(direct), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 static_cast<int>(kLds));
-    }();
-    if (attr != hipSuccess) return attr;
+    static PerDevice granted[2];
+    if (hipError_t e = allow_lds(granted[gathered], reinterpret_cast<const void*>(kernel), static_cast<int>(kLds)); e != hipSuccess) return e;
   }
-  if (a.ids != nullptr)
-    launch_timed(kKernelCachedCandidates, gathered, dim3(grid), dim3(64 * H), kLds, s, a);
-  else
-    launch_timed(kKernelCachedCandidates, direct, dim3(grid), dim3(64 * H), kLds, s, a);
+  launch_timed(kKernelCachedCandidates, kernel, dim3(grid), dim3(64 * H), kLds, s, a);
   return hipGetLastError();
 }
 

@@ -757,8 +757,8 @@ hipError_t launch_shape(const HistArgs& a, int users, hipStream_t s) {
   static_assert(S::kLds <= 160 * 1024, "LDS");
   auto kernel = links_over_history_kernel<DH, M, H, PHI, HG, TP>;
   if (S::kLds > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
-    if (attr != hipSuccess) return attr;
+    static PerDevice granted;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), S::kLds); e != hipSuccess) return e;
   }
   launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H / HG), dim3(S::kThreads), S::kLds, s, a);
   return hipGetLastError();
@@ -820,8 +820,8 @@ hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStre
   using T = MergeTile<PHI, D, ROWS>;
   auto kernel = merge_values_tile_kernel<PHI, D, ROWS, GROUPS>;
   if (T::kLds > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLds);
-    if (attr != hipSuccess) return attr;
+    static PerDevice granted;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), T::kLds); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kernel, dim3(a.m.m / ROWS, users), dim3(2 * D), T::kLds, s, a);
   return hipGetLastError();

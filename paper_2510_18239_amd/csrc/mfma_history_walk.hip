@@ -283,9 +283,8 @@ hipError_t launch_main(const HistArgs& a, int users, bool coop, hipStream_t s) {
       constexpr size_t lds = slice * H;
       auto kernel = walk_history_kernel<DH, M, H, kWkLds, true>;
       if (lds > 64 * 1024) {
-        static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-        if (attr != hipSuccess) return attr;
+        static PerDevice granted;
+        if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), static_cast<int>(lds)); e != hipSuccess) return e;
       }
       launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users), dim3(64 * H), lds, s, a);
       return hipGetLastError();
@@ -293,9 +292,8 @@ hipError_t launch_main(const HistArgs& a, int users, bool coop, hipStream_t s) {
   }
   auto kernel = walk_history_kernel<DH, M, H, kWkLds, false>;
   if (slice > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(slice));
-    if (attr != hipSuccess) return attr;
+    static PerDevice granted;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), static_cast<int>(slice)); e != hipSuccess) return e;
   }
   launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H), dim3(64), slice, s, a);
   return hipGetLastError();

@@ -520,8 +520,8 @@ hipError_t launch_mlp(const MlpArgs& a, hipStream_t s) {
   using S = MlpStream<D, H1, H2, H3>;
   const unsigned grid = static_cast<unsigned>((a.rows + 127) / 128);
   auto kernel = interaction_mlp_kernel<D, H1, H2, H3>;
-  static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
-  if (attr != hipSuccess) return attr;
+  static PerDevice granted;
+  if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), S::kLds); e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), S::kLds, s, a);
   return hipGetLastError();
 }

@@ -884,9 +884,8 @@ template <int DH, int MB>
 hipError_t launch_fused(const FusedArgs& a, dim3 grid, hipStream_t s) {
   auto kernel = xor_backward_fused_kernel<DH, MB>;
   constexpr size_t lds = fused_lds_bytes<DH, MB>();
-  static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-  if (attr != hipSuccess) return attr;
+  static PerDevice granted;
+  if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), static_cast<int>(lds)); e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(64 * fused_waves(DH, MB)), lds, s, a);
   return hipGetLastError();
 }
