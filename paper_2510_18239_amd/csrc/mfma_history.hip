@@ -828,8 +828,13 @@ hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStre
 }
 template <int PHI, int D, int ROWS>
 hipError_t launch_merge_values_tile(const MergeValuesArgs& a, int users, hipStream_t s) {
-  return a.m.chunks <= kMergeGroups ? launch_merge_values_tile<PHI, D, ROWS, 1>(a, users, s)
-                                    : launch_merge_values_tile<PHI, D, ROWS, kMergeBatch / kMergeGroups>(a, users, s);
+  if (a.m.chunks <= kMergeGroups) return launch_merge_values_tile<PHI, D, ROWS, 1>(a, users, s);
+  // (sixteen rows a workgroup: users x m d > 2048 compute units, and plan() then makes no more than eight chunks; only the
+  // histories of mfma_history_walk.hip, softmax all, come in more)
+  if constexpr (ROWS == 16 && PHI == kPhiSilu)
+    return hipErrorInvalidValue;
+  else
+    return launch_merge_values_tile<PHI, D, ROWS, kMergeBatch / kMergeGroups>(a, users, s);
 }
 template <int PHI, int D>
 hipError_t launch_merge_values(const MergeValuesArgs& a, int users, hipStream_t s) {

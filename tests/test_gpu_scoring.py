@@ -189,6 +189,20 @@ def test_lime_scores_normalised_link_rows(B, d, h, m):
     _request(780 + d, B, 70, 45, d, h, m, 8, 40, [96, 1], "bf16", (20, 70))
 
 
+@pytest.mark.parametrize("B,N,d,h,m", [(17, 2048, 256, 4, 128), (33, 1024, 128, 4, 128)])
+def test_lime_scores_many_link_states_of_long_histories(B, N, d, h, m):
+    """13 and 11 chunks a history and more link states than run at once with eight a workgroup: sixteen a workgroup in the
+    merge's form for many chunks."""
+    _request(800 + d, B, N, 9, d, h, m, 8, 40, [96, 1], "bf16", (N // 3, N), lens=[0, 1, N, 161, 160])
+
+
+@pytest.mark.parametrize("B,m,d,dhid,widths", [(33, 64, 128, 40, [512, 128, 64, 1]), (2, 32, 256, 30, [96, 1])])
+def test_lime_scores_without_the_shared_first_launch(B, m, d, dhid, widths):
+    """Rows or a width of the hidden layer that the first launch does not take, with the interaction network on the matrix cores
+    all the same: its weight images are then packed by its own launch."""
+    _request(810 + d, B, 90, 70, d, 4, m, 8, dhid, widths, "bf16", (30, 90))
+
+
 @pytest.mark.parametrize("d,h,m,B,N", [(256, 4, 64, 40, 1024), (256, 4, 32, 36, 1000), (256, 2, 128, 36, 1000), (128, 2, 64, 70, 600),
                                        (128, 4, 96, 70, 600), (64, 2, 32, 70, 600)])
 def test_lime_scores_cooperative_history_walk_on_edge_lengths(d, h, m, B, N):
