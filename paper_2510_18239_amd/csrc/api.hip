@@ -616,7 +616,7 @@ int32_t lime_request_prepared(const void* E, const int32_t* lens, const void* T,
   q.phi = xor_attention ? lime::kPhiSilu : lime::kPhiSoftmax;
   // three kernels: the merge step of the history side also projects the finished link states and writes the value
   // image where the candidate-side kernel of this request expects it
-  q.Wv_values = Wv, q.values_image = lime::queries_over_links_operands(c, cand_ws).values;
+  q.Wv_values = Wv, q.values_image = lime::queries_over_links_values(c, cand_ws);
   c.packed = true;
   LIME_HIP(lime::links_over_history(q, workspace, s));
   LIME_HIP(lime::queries_over_links(c, cand_ws, s));
@@ -736,7 +736,7 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   lime::queries_over_links_jobs(c, cand_ws, jobs, /*values=*/false);
   LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
   q.packed = c.packed = true;
-  q.Wv_values = Wv_cand, q.values_image = lime::queries_over_links_operands(c, cand_ws).values;
+  q.Wv_values = Wv_cand, q.values_image = lime::queries_over_links_values(c, cand_ws);
   LIME_HIP(lime::links_over_history(q, workspace, s));
   LIME_HIP(lime::queries_over_links(c, cand_ws, s));
   return LIME_OK;

@@ -323,11 +323,8 @@ struct QueriesOverLinks {
   RowNorm x_norm;       // applied to the query rows as their tiles are loaded (softmax, O output, per-call operands)
   RowNorm k_norm, v_norm;  // applied to the key / value rows by the pack step
 };
-// where the images of a call live in its workspace (without `prepared`)
-struct QueriesOverLinksOperands {
-  void *queries, *keys, *values;
-};
-QueriesOverLinksOperands queries_over_links_operands(const QueriesOverLinks& a, void* workspace);
+// where the value image of a call lives in its workspace
+void* queries_over_links_values(const QueriesOverLinks& a, void* workspace);
 // The pack jobs of a call, appended to `jobs` instead of being launched by queries_over_links (not with `prepared`);
 // without `values` when someone else writes the value image (the history side's merge step).
 void queries_over_links_jobs(const QueriesOverLinks& a, void* workspace, PackJobs& jobs, bool values = true);

@@ -584,10 +584,9 @@ size_t queries_over_links_workspace(int B, int d, int m, bool k_per_user) {
   return wq + ka + va;
 }
 
-QueriesOverLinksOperands queries_over_links_operands(const QueriesOverLinks& q, void* workspace) {
-  char* ws = static_cast<char*>(workspace);
-  char* keys = ws + align_up(static_cast<size_t>(q.d) * q.d * 2 + kQueryImagePadBytes);
-  return {ws, keys, keys + align_up(static_cast<size_t>(q.k_user_stride != 0 ? q.B : 1) * q.m * q.d * 2)};
+void* queries_over_links_values(const QueriesOverLinks& q, void* workspace) {
+  char* keys = static_cast<char*>(workspace) + align_up(static_cast<size_t>(q.d) * q.d * 2 + kQueryImagePadBytes);
+  return keys + align_up(static_cast<size_t>(q.k_user_stride != 0 ? q.B : 1) * q.m * q.d * 2);
 }
 
 void queries_over_links_jobs(const QueriesOverLinks& q, void* workspace, PackJobs& jobs, bool values) {
