@@ -370,7 +370,7 @@ struct MergeRow {
   static constexpr int kThreads = 2 * D, kQuads = D / 4, kLoads = kMergeBatch / kMergeGroups, kMaxHeads = D / 32;
   static constexpr int kMlPitch = kMergeBatch + 4;
   static_assert(kThreads == kQuads * kMergeGroups && 32 * kMaxHeads <= kThreads, "every chunk and every (head, chunk) has its thread");
-  struct Lds {
+  struct alignas(16) Lds {
     float part[kMergeBatch * D];
     float w[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];  // the chunks' weights and sums, by head
     float sum[PHI == kPhiSoftmax ? kMaxHeads * kMlPitch : 1];
