@@ -463,7 +463,7 @@ struct MergeRow {
 // asked for during the group before (lime_request_prepared, 512 candidates, against reading the maxima group by group and
 // again: 41.5 -> 39.6 us at B=5 N=13000 d=128 h=2 m=128, 36.7 -> 35.8 at B=3 N=8000 d=256 m=96, 31.9 -> 31.4 at B=4 N=4096
 // d=256 m=128).  GROUPS: of a batch; 1 where a history has no more than kMergeGroups chunks, which the registers of the
-// general form would slow (16.6 | 17.1 us at B=5 N=300 d=256 m=64, 15.1 | 15.7 at B=16 N=1024 d=128).
+// general form would slow (15.3 | 15.6 us at B=5 N=300 d=256 m=64, 14.5 | 14.8 at B=16 N=1024 d=128).
 template <int PHI, int D, int GROUPS>
 struct MergeQuad {
   static constexpr int kBatch = GROUPS * kMergeGroups;
@@ -799,9 +799,11 @@ hipError_t dispatch_h(const HistArgs& a, int h, int links, int phi, int users, i
   return hipErrorInvalidValue;
 }
 
-// One link state per workgroup where all of them run at once with eight waves a compute unit (what the registers of the value
-// projection leave room for; without it four times as many do, but a thread per four columns is then ahead all the same:
-// history + merge at 2048 rows 15.5 us so and 14.1 us by thread at B=32 N=1024 d=128 m=64).
+// One link state per workgroup where all of them run at once with eight waves a compute unit.  What a workgroup takes off is
+// the wait for many chunks, so the two sides cross at different numbers of rows.  In us, a workgroup a row | the other form,
+// lime_request_prepared with 16 candidates: d=256 m=64 B=4 (256 rows) N=2048 18.4|20.3, N=300 15.6|15.5, B=6 N=300 17.2|16.2; m=128
+// B=2 N=2048 23.2|28.0; d=128 m=64 B=4 N=2048 12.8|13.7, B=8 (512 rows) N=500 13.2|12.6, B=12 13.9|12.6.  lime_link_history: d=256 m=64
+// B=1 N=2048 12.6|14.7; d=128 m=64 B=8 N=16384 26.7|28.0, N=500 12.1|11.5, B=32 N=1024 17.3|15.5.
 bool few_rows(int64_t rows, int d) { return rows <= static_cast<int64_t>(compute_units()) * (256 / d); }
 
 template <int PHI, int D>
@@ -843,7 +845,11 @@ hipError_t launch_merge_values(const MergeValuesArgs& a, int users, hipStream_t 
     hipLaunchKernelGGL((merge_values_kernel<PHI, D>), dim3(a.m.m, users), dim3(2 * D), 0, s, a);
     return hipGetLastError();
   }
-  // eight rows each as long as the workgroups then all run at once
+  // Eight rows each as long as the workgroups then all run at once, counted as in few_rows.  lime_request_prepared with 16
+  // candidates, N=60, eight | sixteen rows, us: d=256 m=64 1536 rows 15.6|17.4, 2048 16.0|17.5, 2560 19.8|18.1, 4096 21.7|19.2
+  // (m=128 20.4|21.9, 21.6|22.2, 25.1|22.5, 26.6|23.8); d=128 m=64 2048 rows 13.0|13.7, 4096 14.8|14.8, 8192 25.6|24.8; d=64 m=64
+  // 6144 rows 12.7|13.2, 8192 13.2|13.5, 16384 22.1|21.8.  (Below d = 256 the form for few chunks leaves room for more at once,
+  // and the two are within 6 % of each other around the line.)
   return few_rows(rows / 8, D) ? launch_merge_values_tile<PHI, D, 8>(a, users, s) : launch_merge_values_tile<PHI, D, 16>(a, users, s);
 }
 

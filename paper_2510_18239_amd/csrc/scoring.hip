@@ -369,8 +369,8 @@ struct MlpStream {
 // before: 51 instead of 37 cycles; a block's sums still start at the bias and take their k-steps in ascending order, in one
 // accumulator), and a finished block is rounded and packed between the next blocks' products.
 // What bounds it: one wavefront per SIMD (registers), so matrix cores and everything else take turns; LDS reads, 4 KiB per
-// product of the four wavefronts, take as long as the product.  32 768 rows of 256 -> 512 -> 128 -> 64 -> 1: 16 us (13.4
-// GFLOP, 0.84 PFLOP/s), 22 us with a chunk's fragments all read before the first of its products, into one accumulator.
+// product of the four wavefronts, take as long as the product.  32 768 rows of 256 -> 512 -> 128 -> 64 -> 1, in traces: 18.6 us
+// (13.5 GFLOP, 0.72 PFLOP/s), 23.4 with a chunk's fragments all read before the first of its products, one block at a time.
 template <int D, int H1, int H2, int H3>
 __global__ __launch_bounds__(256) void interaction_mlp_kernel(MlpArgs a) {
   using S = MlpStream<D, H1, H2, H3>;
