@@ -188,6 +188,17 @@ lime::GenericAttention history_attention(const HistoryPlan& p, const int32_t* le
   return t;
 }
 
+// A stage whose projections the general kernels form themselves (fused_history.hip, fused_rows.hip).  The states of a history's
+// chunks lie where the projected history would.
+bool history_fused(const void* E, const void* LC, const void* Wq, const void* Wk, const void* Wv, const void* LP, int32_t B, int32_t N,
+                   int32_t d, int32_t h, int32_t m) {
+  return Wq && Wk && Wv && all_aligned16(E, LC, Wq, Wk, Wv, LP) && lime::fused_history_supported(B, N, d, h, m);
+}
+bool rows_fused(const void* X, const void* Ksrc, const void* Vsrc, const void* Wq, const void* Wk, const void* Wv, const void* O, int32_t B,
+                int32_t rows, int32_t d, int32_t h, int32_t m) {
+  return Wq && Wk && Wv && all_aligned16(X, Ksrc, Vsrc, Wq, Wk, Wv, O) && lime::fused_rows_supported(B, rows, d, h, m);
+}
+
 // O[S] of XORA on the candidate-side kernel: every history row attends over the m links, SiLU / m.
 lime::QueriesOverLinks os_query(const void* E, const int32_t* lens, const void* LC, int64_t link_stride, const void* Wq,
                                 const void* Wk, const void* Wv, void* OS, int32_t B, int32_t N, int32_t d, int32_t h,
@@ -248,11 +259,22 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     const bool chunked = ws_bytes >= p.bytes;
     p = plan_history(workspace, B, N, d, h, m, per_user, want_os);
     if (!chunked) p.scratch = nullptr;
-    const lime::Projection jobs[6] = {{LC, Wq, p.Qt, link_rows}, {E, Wk, p.Ks, hist_rows, lens, N}, {E, Wv, p.Vs, hist_rows, lens, N},
-                                      {E, Wq, p.Qs, hist_rows, lens, N}, {LC, Wk, p.Kt, link_rows}, {LC, Wv, p.Vt, link_rows}};
-    LIME_HIP(lime::generic_project(jobs, want_os ? 6 : 3, d, dtype, s));
-    LIME_HIP(lime::generic_attention(history_attention(p, lens, link_stride, LP, B, N, d, h, m, scale, phi, dtype), s));
-    if (want_os) {
+    const bool lp_fused = history_fused(E, LC, Wq, Wk, Wv, LP, B, N, d, h, m);
+    const bool os_fused = want_os && rows_fused(E, LC, LC, Wq, Wk, Wv, OS, B, N, d, h, m);
+    lime::Projection jobs[6];
+    int n = 0;
+    auto project = [&](const lime::Projection& j) { jobs[n++] = j; };
+    if (!lp_fused) project({LC, Wq, p.Qt, link_rows}), project({E, Wk, p.Ks, hist_rows, lens, N}), project({E, Wv, p.Vs, hist_rows, lens, N});
+    if (want_os && !os_fused) project({E, Wq, p.Qs, hist_rows, lens, N}), project({LC, Wk, p.Kt, link_rows}), project({LC, Wv, p.Vt, link_rows});
+    if (n > 0) LIME_HIP(lime::generic_project(jobs, n, d, dtype, s));
+    if (lp_fused) {
+      LIME_HIP(lime::fused_history({E, lens, LC, link_stride, Wq, Wk, Wv, LP, B, N, d, h, m, scale, phi, dtype, p.Qt}, s));
+    } else {
+      LIME_HIP(lime::generic_attention(history_attention(p, lens, link_stride, LP, B, N, d, h, m, scale, phi, dtype), s));
+    }
+    if (os_fused) {
+      LIME_HIP(lime::fused_rows({E, lens, LC, link_stride, LC, link_stride, Wq, Wk, Wv, OS, B, N, d, h, m, scale, lime::kPhiSilu, dtype}, s));
+    } else if (want_os) {
       lime::GenericAttention o{};
       o.Q = p.Qs, o.K = p.Kt, o.V = p.Vt;
       o.q_user_stride = static_cast<int64_t>(N) * d, o.k_user_stride = o.v_user_stride = link_stride;
@@ -307,6 +329,12 @@ lime::GenericAttention candidate_attention(const QueryPlan& p, void* O, int32_t 
   a.O = O, a.q_lens = nullptr, a.k_lens = nullptr, a.scratch = p.scratch;
   a.B = B, a.q_rows = C, a.n_keys = m, a.d = d, a.h = h, a.scale = scale, a.phi = lime::kPhiSoftmax, a.dtype = dtype;
   return a;
+}
+
+// The same with the projections inside.
+lime::FusedRows candidate_rows(const void* T, const void* L, const void* LP, const void* Wq, const void* Wk, const void* Wv, void* O, int32_t B,
+                               int32_t C, int32_t d, int32_t h, int32_t m, float scale, int32_t dtype) {
+  return {T, nullptr, L, 0, LP, static_cast<int64_t>(m) * d, Wq, Wk, Wv, O, B, C, d, h, m, scale, lime::kPhiSoftmax, dtype};
 }
 
 // lime_xor_layers where a layer's stationary operands fit the registers.  The weights' images and the first layer's link
@@ -402,6 +430,10 @@ int32_t lime_score_candidates(const void* T, const void* L, const void* LP, cons
   const bool chunked = ws_bytes >= p.bytes;
   p = plan_candidates(workspace, B, C, d, h, m);
   if (!chunked) p.scratch = nullptr;
+  if (rows_fused(T, L, LP, Wq, Wk, Wv, O, B, C, d, h, m)) {
+    LIME_HIP(lime::fused_rows(candidate_rows(T, L, LP, Wq, Wk, Wv, O, B, C, d, h, m, scale, dtype), s));
+    return LIME_OK;
+  }
   const lime::Projection jobs[3] = {{T, Wq, p.Qt, q_rows}, {L, Wk, p.Kt, m}, {LP, Wv, p.Vt, v_rows}};
   LIME_HIP(lime::generic_project(jobs, 3, d, dtype, s));
   LIME_HIP(lime::generic_attention(candidate_attention(p, O, B, C, d, h, m, scale, dtype), s));
@@ -691,24 +723,37 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   void* cand_ws = static_cast<char*>(workspace) + p.hist_bytes;
   if (!p.on_mfma && norms != nullptr) return fail(LIME_UNSUPPORTED, "%s: normalised operands need the matrix-core path", fn);
   if (!p.on_mfma && (dtype != LIME_BF16 || !lime::links_over_history_supported(d, h, m))) {
-    // Both stages on the general kernels: everything but the projection of the link states does not depend on the
-    // history stage's result and is projected by one launch, so that the request is four launches (with the history cut
-    // into chunks five).
+    // Both stages on the general kernels.  A stage that projects by itself is one launch (with a history of several chunks
+    // two).  What the others project, but for the link states, does not depend on the history stage's result and is one launch
+    // ahead of it: with neither, a request is four launches (with the history cut into chunks five).
     hipStream_t s = static_cast<hipStream_t>(stream);
     HistoryPlan hp = plan_history(workspace, B, N, d, h, m, per_user, false);
     QueryPlan cp = plan_candidates(cand_ws, B, C, d, h, m);
     if (p.hist_bytes < hp.bytes) hp.scratch = nullptr;
     if (p.total - p.hist_bytes < cp.bytes) cp.scratch = nullptr;
     const int64_t link_rows = (per_user ? B : 1) * static_cast<int64_t>(m), hist_rows = static_cast<int64_t>(B) * N;
-    const lime::Projection first[5] = {{LC, Wq_hist, hp.Qt, link_rows}, {E, Wk_hist, hp.Ks, hist_rows, lens, N},
-                                       {E, Wv_hist, hp.Vs, hist_rows, lens, N}, {T, Wq_cand, cp.Qt, static_cast<int64_t>(B) * C},
-                                       {L, Wk_cand, cp.Kt, m}};
-    const lime::Projection values{LP, Wv_cand, cp.Vt, static_cast<int64_t>(B) * m};
-    LIME_HIP(lime::generic_project(first, 5, d, dtype, s));
-    LIME_HIP(lime::generic_attention(history_attention(hp, lens, per_user ? static_cast<int64_t>(m) * d : 0, LP, B, N, d, h, m, scale_hist,
-                                                       phi, dtype), s));
-    LIME_HIP(lime::generic_project(&values, 1, d, dtype, s));
-    LIME_HIP(lime::generic_attention(candidate_attention(cp, O, B, C, d, h, m, scale_cand, dtype), s));
+    const int64_t link_stride = per_user ? static_cast<int64_t>(m) * d : 0;
+    const bool hist_fused = history_fused(E, LC, Wq_hist, Wk_hist, Wv_hist, LP, B, N, d, h, m);
+    const bool cand_fused = rows_fused(T, L, LP, Wq_cand, Wk_cand, Wv_cand, O, B, C, d, h, m);
+    lime::Projection first[5];
+    int n = 0;
+    auto project = [&](const lime::Projection& j) { first[n++] = j; };
+    if (!hist_fused)
+      project({LC, Wq_hist, hp.Qt, link_rows}), project({E, Wk_hist, hp.Ks, hist_rows, lens, N}), project({E, Wv_hist, hp.Vs, hist_rows, lens, N});
+    if (!cand_fused) project({T, Wq_cand, cp.Qt, static_cast<int64_t>(B) * C}), project({L, Wk_cand, cp.Kt, m});
+    if (n > 0) LIME_HIP(lime::generic_project(first, n, d, dtype, s));
+    if (hist_fused) {
+      LIME_HIP(lime::fused_history({E, lens, LC, link_stride, Wq_hist, Wk_hist, Wv_hist, LP, B, N, d, h, m, scale_hist, phi, dtype, hp.Qt}, s));
+    } else {
+      LIME_HIP(lime::generic_attention(history_attention(hp, lens, link_stride, LP, B, N, d, h, m, scale_hist, phi, dtype), s));
+    }
+    if (cand_fused) {
+      LIME_HIP(lime::fused_rows(candidate_rows(T, L, LP, Wq_cand, Wk_cand, Wv_cand, O, B, C, d, h, m, scale_cand, dtype), s));
+    } else {
+      const lime::Projection values{LP, Wv_cand, cp.Vt, static_cast<int64_t>(B) * m};
+      LIME_HIP(lime::generic_project(&values, 1, d, dtype, s));
+      LIME_HIP(lime::generic_attention(candidate_attention(cp, O, B, C, d, h, m, scale_cand, dtype), s));
+    }
     return LIME_OK;
   }
   if (!p.on_mfma) {  // the two stages as they are (general kernels, or the matrix-core ones where each applies)

@@ -86,8 +86,44 @@ struct GenericAttention {
   int dtype;  // of O
   void* scratch;  // generic_attention_scratch bytes; nullptr = a workgroup takes all chunks of the keys (the same bits)
 };
+// The states of a history's chunks (chunk_keys items each) folded: acc [B][chunks][m][d], ml [B][chunks][m][h][2] (maximum, sum).
+hipError_t generic_merge_chunks(const float* acc, const float* ml, const int32_t* lens, void* O, int B, int m, int N, int chunk_keys,
+                                int d, int h, int phi, int dtype, hipStream_t s);
 size_t generic_attention_scratch(int64_t B, int64_t q_rows, int64_t n_keys, int64_t d, int64_t h);
 hipError_t generic_attention(const GenericAttention& a, hipStream_t s);
+
+// Both stages with their projections inside (fused_history.hip, fused_rows.hip): every pointer 16-byte aligned, no weight null.
+// LP[b][m][d] = the links over user b's history.
+struct FusedHistory {
+  const void* E;        // [B][N][d]
+  const int32_t* lens;  // nullable
+  const void* L;        // [.][m][d]
+  int64_t l_user_stride;
+  const void *Wq, *Wk, *Wv;
+  void* LP;
+  int B, N, d, h, m;
+  float scale;
+  int phi, dtype;
+  void* scratch;  // room for 2 B N d floats
+};
+bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m);
+hipError_t fused_history(const FusedHistory& q, hipStream_t s);
+// O[b][rows][d] = rows over m links, kPhiSoftmax or kPhiSilu / m.
+struct FusedRows {
+  const void* X;            // [B][rows][d]
+  const int32_t* row_lens;  // nullable; rows at or past it are written as zeros
+  const void* Ksrc;         // [.][m][d]: keys are Ksrc Wk ...
+  int64_t k_user_stride;
+  const void* Vsrc;         // ... and values Vsrc Wv
+  int64_t v_user_stride;
+  const void *Wq, *Wk, *Wv;
+  void* O;
+  int B, rows, d, h, m;
+  float scale;
+  int phi, dtype;
+};
+bool fused_rows_supported(int64_t B, int64_t rows, int d, int h, int m);
+hipError_t fused_rows(const FusedRows& q, hipStream_t s);
 
 // QK cache (Section 3.3): W[rows][h][m] = softmax over m of scale * <Q[row]_head, K[i]_head> (Q, K projected, fp32);
 // and the online weighted sum O[b][c][col] = sum_i W[b][c][head(col)][i] * V[b][i][col] (V projected, fp32);

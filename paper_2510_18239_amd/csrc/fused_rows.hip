@@ -1,0 +1,315 @@
+// Rows over the m links with its projections inside, see fused.hpp.
+#include "fused.hpp"
+
+namespace lime {
+namespace {
+
+// ----------------------------------------------------------------------------- rows over the m links
+struct RowsDev {
+  const void *X, *Ksrc, *Vsrc, *Wq, *Wk, *Wv;
+  const int32_t* row_lens;
+  int64_t k_user_stride, v_user_stride;
+  void* O;
+  int B, rows, h, m, parts, total;  // workgroups per (user, head)
+  float scale;
+};
+
+template <typename T, int D, int DH, int MH>
+struct RowsLds {
+  using H = Head<DH>;
+  static constexpr int MT = (MH + 1) / 2;
+  using W = Weights<T, D, DH>;
+  static constexpr int kKeys = MT * H::KF * 3 * 1024, kValues = MH * H::DB * H::VP * 1024, kParts = kWaves * 4096;
+  static constexpr int kBytes = W::kBytes + kKeys + kValues + kParts;
+};
+
+// A workgroup: a part of a user's rows, one head, all m <= 16 MH links; a wave takes every eighth tile of 32 rows.  Keys and
+// values of the links are computed by all waves first.  What bounds it: as above at few rows; from a few thousand tiles on the
+// vector ALUs (exponentials, and the planes of queries and weights).
+template <typename T, int D, int DH, int MH, int PHI>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fused_rows_kernel(RowsDev a) {
+  using H = Head<DH>;
+  using Lds = RowsLds<T, D, DH, MH>;
+  constexpr int K1 = D / 16, DB = H::DB, NP = kPlanes<T>, MT = Lds::MT, kBlocks = MT * DB, kSplits = std::max(1, std::min(kWaves / (2 * kBlocks), K1));
+  constexpr int kRegs = MH == 1 ? 8 : 16;  // registers of a tile of links that count
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  using W = typename Lds::W;
+  unsigned char* const weights = lds;
+  bf16x8* const keys = reinterpret_cast<bf16x8*>(lds + W::kBytes);
+  bf16x8* const values = keys + Lds::kKeys / 16;
+  float* const parts = reinterpret_cast<float*>(values + Lds::kValues / 16);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, g = lane >> 5;
+  int id = block_on_xcd(a.total);
+  if (id >= a.total) return;
+  const int head = id % a.h;
+  id /= a.h;
+  const int share = id % a.parts, b = id / a.parts;
+  const int tiles = (a.rows + 31) / 32, step = a.parts * kWaves;
+  // keys and values of the links: blocks (side, link tile, 32 columns), each by kSplits waves
+  const int c0 = n % DH;  // this lane's column of the head's (first) block
+  const T* const keys_from = static_cast<const T*>(a.Ksrc) + b * a.k_user_stride;
+  const T* const values_from = static_cast<const T*>(a.Vsrc) + b * a.v_user_stride;
+  const T *const wk = static_cast<const T*>(a.Wk) + head * DH, *const wv = static_cast<const T*>(a.Wv) + head * DH, *const wq = static_cast<const T*>(a.Wq) + head * DH;
+  auto link_row = [&](const T* from, int lt, int i) { return from + static_cast<int64_t>(min(32 * lt + i, a.m - 1)) * D; };
+  const int block = wave % (2 * kBlocks), part = wave / (2 * kBlocks);
+  const bool of_values = block >= kBlocks;  // uniform over the wave
+  unsigned char* const own = reinterpret_cast<unsigned char*>(parts) + wave * 4096;
+
+  // everything the workgroup reads at first is asked for here, in the order of its use
+  W columns;
+  RowTile<T, D / kSplits> links;
+  RowTile<T, D> items;
+  columns.load(wk, wv, wq, threadIdx.x);
+  if (part < kSplits)
+    links.load([&](int i) { return link_row(of_values ? values_from : keys_from, block / DB % MT, i) + part * (D / kSplits); }, lane);
+  __builtin_amdgcn_sched_barrier(0);  // (ahead of the wait for the length)
+  const int rlen = a.row_lens ? min(a.row_lens[b], a.rows) : a.rows, last = max(rlen, 1) - 1;
+  auto row_of = [&](int t, int i) { return static_cast<const T*>(a.X) + (static_cast<int64_t>(b) * a.rows + min(32 * t + i, last)) * D; };
+  auto wanted = [&](int t) { return t < tiles && 32 * t < rlen; };  // uniform over the wave
+  auto fetch = [&](int t) {
+    if (wanted(t)) items.load([&](int i) { return row_of(t, i); }, lane);
+  };
+  f32x16 q[DB];  // queries of a tile (lane = row)
+  auto project = [&] {
+    Planes<NP> w[2][DB];
+#pragma unroll
+    for (int ob = 0; ob < DB; ++ob) q[ob] = zeros();
+    items.each(own, lane, [&](int kk) {
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob) w[kk & 1][ob] = W::fragment(weights, 2, ob, kk, lane);
+    }, [&](int kk, const Planes<NP>& x) {
+      Planes<NP> r[DB];
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob) r[ob] = x;
+      products(w[kk & 1], r, q);
+    });
+  };
+  int t = share * kWaves + wave;
+  fetch(t);
+  __builtin_amdgcn_sched_barrier(0);
+  columns.park(weights, threadIdx.x);
+  lds_barrier();
+  f32x16 links_part = zeros();
+  if (part < kSplits) links_part = partial_block<W>(links, weights, of_values, block % DB, part, own, !of_values, lane);
+  if (wanted(t)) project();
+  if (part < kSplits) park_block(reinterpret_cast<float*>(own), links_part, lane);
+  fetch(t + step);
+  lds_barrier();
+#pragma unroll
+  for (int u = wave; u < 4 * kBlocks; u += kWaves) {  // half a block's sum each: registers 8f .. of block (side, link tile, 32 columns)
+    const int f = u % 2, ob = u / 2 % DB, lt = u / 2 / DB % MT;
+    const bool is_value = u >= 2 * kBlocks;
+    const float* src = parts + (u / 2) * 1024 + 512 * f + lane;
+    float x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      x[t] = src[t * 64];
+#pragma unroll
+      for (int p = 1; p < kSplits; ++p) x[t] += src[p * 2 * kBlocks * 1024 + t * 64];
+    }
+    if (__any(has_nan(x, 8))) {
+      const f32x16 y = is_value ? exact_block<T, D, false>(link_row(values_from, lt, n), wv + c0 + 32 * ob, g)
+                                : exact_block<T, D, true>(link_row(keys_from, lt, n), wk + c0 + 32 * ob, g);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] = x[t] == x[t] ? x[t] : f ? y[8 + t] : y[t];
+    }
+    if (is_value) {
+      // links past the last have weight zero; what was read in their place may be infinite
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] = 32 * lt + 16 * f + 8 * (t >> 2) + 4 * g + (t & 3) < a.m ? x[t] : 0.f;
+      if (2 * lt + f < MH) park(values + ((2 * lt + f) * DB + ob) * H::VP * 64, value_planes<DH>(split(x), n), lane);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] *= a.scale;
+      // (a narrow head's columns are in the first registers)
+      if (DH >= 32 || f == 0) park(keys + (lt * H::KF + (DH >= 32 ? 2 * ob + f : 0)) * 3 * 64, column_planes<DH, true>(x), lane);
+    }
+  }
+  lds_barrier();
+
+  // logits of all links to weights in place; the factor of the result
+  auto to_weights = [&](f32x16 (&s)[MT], float& top, auto exact_tag) {
+    constexpr bool kExact = decltype(exact_tag)::value;
+    if (a.m < 16 * MH) {  // uniform
+#pragma unroll
+      for (int lt = 0; lt < MT; ++lt)
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i)
+          if (32 * lt + 8 * (i >> 2) + 4 * g + (i & 3) >= a.m) s[lt][i] = PHI != kPhiSoftmax ? 0.f : kExact ? -INFINITY : kMaskedLogit;
+    }
+    if (PHI != kPhiSoftmax) {
+#pragma unroll
+      for (int lt = 0; lt < MT; ++lt)
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) s[lt][i] = kExact ? silu(s[lt][i]) : silu_finite(s[lt][i]);
+      return 1.f / static_cast<float>(a.m);
+    }
+    float total = 0.f;
+    top = s[0][0];
+#pragma unroll
+    for (int lt = 0; lt < MT; ++lt)
+#pragma unroll
+      for (int i = 0; i < kRegs; ++i) top = fmaxf(top, s[lt][i]);
+    top = pair_max(top);
+    const float base = kExact && top == -INFINITY ? 0.f : top;
+#pragma unroll
+    for (int lt = 0; lt < MT; ++lt)
+#pragma unroll
+      for (int i = 0; i < kRegs; ++i) s[lt][i] = kExact ? expf(s[lt][i] - base) : exp_finite(s[lt][i] - base), total += s[lt][i];
+    return 1.f / pair_sum(total);
+  };
+
+  for (bool first = true; t < tiles; t += step, first = false) {
+    float res[DH / 2], inv = 0.f;
+    if (32 * t < rlen) {  // uniform over the wave
+      if (!first) {
+        project();
+        fetch(t + step);
+      }
+      f32x16 s[MT];
+      {
+        Planes<3> x[H::KF], k[MT][H::KF];
+#pragma unroll
+        for (int f = 0; f < H::KF; ++f) {
+          x[f] = column_planes<DH, false>(half_of(q[f / 2], f % 2).x);
+#pragma unroll
+          for (int lt = 0; lt < MT; ++lt) k[lt][f] = parked<3>(keys + (lt * H::KF + f) * 3 * 64, lane);
+        }
+#pragma unroll
+        for (int lt = 0; lt < MT; ++lt) s[lt] = zeros();
+#pragma unroll
+        for (int t = 0; t < kColumnTerms<DH>; ++t)
+#pragma unroll
+          for (int f = 0; f < H::KF; ++f)
+#pragma unroll
+            for (int lt = 0; lt < MT; ++lt) s[lt] = column_term<DH>(t, k[lt][f], x[f], s[lt]);
+      }
+      float top = 0.f;
+      inv = to_weights(s, top, std::false_type{});
+      f32x16 acc[DB];
+      Planes<3> p[MH];
+#pragma unroll
+      for (int ob = 0; ob < DB; ++ob) acc[ob] = zeros();
+#pragma unroll
+      for (int f = 0; f < MH; ++f) p[f] = split_half(s[f / 2], f % 2);
+      // (the last term apart: with two blocks the values' planes are read again rather than kept)
+      auto terms = [&](int from, int to) {
+        Planes<H::VP> v[MH][DB];
+#pragma unroll
+        for (int f = 0; f < MH; ++f)
+#pragma unroll
+          for (int ob = 0; ob < DB; ++ob) v[f][ob] = parked<H::VP>(values + (f * DB + ob) * H::VP * 64, lane);
+        auto term = [&](int t, int f) {
+#pragma unroll
+          for (int ob = 0; ob < DB; ++ob) acc[ob] = value_term<DH>(t, v[f][ob], p[f], acc[ob]);
+        };
+        if constexpr (DB == 1) {
+#pragma unroll
+          for (int t = from; t < to; ++t)
+#pragma unroll
+            for (int f = 0; f < MH; ++f) term(t, f);
+        } else {
+#pragma unroll
+          for (int f = 0; f < MH; ++f)
+#pragma unroll
+            for (int t = from; t < to; ++t) term(t, f);
+        }
+      };
+      if constexpr (DB == 1) {
+        terms(0, kValueTerms<DH>);
+      } else {
+        terms(0, kValueTerms<DH> - 1);
+        wave_lds_fence();
+        terms(kValueTerms<DH> - 1, kValueTerms<DH>);
+      }
+      head_result<DH>(acc, res);
+      const bool bad = either_lane(has_nan(res, DH / 2) || inv != inv || top < kLowLogit);  // (both lanes of a row)
+      if (__any(bad)) {
+#pragma unroll
+        for (int lt = 0; lt < MT; ++lt) s[lt] = zeros();
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) {
+          const f32x16 x = exact_block<T, D, true>(row_of(t, n), wq + c0 + 32 * ob, g);
+#pragma unroll
+          for (int lt = 0; lt < MT; ++lt) {
+            const f32x16 k = exact_block<T, D, true>(link_row(keys_from, lt, n), wk + c0 + 32 * ob, g);
+#pragma unroll
+            for (int i = 0; i < std::min(DH / 2, 16); ++i) s[lt] = mfma_f32(k[i] * a.scale, x[i], s[lt]);
+          }
+        }
+        const float exact_inv = to_weights(s, top, std::true_type{});
+        inv = bad ? exact_inv : inv;
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) {
+          f32x16 x = zeros();
+#pragma unroll
+          for (int lt = 0; lt < MT; ++lt) {
+            const f32x16 v = exact_block<T, D, false>(link_row(values_from, lt, n), wv + c0 + 32 * ob, g);
+#pragma unroll
+            for (int i = 0; i < kRegs; ++i) x = mfma_f32(32 * lt + 8 * (i >> 2) + 4 * g + (i & 3) < a.m ? v[i] : 0.f, s[lt][i], x);
+          }
+#pragma unroll
+          for (int i = 0; i < std::min(DH / 2, 16); ++i) res[16 * ob + i] = bad ? x[i] : res[16 * ob + i];
+        }
+      }
+    }
+    const int r = 32 * t + n;
+    if (r >= a.rows) continue;
+    T* orow = static_cast<T*>(a.O) + (static_cast<int64_t>(b) * a.rows + r) * D + head * DH + 4 * g;
+#pragma unroll
+    for (int q = 0; q < H::QUADS; ++q) {
+      float x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = r < rlen ? res[4 * q + i] * inv : 0.f;
+      store_quad(orow + 8 * q, x);
+    }
+  }
+}
+
+template <typename T, int D, int DH, int MH, int PHI>
+hipError_t launch_rows(const RowsDev& a, hipStream_t s) {
+  constexpr int kBytes = RowsLds<T, D, DH, MH>::kBytes;
+  static_assert(kBytes <= 160 * 1024);
+  if constexpr (kBytes > 64 * 1024) {
+    static PerDevice granted;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(fused_rows_kernel<T, D, DH, MH, PHI>), kBytes); e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((fused_rows_kernel<T, D, DH, MH, PHI>), dim3((a.total + 7) / 8 * 8), dim3(kThreads), kBytes, s, a);
+  return hipGetLastError();
+}
+
+template <typename T, int D, int DH, int PHI>
+hipError_t dispatch_rows(const RowsDev& a, hipStream_t s) {
+  if (a.m <= 16) return launch_rows<T, D, DH, 1, PHI>(a, s);
+  if (a.m <= 32) return launch_rows<T, D, DH, 2, PHI>(a, s);
+  if constexpr (DH >= 32) return launch_rows<T, D, DH, 4, PHI>(a, s);
+  return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t dispatch_rows_shape(const RowsDev& a, int d, int phi, hipStream_t s) {
+#define LIME_CASE(D, DH) \
+  if (d == D && d / a.h == DH) return phi == kPhiSoftmax ? dispatch_rows<T, D, DH, kPhiSoftmax>(a, s) : dispatch_rows<T, D, DH, kPhiSilu>(a, s);
+  LIME_FUSED_SHAPES(LIME_CASE)
+#undef LIME_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// All links' logits of a row lie in registers: 64 of them, 32 where the head is narrow.
+bool fused_rows_supported(int64_t B, int64_t rows, int d, int h, int m) {
+  if (!fused_shape(d, h) || m > (d / h >= 32 ? 64 : 32)) return false;
+  return B * ((rows + 32 * kWaves - 1) / (32 * kWaves)) * h < (int64_t{1} << 31) - 8 && rows < (int64_t{1} << 31) - 64 * kWaves * compute_units();
+}
+
+hipError_t fused_rows(const FusedRows& q, hipStream_t s) {
+  // a workgroup per compute unit where the rows are many, a tile per wave where they are few
+  const int64_t pairs = static_cast<int64_t>(q.B) * q.h, tiles = (static_cast<int64_t>(q.rows) + 31) / 32;
+  const int parts = static_cast<int>(std::min((compute_units() + pairs - 1) / pairs, (tiles + kWaves - 1) / kWaves));
+  const RowsDev a{q.X, q.Ksrc, q.Vsrc, q.Wq, q.Wk, q.Wv, q.row_lens, q.k_user_stride, q.v_user_stride, q.O,
+                  q.B, q.rows, q.h, q.m, parts, static_cast<int>(pairs * parts), q.scale};
+  return q.dtype == 0 ? dispatch_rows_shape<float>(a, q.d, q.phi, s) : dispatch_rows_shape<bf16_t>(a, q.d, q.phi, s);
+}
+
+}  // namespace lime

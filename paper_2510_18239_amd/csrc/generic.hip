@@ -208,6 +208,7 @@ struct AttnDev {
   int q_rows, n_keys, d, dh, q_tiles, h, chunks;  // chunks > 1: a workgroup takes one chunk
   float scale;
   float *part_acc, *part_ml;  // chunks > 1: [B][chunks][q_rows][d], [B][chunks][q_rows][h][2] (running max, running sum)
+  int chunk_keys = 32 * kChunkTiles;
 };
 
 // The weights of two states that are folded into one: their maxima relative to the common one, which `mx` becomes.  (A
@@ -552,7 +553,7 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
   const int row = static_cast<int>(idx / a.d), col = static_cast<int>(idx % a.d), head = col / a.dh;
   const int qlen = a.q_lens ? min(a.q_lens[b], a.q_rows) : a.q_rows;
   const int klen = a.k_lens ? min(a.k_lens[b], a.n_keys) : a.n_keys;
-  const int used = (klen + 32 * kChunkTiles - 1) / (32 * kChunkTiles);
+  const int used = (klen + a.chunk_keys - 1) / a.chunk_keys;
   float out = 0.f;
   if (used > 0 && row < qlen) {
     const int64_t slot0 = static_cast<int64_t>(b) * a.chunks * a.q_rows + row;
@@ -568,6 +569,13 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(AttnDev a) {
     out = num * (1.f / (PHI == kPhiSoftmax ? den : static_cast<float>(klen)));
   }
   store_as(static_cast<OutT*>(a.O) + static_cast<int64_t>(b) * a.q_rows * a.d + idx, out);
+}
+
+template <typename OutT, int PHI>
+hipError_t launch_merge(const AttnDev& dev, int B, hipStream_t s) {
+  const int64_t total = static_cast<int64_t>(dev.q_rows) * dev.d;
+  hipLaunchKernelGGL((attention_merge_kernel<OutT, PHI>), dim3(static_cast<unsigned>((total + 255) / 256), B), dim3(256), 0, s, dev);
+  return hipGetLastError();
 }
 
 // (a workgroup's waves share the keys, chunks with workgroups of their own) of an attention: what fills the compute units.
@@ -591,10 +599,7 @@ hipError_t launch_attention(const AttnDev& dev, int B, bool split, hipStream_t s
     hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, true, ROWS>), dim3(units, dev.chunks, B), dim3(256), 0, s, dev);
   else
     hipLaunchKernelGGL((attention_kernel<OutT, PHI, KJ, false, ROWS>), dim3((units + 3) / 4, 1, B), dim3(256), 0, s, dev);
-  if (dev.chunks > 1) {
-    const int64_t total = static_cast<int64_t>(dev.q_rows) * dev.d;
-    hipLaunchKernelGGL((attention_merge_kernel<OutT, PHI>), dim3(static_cast<unsigned>((total + 255) / 256), B), dim3(256), 0, s, dev);
-  }
+  if (dev.chunks > 1) return launch_merge<OutT, PHI>(dev, B, s);
   return hipGetLastError();
 }
 
@@ -786,6 +791,16 @@ hipError_t gated_block_typed(const GenericGatedBlock& g, hipStream_t s) {
 hipError_t generic_gated_block(const GenericGatedBlock& g, hipStream_t s) {
   if (g.B <= 0 || g.rows <= 0) return hipSuccess;
   return g.dtype == 0 ? gated_block_typed<float>(g, s) : gated_block_typed<bf16_t>(g, s);
+}
+
+hipError_t generic_merge_chunks(const float* acc, const float* ml, const int32_t* lens, void* O, int B, int m, int N, int chunk_keys,
+                                int d, int h, int phi, int dtype, hipStream_t s) {
+  AttnDev dev{};
+  dev.O = O, dev.k_lens = lens, dev.q_rows = m, dev.n_keys = N, dev.d = d, dev.dh = d / h, dev.h = h;
+  dev.chunks = (N + chunk_keys - 1) / chunk_keys, dev.chunk_keys = chunk_keys;
+  dev.part_acc = const_cast<float*>(acc), dev.part_ml = const_cast<float*>(ml);
+  if (dtype == 0) return phi == kPhiSoftmax ? launch_merge<float, kPhiSoftmax>(dev, B, s) : launch_merge<float, kPhiSilu>(dev, B, s);
+  return phi == kPhiSoftmax ? launch_merge<bf16_t, kPhiSoftmax>(dev, B, s) : launch_merge<bf16_t, kPhiSilu>(dev, B, s);
 }
 
 size_t generic_attention_scratch(int64_t B, int64_t q_rows, int64_t n_keys, int64_t d, int64_t h) {

@@ -1,0 +1,116 @@
+"""The stages that project by themselves (fused_history.hip, fused_rows.hip) against plain 64-bit arithmetic, at the edges of
+their tiles (32 items, 16 links), chunks (256 items) and forms (one per head width and number of links)."""
+
+import pytest
+import torch
+
+from paper_2510_18239_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+# fp32: a result is behind three sums in a row (projection, logits, weighted sum) of at most 48 roundings of 2^-24 each, and an
+# error of a logit is one of its weight: 3 * 48 * 2^-24 = 8.6e-6.  bf16: operands and results rounded to 2^-9 once each.
+TOLERANCE = {torch.float32: 1e-5, torch.bfloat16: 1e-2}
+
+
+def _attention(q, k, v, h, scale, lens, silu):
+    (B, R, d), n = q.shape, k.shape[1]
+    q, k, v = (x.reshape(B, -1, h, d // h).transpose(1, 2) for x in (q, k, v))
+    s = q @ k.transpose(2, 3) * scale
+    live = torch.ones((B, 1, 1, n), dtype=torch.bool, device=q.device)
+    count = torch.full((B, 1, 1, 1), n, device=q.device)
+    if lens is not None:
+        live = (torch.arange(n, device=q.device)[None, :] < lens[:, None])[:, None, None]
+        count = lens[:, None, None, None]
+    p = torch.where(live, s * torch.sigmoid(s), 0.0) / count if silu else torch.softmax(torch.where(live, s, -torch.inf), dim=-1)
+    return (p @ v).transpose(1, 2).reshape(B, R, d)
+
+
+def _request(E, lens, L, W, T, LP, h, scale, silu):
+    """Both stages in 64 bits; the second from the link states as they were stored."""
+    D = lambda x: x.double()  # noqa: E731
+    B = E.shape[0]
+    rows = lambda w: (D(L) @ D(w))[None].expand(B, -1, -1)  # noqa: E731
+    E = torch.where((torch.arange(E.shape[1], device=E.device)[None, :] < lens[:, None])[:, :, None], D(E), 0.0)
+    return (_attention(rows(W[0]), E @ D(W[1]), E @ D(W[2]), h, scale, lens, silu),
+            _attention(D(T) @ D(W[3]), rows(W[4]), D(LP) @ D(W[5]), h, scale, None, False))
+
+
+def _inputs(B, N, C, d, m, dtype, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rn = lambda shape, std=1.0: (torch.randn(shape, generator=g, device="cuda") * std).to(dtype)  # noqa: E731
+    lens = torch.randint(1, N + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lens[0] = N
+    E = rn((B, N, d))
+    E[torch.arange(N, device="cuda")[None, :] >= lens[:, None]] = torch.nan  # padding is never read
+    return E, lens, rn((m, d)), rn((B, C, d)), [rn((d, d), d ** -0.5) for _ in range(6)]
+
+
+def _error(x, ref):
+    return float((x.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,N,C,d,h,m", [
+    (2, 1, 1, 32, 4, 1), (3, 31, 33, 32, 4, 8), (2, 32, 31, 32, 2, 16), (1, 33, 300, 32, 1, 17), (2, 255, 257, 64, 8, 16),
+    (2, 256, 32, 64, 4, 32), (3, 257, 65, 64, 2, 33), (1, 513, 96, 64, 1, 64), (2, 100, 40, 128, 8, 31), (5, 777, 129, 128, 4, 64),
+    (1, 300, 20, 128, 4, 128), (2, 70, 64, 64, 1, 15), (40, 64, 600, 32, 4, 16),
+])
+@pytest.mark.parametrize("silu", [False, True])
+def test_against_64_bits(B, N, C, d, h, m, dtype, silu):
+    if dtype == torch.bfloat16 and d // h >= 32 and m % 32 == 0:
+        m -= 4  # (the bf16 matrix-core kernels' otherwise)
+    E, lens, L, T, W = _inputs(B, N, C, d, m, dtype, seed=N + C)
+    scale = (d // h) ** -0.5
+    LP, O = binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, scale, scale, xor_attention=silu)
+    refs = _request(E, lens, L, W, T, LP, h, scale, silu)
+    assert _error(LP, refs[0]) <= TOLERANCE[dtype] and _error(O, refs[1]) <= TOLERANCE[dtype]
+    # the stages by themselves, and O[S] (rows over links with SiLU, per-user links)
+    call = binding.lime_xor_history if silu else binding.lime_link_history
+    alone = call(E, lens, L, *W[:3], h, scale)
+    assert torch.equal(alone[0] if silu else alone, LP)
+    assert torch.equal(binding.lime_score_candidates(T, L, LP, *W[3:], h, scale), O)
+    if silu:
+        links = torch.stack([L.roll(b, 0) for b in range(B)])
+        OT, OS = binding.lime_xor_history(E, lens, links, *W[:3], h, scale, want_os=True)
+        x = E.double()
+        p = [links.double() @ w.double() for w in W[:3]]
+        live = torch.arange(N, device="cuda")[None, :] < lens[:, None]
+        assert _error(OT[0], _request(E[:1], lens[:1], links[0], W, T[:1], LP[:1], h, scale, True)[0][0]) <= TOLERANCE[dtype]
+        ref = _attention(torch.nan_to_num(x) @ W[0].double(), p[1], p[2], h, scale, None, True) * live[:, :, None]
+        assert _error(OS, ref) <= TOLERANCE[dtype] and torch.equal(OS[~live], torch.zeros_like(OS[~live]))
+
+
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+@pytest.mark.parametrize("silu", [False, True])
+def test_numbers_without_planes(d, h, m, silu):
+    """fp32 numbers that round to an infinite bf16 number, and infinities and NaN: each stays with its row."""
+    B, N, C = 3, 90, 70
+    E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=d + m)
+    lens[:] = torch.tensor([N, 33, 40])
+    E = torch.where((torch.arange(N, device="cuda")[None, :] < lens[:, None])[:, :, None], torch.nan_to_num(E), torch.nan)
+    scale = (d // h) ** -0.5
+    run = lambda: binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, scale, scale, xor_attention=silu)  # noqa: E731
+    plain = run()
+    # the same request with the second user's items, and some candidates, at the upper end of the range and the weights at the lower
+    big, Wb = 3.4e38, [w.clone() for w in W]
+    E2, T2, Wb[1], Wb[2], Wb[3] = E.sign() * big, T.sign() * big, W[1] / big, W[2] / big, W[3] / big
+    LP, O = binding.lime_request(E2, lens, L, *Wb[:3], T2, L, *Wb[3:], h, scale, scale, xor_attention=silu)
+    refs = _request(E2, lens, L, Wb, T2, LP, h, scale, silu)
+    # (W / 3.4e38 is about 2^-131: 18 bits of it are left, and the products' sums are of that precision)
+    assert _error(LP, refs[0]) <= 2 ** -14 and _error(O, refs[1]) <= 2 ** -14
+    E[1, 5, 3], T[0, 40, 0], T[2, 69, 1] = torch.inf, -torch.inf, torch.nan
+    LP, O = run()
+    assert torch.equal(LP[::2], plain[0][::2]) and not torch.isfinite(LP[1]).any()
+    clean = torch.ones((B, C), dtype=torch.bool, device="cuda")
+    clean[1], clean[0, 40], clean[2, 69] = False, False, False
+    assert torch.equal(O[clean], plain[1][clean]) and not torch.isfinite(O[~clean]).any()
+
+
+def test_unaligned_rows_take_the_general_kernels():
+    B, N, C, d, h, m = 2, 300, 50, 64, 2, 32
+    E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=3)
+    off = lambda x: torch.cat([x.new_zeros(1), x.reshape(-1)])[1:].view(x.shape)  # noqa: E731
+    LP, O = binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, 0.2, 0.2)
+    LP1, O1 = binding.lime_request(off(E), lens, L, *W[:3], off(T), L, *W[3:], h, 0.2, 0.2)
+    assert _error(LP1, LP.double()) <= 1e-5 and _error(O1, O.double()) <= 1e-5
