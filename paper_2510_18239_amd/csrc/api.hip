@@ -191,8 +191,8 @@ lime::GenericAttention history_attention(const HistoryPlan& p, const int32_t* le
 // A stage whose projections the general kernels form themselves (fused_history.hip, fused_rows.hip).  The states of a history's
 // chunks lie where the projected history would.
 bool history_fused(const void* E, const void* LC, const void* Wq, const void* Wk, const void* Wv, const void* LP, int32_t B, int32_t N,
-                   int32_t d, int32_t h, int32_t m) {
-  return Wq && Wk && Wv && all_aligned16(E, LC, Wq, Wk, Wv, LP) && lime::fused_history_supported(B, N, d, h, m);
+                   int32_t d, int32_t h, int32_t m, int32_t dtype) {
+  return Wq && Wk && Wv && all_aligned16(E, LC, Wq, Wk, Wv, LP) && lime::fused_history_supported(B, N, d, h, m, dtype);
 }
 bool rows_fused(const void* X, const void* Ksrc, const void* Vsrc, const void* Wq, const void* Wk, const void* Wv, const void* O, int32_t B,
                 int32_t rows, int32_t d, int32_t h, int32_t m) {
@@ -259,7 +259,7 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     const bool chunked = ws_bytes >= p.bytes;
     p = plan_history(workspace, B, N, d, h, m, per_user, want_os);
     if (!chunked) p.scratch = nullptr;
-    const bool lp_fused = history_fused(E, LC, Wq, Wk, Wv, LP, B, N, d, h, m);
+    const bool lp_fused = history_fused(E, LC, Wq, Wk, Wv, LP, B, N, d, h, m, dtype);
     const bool os_fused = want_os && rows_fused(E, LC, LC, Wq, Wk, Wv, OS, B, N, d, h, m);
     lime::Projection jobs[6];
     int n = 0;
@@ -733,7 +733,7 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
     if (p.total - p.hist_bytes < cp.bytes) cp.scratch = nullptr;
     const int64_t link_rows = (per_user ? B : 1) * static_cast<int64_t>(m), hist_rows = static_cast<int64_t>(B) * N;
     const int64_t link_stride = per_user ? static_cast<int64_t>(m) * d : 0;
-    const bool hist_fused = history_fused(E, LC, Wq_hist, Wk_hist, Wv_hist, LP, B, N, d, h, m);
+    const bool hist_fused = history_fused(E, LC, Wq_hist, Wk_hist, Wv_hist, LP, B, N, d, h, m, dtype);
     const bool cand_fused = rows_fused(T, L, LP, Wq_cand, Wk_cand, Wv_cand, O, B, C, d, h, m);
     lime::Projection first[5];
     int n = 0;

@@ -106,7 +106,7 @@ struct FusedHistory {
   int phi, dtype;
   void* scratch;  // room for 2 B N d floats
 };
-bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m);
+bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m, int dtype);
 hipError_t fused_history(const FusedHistory& q, hipStream_t s);
 // O[b][rows][d] = rows over m links, kPhiSoftmax or kPhiSilu / m.
 struct FusedRows {

@@ -11,7 +11,7 @@ struct HistoryDev {
   int64_t l_user_stride;
   void* LP;
   float *part_acc, *part_ml;  // more than one chunk: [B][chunks][m][d], [B][chunks][m][h][2]
-  int B, N, h, m, chunks, groups, total;  // groups of 32 MT links
+  int B, N, h, m, chunks, total;
   float scale;
 };
 
@@ -28,7 +28,7 @@ struct HistoryLds {
 // of these calls the chain of latencies of one tile (rows and weights from memory, projections, logits, weights), which is why
 // a tile has a wave of its own and the small operands are computed by all waves, a part of the sum each.
 template <typename T, int D, int DH, int MT, int PHI>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fused_history_kernel(HistoryDev a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_history_kernel(HistoryDev a) {
   using H = Head<DH>;
   using Lds = HistoryLds<T, D, DH, MT>;
   constexpr int K1 = D / 16, DB = H::DB, NP = kPlanes<T>, kBlocks = MT * DB, kSplits = std::min(kWaves / kBlocks, K1);
@@ -41,14 +41,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   int id = block_on_xcd(a.total);
   if (id >= a.total) return;
   const int head = id % a.h;
-  id /= a.h;
-  const int group = id % a.groups;
-  id /= a.groups;
-  const int chunk = id % a.chunks, b = id / a.chunks;
   const int c0 = n % DH;  // this lane's column of the head's (first) block
-  const int link0 = group * 32 * MT;
+  id /= a.h;
+  const int chunk = id % a.chunks, b = id / a.chunks;
   auto link_row = [&](int lt, int i) {
-    return static_cast<const T*>(a.L) + b * a.l_user_stride + static_cast<int64_t>(min(link0 + 32 * lt + i, a.m - 1)) * D;
+    return static_cast<const T*>(a.L) + b * a.l_user_stride + static_cast<int64_t>(min(32 * lt + i, a.m - 1)) * D;
   };
   const int block = wave % kBlocks, part = wave / kBlocks;  // queries: block (link tile, 32 columns), a part of its sum
   const T *const wq = static_cast<const T*>(a.Wq) + head * DH, *const wk = static_cast<const T*>(a.Wk) + head * DH, *const wv = static_cast<const T*>(a.Wv) + head * DH;
@@ -238,7 +235,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int used = min(kWaves, (klen - chunk * kChunkKeys + 31) / 32);  // (none for a user without history)
 #pragma unroll
   for (int u = wave; u < MT * H::QUADS; u += kWaves) {
-    const int lt = u / H::QUADS, q = u % H::QUADS, link = link0 + 32 * lt + n;
+    const int lt = u / H::QUADS, q = u % H::QUADS, link = 32 * lt + n;
     const float* st = states + lt * kTile + lane;
     float m[kWaves], top = -INFINITY;
 #pragma unroll
@@ -285,21 +282,21 @@ hipError_t launch_history(const HistoryDev& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A narrow head's links come 32 at a time, others 64 where there are more than 32 (registers).
+// Whether a head of dh columns is one that this kernel is for, see fused_history_supported.
+constexpr bool narrow_pays(int d, int dh, bool fp32) { return dh >= 32 || (fp32 ? d == 32 : d != 64 || dh > 8); }
+
 template <typename T, int D, int DH>
-hipError_t dispatch_history(HistoryDev a, int phi, hipStream_t s) {
-  const bool wide = DH >= 32 && a.m > 32;
-  a.groups = (a.m + (wide ? 63 : 31)) / (wide ? 64 : 32);
-  a.total = a.B * a.chunks * a.groups * a.h;
+hipError_t dispatch_history(const HistoryDev& a, int phi, hipStream_t s) {
   if constexpr (DH >= 32)
-    if (wide) return phi == kPhiSoftmax ? launch_history<T, D, DH, 2, kPhiSoftmax>(a, s) : launch_history<T, D, DH, 2, kPhiSilu>(a, s);
+    if (a.m > 32) return phi == kPhiSoftmax ? launch_history<T, D, DH, 2, kPhiSoftmax>(a, s) : launch_history<T, D, DH, 2, kPhiSilu>(a, s);
   return phi == kPhiSoftmax ? launch_history<T, D, DH, 1, kPhiSoftmax>(a, s) : launch_history<T, D, DH, 1, kPhiSilu>(a, s);
 }
 
 template <typename T>
 hipError_t dispatch_history_shape(const HistoryDev& a, int d, int phi, hipStream_t s) {
 #define LIME_CASE(D, DH) \
-  if (d == D && d / a.h == DH) return dispatch_history<T, D, DH>(a, phi, s);
+  if constexpr (narrow_pays(D, DH, sizeof(T) == 4)) \
+    if (d == D && d / a.h == DH) return dispatch_history<T, D, DH>(a, phi, s);
   LIME_FUSED_SHAPES(LIME_CASE)
 #undef LIME_CASE
   return hipErrorInvalidValue;
@@ -309,15 +306,21 @@ int history_chunks(int64_t N) { return static_cast<int>((N + kChunkKeys - 1) / k
 
 }  // namespace
 
-// Any number of links up to 128: the states of a history's chunks then fit where separate kernels keep its keys and values
-// (2 N d numbers of a user; m (d + 2h) of each 256 items or part of them), with room to align them.
-bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m) {
-  if (m > 128 || !fused_shape(d, h)) return false;
-  return B * history_chunks(N) * ((m + 31) / 32) * h < (int64_t{1} << 31) - 8;
+// As many links as one workgroup takes, since a second one would project the history once more (64 links of 8 heads of 16
+// columns, 128 users of 512 items in fp32: 186 us, the general kernels 110); and narrow heads, each of whose workgroups projects
+// 32 columns whatever it uses, where that is cheap: in bf16 but for the narrowest of eight (57 us for the 65 536 items and 16
+// candidates, the general kernels 56), in fp32 at d = 32 (27 and 35; 80 and 77 at 262 144 items).  In fp32 at d = 64 four heads
+// take 39 and 43 us, but 123 and 112 at four times the items, eight heads 77 and 53.
+// The states of a history's chunks fit where separate kernels keep its keys and values (2 N d numbers of a user; m (d + 2h) of
+// each 256 items or part of them), with room to align them.
+bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m, int dtype) {
+  if (!fused_shape(d, h) || m > (d / h >= 32 ? 64 : 32)) return false;
+  return narrow_pays(d, d / h, dtype == 0) && B * history_chunks(N) * h < (int64_t{1} << 31) - 8;
 }
 
 hipError_t fused_history(const FusedHistory& q, hipStream_t s) {
-  HistoryDev a{q.E, q.L, q.Wq, q.Wk, q.Wv, q.lens, q.l_user_stride, q.LP, nullptr, nullptr, q.B, q.N, q.h, q.m, history_chunks(q.N), 0, 0, q.scale};
+  HistoryDev a{q.E, q.L, q.Wq, q.Wk, q.Wv, q.lens, q.l_user_stride, q.LP, nullptr, nullptr, q.B, q.N, q.h, q.m, history_chunks(q.N), 0, q.scale};
+  a.total = a.B * a.chunks * a.h;
   if (a.chunks > 1) {
     char* scratch = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(q.scratch) + 15) & ~uintptr_t{15});
     a.part_acc = reinterpret_cast<float*>(scratch);

@@ -27,7 +27,7 @@ struct RowsLds {
 // values of the links are computed by all waves first.  What bounds it: as above at few rows; from a few thousand tiles on the
 // vector ALUs (exponentials, and the planes of queries and weights).
 template <typename T, int D, int DH, int MH, int PHI>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fused_rows_kernel(RowsDev a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_rows_kernel(RowsDev a) {
   using H = Head<DH>;
   using Lds = RowsLds<T, D, DH, MH>;
   constexpr int K1 = D / 16, DB = H::DB, NP = kPlanes<T>, MT = Lds::MT, kBlocks = MT * DB, kSplits = std::max(1, std::min(kWaves / (2 * kBlocks), K1));
