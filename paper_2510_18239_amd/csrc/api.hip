@@ -245,12 +245,16 @@ int32_t history_impl(const char* fn, int phi, const void* E, const int32_t* lens
     q.B = B, q.N = N, q.d = d, q.h = h, q.m = m, q.scale = scale, q.phi = phi, q.walk = walk;
     // one pack launch for everything this call needs on the matrix cores: the operands of both kernels and `extra`
     lime::PackJobs jobs;
-    lime::links_over_history_jobs(q, workspace, jobs);
     if (os_on_mfma) lime::queries_over_links_jobs(os_query(E, lens, LC, link_stride, Wq, Wk, Wv, OS, B, N, d, h, m, scale),
                                                    static_cast<char*>(workspace) + p.bytes, jobs);
     for (int i = 0; i < n_extra; ++i) jobs.weights[jobs.n_weights++] = extra[i];
-    LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
-    q.packed = true;
+    if (lime::links_over_history_takes(q, jobs)) {
+      q.beside = &jobs;
+    } else {
+      lime::links_over_history_jobs(q, workspace, jobs);
+      LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
+      q.packed = true;
+    }
     LIME_HIP(lime::links_over_history(q, workspace, s));
   } else {
     p = plan_history(nullptr, B, N, d, h, m, per_user, want_os);
@@ -763,8 +767,9 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
     return lime_score_candidates(T, L, LP, Wq_cand, Wk_cand, Wv_cand, O, B, C, d, h, m, scale_cand, dtype, cand_ws,
                                  p.total - p.hist_bytes, stream);
   }
-  // Four kernels: one pack launch for the operands of both stages, the history kernel, the merge step that also writes
-  // the candidate stage's value image, the candidate kernel.
+  // Three or four kernels: the history kernel, beside which the candidate stage's operands are packed (few rows), or one pack
+  // launch for the operands of both stages and the history kernel; the merge step that also writes the candidate stage's
+  // value image, the candidate kernel.
   hipStream_t s = static_cast<hipStream_t>(stream);
   lime::LinksOverHistory q{};
   q.E = E, q.lens = lens, q.LC = LC, q.lc_user_stride = per_user ? static_cast<int64_t>(m) * d : 0;
@@ -777,10 +782,15 @@ int32_t request_impl(const char* fn, const RequestPlan& p, const void* E, const 
   if (norms != nullptr)
     q.q_norm = norms->hist_q, q.values_norm = norms->cand_v, c.x_norm = norms->cand_q, c.k_norm = norms->cand_k, q.walk = phi == lime::kPhiSoftmax;
   lime::PackJobs jobs;
-  lime::links_over_history_jobs(q, workspace, jobs);
   lime::queries_over_links_jobs(c, cand_ws, jobs, /*values=*/false);
-  LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
-  q.packed = c.packed = true;
+  c.packed = true;
+  if (lime::links_over_history_takes(q, jobs)) {
+    q.beside = &jobs;
+  } else {
+    lime::links_over_history_jobs(q, workspace, jobs);
+    LIME_HIP(lime::pack_operands(jobs, d, h, m, s));
+    q.packed = true;
+  }
   q.Wv_values = Wv_cand, q.values_image = lime::queries_over_links_values(c, cand_ws);
   LIME_HIP(lime::links_over_history(q, workspace, s));
   LIME_HIP(lime::queries_over_links(c, cand_ws, s));

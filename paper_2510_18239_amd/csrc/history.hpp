@@ -22,6 +22,9 @@ struct WalkPlan {
   bool coop;  // h-wave workgroups that stage each tile once through LDS
 };
 WalkPlan walk_plan(int B, int N, int d, int h);
+// mfma_history_raw.hip: the kernel that takes its operands as they are; `workgroups` of it and those of `beside`.
+bool history_raw_fits(const LinksOverHistory& q, int64_t workgroups, const PackJobs& beside);
+hipError_t history_raw(const HistArgs& a, const LinksOverHistory& q, hipStream_t s);
 hipError_t walk_history(const HistArgs& a, int d, int h, int m, int users, bool coop, hipStream_t s);
 
 }  // namespace lime

@@ -435,7 +435,10 @@ struct LinksOverHistory {
   RowNorm q_norm;       // applied to the link rows LC by the pack step
   bool walk;            // run on the kernel of mfma_history_walk.hip (softmax only)
   const void* images[3];  // when set: W_K^T, W_V and Q~ (per user where lc_user_stride is set) come from here
+  const PackJobs* beside; // when set (links_over_history_takes): the operands are taken as they are, and these jobs run in the
+                          // same launch
 };
+bool links_over_history_takes(const LinksOverHistory& a, const PackJobs& beside);
 void links_over_history_jobs(const LinksOverHistory& a, void* workspace, PackJobs& jobs);
 bool links_over_history_supported(int d, int h, int m);
 size_t links_over_history_workspace(int B, int N, int d, int h, int m, bool q_per_user);
