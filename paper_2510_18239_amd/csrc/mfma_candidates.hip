@@ -63,13 +63,16 @@ __global__ __launch_bounds__(64 * H) void queries_over_links_kernel(MainArgs a) 
   // H waves read it.
   constexpr int P = 2;
   constexpr int LW = DH / 16;
-  // With d = 256 the W_Q^T slice alone is a quarter of the register file; with many links (whose
-  // logits and weights need registers too) the second half of its k-steps lives in LDS instead and is
-  // read once per tile, which keeps the kernel free of register spills.
-  // (eight heads: eight waves share the register file two to a SIMD, so with many links three quarters go there)
-  constexpr int KL = D < 256 ? 0 : H == 8 ? (M >= 96 ? 3 * K1 / 4 : 0) : (M >= 128 ? K1 / 2 : 0);  // k-steps of W_Q^T kept in LDS
+  // Eight heads at d = 256: eight waves share the register file two to a SIMD, so with many links (whose logits and weights
+  // need registers too) three quarters of the W_Q^T slice live in LDS instead and are read once per tile.
+  constexpr int KL = D == 256 && H == 8 && M >= 96 ? 3 * K1 / 4 : 0;  // k-steps of W_Q^T kept in LDS
   static_assert(!FUSED || (KL == 0 && M <= DH), "the fused form is for few links");
   constexpr int KR = K1 - KL;                // k-steps kept in registers
+  // With up to four heads the stationary operands of many links fill the AGPRs exactly, from where the matrix cores read them as
+  // readily: pinned there, W_Q^T needs no LDS and none of them the 160 copies a tile (of 770 vector instructions) that the
+  // compiler makes where it keeps them there by itself.  131 072 rows of d=256 h=4 m=128: 51 -> 47 us, and 91.5 -> 87.5 us for the
+  // prepared request.  With 64 links there are few copies to save (headline request 23.4 | 23.7 us pinned).
+  constexpr bool kPinned = D == 256 && H < 8 && M >= 96;
   constexpr int CPR = D / 8;            // 16-byte chunks per row of X
   constexpr int PITCH = 2 * D + 16;     // LDS row pitch of an X tile, bytes
   constexpr int OCPR = DH / 8;          // 16-byte chunks per row of one head's output slice
@@ -369,6 +372,24 @@ __global__ __launch_bounds__(64 * H) void queries_over_links_kernel(MainArgs a) 
     first_product(xs[0]);
   }
   int b = b_first, r0 = r0_first;  // the tile being computed
+  auto settle = [](bf16x8& x) {
+    if constexpr (kPinned) asm volatile("" : "+a"(x));
+    else asm volatile("" : "+v"(x));
+  };
+  if constexpr (kPinned) {
+#pragma unroll
+    for (int kk = 0; kk < KR; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < FB; ++mb) settle(wq[kk][mb]);
+#pragma unroll
+    for (int kk = 0; kk < K2; ++kk)
+#pragma unroll
+      for (int lb = 0; lb < LB; ++lb) settle(ka[kk][lb]);
+#pragma unroll
+    for (int kk = 0; kk < K3; ++kk)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) settle(va[kk][mb]);
+  }
 
   for (int base = first; base < last; base += P) {
 #pragma unroll
@@ -385,11 +406,11 @@ __global__ __launch_bounds__(64 * H) void queries_over_links_kernel(MainArgs a) 
 #pragma unroll
         for (int kk = 0; kk < K2; ++kk)
 #pragma unroll
-          for (int lb = 0; lb < LB; ++lb) asm volatile("" : "+v"(ka[kk][lb]));
+          for (int lb = 0; lb < LB; ++lb) settle(ka[kk][lb]);
 #pragma unroll
         for (int kk = 0; kk < K3; ++kk)
 #pragma unroll
-          for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(va[kk][mb]));
+          for (int mb = 0; mb < MB; ++mb) settle(va[kk][mb]);
         asm volatile("" : "+v"(rlen));
       }
 
