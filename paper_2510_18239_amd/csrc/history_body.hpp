@@ -80,16 +80,29 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
   const int i_end = min(len, i_begin + a.chunk_items);
 
   const bf16_t* Eb = a.E + static_cast<int64_t>(b) * a.N * D;
-  auto ask_rows = [&](int i0, int buf) {  // this wave's part of a step; rows past the tensor's end as its last one
-    const int last = a.N - 1 - i0;
+  // This wave's part of a step.  A load's rows are RPL j past its first one's, whose row number has those bits clear: the pieces
+  // of the others lie where its own do, but for a constant in the swizzle.
+  constexpr int RPL = 64 / CPR;
+  static_assert((LW & (LW - 1)) == 0 && LW > 0, "row numbers split into bits");
+  const int first_row = wave * (LW * RPL) + lane / CPR;
+  const int first_piece = first_row * (2 * D) + (lane % CPR ^ row_swizzle<D>(first_row)) * 16;
+  auto ask_rows = [&](int i0, int buf) {
     const bf16_t* base = Eb + static_cast<int64_t>(i0) * D;
-    int q0 = wave * LW * 64 + lane;
-    asm volatile("" : "+v"(q0));  // (what follows from it is formed here, not carried through the loop)
+    const unsigned dst = lds_offset_of(lds) + buf * S::kXBytes + wave * LW * 1024;
+    if (i0 + S::kRows <= a.N) {  // uniform
+      int piece = first_piece;
+      asm volatile("" : "+v"(piece));  // (the others are formed here, not carried through the loop)
+#pragma unroll
+      for (int j = 0; j < LW; ++j) load_to_lds(dst + j * 1024, piece ^ (row_swizzle<D>(RPL * j) * 16), base + RPL * j * D);
+      return;
+    }
+    const int last = a.N - 1 - i0;  // rows past the tensor's end as its last one
+    int row = first_row;
+    asm volatile("" : "+v"(row));
 #pragma unroll
     for (int j = 0; j < LW; ++j) {
-      const int q = q0 + j * 64, r = q / CPR;
-      load_to_lds(lds_offset_of(lds) + buf * S::kXBytes + (wave * LW + j) * 1024,
-                  min(r, last) * (2 * D) + (q % CPR ^ row_swizzle<D>(r)) * 16, base);
+      const int r = row + RPL * j;
+      load_to_lds(dst + j * 1024, min(r, last) * (2 * D) + (lane % CPR ^ row_swizzle<D>(r)) * 16, base);
     }
   };
   auto clear_tail = [&](int i0, int buf) {  // what this wave asked for past the chunk's end becomes zeros
