@@ -6,9 +6,9 @@ A "step" is one LIME request of the headline workload: the link states of the N-
 h=4, m=64, bf16, inputs resident in HBM.  Candidate and output buffers rotate through more
 memory than the 256 MiB last-level cache holds, so the candidate stream really comes from HBM.
 
-Throughput is that of a serving loop: a request is one C-ABI call, lime_request (four kernels: pack,
+Throughput is that of a serving loop: a request is one C-ABI call, lime_request (three kernels: pack beside
 history, merge + value projection, candidates; --calls two: lime_link_history + lime_score_candidates,
-five kernels), launched from the host with arguments marshalled once, and requests of different users
+four kernels), launched from the host with arguments marshalled once, and requests of different users
 are independent, so the loop keeps --streams of them in flight, each on its own stream with its own
 link states and workspace; the small kernels of one request then run beside the candidate kernel of
 another.  (--graphs replays one captured HIP graph per request instead; on this runtime that costs
@@ -47,7 +47,7 @@ def parse_args():
     p.add_argument("--history", type=int, default=2048, help="N of the headline workload")
     p.add_argument("--rotate-mib", type=int, default=544, help="candidate+output bytes to rotate through (0 = reuse one pair)")
     p.add_argument("--streams", type=int, default=4, help="requests kept in flight (one stream, link-state buffer and workspace each)")
-    p.add_argument("--graphs", action="store_true", help="replay one captured HIP graph per request instead of launching its five kernels from the host")
+    p.add_argument("--graphs", action="store_true", help="replay one captured HIP graph per request instead of launching its kernels from the host")
     p.add_argument("--calls", choices=("one", "two"), default="one",
                    help="a request as one C-ABI call (lime_request) or as lime_link_history + lime_score_candidates")
     p.add_argument("--no-cpu-baseline", action="store_true")
@@ -609,7 +609,7 @@ def extras(binding, synth, torch, dev, timed, pct):
         res[f"candidate_kernel_{label}"] = {"kernel_avg_ms": kavg, "kernel_min_ms": min(k), "GBps": nbytes / (kavg * 1e-3) / 1e9,
                                             "frac_of_hbm_peak": nbytes / (kavg * 1e-3) / 1e9 / HBM_PEAK_GBS}
     binding.profile_enable(False)
-    # the request on operands prepared once per model (lime_prepare): four kernels instead of five, no weight packing
+    # the request on operands prepared once per model (lime_prepare): no weight packing
     prepared = binding.lime_prepare(L, L, Wq, Wk, Wv, Wq, Wk, w.h, w.softmax_scale, w.softmax_scale)
     hip = HipRuntime()
     st = hip.stream()

@@ -197,7 +197,7 @@ int32_t lime_request_prepared(const void* E, const int32_t* lens, const void* T,
  * lime_score_candidates on that LP with the *_cand weights and scale_cand.  Arguments, layouts, nullable pointers
  * (Wq_cand, Wk_cand, Wv_cand: NULL = identity) and errors as for those two entry points; LP[B][m][d] and
  * O[B][C][d] are both written, nothing is kept between calls.  On the bf16 matrix-core shapes with 16-byte aligned
- * pointers this is four kernels instead of six: one launch packs the operands of both stages, and the step that
+ * pointers this is three or four kernels instead of six: one launch packs the operands of both stages (few history rows: the candidate stage's, beside the history kernel), and the step that
  * finishes the link states also projects them with Wv_cand into the layout the candidate kernel loads.  LP is then
  * bit-identical to lime_link_history / lime_xor_history; O agrees with lime_score_candidates within the bf16
  * tolerance (the value projection sums in another order).  Otherwise the two stages run one after the other as
