@@ -84,25 +84,23 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
   // of the others lie where its own do, but for a constant in the swizzle.
   constexpr int RPL = 64 / CPR;
   static_assert((LW & (LW - 1)) == 0 && LW > 0, "row numbers split into bits");
-  const int first_row = wave * (LW * RPL) + lane / CPR;
-  const int first_piece = first_row * (2 * D) + (lane % CPR ^ row_swizzle<D>(first_row)) * 16;
   auto ask_rows = [&](int i0, int buf) {
     const bf16_t* base = Eb + static_cast<int64_t>(i0) * D;
     const unsigned dst = lds_offset_of(lds) + buf * S::kXBytes + wave * LW * 1024;
+    int l = lane;
+    asm volatile("" : "+v"(l));  // (what follows from it is formed here, not carried through the loop: registers)
+    const int first_row = wave * (LW * RPL) + l / CPR;
     if (i0 + S::kRows <= a.N) {  // uniform
-      int piece = first_piece;
-      asm volatile("" : "+v"(piece));  // (the others are formed here, not carried through the loop)
+      const int piece = first_row * (2 * D) + (l % CPR ^ row_swizzle<D>(first_row)) * 16;
 #pragma unroll
       for (int j = 0; j < LW; ++j) load_to_lds(dst + j * 1024, piece ^ (row_swizzle<D>(RPL * j) * 16), base + RPL * j * D);
       return;
     }
     const int last = a.N - 1 - i0;  // rows past the tensor's end as its last one
-    int row = first_row;
-    asm volatile("" : "+v"(row));
 #pragma unroll
     for (int j = 0; j < LW; ++j) {
-      const int r = row + RPL * j;
-      load_to_lds(dst + j * 1024, min(r, last) * (2 * D) + (lane % CPR ^ row_swizzle<D>(r)) * 16, base);
+      const int r = first_row + RPL * j;
+      load_to_lds(dst + j * 1024, min(r, last) * (2 * D) + (l % CPR ^ row_swizzle<D>(r)) * 16, base);
     }
   };
   auto clear_tail = [&](int i0, int buf) {  // what this wave asked for past the chunk's end becomes zeros

@@ -68,11 +68,13 @@ __global__ __launch_bounds__(64 * H) void queries_over_links_kernel(MainArgs a) 
   constexpr int KL = D == 256 && H == 8 && M >= 96 ? 3 * K1 / 4 : 0;  // k-steps of W_Q^T kept in LDS
   static_assert(!FUSED || (KL == 0 && M <= DH), "the fused form is for few links");
   constexpr int KR = K1 - KL;                // k-steps kept in registers
-  // With up to four heads the stationary operands of many links fill the AGPRs exactly, from where the matrix cores read them as
-  // readily: pinned there, W_Q^T needs no LDS and none of them the 160 copies a tile (of 770 vector instructions) that the
-  // compiler makes where it keeps them there by itself.  131 072 rows of d=256 h=4 m=128: 51 -> 47 us, and 91.5 -> 87.5 us for the
-  // prepared request.  With 64 links there are few copies to save (headline request 23.4 | 23.7 us pinned).
-  constexpr bool kPinned = D == 256 && H < 8 && M >= 96;
+  // With four heads the stationary operands of 128 links fill the AGPRs exactly, from where the matrix cores read them as readily:
+  // pinned there, W_Q^T needs no LDS and none of them the 160 copies a tile (of 770 vector instructions) that the compiler makes
+  // where it keeps them there by itself.  131 072 rows of d=256 h=4 m=128: 51 -> 47 us, and 91.5 -> 87.5 us for the prepared
+  // request.  Fewer links have fewer copies, and pinning costs a workgroup 128 moves ahead of its first tile: with 96 the prepared
+  // request of 8 users takes 34.4 | 34.1 us pinned (8192 candidates each), 18.0 | 18.2 with one user and 16 candidates; with 64 the
+  // headline request 23.4 | 23.7.
+  constexpr bool kPinned = D == 256 && H < 8 && M >= 128;
   constexpr int CPR = D / 8;            // 16-byte chunks per row of X
   constexpr int PITCH = 2 * D + 16;     // LDS row pitch of an X tile, bytes
   constexpr int OCPR = DH / 8;          // 16-byte chunks per row of one head's output slice

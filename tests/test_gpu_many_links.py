@@ -1,4 +1,4 @@
-"""Rows over 96 or 128 links at d = 256, four heads (the candidate-side kernel with its operands pinned in AGPRs), against plain
+"""Rows over 96 or 128 links at d = 256, four heads (128: the candidate-side kernel with its operands pinned in AGPRs), against plain
 64-bit arithmetic: one row, remainders of a 32-row tile, and workgroups that pass from one user to the next."""
 
 import pytest
