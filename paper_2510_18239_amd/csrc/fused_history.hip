@@ -247,7 +247,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       if (w >= used) break;  // uniform
-      const float f = PHI != kPhiSoftmax ? 1.f : m[w] == -INFINITY ? 0.f : exp_finite(m[w] - top);
+      // (expf: tiles' maxima may lie further apart than exp_finite, which is NaN from -2.36e38 on, takes)
+      const float f = PHI != kPhiSoftmax ? 1.f : m[w] == -INFINITY ? 0.f : expf(m[w] - top);
       den = fmaf(f, st[w * kState + 64], den);
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = fmaf(f, st[w * kState + (2 + 4 * q + r) * 64], x[r]);

@@ -107,6 +107,37 @@ def test_numbers_without_planes(d, h, m, silu):
     assert torch.equal(O[clean], plain[1][clean]) and not torch.isfinite(O[~clean]).any()
 
 
+def _first_column(d, h):
+    """Weights under which each head's logit is the product of the two rows' first columns, which the values do not hear of."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    Wq, Wk = torch.zeros((d, d), device="cuda"), torch.zeros((d, d), device="cuda")
+    Wq[0, :: d // h] = Wk[0, :: d // h] = 1.0
+    Wv = torch.randn((d, d), generator=g, device="cuda") * d ** -0.5
+    Wv[0] = 0.0
+    return Wq, Wk, Wv
+
+
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+def test_tiles_of_a_chunk_at_the_ends_of_the_range(d, h, m):
+    """Finite logits of one chunk's tiles so far apart that their difference times log2 e, or the difference itself, is not finite."""
+    Wq, Wk, Wv = _first_column(d, h)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    rn = lambda shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    B, N = 3, 160
+    E, L, T = rn((B, N, d)), torch.zeros((m, d), device="cuda"), rn((B, 40, d))
+    L[:, 0] = 1.0
+    for b, (high, low) in enumerate([(1.2e38, -1.2e38), (3e38, -3e38), (1.0, -1.2e38)]):
+        E[b, :, 0] = low
+        E[b, 32 * b : 32 * b + 32, 0] = high
+    W = [Wq, Wk, Wv] + [rn((d, d)) * d ** -0.5 for _ in range(3)]
+    lens = torch.full((B,), N, dtype=torch.int32, device="cuda")
+    LP, O = binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, 1.0, 0.2)
+    ref = _attention((L.double() @ Wq.double())[None].expand(B, -1, -1), E.double() @ Wk.double(), E.double() @ Wv.double(), h, 1.0, lens, False)
+    for b in range(B):
+        assert _error(LP[b], ref[b]) <= TOLERANCE[torch.float32], b
+    assert torch.isfinite(O).all()
+
+
 def test_unaligned_rows_take_the_general_kernels():
     B, N, C, d, h, m = 2, 300, 50, 64, 2, 32
     E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=3)
