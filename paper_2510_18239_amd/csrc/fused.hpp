@@ -3,14 +3,19 @@
 // user; projected queries, keys and values never exist in memory, and a request is two launches (three with a history of more
 // than kChunkKeys items) where projections and attentions as kernels of their own (generic.hip) are four.
 //
-// fp32 products on the bf16 matrix instruction.  An fp32 number is the exact sum of three bf16 numbers, x = x0 + x1 + x2 (each
-// the remainder rounded to nearest: at most 2^-9 and 2^-18 of x), and a product is taken as x0 y0 + x0 y1 + x1 y0 + x1 y1 +
-// x0 y2 + x2 y0 with fp32 sums: what is left out is below 2^-26 of |x y|, less than a rounding of the sum.  Six instructions of
-// 32 cycles for 16 terms, against eight of 64 for the fp32 instruction (v_mfma_f32_32x32x2_f32), and fewer roundings of the
-// accumulator: six per 16 terms instead of eight.  bf16 inputs are one plane, their products one instruction.
-// Where an operand is infinite, or rounds to infinity, its remainders are NaN: a result that holds a NaN is computed again
-// with the fp32 instruction (`exact`) and taken from there, so that infinities stay where they are and no other row's bits
-// change.
+// fp32 products on the bf16 matrix instruction.  An fp32 number is the sum of three bf16 numbers, x = x0 + x1 + x2 (each the
+// remainder rounded to nearest: at most 2^-8 and 2^-17 of x), and a product is taken as x0 y0 + x0 y1 + x1 y0 + x1 y1 +
+// x0 y2 + x2 y0 with fp32 sums: what is left out is 2^-27 of |x y| in the root mean square and 2^-24 at most, of either sign.
+// Six instructions of 32 cycles for 16 terms, against eight of 64 for the fp32 instruction (v_mfma_f32_32x32x2_f32), and fewer
+// roundings of the accumulator: six per 16 terms instead of eight.  bf16 inputs are one plane, their products one instruction.
+// The sum of the planes is exact where none of them lies under the smallest bf16 number (2^-133), as the third one of a number
+// below 2^-110 would.  So with fp32 storage whatever is split is taken 2^24 times as large (kUp), or 2^48 times as sums of two such
+// come, and is exact down to the smallest number; the units of sums (kSum, kUnit) are taken out where it costs least.  (About 100 of the
+// kernels' some 1000 vector instructions a tile at d = 128: 16 users of 777 items and 1001 candidates 32.1 -> 33.0 us, the smallest
+// request 15.3 -> 15.6.)  With bf16 storage everything is taken as it is: what results are rounded to, nine bits, is held from 2^-124 on.
+// Where an operand is infinite, or rounds to infinity (fp32: from 2^104 on, being 2^24 times as large), its remainders are NaN; a
+// sum may pass the range too (fp32: from 2^79 on, a logit or result from 2^55 on).  A result that is not finite is computed again with the fp32
+// instruction (`exact`) and taken from there, so that infinities stay where they are and no other row's bits change.
 //
 // Fragments as in mfma.hpp.  A head narrower than 32 columns has its columns repeated over the 32 lanes of a weight fragment,
 // which makes room for the planes: at d/h = 8 a lane's slots of one key fragment hold two planes, and the 32 rows of a value
@@ -57,6 +62,16 @@ __device__ __forceinline__ unsigned take_pair(float& a, float& b) {
   a -= __uint_as_float(p << 16), b -= __uint_as_float(p & 0xffff0000u);
   return p;
 }
+// How much larger what is split is; what a projection's sum, of rows and weights so much larger, stands for is kSum of it, what a
+// product of such sums with other numbers so much larger stands for is kUnit of it.
+template <typename T>
+constexpr float kUp = sizeof(T) == 4 ? 0x1p24f : 1.f;
+template <typename T>
+constexpr float kDown = 1.f / kUp<T>;
+template <typename T>
+constexpr float kSum = kDown<T> * kDown<T>;
+template <typename T>
+constexpr float kUnit = kSum<T> * kDown<T>;
 __device__ __forceinline__ Planes<3> split(const float (&x)[8]) {
   u32x4 p[3];
 #pragma unroll
@@ -98,7 +113,7 @@ __device__ __forceinline__ void products(const Planes<1> (&a)[N], const Planes<1
 __device__ __forceinline__ Planes<3> planes_of(u32x4 a, u32x4 b) {
   float x[8];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(a[t]), x[4 + t] = __uint_as_float(b[t]);
+  for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(a[t]) * kUp<float>, x[4 + t] = __uint_as_float(b[t]) * kUp<float>;
   return split(x);
 }
 
@@ -186,7 +201,7 @@ struct RowTile {
   }
 };
 
-// 32 rows times 32 columns with the fp32 instruction, for results that the planes made NaN.  `row` and `col`: this lane's.
+// 32 rows times 32 columns with the fp32 instruction, for results that are not finite from the planes.  `row` and `col`: this lane's.
 // ROWS_KEPT: lane = row, registers = columns; otherwise lane = column, registers = rows.
 template <typename T, int D, bool ROWS_KEPT>
 __device__ __forceinline__ f32x16 exact_block(const T* row, const T* col, int g) {
@@ -199,14 +214,14 @@ __device__ __forceinline__ f32x16 exact_block(const T* row, const T* col, int g)
   return acc;
 }
 
-// (also where infinities of both signs meet: their exact results are computed for nothing)
+__device__ __forceinline__ bool not_finite(float x) { return !(fabsf(x) < INFINITY); }
+// Whether any is not finite (or, for nothing, their sum).
 template <typename V>
-__device__ __forceinline__ bool has_nan(const V& x, int count) {
+__device__ __forceinline__ bool any_not_finite(const V& x, int count) {
   float z[2] = {x[0], x[1]};
 #pragma unroll
   for (int i = 2; i < count; ++i) z[i % 2] += x[i];
-  z[0] += z[1];
-  return z[0] != z[0];
+  return not_finite(z[0] + z[1]);
 }
 
 __device__ __forceinline__ bool either_lane(bool x) { return pair_max(x ? 1.f : 0.f) != 0.f; }
@@ -299,27 +314,29 @@ __device__ __forceinline__ void store_quad(OutT* dst, const float (&x)[4]) {
   }
 }
 
-// exp to a unit in the last place without the handling of its ends: 2^(x log2 e) from the product rounded, times what the
-// rounding left out (x log2 e = t + r, e^x = 2^t (1 + r ln 2)).  NaN where x is infinite.
-__device__ __forceinline__ float exp_finite(float x) {
-  constexpr float kLog2e = 1.44269502f, kLog2eRest = 1.92596303e-8f, kLn2 = 0.693147182f;
+// `times` e^x for unit x, to a unit in the last place without the handling of its ends: 2^(x log2 e) from the product rounded,
+// times what the rounding left out (x log2 e = t + r, e^x = 2^t (1 + r ln 2)).  NaN where x is infinite, zero below 2^-126.
+// (unit, times: powers of two)
+__device__ __forceinline__ float exp_finite(float x, float unit, float times) {
+  const float kLog2e = 1.44269502f * unit, kLog2eRest = 1.92596303e-8f * unit, kLn2 = 0.693147182f;
   const float t = x * kLog2e;
   const float r = fmaf(x, kLog2eRest, fmaf(x, kLog2e, -t));
   const float p = __builtin_amdgcn_exp2f(t);
-  return fmaf(p, r * kLn2, p);
+  return p * fmaf(r, kLn2 * times, times);
 }
-// x / (1 + e^-x), the quotient corrected once.  (Past 88 the exponential is as good as infinite; NaN where x is infinite.)
-__device__ __forceinline__ float silu_finite(float x) {
-  const float den = 1.f + exp_finite(fminf(-x, 88.f));
-  const float r = __builtin_amdgcn_rcpf(den), q = x * r;
-  return fmaf(fmaf(-den, q, x), r, q);
+// `times` x / (1 + e^-x) for unit x, the quotient corrected once.  (Past 88 the exponential is as good as infinite; NaN where x is
+// infinite.)
+__device__ __forceinline__ float silu_finite(float x, float unit, float times) {
+  const float den = 1.f + exp_finite(fminf(-x, 88.f / unit), unit, 1.f);
+  const float r = __builtin_amdgcn_rcpf(den), y = x * (unit * times), q = y * r;
+  return fmaf(fmaf(-den, q, y), r, q);
 }
 __device__ __forceinline__ float silu(float x) { return x / (1.f + expf(-x)); }
-// The logit of a key that does not count, in place of -infinity where NaN asks for the exact way.  kLowLogit: maxima below it
-// (which no finite operands of ordinary size give) take that way too.
+// The logit (as the sum that stands for it) of a key that does not count, in place of -infinity where NaN asks for the exact way.
+// kLowLogit: maxima below it (which no finite operands of ordinary size give) take that way too.
 constexpr float kMaskedLogit = -2e38f, kLowLogit = -1e38f;
 
-// A head's columns of three weight matrices in LDS, as planes in rows: [matrix][DB][planes][D][columns, 32 at most].
+// A head's columns of three weight matrices in LDS, kUp times as large, as planes in rows: [matrix][DB][planes][D][columns, 32 at most].
 // Fetched in whole lines (a load instruction costs a compute unit 16 cycles, whatever it brings: column by column they were 2.8
 // of the 19.6 us of the history kernel at 16 x 777 rows), and read as fragments through the transposing LDS read.
 template <typename T, int D, int DH>
@@ -350,7 +367,7 @@ struct Weights {
       if constexpr (NP == 3) {
         float x[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] = __uint_as_float(v[i][t % 4]);
+        for (int t = 0; t < 8; ++t) x[t] = __uint_as_float(v[i][t % 4]) * kUp<T>;
         const Planes<3> p = split(x);  // (both halves alike)
 #pragma unroll
         for (int k = 0; k < 3; ++k) *reinterpret_cast<bf16x4*>(dst + k * kPlane) = __builtin_shufflevector(p.p[k], p.p[k], 0, 1, 2, 3);

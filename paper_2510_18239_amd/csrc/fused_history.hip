@@ -96,13 +96,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
       for (int p = 1; p < kSplits; ++p) q[t] += src[p * kBlocks * 1024 + t * 64];
     }
-    if (__any(has_nan(q, 8))) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) q[t] *= kSum<T>;
+    if (__any(any_not_finite(q, 8))) {
       const f32x16 x = exact_block<T, D, true>(link_row(lt, n), wq + c0 + 32 * ob, g);
 #pragma unroll
-      for (int t = 0; t < 8; ++t) q[t] = q[t] == q[t] ? q[t] : f ? x[8 + t] : x[t];
+      for (int t = 0; t < 8; ++t) q[t] = !not_finite(q[t]) ? q[t] : f ? x[8 + t] : x[t];
     }
 #pragma unroll
-    for (int t = 0; t < 8; ++t) q[t] *= a.scale;
+    for (int t = 0; t < 8; ++t) q[t] = q[t] * a.scale * kUp<T>;
     // (a narrow head's columns are in the first registers)
     if (DH >= 32 || f == 0) park(queries + (lt * H::KF + (DH >= 32 ? 2 * ob + f : 0)) * 3 * 64, column_planes<DH, false>(q), lane);
   }
@@ -112,7 +114,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   const int left = klen - k0 - 4 * g;
   const bool ragged = k0 + 32 > klen;  // uniform over the wave
   auto past = [&](int i) { return 8 * (i >> 2) + (i & 3) >= left; };
-  // logits of a tile to weights in place: register i of this lane is item k0 + 8 (i / 4) + 4g + i % 4
+  // logits of a tile (kUnit) to weights (kUp times as large) in place, all as they are the exact way: register i of this lane is
+  // item k0 + 8 (i / 4) + 4g + i % 4
   auto to_weights = [&](f32x16& s, float& top, float& total, auto exact_tag) {
     constexpr bool kExact = decltype(exact_tag)::value;
     if (ragged) {
@@ -127,11 +130,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
       top = pair_max(top);
       const float base = kExact && top == -INFINITY ? 0.f : top;  // (every logit is -inf: weights of zero)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = kExact ? expf(s[i] - base) : exp_finite(s[i] - base), total += s[i];
+      for (int i = 0; i < 16; ++i) s[i] = kExact ? expf(s[i] - base) : exp_finite(s[i] - base, kUnit<T>, kUp<T>), total += s[i];
       total = pair_sum(total);
     } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = kExact ? silu(s[i]) : silu_finite(s[i]);
+      for (int i = 0; i < 16; ++i) s[i] = kExact ? silu(s[i]) : silu_finite(s[i], kUnit<T>, kUp<T>);
     }
   };
   // items past the last: what was read in their place may be infinite
@@ -182,7 +185,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
     for (int lt = 0; lt < MT; ++lt) {
       head_result<DH>(acc[lt], res[lt]);
-      bad[lt] = either_lane(has_nan(res[lt], DH / 2) || sum[lt] != sum[lt] || (PHI == kPhiSoftmax && mx[lt] < kLowLogit));
+      bad[lt] = either_lane(any_not_finite(res[lt], DH / 2) || sum[lt] != sum[lt] || (PHI == kPhiSoftmax && mx[lt] < kLowLogit));
+      mx[lt] *= kUnit<T>, sum[lt] *= kDown<T>;
+#pragma unroll
+      for (int i = 0; i < DH / 2; ++i) res[lt][i] *= kUnit<T>;
     }
     bool any = bad[0];
 #pragma unroll
@@ -247,8 +253,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       if (w >= used) break;  // uniform
-      // (expf: tiles' maxima may lie further apart than exp_finite, which is NaN from -2.36e38 on, takes)
-      const float f = PHI != kPhiSoftmax ? 1.f : m[w] == -INFINITY ? 0.f : expf(m[w] - top);
+      // (-200: maxima of tiles taken the exact way may lie further apart than exp_finite, which is NaN from -2.36e38 on, takes; a NaN
+      // among the operands is in the sums)
+      const float f = PHI != kPhiSoftmax ? 1.f : exp_finite(fmaxf(m[w] - top, -200.f), 1.f, 1.f);
       den = fmaf(f, st[w * kState + 64], den);
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = fmaf(f, st[w * kState + (2 + 4 * q + r) * 64], x[r]);

@@ -107,27 +107,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
       for (int p = 1; p < kSplits; ++p) x[t] += src[p * 2 * kBlocks * 1024 + t * 64];
     }
-    if (__any(has_nan(x, 8))) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] *= kSum<T>;
+    if (__any(any_not_finite(x, 8))) {
       const f32x16 y = is_value ? exact_block<T, D, false>(link_row(values_from, lt, n), wv + c0 + 32 * ob, g)
                                 : exact_block<T, D, true>(link_row(keys_from, lt, n), wk + c0 + 32 * ob, g);
 #pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = x[t] == x[t] ? x[t] : f ? y[8 + t] : y[t];
+      for (int t = 0; t < 8; ++t) x[t] = !not_finite(x[t]) ? x[t] : f ? y[8 + t] : y[t];
     }
     if (is_value) {
       // links past the last have weight zero; what was read in their place may be infinite
 #pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = 32 * lt + 16 * f + 8 * (t >> 2) + 4 * g + (t & 3) < a.m ? x[t] : 0.f;
+      for (int t = 0; t < 8; ++t) x[t] = 32 * lt + 16 * f + 8 * (t >> 2) + 4 * g + (t & 3) < a.m ? x[t] * kUp<T> : 0.f;
       if (2 * lt + f < MH) park(values + ((2 * lt + f) * DB + ob) * H::VP * 64, value_planes<DH>(split(x), n), lane);
     } else {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] *= a.scale;
+      for (int t = 0; t < 8; ++t) x[t] = x[t] * a.scale * kUp<T>;
       // (a narrow head's columns are in the first registers)
       if (DH >= 32 || f == 0) park(keys + (lt * H::KF + (DH >= 32 ? 2 * ob + f : 0)) * 3 * 64, column_planes<DH, true>(x), lane);
     }
   }
   lds_barrier();
 
-  // logits of all links to weights in place; the factor of the result
+  // logits of all links (kUnit) to weights (kUp times as large) in place, all as they are the exact way; the factor of the result
   auto to_weights = [&](f32x16 (&s)[MT], float& top, auto exact_tag) {
     constexpr bool kExact = decltype(exact_tag)::value;
     if (a.m < 16 * MH) {  // uniform
@@ -141,8 +143,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
       for (int lt = 0; lt < MT; ++lt)
 #pragma unroll
-        for (int i = 0; i < kRegs; ++i) s[lt][i] = kExact ? silu(s[lt][i]) : silu_finite(s[lt][i]);
-      return 1.f / static_cast<float>(a.m);
+        for (int i = 0; i < kRegs; ++i) s[lt][i] = kExact ? silu(s[lt][i]) : silu_finite(s[lt][i], kUnit<T>, kUp<T>);
+      return (kExact ? 1.f : kSum<T>) / static_cast<float>(a.m);
     }
     float total = 0.f;
     top = s[0][0];
@@ -155,8 +157,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
     for (int lt = 0; lt < MT; ++lt)
 #pragma unroll
-      for (int i = 0; i < kRegs; ++i) s[lt][i] = kExact ? expf(s[lt][i] - base) : exp_finite(s[lt][i] - base), total += s[lt][i];
-    return 1.f / pair_sum(total);
+      for (int i = 0; i < kRegs; ++i)
+        s[lt][i] = kExact ? expf(s[lt][i] - base) : exp_finite(s[lt][i] - base, kUnit<T>, kUp<T>), total += s[lt][i];
+    return (kExact ? 1.f : kDown<T>) / pair_sum(total);
   };
 
   for (bool first = true; t < tiles; t += step, first = false) {
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
         terms(kValueTerms<DH> - 1, kValueTerms<DH>);
       }
       head_result<DH>(acc, res);
-      const bool bad = either_lane(has_nan(res, DH / 2) || inv != inv || top < kLowLogit);  // (both lanes of a row)
+      const bool bad = either_lane(any_not_finite(res, DH / 2) || inv != inv || top < kLowLogit);  // (both lanes of a row)
       if (__any(bad)) {
 #pragma unroll
         for (int lt = 0; lt < MT; ++lt) s[lt] = zeros();

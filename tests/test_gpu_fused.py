@@ -138,6 +138,70 @@ def test_tiles_of_a_chunk_at_the_ends_of_the_range(d, h, m):
     assert torch.isfinite(O).all()
 
 
+# Numbers at the lower end of the range (2^-126), whose remainders are below any bf16 number: which operand they come to.
+# Powers of two, so that what follows from them is scaled and no digit is lost in the inputs themselves.
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+@pytest.mark.parametrize("silu", [False, True])
+@pytest.mark.parametrize("small", ["rows", "key weights", "value weights", "links"])
+def test_small_numbers(d, h, m, silu, small):
+    B, N, C = 2, 90, 70
+    E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=d + m)
+    E = torch.where(torch.arange(N, device="cuda")[None, :, None] < lens[:, None, None], E, 0.0)
+    down, up = 2.0 ** -118, 2.0 ** 59
+    if small == "rows":  # queries and keys that make ordinary logits of them
+        E, T, W[0], W[1], W[2], W[3], W[4] = E * down, T * down, W[0] * up, W[1] * up, W[2] * up, W[3] * up, W[4] * up
+    elif small == "key weights":  # (SiLU: tiny logits, and weights)
+        W[1], W[4] = W[1] * down, W[4] * down
+    elif small == "value weights":
+        W[2], W[5] = W[2] * down, W[5] * up
+    else:
+        L, W[0], W[1], W[3], W[4] = L * down, W[0] * up, W[1] * up, W[3] * up, W[4] * up
+    scale = (d // h) ** -0.5
+    LP, O = binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, scale, scale, xor_attention=silu)
+    refs = _request(E, lens, L, W, T, LP, h, scale, silu)
+    assert float(refs[0].abs().max()) < 2.0 ** 100 and float(refs[1].abs().max()) > 2.0 ** -126
+    assert _error(LP, refs[0]) <= TOLERANCE[torch.float32] and _error(O, refs[1]) <= TOLERANCE[torch.float32]
+
+
+# Keys and values of 2^50 to 2^110: sums, products of them with weights, and the numbers themselves pass what the planes hold.
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+@pytest.mark.parametrize("silu", [False, True])
+@pytest.mark.parametrize("power", [50, 60, 85, 110])
+def test_large_numbers(d, h, m, silu, power):
+    B, N, C = 2, 90, 70
+    E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=d + m)
+    E = torch.where(torch.arange(N, device="cuda")[None, :, None] < lens[:, None, None], E, 0.0)
+    W[1], W[2], W[3], W[5] = W[1] * 2.0 ** power, W[2] * 2.0 ** power, W[3] * 2.0 ** power, W[5] * 2.0 ** -power
+    scale = (d // h) ** -0.5 * 2.0 ** -power
+    LP, O = binding.lime_request(E, lens, L, *W[:3], T, L, *W[3:], h, scale, scale, xor_attention=silu)
+    refs = _request(E, lens, L, W, T, LP, h, scale, silu)
+    assert _error(LP, refs[0]) <= TOLERANCE[torch.float32] and _error(O, refs[1]) <= TOLERANCE[torch.float32]
+
+
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+def test_small_attention_weights(d, h, m):
+    """A result that comes from the small weights alone: the item (link) with the large one has the value zero."""
+    Wq, Wk, Wv = _first_column(d, h)
+    B, N, C = 2, 70, 40
+    g = torch.Generator(device="cuda").manual_seed(m)
+    rows = lambda shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    E, T, L = rows((B, N, d)), rows((B, C, d)), rows((m, d))
+    E[:, :, 0] = -86.0 - torch.rand((B, N), generator=g, device="cuda").mul(8).round() / 8
+    E[:, 3], L[:, 0] = 0.0, 1.0
+    lens = torch.full((B,), N, dtype=torch.int32, device="cuda")
+    LP, _ = binding.lime_request(E, lens, L, Wq, Wk, Wv, T, L, Wq, Wk, Wv, h, 1.0, 1.0)
+    D = lambda x: x.double()  # noqa: E731
+    q = (D(L) @ D(Wq))[None].expand(B, -1, -1)
+    assert _error(LP, _attention(q, D(E) @ D(Wk), D(E) @ D(Wv), h, 1.0, lens, False)) <= TOLERANCE[torch.float32]
+    # candidates over links: the links' first columns decide, the values are those of given link states
+    K, V = L.clone(), rows((B, m, d))
+    K[:, 0] = -86.0 - torch.rand((m,), generator=g, device="cuda").mul(8).round() / 8
+    K[2], V[:, 2], T[:, :, 0] = 0.0, 0.0, 1.0
+    O = binding.lime_score_candidates(T, K, V, Wq, Wk, Wv, h, 1.0)
+    k = (D(K) @ D(Wk))[None].expand(B, -1, -1)
+    assert _error(O, _attention(D(T) @ D(Wq), k, D(V) @ D(Wv), h, 1.0, None, False)) <= TOLERANCE[torch.float32]
+
+
 def test_unaligned_rows_take_the_general_kernels():
     B, N, C, d, h, m = 2, 300, 50, 64, 2, 32
     E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=3)
