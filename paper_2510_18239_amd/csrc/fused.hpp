@@ -16,6 +16,10 @@
 // Where an operand is infinite, or rounds to infinity (fp32: from 2^104 on, being 2^24 times as large), its remainders are NaN; a
 // sum may pass the range too (fp32: from 2^79 on, a logit or result from 2^55 on).  A result that is not finite is computed again with the fp32
 // instruction (`exact`) and taken from there, so that infinities stay where they are and no other row's bits change.
+// The bf16 matrix instruction rounds downward a little more often than upward (the mean of its result and that of its negated operands
+// is -1.2e-8 where accumulator and products are near one; the fp32 instruction's is zero), which over many items adds up: the mean
+// of 4096 items' values was 6.9e-7 off, 3.6e-7 with the fp32 instruction.  So every other item of a history is taken negated, row
+// and weight, and every other tile's result.  (fp32 storage only; bf16 results are rounded to 2^-9.)
 //
 // Fragments as in mfma.hpp.  A head narrower than 32 columns has its columns repeated over the 32 lanes of a weight fragment,
 // which makes room for the planes: at d/h = 8 a lane's slots of one key fragment hold two planes, and the 32 rows of a value
@@ -110,10 +114,10 @@ __device__ __forceinline__ void products(const Planes<1> (&a)[N], const Planes<1
   for (int i = 0; i < N; ++i) c[i] = mfma32(a[i].p[0], b[i].p[0], c[i]);
 }
 
-__device__ __forceinline__ Planes<3> planes_of(u32x4 a, u32x4 b) {
+__device__ __forceinline__ Planes<3> planes_of(u32x4 a, u32x4 b, float times) {
   float x[8];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(a[t]) * kUp<float>, x[4 + t] = __uint_as_float(b[t]) * kUp<float>;
+  for (int t = 0; t < 4; ++t) x[t] = __uint_as_float(a[t]) * times, x[4 + t] = __uint_as_float(b[t]) * times;
   return split(x);
 }
 
@@ -170,33 +174,34 @@ struct RowTile {
     }
     return r;
   }
-  // Calls ahead(kk + 1) and then use(kk, planes) for every 16 columns: what a step needs is asked for a step ahead.
+  // Calls ahead(kk + 1) and then use(kk, planes) for every 16 columns: what a step needs is asked for a step ahead.  (fp32: of
+  // `times` the row)
   template <typename A, typename F>
-  __device__ __forceinline__ void each(unsigned char* own, int lane, A ahead, F use) const {
+  __device__ __forceinline__ void each(unsigned char* own, int lane, float times, A ahead, F use) const {
     Piece now = piece(own, lane, 0);
     ahead(0);
-    Planes<kPlanes<T>> p = step(now, 0);
+    Planes<kPlanes<T>> p = step(now, 0, times);
 #pragma unroll
     for (int kk = 0; kk < kSteps; ++kk) {
       if (kLines && (kk + 1) % kStepsPerPiece == 0 && kk + 1 < kSteps) now = piece(own, lane, (kk + 1) / kStepsPerPiece);
       if (kk + 1 < kSteps) ahead(kk + 1);
       __builtin_amdgcn_sched_barrier(0);
       use(kk, p);
-      if (kk + 1 < kSteps) p = step(now, kk + 1);
+      if (kk + 1 < kSteps) p = step(now, kk + 1, times);
     }
   }
-  __device__ __forceinline__ Planes<kPlanes<T>> step(const Piece& now, int kk) const {
+  __device__ __forceinline__ Planes<kPlanes<T>> step(const Piece& now, int kk, float times) const {
     if constexpr (kLines) {
-      return planes(now.u[kk % kStepsPerPiece]);
+      return planes(now.u[kk % kStepsPerPiece], times);
     } else {
       u32x4 u[kUnits];
 #pragma unroll
       for (int j = 0; j < kUnits; ++j) u[j] = v[kk * kUnits + j];
-      return planes(u);
+      return planes(u, times);
     }
   }
-  __device__ static __forceinline__ Planes<kPlanes<T>> planes(const u32x4 (&u)[kUnits]) {
-    if constexpr (sizeof(T) == 4) return planes_of(u[0], u[1]);
+  __device__ static __forceinline__ Planes<kPlanes<T>> planes(const u32x4 (&u)[kUnits], float times) {
+    if constexpr (sizeof(T) == 4) return planes_of(u[0], u[1], times);
     else return {{__builtin_bit_cast(bf16x8, u[0])}};
   }
 };
@@ -403,7 +408,7 @@ __device__ __forceinline__ f32x16 partial_block(const RowTile<T, COLS>& x, const
                                                 unsigned char* own, bool rows_kept, int lane) {
   f32x16 acc[1] = {zeros()};
   Planes<kPlanes<T>> w[2];
-  x.each(own, lane, [&](int kk) { w[kk & 1] = W::fragment(weights, matrix, ob, part * (COLS / 16) + kk, lane); },
+  x.each(own, lane, kUp<T>, [&](int kk) { w[kk & 1] = W::fragment(weights, matrix, ob, part * (COLS / 16) + kk, lane); },
          [&](int kk, const Planes<kPlanes<T>>& p) {
            const Planes<kPlanes<T>> a[1] = {p}, b[1] = {w[kk & 1]};
            if (rows_kept) products(b, a, acc);

@@ -31,6 +31,7 @@ template <typename T, int D, int DH, int MT, int PHI>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_history_kernel(HistoryDev a) {
   using H = Head<DH>;
   using Lds = HistoryLds<T, D, DH, MT>;
+  constexpr bool kAlternate = sizeof(T) == 4;  // every other item negated
   constexpr int K1 = D / 16, DB = H::DB, NP = kPlanes<T>, kBlocks = MT * DB, kSplits = std::min(kWaves / kBlocks, K1);
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   using W = typename Lds::W;
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
     for (int i = 0; i < 2 * DB; ++i) kv[i] = zeros();
     Planes<NP> w[2][2 * DB];
-    items.each(own, lane, [&](int kk) {
+    items.each(own, lane, kAlternate && n % 2 ? -kUp<T> : kUp<T>, [&](int kk) {
 #pragma unroll
       for (int i = 0; i < 2 * DB; ++i) w[kk & 1][i] = W::fragment(weights, 1 + i / DB, i % DB, kk, lane);
     }, [&](int kk, const Planes<NP>& x) {
@@ -114,27 +115,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   const int left = klen - k0 - 4 * g;
   const bool ragged = k0 + 32 > klen;  // uniform over the wave
   auto past = [&](int i) { return 8 * (i >> 2) + (i & 3) >= left; };
-  // logits of a tile (kUnit) to weights (kUp times as large) in place, all as they are the exact way: register i of this lane is
-  // item k0 + 8 (i / 4) + 4g + i % 4
+  // logits of a tile (kUnit) to weights (`up` times as large) in place, those of odd items negated before and after, all as they are
+  // the exact way: register i of this lane is item k0 + 8 (i / 4) + 4g + i % 4
+  auto sign = [](int i) { return kAlternate && i % 2 ? -1.f : 1.f; };
+  const float tile_sign = kAlternate && wave % 2 ? -1.f : 1.f, up = tile_sign * kUp<T>;  // uniform
   auto to_weights = [&](f32x16& s, float& top, float& total, auto exact_tag) {
     constexpr bool kExact = decltype(exact_tag)::value;
     if (ragged) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (past(i)) s[i] = PHI != kPhiSoftmax ? 0.f : kExact ? -INFINITY : kMaskedLogit;  // (SiLU(0) = 0)
+        if (past(i)) s[i] = PHI != kPhiSoftmax ? 0.f : kExact ? -INFINITY : sign(i) * kMaskedLogit;  // (SiLU(0) = 0)
     }
     top = -INFINITY, total = 0.f;
     if (PHI == kPhiSoftmax) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) top = fmaxf(top, s[i]);
+      for (int i = 0; i < 16; ++i) top = fmaxf(top, kExact ? s[i] : sign(i) * s[i]);
       top = pair_max(top);
       const float base = kExact && top == -INFINITY ? 0.f : top;  // (every logit is -inf: weights of zero)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = kExact ? expf(s[i] - base) : exp_finite(s[i] - base, kUnit<T>, kUp<T>), total += s[i];
+      for (int i = 0; i < 16; ++i) {
+        s[i] = kExact ? expf(s[i] - base) : exp_finite(sign(i) * s[i] - base, kUnit<T>, sign(i) * up);
+        total += kExact ? s[i] : sign(i) * s[i];
+      }
       total = pair_sum(total);
     } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = kExact ? silu(s[i]) : silu_finite(s[i], kUnit<T>, kUp<T>);
+      for (int i = 0; i < 16; ++i) s[i] = kExact ? silu(s[i]) : silu_finite(sign(i) * s[i], kUnit<T>, sign(i) * up);
     }
   };
   // items past the last: what was read in their place may be infinite
@@ -186,9 +192,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     for (int lt = 0; lt < MT; ++lt) {
       head_result<DH>(acc[lt], res[lt]);
       bad[lt] = either_lane(any_not_finite(res[lt], DH / 2) || sum[lt] != sum[lt] || (PHI == kPhiSoftmax && mx[lt] < kLowLogit));
-      mx[lt] *= kUnit<T>, sum[lt] *= kDown<T>;
+      mx[lt] *= kUnit<T>, sum[lt] *= tile_sign * kDown<T>;
 #pragma unroll
-      for (int i = 0; i < DH / 2; ++i) res[lt][i] *= kUnit<T>;
+      for (int i = 0; i < DH / 2; ++i) res[lt][i] *= tile_sign * kUnit<T>;
     }
     bool any = bad[0];
 #pragma unroll

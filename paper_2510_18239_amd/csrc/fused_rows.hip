@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     Planes<NP> w[2][DB];
 #pragma unroll
     for (int ob = 0; ob < DB; ++ob) q[ob] = zeros();
-    items.each(own, lane, [&](int kk) {
+    items.each(own, lane, kUp<T>, [&](int kk) {
 #pragma unroll
       for (int ob = 0; ob < DB; ++ob) w[kk & 1][ob] = W::fragment(weights, 2, ob, kk, lane);
     }, [&](int kk, const Planes<NP>& x) {

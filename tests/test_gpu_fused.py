@@ -202,6 +202,28 @@ def test_small_attention_weights(d, h, m):
     assert _error(O, _attention(D(T) @ D(Wq), k, D(V) @ D(Wv), h, 1.0, None, False)) <= TOLERANCE[torch.float32]
 
 
+@pytest.mark.parametrize("d,h,m", [(32, 4, 16), (64, 2, 32), (64, 1, 40), (128, 4, 64)])
+@pytest.mark.parametrize("silu", [False, True])
+def test_long_histories_have_no_error_common_to_all_items(d, h, m, silu):
+    """The mean of N items' values (weights all alike) is sqrt(N) times smaller than they are, and so are errors of either sign; an
+    error that all items share stays as it is."""
+    B, N = 4, 8192
+    g = torch.Generator(device="cuda").manual_seed(d + m)
+    rn = lambda shape, std=1.0: torch.randn(shape, generator=g, device="cuda") * std  # noqa: E731
+    E, L, W = rn((B, N, d)), rn((m, d)), [rn((d, d), d ** -0.5) for _ in range(3)]
+    if silu:  # logits of one: every weight is SiLU(1)
+        W[0], W[1] = torch.zeros((d, d), device="cuda"), torch.zeros((d, d), device="cuda")
+        E[:, :, 0] = L[:, 0] = 1.0
+        W[0][0, :: d // h] = W[1][0, :: d // h] = 1.0
+        W[2][0] = 0.0
+    call = (lambda *a: binding.lime_xor_history(*a)[0]) if silu else binding.lime_link_history
+    LP = call(E, None, L, *W, h, 1.0 if silu else 0.0)[:, 0].double()
+    ref = (E.double() @ W[2].double()).mean(dim=1) * (torch.sigmoid(torch.ones((), dtype=torch.float64)).item() if silu else 1.0)
+    # a value is d products and roundings of 2^-24 at most, in the root mean square a third of that each, and a tile's and the tiles'
+    # sums are as good: 2^-24 * sqrt(3 * 128) / 3 = 3.9e-7 (it was 6e-7 to 1e-6 with the shared error)
+    assert _error(LP, ref) <= 4e-7
+
+
 def test_unaligned_rows_take_the_general_kernels():
     B, N, C, d, h, m = 2, 300, 50, 64, 2, 32
     E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=3)
