@@ -29,13 +29,11 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "fused_grid.hpp"
 #include "mfma.hpp"
 
 namespace lime {
 namespace {
-
-constexpr int kWaves = 8, kThreads = 64 * kWaves;
-constexpr int kChunkKeys = 32 * kWaves;  // history items of a workgroup: a tile per wave
 
 __device__ __forceinline__ f32x16 zeros() {
   f32x16 x;

@@ -292,7 +292,7 @@ hipError_t launch_history(const HistoryDev& a, hipStream_t s) {
     static PerDevice granted;
     if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(fused_history_kernel<T, D, DH, MT, PHI>), kBytes); e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fused_history_kernel<T, D, DH, MT, PHI>), dim3((a.total + 7) / 8 * 8), dim3(kThreads), kBytes, s, a);
+  hipLaunchKernelGGL((fused_history_kernel<T, D, DH, MT, PHI>), dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
   return hipGetLastError();
 }
 
@@ -329,12 +329,12 @@ int history_chunks(int64_t N) { return static_cast<int>((N + kChunkKeys - 1) / k
 // each 256 items or part of them), with room to align them.
 bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m, int dtype) {
   if (!fused_shape(d, h) || m > (d / h >= 32 ? 64 : 32)) return false;
-  return narrow_pays(d, d / h, dtype == 0) && B * history_chunks(N) * h < (int64_t{1} << 31) - 8;
+  return narrow_pays(d, d / h, dtype == 0) && launch_fits(history_workgroups(B, N, h));
 }
 
 hipError_t fused_history(const FusedHistory& q, hipStream_t s) {
   HistoryDev a{q.E, q.L, q.Wq, q.Wk, q.Wv, q.lens, q.l_user_stride, q.LP, nullptr, nullptr, q.B, q.N, q.h, q.m, history_chunks(q.N), 0, q.scale};
-  a.total = a.B * a.chunks * a.h;
+  a.total = static_cast<int>(history_workgroups(a.B, a.N, a.h));
   if (a.chunks > 1) {
     char* scratch = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(q.scratch) + 15) & ~uintptr_t{15});
     a.part_acc = reinterpret_cast<float*>(scratch);

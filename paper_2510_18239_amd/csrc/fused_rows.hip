@@ -277,7 +277,7 @@ hipError_t launch_rows(const RowsDev& a, hipStream_t s) {
     static PerDevice granted;
     if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(fused_rows_kernel<T, D, DH, MH, PHI>), kBytes); e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fused_rows_kernel<T, D, DH, MH, PHI>), dim3((a.total + 7) / 8 * 8), dim3(kThreads), kBytes, s, a);
+  hipLaunchKernelGGL((fused_rows_kernel<T, D, DH, MH, PHI>), dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
   return hipGetLastError();
 }
 
@@ -303,7 +303,7 @@ hipError_t dispatch_rows_shape(const RowsDev& a, int d, int phi, hipStream_t s) 
 // All links' logits of a row lie in registers: 64 of them, 32 where the head is narrow.
 bool fused_rows_supported(int64_t B, int64_t rows, int d, int h, int m) {
   if (!fused_shape(d, h) || m > (d / h >= 32 ? 64 : 32)) return false;
-  return B * ((rows + 32 * kWaves - 1) / (32 * kWaves)) * h < (int64_t{1} << 31) - 8 && rows < (int64_t{1} << 31) - 64 * kWaves * compute_units();
+  return launch_fits(B * h + compute_units()) && rows < (int64_t{1} << 31) - 64 * kWaves * compute_units();
 }
 
 hipError_t fused_rows(const FusedRows& q, hipStream_t s) {
