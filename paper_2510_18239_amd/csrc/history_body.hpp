@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "history.hpp"
+#include "pack.hpp"
 
 namespace lime {
 namespace {
@@ -48,11 +49,15 @@ struct HistShape {
   static constexpr int kLds = RAW ? std::max(kXBytes + kShared + 2 * kSlice, kCombine) : std::max(NX * (kXBytes + kExchange) + kQueries, kCombine);
 };
 
+// What a launch brings besides HistArgs: RAW, the operands, and jobs for as many workgroups more (blockIdx.z from H on).
 struct RawArgs {
   const bf16_t *LC, *Wq, *Wk, *Wv;
   int64_t lc_user_stride;
   int negate;    // the logit scale is negative: its sign is the queries'
+  int pack_blocks;
+  PackArgs pack;
 };
+struct PackedArgs {};
 
 // A 16-byte piece c of row r of a staged tile lies at piece c ^ row_swizzle<D>(r) of the row, so that the 16 lanes that an
 // LDS read serves at once (16 rows, one column) touch all banks.
@@ -62,9 +67,20 @@ __device__ __forceinline__ int row_swizzle(int r) {
   return CPR >= 16 ? r & 15 : r / (16 / CPR) & (CPR - 1);
 }
 
+// (Both forms from one text, but each a kernel of its own body: as a function that two kernels call, the same text takes up to 31
+// registers more (softmax, d/h = 32, 96 or 128 links), spills 46 instead of 17 at h = 8 and m = 128, and is slower by a quarter there:
+// 8 prepared users of 8000 items, d=256 h=8, m=128 71.6 | 57.1 us, m=96 48.3 | 45.6.)
 template <int DH, int M, int H, int PHI, int HG, int TP, bool RAW>
-__device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs& r, unsigned char* lds) {
+__global__ __launch_bounds__((HistShape<DH, M, H, HG, TP, RAW>::kThreads), 2) void links_over_history_kernel(HistArgs a, std::conditional_t<RAW, RawArgs, PackedArgs> r) {
   using S = HistShape<DH, M, H, HG, TP, RAW>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  if constexpr (RAW) {
+    if (blockIdx.z >= H) {  // uniform
+      const int i = ((blockIdx.z - H) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+      if (i < r.pack_blocks) pack_block<DH * H, 0, 0>(r.pack, i, lds);
+      return;
+    }
+  }
   constexpr int D = S::D, K1 = S::K1, MB = S::MB, K2 = S::K2, LB = S::LB, LBW = S::LBW, NX = S::NX, kWaves = S::kWaves;
   constexpr int CPR = D / 8, LW = S::kXBytes / (kWaves * 1024);  // 1 KiB loads per wave and step
   unsigned char* const ex_lds = lds + NX * S::kXBytes;
@@ -131,7 +147,7 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
       load_to_lds(lds_offset_of(to) + f * 1024, (lane / 4) * (2 * D) + lane % 4 * 16, w + static_cast<int64_t>(16 * (f / MB)) * D + head * DH + 32 * (f % MB));
     }
   };
-  auto ask_raw = [&] {
+  auto ask_raw = [&](const auto& r) {
     const bf16_t* lc = r.LC + b * r.lc_user_stride;
 #pragma unroll
     for (int j = 0; j < kLinkLoads; ++j) {
@@ -142,7 +158,7 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
     ask_slice(r.Wk, keys_lds);
     ask_slice(r.Wv, values_lds);
   };
-  auto lay_out_raw = [&] {
+  auto lay_out_raw = [&](const auto& r) {
     constexpr int kBlocks = LB * MB, kMine = (kBlocks + kWaves - 1) / kWaves;
     wait_lds_loads<2 * kSliceLoads>();
     lds_barrier();
@@ -182,7 +198,7 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
   // The rows come from HBM and are asked for ahead of the operands, which come from L2.
   ask_rows(i_begin, 0);
   if constexpr (RAW) {
-    ask_raw();
+    ask_raw(r);
   } else {
     {
       // the heads' query fragments: kept in LDS, read once per tile
@@ -212,7 +228,7 @@ __device__ __forceinline__ void links_over_rows(const HistArgs& a, const RawArgs
   const int row = 32 * tp + n, row_base = row * (2 * D) + (g ^ row_swizzle<D>(row)) * 16;
 
   if constexpr (RAW) {
-    lay_out_raw();
+    lay_out_raw(r);
   } else {
     // (the weights are waited for here: left pending, the loop would wait for them, and with them for the rows, every time)
 #pragma unroll

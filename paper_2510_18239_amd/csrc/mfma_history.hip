@@ -399,23 +399,17 @@ __global__ __launch_bounds__(2 * D) void merge_values_tile_kernel(MergeValuesArg
     *reinterpret_cast<bf16x4*>(dst + link0 % 16 / 2) = __builtin_shufflevector(values, values, 0, 1, 2, 3);
 }
 
-template <int DH, int M, int H, int PHI, int HG, int TP>
-__global__ __launch_bounds__((HistShape<DH, M, H, HG, TP>::kThreads), 2) void links_over_history_kernel(HistArgs a) {
-  extern __shared__ unsigned char lds[];
-  links_over_rows<DH, M, H, PHI, HG, TP, false>(a, RawArgs{}, lds);
-}
-
 template <int DH, int M, int H, int PHI, int FORM>
 hipError_t launch_shape(const HistArgs& a, int users, hipStream_t s) {
   constexpr int HG = heads_per_group(DH, H, FORM), TP = tiles_per_step(DH, H, FORM);
   using S = HistShape<DH, M, H, HG, TP>;
   static_assert(S::kLds <= 160 * 1024, "LDS");
-  auto kernel = links_over_history_kernel<DH, M, H, PHI, HG, TP>;
+  auto kernel = links_over_history_kernel<DH, M, H, PHI, HG, TP, false>;
   if (S::kLds > 64 * 1024) {
     static PerDevice granted;
     if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), S::kLds); e != hipSuccess) return e;
   }
-  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H / HG), dim3(S::kThreads), S::kLds, s, a);
+  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H / HG), dim3(S::kThreads), S::kLds, s, a, PackedArgs{});
   return hipGetLastError();
 }
 

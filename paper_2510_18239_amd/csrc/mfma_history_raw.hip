@@ -2,7 +2,6 @@
 // operands that another kernel of the call needs are packed by workgroups of the same launch.  It takes the place of a pack
 // launch ahead of the history kernel, with the same sums and roundings.
 #include "history_body.hpp"
-#include "pack.hpp"
 
 namespace lime {
 namespace {
@@ -17,31 +16,19 @@ struct RawShape {
   static constexpr int kLds = std::max(S::kLds, PackLds<D>::kBytes);
 };
 
-// What bounds it is the wait for its operands, 64 to 160 KiB a workgroup, all asked for at once; the queries (16 products a wave
+// What bounds this form is the wait for its operands, 64 to 160 KiB a workgroup, all asked for at once; the queries (16 products a wave
 // at d = 256) are formed while the last of them arrive.  A pass of the request, with a pack launch | so, in us: d=256 h=4 m=64
 // N=2048 with 16 candidates 19.4 | 16.6, with 32 768 26.3 | 23.9 (15.2 instead of 16.5 with four requests in flight).
 template <int DH, int M, int H, int PHI>
-__global__ __launch_bounds__(256, 2) void history_raw_kernel(HistArgs a, RawArgs r, PackArgs p, int pack_blocks) {
+hipError_t launch(const HistArgs& a, const RawArgs& r, int users, hipStream_t s) {
   using R = RawShape<DH, M, H>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  if (blockIdx.z >= H) {  // uniform
-    const int i = ((blockIdx.z - H) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    if (i < pack_blocks) pack_block<R::D, 0, 0>(p, i, lds);
-    return;
-  }
-  links_over_rows<DH, M, H, PHI, R::HG, R::TP, true>(a, r, lds);
-}
-
-template <int DH, int M, int H, int PHI>
-hipError_t launch(const HistArgs& a, const RawArgs& r, const PackArgs& p, int pack_blocks, int users, hipStream_t s) {
-  constexpr int kLds = RawShape<DH, M, H>::kLds;
-  auto kernel = history_raw_kernel<DH, M, H, PHI>;
-  if (kLds > 64 * 1024) {
+  auto kernel = links_over_history_kernel<DH, M, H, PHI, R::HG, R::TP, true>;
+  if (R::kLds > 64 * 1024) {
     static PerDevice granted;
-    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), kLds); e != hipSuccess) return e;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), R::kLds); e != hipSuccess) return e;
   }
   const int plane = a.chunks * users;
-  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H + (pack_blocks + plane - 1) / plane), dim3(256), kLds, s, a, r, p, pack_blocks);
+  launch_timed(kKernelLinksOverHistory, kernel, dim3(a.chunks, users, H + (r.pack_blocks + plane - 1) / plane), dim3(256), R::kLds, s, a, r);
   return hipGetLastError();
 }
 
@@ -84,15 +71,14 @@ bool history_raw_fits(const LinksOverHistory& q, int64_t workgroups, const PackJ
 }
 
 hipError_t history_raw(const HistArgs& a, const LinksOverHistory& q, hipStream_t s) {
-  const RawArgs r{static_cast<const bf16_t*>(q.LC), static_cast<const bf16_t*>(q.Wq), static_cast<const bf16_t*>(q.Wk),
-                  static_cast<const bf16_t*>(q.Wv), q.lc_user_stride, q.scale < 0.f};
-  PackArgs p;
-  const int blocks = pack_jobs(p, *q.beside, q.d, q.h, q.m);
+  RawArgs r{static_cast<const bf16_t*>(q.LC), static_cast<const bf16_t*>(q.Wq), static_cast<const bf16_t*>(q.Wk),
+            static_cast<const bf16_t*>(q.Wv), q.lc_user_stride, q.scale < 0.f, 0, {}};
+  r.pack_blocks = pack_jobs(r.pack, *q.beside, q.d, q.h, q.m);
   hipError_t e = hipErrorInvalidValue;
   for_shape(q.d / q.h, q.h, q.m, [&](auto shape, auto links) {
     using R = decltype(shape);
     constexpr int M = decltype(links)::value, H = R::D / (32 * R::S::MB);
-    e = q.phi == kPhiSoftmax ? launch<32 * R::S::MB, M, H, kPhiSoftmax>(a, r, p, blocks, q.B, s) : launch<32 * R::S::MB, M, H, kPhiSilu>(a, r, p, blocks, q.B, s);
+    e = q.phi == kPhiSoftmax ? launch<32 * R::S::MB, M, H, kPhiSoftmax>(a, r, q.B, s) : launch<32 * R::S::MB, M, H, kPhiSilu>(a, r, q.B, s);
   });
   return e;
 }

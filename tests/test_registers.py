@@ -1,0 +1,35 @@
+"""The compiler's registers for kernels that have lost speed by needing more: instances whose operands fill the register file, at
+the most that they may take.  (Built for the device alone, a few instances at a time.)"""
+
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2510_18239_amd import build
+
+
+def _resources(tmp_path, text):
+    src = tmp_path / "t.hip"
+    src.write_text(text)
+    cmd = ["hipcc", *build.HIPCC_FLAGS, "--cuda-device-only", "-c", str(src), "-o", os.devnull, "-I", build.CSRC, "-Rpass-analysis=kernel-resource-usage"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    number = lambda name, block: int(re.search(name + r"[^:]*: (\d+)", block).group(1))  # noqa: E731
+    return [{"name": b.split()[0], "vgprs": number(" VGPRs", b), "spill": number("VGPRs Spill", b), "waves": number("Occupancy", b)}
+            for b in r.stderr.split("Function Name: ")[1:]]
+
+
+@pytest.mark.parametrize("m,h,tiles,heads,raw,spill,waves", [
+    (128, 8, 2, 4, False, 19, 2), (128, 8, 4, 1, False, 17, 2), (96, 8, 2, 4, False, 0, 2), (96, 8, 4, 1, False, 0, 2), (96, 8, 4, 1, True, 0, 2),
+    (128, 4, 2, 4, False, 0, 2), (128, 1, 4, 1, False, 0, 3), (96, 2, 4, 2, False, 0, 3), (96, 2, 4, 1, True, 0, 3),
+])
+def test_history_kernel(tmp_path, m, h, tiles, heads, raw, spill, waves):
+    args = "RawArgs" if raw else "PackedArgs"
+    got, = _resources(tmp_path, f"""
+#include "history_body.hpp"
+namespace lime {{ namespace {{
+template __global__ void links_over_history_kernel<32, {m}, {h}, kPhiSoftmax, {heads}, {tiles}, {str(raw).lower()}>(HistArgs, {args});
+}} }}""")
+    assert got["spill"] <= spill and got["waves"] >= waves, got
