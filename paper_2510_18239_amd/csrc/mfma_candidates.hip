@@ -63,18 +63,20 @@ __global__ __launch_bounds__(64 * H) void queries_over_links_kernel(MainArgs a) 
   // H waves read it.
   constexpr int P = 2;
   constexpr int LW = DH / 16;
-  // Eight heads at d = 256: eight waves share the register file two to a SIMD, so with many links (whose logits and weights
-  // need registers too) three quarters of the W_Q^T slice live in LDS instead and are read once per tile.
-  constexpr int KL = D == 256 && H == 8 && M >= 96 ? 3 * K1 / 4 : 0;  // k-steps of W_Q^T kept in LDS
-  static_assert(!FUSED || (KL == 0 && M <= DH), "the fused form is for few links");
-  constexpr int KR = K1 - KL;                // k-steps kept in registers
   // With four heads the stationary operands of 128 links fill the AGPRs exactly, from where the matrix cores read them as readily:
   // pinned there, W_Q^T needs no LDS and none of them the 160 copies a tile (of 770 vector instructions) that the compiler makes
   // where it keeps them there by itself.  131 072 rows of d=256 h=4 m=128: 51 -> 47 us, and 91.5 -> 87.5 us for the prepared
-  // request.  Fewer links have fewer copies, and pinning costs a workgroup 128 moves ahead of its first tile: with 96 the prepared
-  // request of 8 users takes 34.4 | 34.1 us pinned (8192 candidates each), 18.0 | 18.2 with one user and 16 candidates; with 64 the
-  // headline request 23.4 | 23.7.
-  constexpr bool kPinned = D == 256 && H < 8 && M >= 128;
+  // request; NORM, 32 768 rows: 61.1 -> 58.6 us for the scores.  Fewer links have fewer copies, and pinning costs a workgroup 128
+  // moves ahead of its first tile: with 96 the prepared request of 8 users takes 34.4 | 34.1 us pinned (8192 candidates each), 18.0 |
+  // 18.2 with one user and 16 candidates; with 64 the headline request 23.4 | 23.7.  SiLU needs more registers beside them, and would
+  // spill 135 (lime_xor_history with O[S], 8 users of 4096 items: 48.4 us pinned, 43.4 not).
+  constexpr bool kPinned = D == 256 && H < 8 && M >= 128 && PHI == kPhiSoftmax;
+  // Where they are not pinned, many links' logits and weights leave too few registers at d = 256, where the W_Q^T slice alone is a
+  // quarter of the file: the last half of its k-steps live in LDS instead and are read once per tile.  (Eight heads: eight waves share
+  // the file two to a SIMD, so three quarters of them.)
+  constexpr int KL = D < 256 || kPinned ? 0 : H == 8 ? (M >= 96 ? 3 * K1 / 4 : 0) : (M >= 128 ? K1 / 2 : 0);  // k-steps of W_Q^T kept in LDS
+  static_assert(!FUSED || (KL == 0 && M <= DH), "the fused form is for few links");
+  constexpr int KR = K1 - KL;                // k-steps kept in registers
   constexpr int CPR = D / 8;            // 16-byte chunks per row of X
   constexpr int PITCH = 2 * D + 16;     // LDS row pitch of an X tile, bytes
   constexpr int OCPR = DH / 8;          // 16-byte chunks per row of one head's output slice

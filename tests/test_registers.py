@@ -33,3 +33,16 @@ namespace lime {{ namespace {{
 template __global__ void links_over_history_kernel<32, {m}, {h}, kPhiSoftmax, {heads}, {tiles}, {str(raw).lower()}>(HistArgs, {args});
 }} }}""")
     assert got["spill"] <= spill and got["waves"] >= waves, got
+
+
+@pytest.mark.parametrize("phi,weights,norm,spill", [("kPhiSilu", "false", "false", 0), ("kPhiSoftmax", "false", "false", 0),
+                                                    ("kPhiSoftmax", "true", "false", 0), ("kPhiSoftmax", "false", "true", 2)])
+def test_rows_over_128_links(tmp_path, phi, weights, norm, spill):
+    """d = 256, four heads: the stationary operands are most of the registers."""
+    kernels = open(os.path.join(build.CSRC, "mfma_candidates.hip")).read()
+    kernels = kernels[: kernels.index("hipError_t launch_form")]  # without the launches of every instance
+    kernels = kernels[: kernels.rindex("template <")]
+    got, = _resources(tmp_path, kernels + f"""
+template __global__ void queries_over_links_kernel<64, 128, 4, {phi}, {weights}, false, {norm}>(MainArgs);
+}} }}""")
+    assert got["spill"] <= spill, got
