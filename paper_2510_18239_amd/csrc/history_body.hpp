@@ -47,6 +47,8 @@ struct HistShape {
   static constexpr int kSlice = K1 * MB * 1024, kLinks = M * 2 * D;
   static constexpr int kShared = std::max(kLinks + kSlice, kExchange + kQueries);
   static constexpr int kLds = RAW ? std::max(kXBytes + kShared + 2 * kSlice, kCombine) : std::max(NX * (kXBytes + kExchange) + kQueries, kCombine);
+  // What the compiler is held to.  RAW: three where LDS lets a compute unit have three workgroups (of four waves, one a SIMD).
+  static constexpr int kWavesPerSimd = RAW && 3 * kLds <= 160 * 1024 ? 3 : 2;
 };
 
 // What a launch brings besides HistArgs: RAW, the operands, and jobs for as many workgroups more (blockIdx.z from H on).
@@ -71,7 +73,7 @@ __device__ __forceinline__ int row_swizzle(int r) {
 // registers more (softmax, d/h = 32, 96 or 128 links), spills 46 instead of 17 at h = 8 and m = 128, and is slower by a quarter there:
 // 8 prepared users of 8000 items, d=256 h=8, m=128 71.6 | 57.1 us, m=96 48.3 | 45.6.)
 template <int DH, int M, int H, int PHI, int HG, int TP, bool RAW>
-__global__ __launch_bounds__((HistShape<DH, M, H, HG, TP, RAW>::kThreads), 2) void links_over_history_kernel(HistArgs a, std::conditional_t<RAW, RawArgs, PackedArgs> r) {
+__global__ __launch_bounds__((HistShape<DH, M, H, HG, TP, RAW>::kThreads), (HistShape<DH, M, H, HG, TP, RAW>::kWavesPerSimd)) void links_over_history_kernel(HistArgs a, std::conditional_t<RAW, RawArgs, PackedArgs> r) {
   using S = HistShape<DH, M, H, HG, TP, RAW>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   if constexpr (RAW) {

@@ -14,6 +14,7 @@ struct RawShape {
   using S = HistShape<DH, M, H, HG, TP, true>;
   static_assert(HG == 1 && S::kThreads == 256, "a workgroup of the pack jobs is as large");
   static constexpr int kLds = std::max(S::kLds, PackLds<D>::kBytes);
+  static constexpr int kPerUnit = std::min(kUnitLds / kLds, S::kWavesPerSimd);  // workgroups of a compute unit, by LDS and by registers
 };
 
 // What bounds this form is the wait for its operands, 64 to 160 KiB a workgroup, all asked for at once; the queries (16 products a wave
@@ -66,7 +67,7 @@ bool history_raw_fits(const LinksOverHistory& q, int64_t workgroups, const PackJ
   PackArgs p;
   const int64_t all = workgroups + pack_jobs(p, beside, q.d, q.h, q.m);
   bool fits = false;
-  for_shape(q.d / q.h, q.h, q.m, [&](auto shape, auto) { fits = all <= static_cast<int64_t>(compute_units()) * (kUnitLds / decltype(shape)::kLds); });
+  for_shape(q.d / q.h, q.h, q.m, [&](auto shape, auto) { fits = all <= static_cast<int64_t>(compute_units()) * decltype(shape)::kPerUnit; });
   return fits;
 }
 

@@ -35,6 +35,18 @@ template __global__ void links_over_history_kernel<32, {m}, {h}, kPhiSoftmax, {h
     assert got["spill"] <= spill and got["waves"] >= waves, got
 
 
+# (the rule that counts a compute unit's workgroups takes it that so many waves fit)
+@pytest.mark.parametrize("dh,m,h,waves", [(64, 64, 1, 3), (32, 32, 2, 3), (32, 64, 2, 3), (32, 128, 4, 2)])
+def test_history_kernel_on_raw_operands(tmp_path, dh, m, h, waves):
+    got, = _resources(tmp_path, f"""
+#include "history_body.hpp"
+namespace lime {{ namespace {{
+static_assert(HistShape<{dh}, {m}, {h}, 1, tiles_per_step({dh}, {h}, kShort), true>::kWavesPerSimd == {waves});
+template __global__ void links_over_history_kernel<{dh}, {m}, {h}, kPhiSoftmax, 1, tiles_per_step({dh}, {h}, kShort), true>(HistArgs, RawArgs);
+}} }}""")
+    assert got["spill"] == 0 and got["waves"] >= waves, got
+
+
 @pytest.mark.parametrize("phi,weights,norm,spill", [("kPhiSilu", "false", "false", 0), ("kPhiSoftmax", "false", "false", 0),
                                                     ("kPhiSoftmax", "true", "false", 0), ("kPhiSoftmax", "false", "true", 2)])
 def test_rows_over_128_links(tmp_path, phi, weights, norm, spill):
