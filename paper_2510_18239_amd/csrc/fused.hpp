@@ -439,8 +439,8 @@ inline bool fused_shape(int d, int h) {
   return false;
 }
 
-// Waves per SIMD: two workgroups on a compute unit where their registers fit, nearly (at d = 64 in fp32 up to 21 are spilled: 128
-// users, C = 512, d = 64, h = 8 38.7 us with them, 43.1 with one workgroup; at d = 128 88.5 and 61.3).
+// Waves per SIMD: two workgroups on a compute unit where their registers fit, nearly (in fp32 at d = 64 the rows kernel spills 12:
+// 128 users, C = 512, d = 64, h = 8 38.7 us with them, 43.1 with one workgroup; at d = 128 88.5 and 61.3).
 constexpr int fused_waves(int D, int DH) { return DH < 32 && D < 128 ? 4 : 2; }
 
 // Workgroups that read the same rows (the heads of one user's) on one XCD: consecutive blocks go to consecutive XCDs.

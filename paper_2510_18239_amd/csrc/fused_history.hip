@@ -323,8 +323,11 @@ int history_chunks(int64_t N) { return static_cast<int>((N + kChunkKeys - 1) / k
 // As many links as one workgroup takes, since a second one would project the history once more (64 links of 8 heads of 16
 // columns, 128 users of 512 items in fp32: 186 us, the general kernels 110); and narrow heads, each of whose workgroups projects
 // 32 columns whatever it uses, where that is cheap: in bf16 but for the narrowest of eight (57 us for the 65 536 items and 16
-// candidates, the general kernels 56), in fp32 at d = 32 (27 and 35; 80 and 77 at 262 144 items).  In fp32 at d = 64 four heads
-// take 39 and 43 us, but 123 and 112 at four times the items, eight heads 77 and 53.
+// candidates, the general kernels 56), in fp32 at d = 32.  In fp32 at d = 64 four heads take 39 and 43 us, but 123 and 112 at four
+// times the items, eight heads 77 and 53.  lime_link_history, general kernels | this one, us, at one user's 100 items, one user's 16 384
+// and 64 users' 4096: fp32 d=32 h=4 m=16 9.0|5.6 25.0|18.8 79.5|64.8, d=32 h=2 m=32 9.1|5.4 26.2|18.4 55.5|40.3, d=64 h=1 m=16 12.2|8.4
+// 46.7|24.5 94.7|57.4, d=128 h=4 m=64 11.7|9.5 43.9|26.9 301|251; bf16 d=32 h=4 m=16 9.0|4.8 25.3|17.3 80.5|50.0, d=64 h=4 m=16 9.6|5.1
+// 29.8|18.4 117|60.2, d=128 h=8 m=16 11.7|5.7 40.8|25.9 291|209.
 // The states of a history's chunks fit where separate kernels keep its keys and values (2 N d numbers of a user; m (d + 2h) of
 // each 256 items or part of them), with room to align them.
 bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m, int dtype) {

@@ -300,7 +300,11 @@ hipError_t dispatch_rows_shape(const RowsDev& a, int d, int phi, hipStream_t s) 
 
 }  // namespace
 
-// All links' logits of a row lie in registers: 64 of them, 32 where the head is narrow.
+// All links' logits of a row lie in registers: 64 of them, 32 where the head is narrow.  Narrow heads of any width, though each of
+// their workgroups reads whole rows and projects 32 columns: lime_score_candidates, general kernels | this one, us, at one user's 300
+// candidates, 64 users' 501 and 32 users' 4000: fp32 d=32 h=4 m=16 8.1|5.2 13.7|7.4 39.1|18.8, d=64 h=8 m=16 8.6|7.1 23.5|16.8
+// 62.0|50.5, d=64 h=4 m=32 8.6|7.9 19.9|12.8 44.0|35.0, d=128 h=8 m=31 10.2|9.7 34.6|30.8 106|92.5; bf16 d=32 h=4 m=16 8.5|4.8 13.7|5.6
+// 38.4|12.9, d=64 h=8 m=16 8.8|4.9 23.0|8.7 67.3|25.2, d=128 h=8 m=31 11.0|6.7 37.7|18.2 108|44.1.
 bool fused_rows_supported(int64_t B, int64_t rows, int d, int h, int m) {
   if (!fused_shape(d, h) || m > (d / h >= 32 ? 64 : 32)) return false;
   return launch_fits(B * h + compute_units()) && rows < (int64_t{1} << 31) - 64 * kWaves * compute_units();

@@ -55,6 +55,9 @@ def _error(x, ref):
     (2, 1, 1, 32, 4, 1), (3, 31, 33, 32, 4, 8), (2, 32, 31, 32, 2, 16), (1, 33, 300, 32, 1, 17), (2, 255, 257, 64, 8, 16),
     (2, 256, 32, 64, 4, 32), (3, 257, 65, 64, 2, 33), (1, 513, 96, 64, 1, 64), (2, 100, 40, 128, 8, 31), (5, 777, 129, 128, 4, 64),
     (1, 300, 20, 128, 4, 128), (2, 70, 64, 64, 1, 15), (40, 64, 600, 32, 4, 16),
+    # a workgroup for every compute unit, and more rows than its waves take at once: several tiles a wave, prefetched, in both row
+    # stages (O[S]: lengths that end within, between and before a wave's later tiles)
+    (64, 600, 600, 128, 4, 64), (256, 300, 530, 64, 1, 40), (130, 290, 300, 64, 2, 64),
 ])
 @pytest.mark.parametrize("silu", [False, True])
 def test_against_64_bits(B, N, C, d, h, m, dtype, silu):
