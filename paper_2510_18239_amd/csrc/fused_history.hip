@@ -12,6 +12,7 @@ struct HistoryDev {
   void* LP;
   float *part_acc, *part_ml;  // more than one chunk: [B][chunks][m][d], [B][chunks][m][h][2]
   int B, N, h, m, chunks, total;
+  HistoryTails tails;
   float scale;
 };
 
@@ -26,7 +27,9 @@ struct HistoryLds {
 
 // A workgroup: one chunk of a user's history, one head, 32 MT links; a wave: a tile of 32 items.  What bounds it: at the sizes
 // of these calls the chain of latencies of one tile (rows and weights from memory, projections, logits, weights), which is why
-// a tile has a wave of its own and the small operands are computed by all waves, a part of the sum each.
+// a tile has a wave of its own and the small operands are computed by all waves, a part of the sum each.  With more workgroups than
+// run at once it is the weights' way to planes in LDS: where the users' last (or only) chunks are short, several of them share a
+// workgroup (HistoryTails; a tile's and a user's sums are the same in every place).
 template <typename T, int D, int DH, int MT, int PHI>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_history_kernel(HistoryDev a) {
   using H = Head<DH>;
@@ -44,7 +47,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   const int head = id % a.h;
   const int c0 = n % DH;  // this lane's column of the head's (first) block
   id /= a.h;
-  const int chunk = id % a.chunks, b = id / a.chunks;
+  int chunk = a.chunks - 1, b0 = (id - a.tails.first) * a.tails.users, users = min(a.tails.users, a.B - b0), tiles = a.tails.tiles, per_tile = a.tails.per_tile;
+  if (id < a.tails.first) chunk = id % (a.chunks - 1), b0 = id / (a.chunks - 1), users = 1, tiles = kWaves, per_tile = 65536 / kWaves;
+  const int slot = wave * per_tile >> 16, tile = wave - slot * tiles;  // this wave's user and tile
+  const int b = b0 + min(slot, users - 1);
   auto link_row = [&](int lt, int i) {
     return static_cast<const T*>(a.L) + b * a.l_user_stride + static_cast<int64_t>(min(32 * lt + i, a.m - 1)) * D;
   };
@@ -60,9 +66,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   if (part < kSplits) links.load([&](int i) { return link_row(block / DB, i) + part * (D / kSplits); }, lane);
   __builtin_amdgcn_sched_barrier(0);  // (ahead of the wait for the length)
   const int klen = a.lens ? min(a.lens[b], a.N) : a.N;
-  if (chunk > 0 && chunk * kChunkKeys >= klen) return;  // uniform: nothing in this chunk
-  const int k0 = chunk * kChunkKeys + 32 * wave;
-  const bool live = k0 < klen;  // uniform over the wave
+  if (users == 1 && chunk > 0 && chunk * kChunkKeys >= klen) return;  // uniform: nothing in this chunk
+  const int k0 = chunk * kChunkKeys + 32 * tile;
+  const bool live = slot < users && k0 < klen;  // uniform over the wave
   const int last = max(klen, 1) - 1;
   auto item_row = [&](int i) { return static_cast<const T*>(a.E) + (static_cast<int64_t>(b) * a.N + min(k0 + i, last)) * D; };
   if (live) items.load(item_row, lane);
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   // logits of a tile (kUnit) to weights (`up` times as large) in place, those of odd items negated before and after, all as they are
   // the exact way: register i of this lane is item k0 + 8 (i / 4) + 4g + i % 4
   auto sign = [](int i) { return kAlternate && i % 2 ? -1.f : 1.f; };
-  const float tile_sign = kAlternate && wave % 2 ? -1.f : 1.f, up = tile_sign * kUp<T>;  // uniform
+  const float tile_sign = kAlternate && tile % 2 ? -1.f : 1.f, up = tile_sign * kUp<T>;  // uniform
   auto to_weights = [&](f32x16& s, float& top, float& total, auto exact_tag) {
     constexpr bool kExact = decltype(exact_tag)::value;
     if (ragged) {
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     }
   }
 
-  // The waves' states, folded in ascending order: a quad of a link tile's result by one wave.
+  // A user's tiles' states, folded in ascending order: a quad of a link tile's result by one wave.
   lds_barrier();  // weights and queries have been read
   float* const states = reinterpret_cast<float*>(lds);
   constexpr int kState = Lds::kState / 4, kTile = (4 * H::QUADS + 2) * 64;
@@ -244,11 +250,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     }
   }
   lds_barrier();
-  const int used = min(kWaves, (klen - chunk * kChunkKeys + 31) / 32);  // (none for a user without history)
-#pragma unroll
-  for (int u = wave; u < MT * H::QUADS; u += kWaves) {
-    const int lt = u / H::QUADS, q = u % H::QUADS, link = 32 * lt + n;
-    const float* st = states + lt * kTile + lane;
+#pragma unroll 1
+  for (int u = wave; u < users * MT * H::QUADS; u += kWaves) {
+    const int s = u / (MT * H::QUADS), lt = u / H::QUADS % MT, q = u % H::QUADS, link = 32 * lt + n, b = b0 + s;
+    const int len = users == 1 || !a.lens ? klen : min(a.lens[b], a.N);
+    const int used = min(tiles, (len - chunk * kChunkKeys + 31) / 32);  // (none for a user without history)
+    if (chunk > 0 && used <= 0) continue;  // uniform over the wave
+    const float* st = states + s * tiles * kState + lt * kTile + lane;
     float m[kWaves], top = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
         ml[0] = top, ml[1] = den;
       }
     } else {
-      const float inv = klen > 0 ? 1.f / (PHI == kPhiSoftmax ? den : static_cast<float>(klen)) : 0.f;
+      const float inv = len > 0 ? 1.f / (PHI == kPhiSoftmax ? den : static_cast<float>(len)) : 0.f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] *= inv;
       store_quad(static_cast<T*>(a.LP) + (static_cast<int64_t>(b) * a.m + link) * D + col, x);
@@ -336,8 +344,11 @@ bool fused_history_supported(int64_t B, int64_t N, int d, int h, int m, int dtyp
 }
 
 hipError_t fused_history(const FusedHistory& q, hipStream_t s) {
-  HistoryDev a{q.E, q.L, q.Wq, q.Wk, q.Wv, q.lens, q.l_user_stride, q.LP, nullptr, nullptr, q.B, q.N, q.h, q.m, history_chunks(q.N), 0, q.scale};
-  a.total = static_cast<int>(history_workgroups(a.B, a.N, a.h));
+  HistoryDev a{q.E, q.L, q.Wq, q.Wk, q.Wv, q.lens, q.l_user_stride, q.LP, nullptr, nullptr, q.B, q.N, q.h, q.m, history_chunks(q.N), 0, {}, q.scale};
+  // (links of a user's own are projected by a workgroup of the user's own)
+  const int64_t at_once = static_cast<int64_t>(compute_units()) * fused_waves(q.d, q.d / q.h) / 2;
+  a.tails = history_tails(q.B, q.N, q.h, q.l_user_stride != 0 ? 0 : at_once);
+  a.total = static_cast<int>(tails_workgroups(a.tails, q.B, q.h));
   if (a.chunks > 1) {
     char* scratch = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(q.scratch) + 15) & ~uintptr_t{15});
     a.part_acc = reinterpret_cast<float*>(scratch);

@@ -227,6 +227,33 @@ def test_long_histories_have_no_error_common_to_all_items(d, h, m, silu):
     assert _error(LP, ref) <= 4e-7
 
 
+# Histories of one to five tiles, and of a chunk and one, of more users than workgroups run at once.  The workgroups' shares: 8, 5 (the
+# last short), 4, 2 and 1 users.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,N,d,h,m", [(1030, 20, 32, 4, 16), (643, 50, 64, 2, 36), (900, 90, 128, 4, 60), (700, 270, 64, 1, 20), (600, 150, 64, 4, 16)])
+@pytest.mark.parametrize("silu", [False, True])
+def test_many_users_with_few_rows(B, N, d, h, m, dtype, silu):
+    C = 36
+    E, lens, L, T, W = _inputs(B, N, C, d, m, dtype, seed=B)
+    lens[5], lens[6] = 0, 1
+    E[5] = E[6, 1:] = torch.nan
+    scale = (d // h) ** -0.5
+    run = lambda part: binding.lime_request(E[part], lens[part], L, *W[:3], T[part], L, *W[3:], h, scale, scale, xor_attention=silu)  # noqa: E731
+    LP, O = run(slice(0, B))
+    for b in (0, 4, 5, 6, B // 2, B - 1):  # (alone: a workgroup each)
+        LP1, O1 = run(slice(b, b + 1))
+        assert torch.equal(LP1[0], LP[b]) and torch.equal(O1[0], O[b]), b
+    assert not LP[5].any()
+    live = lens > 0
+    refs = _request(E[live], lens[live], L, W, T[live], LP[live], h, scale, silu)
+    assert _error(LP[live], refs[0]) <= TOLERANCE[dtype] and _error(O[live], refs[1]) <= TOLERANCE[dtype]
+    links = torch.stack([L.roll(b, 0) for b in range(B)])  # links of each user's own
+    call = (lambda *a: binding.lime_xor_history(*a)[0]) if silu else binding.lime_link_history
+    own = call(E, lens, links, *W[:3], h, scale)
+    for b in (0, 5, m, B - 1):
+        assert torch.equal(own[b], LP[b].roll(b, 0)), b
+
+
 def test_unaligned_rows_take_the_general_kernels():
     B, N, C, d, h, m = 2, 300, 50, 64, 2, 32
     E, lens, L, T, W = _inputs(B, N, C, d, m, torch.float32, seed=3)
