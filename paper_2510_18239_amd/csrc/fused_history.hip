@@ -30,7 +30,8 @@ struct HistoryLds {
 // a tile has a wave of its own and the small operands are computed by all waves, a part of the sum each.  With more workgroups than
 // run at once it is the weights' way to planes in LDS: where the users' last (or only) chunks are short, several of them share a
 // workgroup (HistoryTails; a tile's and a user's sums are the same in every place).
-template <typename T, int D, int DH, int MT, int PHI>
+// SHARED: with such workgroups (which cost the others 0.25 us).
+template <typename T, int D, int DH, int MT, int PHI, bool SHARED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_history_kernel(HistoryDev a) {
   using H = Head<DH>;
   using Lds = HistoryLds<T, D, DH, MT>;
@@ -47,10 +48,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   const int head = id % a.h;
   const int c0 = n % DH;  // this lane's column of the head's (first) block
   id /= a.h;
-  int chunk = a.chunks - 1, b0 = (id - a.tails.first) * a.tails.users, users = min(a.tails.users, a.B - b0), tiles = a.tails.tiles, per_tile = a.tails.per_tile;
-  if (id < a.tails.first) chunk = id % (a.chunks - 1), b0 = id / (a.chunks - 1), users = 1, tiles = kWaves, per_tile = 65536 / kWaves;
-  const int slot = wave * per_tile >> 16, tile = wave - slot * tiles;  // this wave's user and tile
-  const int b = b0 + min(slot, users - 1);
+  int chunk, b0, users = 1, tiles = kWaves, slot = 0;  // this wave's user is b0 + slot
+  if constexpr (!SHARED) {
+    chunk = id % a.chunks, b0 = id / a.chunks;
+  } else if (id < a.tails.first) {
+    chunk = id % (a.chunks - 1), b0 = id / (a.chunks - 1);
+  } else {
+    chunk = a.chunks - 1, b0 = (id - a.tails.first) * a.tails.users, users = min(a.tails.users, a.B - b0), tiles = a.tails.tiles;
+    slot = wave * a.tails.per_tile >> 16;
+  }
+  const int tile = wave - slot * tiles, b = b0 + min(slot, users - 1);
   auto link_row = [&](int lt, int i) {
     return static_cast<const T*>(a.L) + b * a.l_user_stride + static_cast<int64_t>(min(32 * lt + i, a.m - 1)) * D;
   };
@@ -250,12 +257,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     }
   }
   lds_barrier();
-#pragma unroll 1
-  for (int u = wave; u < users * MT * H::QUADS; u += kWaves) {
-    const int s = u / (MT * H::QUADS), lt = u / H::QUADS % MT, q = u % H::QUADS, link = 32 * lt + n, b = b0 + s;
-    const int len = users == 1 || !a.lens ? klen : min(a.lens[b], a.N);
+  auto fold = [&](int s, int lt, int q) {  // user b0 + s
+    const int link = 32 * lt + n, b = b0 + s;
+    const int len = !SHARED || !a.lens ? klen : min(a.lens[b], a.N);
     const int used = min(tiles, (len - chunk * kChunkKeys + 31) / 32);  // (none for a user without history)
-    if (chunk > 0 && used <= 0) continue;  // uniform over the wave
+    if (SHARED && chunk > 0 && used <= 0) return;  // uniform over the wave
     const float* st = states + s * tiles * kState + lt * kTile + lane;
     float m[kWaves], top = -INFINITY;
 #pragma unroll
@@ -274,7 +280,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = fmaf(f, st[w * kState + (2 + 4 * q + r) * 64], x[r]);
     }
-    if (link >= a.m) continue;
+    if (link >= a.m) return;
     const int col = head * DH + 8 * q + 4 * g;
     if (a.chunks > 1) {
       const int64_t slot = (static_cast<int64_t>(b) * a.chunks + chunk) * a.m + link;
@@ -289,19 +295,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
       for (int r = 0; r < 4; ++r) x[r] *= inv;
       store_quad(static_cast<T*>(a.LP) + (static_cast<int64_t>(b) * a.m + link) * D + col, x);
     }
+  };
+  constexpr int kUnits = MT * H::QUADS;
+  if constexpr (SHARED) {
+#pragma unroll 1
+    for (int u = wave; u < users * kUnits; u += kWaves) fold(u / kUnits, u / H::QUADS % MT, u % H::QUADS);
+  } else {
+#pragma unroll
+    for (int u = wave; u < kUnits; u += kWaves) fold(0, u / H::QUADS, u % H::QUADS);
   }
+}
+
+template <typename T, int D, int DH, int MT, int PHI, bool SHARED>
+hipError_t launch_form(const HistoryDev& a, hipStream_t s) {
+  constexpr int kBytes = HistoryLds<T, D, DH, MT>::kBytes;
+  static_assert(kBytes <= 160 * 1024);
+  auto kernel = fused_history_kernel<T, D, DH, MT, PHI, SHARED>;
+  if constexpr (kBytes > 64 * 1024) {
+    static PerDevice granted;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), kBytes); e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
+  return hipGetLastError();
 }
 
 template <typename T, int D, int DH, int MT, int PHI>
 hipError_t launch_history(const HistoryDev& a, hipStream_t s) {
-  constexpr int kBytes = HistoryLds<T, D, DH, MT>::kBytes;
-  static_assert(kBytes <= 160 * 1024);
-  if constexpr (kBytes > 64 * 1024) {
-    static PerDevice granted;
-    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(fused_history_kernel<T, D, DH, MT, PHI>), kBytes); e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((fused_history_kernel<T, D, DH, MT, PHI>), dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
-  return hipGetLastError();
+  return a.tails.users > 1 ? launch_form<T, D, DH, MT, PHI, true>(a, s) : launch_form<T, D, DH, MT, PHI, false>(a, s);
 }
 
 // Whether a head of dh columns is one that this kernel is for, see fused_history_supported.

@@ -10,7 +10,7 @@ struct RowsDev {
   const int32_t* row_lens;
   int64_t k_user_stride, v_user_stride;
   void* O;
-  int B, rows, h, m, parts, total;  // workgroups per (user, head)
+  int B, rows, h, m, parts, total;  // workgroups per (user, head); by wave: per head
   float scale;
 };
 
@@ -23,11 +23,19 @@ struct RowsLds {
   static constexpr int kBytes = W::kBytes + kKeys + kValues + kParts;
 };
 
+// (by wave: the values of a user's links lie in registers)
+constexpr int rows_waves(int D, int DH, bool by_wave) { return by_wave ? 2 : fused_waves(D, DH); }
+
 // A workgroup: a part of a user's rows, one head, all m <= 16 MH links; a wave takes every eighth tile of 32 rows.  Keys and
 // values of the links are computed by all waves first.  What bounds it: as above at few rows; from a few thousand tiles on the
 // vector ALUs (exponentials, and the planes of queries and weights).
-template <typename T, int D, int DH, int MH, int PHI>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_waves(D, DH), fused_waves(D, DH)))) void fused_rows_kernel(RowsDev a) {
+// BY_WAVE: a user to a wave, one after the other, with the same sums in the same order; the workgroup shares the weights and the keys
+// (which all users have in common) and no barrier stands between users.  For many users of few rows, where a workgroup each would
+// bring the weights into LDS for a tile or two: lime_score_candidates, general kernels | a workgroup a user | so, in us, 2000 users' 16
+// candidates: fp32 d=128 h=4 m=64 92.5|261|84.4, d=64 h=2 m=32 34.0|75.9|16.6, d=32 h=4 m=16 20.8|54.6|16.7; bf16 d=128 h=8 m=16 56.4|212|27.
+// (fp32 at d=128 stays behind with fewer: 256 users' 19.1|31.8|22.4, 75 users', a workgroup each, 13.5|16.9; 512 users' 30.6|64.8|27.)
+template <typename T, int D, int DH, int MH, int PHI, bool BY_WAVE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(rows_waves(D, DH, BY_WAVE), rows_waves(D, DH, BY_WAVE)))) void fused_rows_kernel(RowsDev a) {
   using H = Head<DH>;
   using Lds = RowsLds<T, D, DH, MH>;
   constexpr int K1 = D / 16, DB = H::DB, NP = kPlanes<T>, MT = Lds::MT, kBlocks = MT * DB, kSplits = std::max(1, std::min(kWaves / (2 * kBlocks), K1));
@@ -43,16 +51,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   if (id >= a.total) return;
   const int head = id % a.h;
   id /= a.h;
-  const int share = id % a.parts, b = id / a.parts;
-  const int tiles = (a.rows + 31) / 32, step = a.parts * kWaves;
+  const int share = id % a.parts;
+  int b = BY_WAVE ? share * kWaves + wave : id / a.parts;
+  const int tiles = (a.rows + 31) / 32, step = BY_WAVE ? 1 : a.parts * kWaves;
   // keys and values of the links: blocks (side, link tile, 32 columns), each by kSplits waves
   const int c0 = n % DH;  // this lane's column of the head's (first) block
-  const T* const keys_from = static_cast<const T*>(a.Ksrc) + b * a.k_user_stride;
-  const T* const values_from = static_cast<const T*>(a.Vsrc) + b * a.v_user_stride;
+  const T* const keys_from = static_cast<const T*>(a.Ksrc) + (BY_WAVE ? 0 : b) * a.k_user_stride;
+  const T* values_from = static_cast<const T*>(a.Vsrc) + b * a.v_user_stride;
   const T *const wk = static_cast<const T*>(a.Wk) + head * DH, *const wv = static_cast<const T*>(a.Wv) + head * DH, *const wq = static_cast<const T*>(a.Wq) + head * DH;
   auto link_row = [&](const T* from, int lt, int i) { return from + static_cast<int64_t>(min(32 * lt + i, a.m - 1)) * D; };
   const int block = wave % (2 * kBlocks), part = wave / (2 * kBlocks);
   const bool of_values = block >= kBlocks;  // uniform over the wave
+  const bool has_part = part < kSplits && !(BY_WAVE && of_values);
   unsigned char* const own = reinterpret_cast<unsigned char*>(parts) + wave * 4096;
 
   // everything the workgroup reads at first is asked for here, in the order of its use
@@ -60,11 +70,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
   RowTile<T, D / kSplits> links;
   RowTile<T, D> items;
   columns.load(wk, wv, wq, threadIdx.x);
-  if (part < kSplits)
+  if (has_part)
     links.load([&](int i) { return link_row(of_values ? values_from : keys_from, block / DB % MT, i) + part * (D / kSplits); }, lane);
   __builtin_amdgcn_sched_barrier(0);  // (ahead of the wait for the length)
-  const int rlen = a.row_lens ? min(a.row_lens[b], a.rows) : a.rows, last = max(rlen, 1) - 1;
-  auto row_of = [&](int t, int i) { return static_cast<const T*>(a.X) + (static_cast<int64_t>(b) * a.rows + min(32 * t + i, last)) * D; };
+  int rlen = 0;
+  auto take_length = [&] { rlen = a.row_lens ? min(a.row_lens[b], a.rows) : a.rows; };
+  if (!BY_WAVE) take_length();
+  auto row_of = [&](int t, int i) { return static_cast<const T*>(a.X) + (static_cast<int64_t>(b) * a.rows + min(32 * t + i, max(rlen, 1) - 1)) * D; };
   auto wanted = [&](int t) { return t < tiles && 32 * t < rlen; };  // uniform over the wave
   auto fetch = [&](int t) {
     if (wanted(t)) items.load([&](int i) { return row_of(t, i); }, lane);
@@ -84,21 +96,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
       products(w[kk & 1], r, q);
     });
   };
-  int t = share * kWaves + wave;
-  fetch(t);
+  int t = BY_WAVE ? 0 : share * kWaves + wave;
+  if (!BY_WAVE) fetch(t);
   __builtin_amdgcn_sched_barrier(0);
   columns.park(weights, threadIdx.x);
   lds_barrier();
   f32x16 links_part = zeros();
-  if (part < kSplits) links_part = partial_block<W>(links, weights, of_values, block % DB, part, own, !of_values, lane);
-  if (wanted(t)) project();
-  if (part < kSplits) park_block(reinterpret_cast<float*>(own), links_part, lane);
-  fetch(t + step);
+  if (has_part) links_part = partial_block<W>(links, weights, of_values, block % DB, part, own, !of_values, lane);
+  if (!BY_WAVE && wanted(t)) project();
+  if (has_part) park_block(reinterpret_cast<float*>(own), links_part, lane);
+  if (!BY_WAVE) fetch(t + step);
   lds_barrier();
+  // half a block of the links' values (registers 8f ..) to fragments; links past the last have weight zero, but what was read in
+  // their place may be infinite
+  auto finish_values = [&](float (&x)[8], int lt, int f, int ob) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] *= kSum<T>;
+    if (__any(any_not_finite(x, 8))) {
+      const f32x16 y = exact_block<T, D, false>(link_row(values_from, lt, n), wv + c0 + 32 * ob, g);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] = !not_finite(x[t]) ? x[t] : f ? y[8 + t] : y[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = 32 * lt + 16 * f + 8 * (t >> 2) + 4 * g + (t & 3) < a.m ? x[t] * kUp<T> : 0.f;
+    return value_planes<DH>(split(x), n);
+  };
 #pragma unroll
   for (int u = wave; u < 4 * kBlocks; u += kWaves) {  // half a block's sum each: registers 8f .. of block (side, link tile, 32 columns)
     const int f = u % 2, ob = u / 2 % DB, lt = u / 2 / DB % MT;
     const bool is_value = u >= 2 * kBlocks;
+    if (BY_WAVE && is_value) continue;
     const float* src = parts + (u / 2) * 1024 + 512 * f + lane;
     float x[8];
 #pragma unroll
@@ -107,20 +134,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
       for (int p = 1; p < kSplits; ++p) x[t] += src[p * 2 * kBlocks * 1024 + t * 64];
     }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) x[t] *= kSum<T>;
-    if (__any(any_not_finite(x, 8))) {
-      const f32x16 y = is_value ? exact_block<T, D, false>(link_row(values_from, lt, n), wv + c0 + 32 * ob, g)
-                                : exact_block<T, D, true>(link_row(keys_from, lt, n), wk + c0 + 32 * ob, g);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = !not_finite(x[t]) ? x[t] : f ? y[8 + t] : y[t];
-    }
     if (is_value) {
-      // links past the last have weight zero; what was read in their place may be infinite
-#pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = 32 * lt + 16 * f + 8 * (t >> 2) + 4 * g + (t & 3) < a.m ? x[t] * kUp<T> : 0.f;
-      if (2 * lt + f < MH) park(values + ((2 * lt + f) * DB + ob) * H::VP * 64, value_planes<DH>(split(x), n), lane);
+      if (2 * lt + f < MH) park(values + ((2 * lt + f) * DB + ob) * H::VP * 64, finish_values(x, lt, f, ob), lane);
     } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] *= kSum<T>;
+      if (__any(any_not_finite(x, 8))) {
+        const f32x16 y = exact_block<T, D, true>(link_row(keys_from, lt, n), wk + c0 + 32 * ob, g);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = !not_finite(x[t]) ? x[t] : f ? y[8 + t] : y[t];
+      }
 #pragma unroll
       for (int t = 0; t < 8; ++t) x[t] = x[t] * a.scale * kUp<T>;
       // (a narrow head's columns are in the first registers)
@@ -162,6 +185,51 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
     return (kExact ? 1.f : kDown<T>) / pair_sum(total);
   };
 
+  Planes<H::VP> own_values[BY_WAVE ? MH : 1][DB];  // BY_WAVE: the user's
+  auto compute_values = [&] {
+    constexpr int kPart = K1 / kSplits;
+#pragma unroll
+    for (int lt = 0; lt < MT; ++lt) {
+      RowTile<T, D> rows;
+      rows.load([&](int i) { return link_row(values_from, lt, i); }, lane);
+      f32x16 acc[DB], total[DB];
+      Planes<NP> w[2][DB];
+      rows.each(own, lane, kUp<T>, [&](int kk) {
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) w[kk & 1][ob] = W::fragment(weights, 1, ob, kk, lane);
+      }, [&](int kk, const Planes<NP>& x) {
+        Planes<NP> l[DB];
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) {
+          l[ob] = x;
+          if (kk % kPart == 0) acc[ob] = zeros();
+        }
+        products(l, w[kk & 1], acc);
+        if (kk % kPart == kPart - 1) {
+#pragma unroll
+          for (int ob = 0; ob < DB; ++ob) total[ob] = kk < kPart ? acc[ob] : total[ob] + acc[ob];
+        }
+      });
+#pragma unroll
+      for (int f = 0; f < 2 && 2 * lt + f < MH; ++f)
+#pragma unroll
+        for (int ob = 0; ob < DB; ++ob) {
+          Half x = half_of(total[ob], f);
+          own_values[BY_WAVE ? 2 * lt + f : 0][ob] = finish_values(x.x, lt, f, ob);
+        }
+    }
+  };
+  // (BY_WAVE: no barrier in here)
+  for (; b < a.B; b += BY_WAVE ? a.parts * kWaves : a.B) {
+  if constexpr (BY_WAVE) {
+    take_length();
+    values_from = static_cast<const T*>(a.Vsrc) + b * a.v_user_stride;
+    t = 0;
+    compute_values();
+    fetch(0);  // (not ahead of it: registers)
+    if (wanted(0)) project();
+    fetch(1);
+  }
   for (bool first = true; t < tiles; t += step, first = false) {
     float res[DH / 2], inv = 0.f;
     if (32 * t < rlen) {  // uniform over the wave
@@ -201,7 +269,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
 #pragma unroll
         for (int f = 0; f < MH; ++f)
 #pragma unroll
-          for (int ob = 0; ob < DB; ++ob) v[f][ob] = parked<H::VP>(values + (f * DB + ob) * H::VP * 64, lane);
+          for (int ob = 0; ob < DB; ++ob)
+            if constexpr (BY_WAVE) v[f][ob] = own_values[f][ob];
+            else v[f][ob] = parked<H::VP>(values + (f * DB + ob) * H::VP * 64, lane);
         auto term = [&](int t, int f) {
 #pragma unroll
           for (int ob = 0; ob < DB; ++ob) acc[ob] = value_term<DH>(t, v[f][ob], p[f], acc[ob]);
@@ -267,32 +337,42 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(fused_
       store_quad(orow + 8 * q, x);
     }
   }
+  if (!BY_WAVE) break;
+  }
 }
 
-template <typename T, int D, int DH, int MH, int PHI>
-hipError_t launch_rows(const RowsDev& a, hipStream_t s) {
+template <typename T, int D, int DH, int MH, int PHI, bool BY_WAVE>
+hipError_t launch_form(const RowsDev& a, hipStream_t s) {
   constexpr int kBytes = RowsLds<T, D, DH, MH>::kBytes;
   static_assert(kBytes <= 160 * 1024);
+  auto kernel = fused_rows_kernel<T, D, DH, MH, PHI, BY_WAVE>;
   if constexpr (kBytes > 64 * 1024) {
     static PerDevice granted;
-    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(fused_rows_kernel<T, D, DH, MH, PHI>), kBytes); e != hipSuccess) return e;
+    if (hipError_t e = allow_lds(granted, reinterpret_cast<const void*>(kernel), kBytes); e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fused_rows_kernel<T, D, DH, MH, PHI>), dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
+  hipLaunchKernelGGL(kernel, dim3(launched_workgroups(a.total)), dim3(kThreads), kBytes, s, a);
   return hipGetLastError();
 }
 
+template <typename T, int D, int DH, int MH, int PHI>
+hipError_t launch_rows(const RowsDev& a, bool by_wave, hipStream_t s) {
+  if constexpr (DH < 64)
+    if (by_wave) return launch_form<T, D, DH, MH, PHI, true>(a, s);
+  return launch_form<T, D, DH, MH, PHI, false>(a, s);
+}
+
 template <typename T, int D, int DH, int PHI>
-hipError_t dispatch_rows(const RowsDev& a, hipStream_t s) {
-  if (a.m <= 16) return launch_rows<T, D, DH, 1, PHI>(a, s);
-  if (a.m <= 32) return launch_rows<T, D, DH, 2, PHI>(a, s);
-  if constexpr (DH >= 32) return launch_rows<T, D, DH, 4, PHI>(a, s);
+hipError_t dispatch_rows(const RowsDev& a, bool by_wave, hipStream_t s) {
+  if (a.m <= 16) return launch_rows<T, D, DH, 1, PHI>(a, by_wave, s);
+  if (a.m <= 32) return launch_rows<T, D, DH, 2, PHI>(a, by_wave, s);
+  if constexpr (DH >= 32) return launch_rows<T, D, DH, 4, PHI>(a, by_wave, s);
   return hipErrorInvalidValue;
 }
 
 template <typename T>
-hipError_t dispatch_rows_shape(const RowsDev& a, int d, int phi, hipStream_t s) {
+hipError_t dispatch_rows_shape(const RowsDev& a, int d, int phi, bool by_wave, hipStream_t s) {
 #define LIME_CASE(D, DH) \
-  if (d == D && d / a.h == DH) return phi == kPhiSoftmax ? dispatch_rows<T, D, DH, kPhiSoftmax>(a, s) : dispatch_rows<T, D, DH, kPhiSilu>(a, s);
+  if (d == D && d / a.h == DH) return phi == kPhiSoftmax ? dispatch_rows<T, D, DH, kPhiSoftmax>(a, by_wave, s) : dispatch_rows<T, D, DH, kPhiSilu>(a, by_wave, s);
   LIME_FUSED_SHAPES(LIME_CASE)
 #undef LIME_CASE
   return hipErrorInvalidValue;
@@ -314,9 +394,19 @@ hipError_t fused_rows(const FusedRows& q, hipStream_t s) {
   // a workgroup per compute unit where the rows are many, a tile per wave where they are few
   const int64_t pairs = static_cast<int64_t>(q.B) * q.h, tiles = (static_cast<int64_t>(q.rows) + 31) / 32;
   const int parts = static_cast<int>(std::min((compute_units() + pairs - 1) / pairs, (tiles + kWaves - 1) / kWaves));
-  const RowsDev a{q.X, q.Ksrc, q.Vsrc, q.Wq, q.Wk, q.Wv, q.row_lens, q.k_user_stride, q.v_user_stride, q.O,
-                  q.B, q.rows, q.h, q.m, parts, static_cast<int>(pairs * parts), q.scale};
-  return q.dtype == 0 ? dispatch_rows_shape<float>(a, q.d, q.phi, s) : dispatch_rows_shape<bf16_t>(a, q.d, q.phi, s);
+  RowsDev a{q.X, q.Ksrc, q.Vsrc, q.Wq, q.Wk, q.Wv, q.row_lens, q.k_user_stride, q.v_user_stride, q.O,
+            q.B, q.rows, q.h, q.m, parts, static_cast<int>(pairs * parts), q.scale};
+  // By wave: in turns of a user each, a workgroup of eight per compute unit.  Such a turn takes as long as three workgroups of one user of
+  // few rows, and half a one more for each tile (in us, a workgroup | a wave a user, pairs a multiple of the compute units: fp32 d=128 h=4 m=64 16
+  // candidates 4 times 31.8|22.4, 8 times 62.0|28, 300 candidates 8 times 132|112, 4 times 60.0|88; d=32 h=4 m=16 16 candidates 2 times
+  // 5.1|6.4, 4 times 8.2|6.4; bf16 d=128 h=8 m=16 15.0|6.4, 300 candidates 24.8|22.5).
+  const int64_t units = compute_units(), turns = (pairs + kWaves * units - 1) / (kWaves * units);
+  const bool by_wave = q.d / q.h < 64 && q.k_user_stride == 0 && turns * (5 + tiles) <= 2 * ((pairs + units - 1) / units);
+  if (by_wave) {
+    a.parts = static_cast<int>(std::min((units + q.h - 1) / q.h, (static_cast<int64_t>(q.B) + kWaves - 1) / kWaves));
+    a.total = a.parts * q.h;
+  }
+  return q.dtype == 0 ? dispatch_rows_shape<float>(a, q.d, q.phi, by_wave, s) : dispatch_rows_shape<bf16_t>(a, q.d, q.phi, by_wave, s);
 }
 
 }  // namespace lime

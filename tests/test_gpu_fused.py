@@ -252,6 +252,25 @@ def test_many_users_with_few_rows(B, N, d, h, m, dtype, silu):
     own = call(E, lens, links, *W[:3], h, scale)
     for b in (0, 5, m, B - 1):
         assert torch.equal(own[b], LP[b].roll(b, 0)), b
+    if silu:  # O[S], rows of every length
+        rows = lambda part: binding.lime_xor_history(E[part], lens[part], L, *W[:3], h, scale, want_os=True)[1]  # noqa: E731
+        OS = rows(slice(0, B))
+        for b in (0, 4, 5, 6, B - 1):
+            assert torch.equal(rows(slice(b, b + 1))[0], OS[b]), b
+        valid = torch.arange(N, device="cuda")[None, :] < lens[:, None]
+        p = [(L.double() @ w.double())[None].expand(B, -1, -1) for w in W[1:3]]
+        ref = _attention(torch.where(valid[:, :, None], E.double(), 0.0) @ W[0].double(), *p, h, scale, None, True) * valid[:, :, None]
+        assert _error(OS, ref) <= TOLERANCE[dtype] and not OS[~valid].any()
+    # what is not finite stays with its user, and its row
+    lens[7] = N
+    E[7], T[9, 3, 1] = torch.nan_to_num(E[7]), torch.nan
+    clean = run(slice(0, B))
+    E[7, 0, 3] = torch.inf
+    LP, O = run(slice(0, B))
+    others = torch.arange(B, device="cuda") != 7
+    assert torch.equal(LP[others], clean[0][others]) and not torch.isfinite(LP[7]).any() and not torch.isfinite(O[7]).any()
+    assert torch.equal(torch.nan_to_num(O[others]), torch.nan_to_num(clean[1][others])) and not torch.isfinite(O[9, 3]).any()
+    assert torch.isfinite(O[9, :3]).all() and torch.isfinite(O[10:]).all()
 
 
 def test_unaligned_rows_take_the_general_kernels():
