@@ -197,7 +197,8 @@ int32_t lime_request_prepared(const void* E, const int32_t* lens, const void* T,
  * lime_score_candidates on that LP with the *_cand weights and scale_cand.  Arguments, layouts, nullable pointers
  * (Wq_cand, Wk_cand, Wv_cand: NULL = identity) and errors as for those two entry points; LP[B][m][d] and
  * O[B][C][d] are both written, nothing is kept between calls.  On the bf16 matrix-core shapes with 16-byte aligned
- * pointers this is three or four kernels instead of six: one launch packs the operands of both stages (few history rows: the candidate stage's, beside the history kernel), and the step that
+ * pointers this is three or four kernels instead of six: one launch packs the operands of both stages (few history
+ * rows: the candidate stage's, beside the history kernel), and the step that
  * finishes the link states also projects them with Wv_cand into the layout the candidate kernel loads.  LP is then
  * bit-identical to lime_link_history / lime_xor_history; O agrees with lime_score_candidates within the bf16
  * tolerance (the value projection sums in another order).  Otherwise the two stages run one after the other as
@@ -234,7 +235,7 @@ size_t lime_request_static_capacity(void);
  * at once: request i is lime_request(requests[i]...) on streams[i % n_streams].  The requests of one stream are
  * submitted in order by one host thread, those of different streams by different threads (the caller's own for
  * stream 0, threads the library keeps for the others, created on first use and alive until the process ends): a
- * request is four kernel launches, each a few microseconds of host time, and a burst handed over from one thread
+ * request is two to five kernel launches, each a few microseconds of host time, and a burst handed over from one thread
  * reaches the GPU that much later.  Every request needs a workspace and an LP of its own (requests in flight at the
  * same time must not share them); the fields are lime_request's arguments with the same meaning, layouts and errors.
  * Returns when everything is enqueued (it does not wait for the GPU); on an error the first failing request's status,

@@ -1,7 +1,8 @@
 // Both stages of a request with their projections inside, for the calls that are held to fp32 (fp32 storage, and bf16 shapes
 // outside the bf16 matrix-core set): the m links over a history, and rows over the m links.  A workgroup takes one head of one
-// user; projected queries, keys and values never exist in memory, and a request is two launches (three with a history of more
-// than kChunkKeys items) where projections and attentions as kernels of their own (generic.hip) are four.
+// user (of several, where users are many and their rows few); projected queries, keys and values never exist in memory, and a
+// request is two launches (three with a history of more than kChunkKeys items) where projections and attentions as kernels of
+// their own (generic.hip) are four.
 //
 // fp32 products on the bf16 matrix instruction.  An fp32 number is the sum of three bf16 numbers, x = x0 + x1 + x2 (each the
 // remainder rounded to nearest: at most 2^-8 and 2^-17 of x), and a product is taken as x0 y0 + x0 y1 + x1 y0 + x1 y1 +
@@ -11,11 +12,11 @@
 // The sum of the planes is exact where none of them lies under the smallest bf16 number (2^-133), as the third one of a number
 // below 2^-110 would.  So with fp32 storage whatever is split is taken 2^24 times as large (kUp), or 2^48 times as sums of two such
 // come, and is exact down to the smallest number; the units of sums (kSum, kUnit) are taken out where it costs least.  (About 100 of the
-// kernels' some 1000 vector instructions a tile at d = 128: 16 users of 777 items and 1001 candidates 32.1 -> 33.0 us, the smallest
+// kernels' some 1200 vector instructions a tile at d = 128: 16 users of 777 items and 1001 candidates 32.1 -> 33.0 us, the smallest
 // request 15.3 -> 15.6.)  With bf16 storage everything is taken as it is: what results are rounded to, nine bits, is held from 2^-124 on.
 // Where an operand is infinite, or rounds to infinity (fp32: from 2^104 on, being 2^24 times as large), its remainders are NaN; a
-// sum may pass the range too (fp32: from 2^79 on, a logit or result from 2^55 on).  A result that is not finite is computed again with the fp32
-// instruction (`exact`) and taken from there, so that infinities stay where they are and no other row's bits change.
+// sum may pass the range too (fp32: from 2^79 on, a logit or result from 2^55 on).  A result that is not finite is computed again
+// with the fp32 instruction (`exact`) and taken from there, so that infinities stay where they are and no other row's bits change.
 // The bf16 matrix instruction rounds downward a little more often than upward (the mean of its result and that of its negated operands
 // is -1.2e-8 where accumulator and products are near one; the fp32 instruction's is zero), which over many items adds up: the mean
 // of 4096 items' values was 6.9e-7 off, 3.6e-7 with the fp32 instruction.  So every other item of a history is taken negated, row

@@ -1,6 +1,6 @@
 // Several independent requests handed to the GPU from several host threads at once.
 //
-// A request (lime_request) is four kernel launches, and a launch costs the host 2-3 us on this runtime: a serving loop
+// A request (lime_request) is two to five kernel launches, and a launch costs the host 2-3 us on this runtime: a serving loop
 // that keeps a few requests in flight on as many streams spends 10-12 us of host time per request, which is most of
 // the 17 us a request takes on the GPU and all of what the start of a burst waits for.  lime_request_many takes a list
 // of requests and a list of streams, gives request i to stream i % n_streams, and submits the requests of each stream
